@@ -272,8 +272,9 @@ lora_status lora_linear_merge(const lora_bf16* W, const lora_bf16* A, const lora
  *   Y, U    HOST arrays [group] of device pointers: Y_g [m, n_g] (bf16) and
  *           U_g [m, r] (fp32), written
  *   r, alpha  one rank and alpha for the group
- * One kernel launch: the output tiles of all projections form one grid, so the
- * group fills the chip as one problem of m x (sum of n_g) outputs.  Each Y_g,
+ * One GEMM launch (after a launch forming every U_g where U has a pass of its
+ * own): the output tiles of all projections form one grid, so the group fills
+ * the chip as one problem of m x (sum of n_g) outputs.  Each Y_g,
  * U_g equals what lora_linear_fwd computes for projection g.  No output may
  * overlap any input or another output.
  */

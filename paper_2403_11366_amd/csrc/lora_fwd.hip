@@ -10,8 +10,9 @@
 //   lora_fwd_kernel     the other tiles (256 x 256, 128 x 256, 128 x 128)
 //                       and grouped launches; described below.
 //   lora_u_kernel       U = X A^T on its own (under dropout with the keep
-//                       mask applied), followed by a GEMM tile without U
-//                       columns.
+//                       mask applied; for a group, of every projection in one
+//                       launch), followed by a GEMM tile without U columns.
+//   lora_fwd_skinny_ks_kernel (lora_fwd_skinny.hip)  few tokens.
 // A launch covers the output columns from n_begin on (plan_gemm_split);
 // the launch whose range starts at column 0 writes U.
 //
@@ -591,9 +592,8 @@ __global__ __launch_bounds__(64 * WM * WN) void lora_fwd_kernel(
 // holds 16 X rows for the 16-token products; rows 8..15 are zeroed once and
 // never copied into, and only the first 8 tokens' U is written.
 template <int RP, int TPW, bool KEEP>
-__global__ __launch_bounds__(256) void lora_u_kernel(const u16* __restrict__ X, const u16* __restrict__ A,
-                                                     const uint8_t* __restrict__ keep, float* __restrict__ U, int m,
-                                                     int k, int r, float inv_keep) {
+__global__ __launch_bounds__(256) void lora_u_kernel(const u16* __restrict__ X, const uint8_t* __restrict__ keep,
+                                                     int m, int k, int r, float inv_keep, int blocks, FwdGroup grp) {
   constexpr int NWV = 4;
   constexpr int XR = TPW < 16 ? 16 : TPW;        // X rows of a stage (rows TPW .. XR-1 stay zero)
   constexpr int ROWS = XR + RP;                  // 128-byte rows per stage: X rows, then A rows
@@ -609,7 +609,13 @@ __global__ __launch_bounds__(256) void lora_u_kernel(const u16* __restrict__ X, 
   static_assert(NSW >= 3 && CPW * (NSW - 2) < 64, "copies in flight fit the wait counter");
   static_assert(FT * TG <= 8, "fragments per wave");
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
-  const int i0 = blockIdx.x * TPW;
+  const int sel = (int)blockIdx.x / blocks;        // the projection (its A and U)
+  const u16* A = grp.A[0];
+  float* U = grp.U[0];
+#pragma unroll
+  for (int q = 1; q < kMaxGroup; ++q)
+    if (q == sel) { A = grp.A[q]; U = grp.U[q]; }
+  const int i0 = ((int)blockIdx.x - sel * blocks) * TPW;
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int g = lane >> 4, c16 = lane & 15;
   const uint32_t rowbytes = (uint32_t)k * 2;
@@ -1182,7 +1188,7 @@ static hipError_t run_fwd_launch(const Launch& L, const FwdArgs& a, const FwdGro
       return with_int<8, 16, 32>(L.tpw, [&](auto tc) {
         return with_bool(L.drop, [&](auto kc) {
           hipLaunchKernelGGL((lora_u_kernel<decltype(rc)::value, decltype(tc)::value, decltype(kc)::value>), grid,
-                             block, 0, st, a.X, a.A, a.keep, a.U, (int)a.m, (int)a.k, (int)a.r, a.inv_keep);
+                             block, 0, st, a.X, a.keep, (int)a.m, (int)a.k, (int)a.r, a.inv_keep, L.tiles_m, grp);
           return hipGetLastError();
         });
       });
@@ -1208,6 +1214,7 @@ static hipError_t run_fwd_launch(const Launch& L, const FwdArgs& a, const FwdGro
       });
     });
   }
+  if (L.id == K_FWD_SKINNY) return launch_fwd_skinny(L, a, grp, st);
   if (L.id != K_FWD) return hipErrorInvalidValue;
   return with_int<0, 1, 2>(tile_code(L), [&](auto tc) {
     constexpr int T = decltype(tc)::value;
@@ -1238,9 +1245,12 @@ static hipError_t run_fwd_launch(const Launch& L, const FwdArgs& a, const FwdGro
 
 hipError_t launch_fwd(const FwdArgs& a, hipStream_t st) {
   const Plan p = plan_fwd(a.m, a.n, a.k, a.r, a.keep != nullptr);
-  const FwdGroup none{};
+  FwdGroup one{};   // the projection as a group of one (the U pass and the few-token forward read it)
+  one.W[0] = a.W; one.A[0] = a.A; one.B[0] = a.B; one.Y[0] = a.Y; one.U[0] = a.U;
+  one.n[0] = (int)a.n;
+  one.count = 1;
   for (int i = 0; i < p.count; ++i) {
-    const hipError_t e = run_fwd_launch(p.l[i], a, none, st);
+    const hipError_t e = run_fwd_launch(p.l[i], a, one, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -1268,7 +1278,7 @@ hipError_t launch_fwd_group(const GroupFwdArgs& a, hipStream_t st) {
   for (int i = 0; i < p.count; ++i) {
     const Launch& L = p.l[i];
     int t0 = 0;
-    for (int g = 0; g < a.count; ++g) {
+    for (int g = 0; g < a.count && L.bn > 0; ++g) {   // (the U pass has no column tiles)
       grp.tile0[g] = t0;
       t0 += (grp.n[g] + L.bn - 1) / L.bn;
     }

@@ -285,7 +285,9 @@ struct MergeArgs {
 // the backward workspace (the largest Llama-2 projection shapes need 21 MiB).
 constexpr size_t kNoAllocScratchBytes = size_t(32) << 20;
 
+struct Launch;
 hipError_t launch_fwd(const FwdArgs& a, hipStream_t st);
+hipError_t launch_fwd_skinny(const Launch& L, const FwdArgs& a, const FwdGroup& grp, hipStream_t st);   // few tokens
 hipError_t launch_bwd_noalloc(const BwdArgs& a, hipStream_t st);   // workspace: the library's scratch array
 hipError_t launch_merge(const MergeArgs& a, hipStream_t st);
 hipError_t launch_bwd(const BwdArgs& a, hipStream_t st);

@@ -25,6 +25,7 @@ enum KernelId : int {
   K_FINALIZE = 7,  // lora_finalize_kernel
   K_MERGE = 8,     // lora_merge_kernel<RP, 64>
   K_MASK = 9,      // lora_keep_mask_kernel: the dropout keep mask from the counter-based generator
+  K_FWD_SKINNY = 10,   // lora_fwd_skinny_ks_kernel<XR, F, AR, UPRE>: forward of few tokens
 };
 
 // One kernel launch.  Fields a kernel does not use stay zero / false.
@@ -83,6 +84,55 @@ inline Launch gemm_launch(KernelId id, GemmTile t, int64_t M, int64_t col_begin,
   return x;
 }
 
+// U pass over the tokens of `count` projections that read one X: 32 tokens per
+// workgroup (A read half as often) unless that leaves compute units idle, then
+// 16, then 8.
+inline Launch upass_launch(int count, int64_t m, int64_t r, bool drop) {
+  Launch u = blank_launch(K_UPASS);
+  u.rp = fwd_rank(r);
+  u.drop = drop;
+  u.tpw = (m + 31) / 32 >= 256 ? 32 : ((m + 15) / 16 >= 256 ? 16 : 8);
+  u.tiles_m = (int)((m + u.tpw - 1) / u.tpw);
+  u.grid = (int64_t)count * u.tiles_m;
+  u.block = 256;
+  return u;
+}
+
+// Forward of few tokens.  Up to kSkinnyTokens tokens the GEMM tiles leave most
+// compute units idle (one row of 128 x 128 tiles) or multiply mostly padding,
+// and a kernel that streams W past blocks of up to 64 tokens is faster
+// (n = k = 4096: 4 tokens 39 -> 11 us, 64 tokens 40 -> 18 us).
+constexpr int64_t kSkinnyTokens = 64;
+inline Plan plan_fwd_skinny(int count, const int64_t* n, int64_t m, int64_t k, int64_t r, bool drop) {
+  Plan p;
+  Launch x = blank_launch(K_FWD_SKINNY);
+  x.upre = drop || r > 16;   // the tile forms U beside W up to rank 16
+  if (x.upre) p.add(upass_launch(count, m, r, drop));
+  x.rp = x.upre ? 0 : 16;
+  x.bm = m <= 16 ? 16 : (m <= 32 ? 32 : 64);
+  x.tiles_m = (int)((m + x.bm - 1) / x.bm);
+  // Features per workgroup: rounds of 256 workgroups times the rows a stage
+  // copies, X and A rows (read from L2) at 0.6 of a W row: 4096 x 24 x 11008
+  // takes 23.3, 25.7, 30.6 us with 48, 64, 96 features, 13824 x 40 x 5120 49.5
+  // us with 32 and 56.4 with 48.
+  double best = 1e300;
+  for (const int f : {16, 32, 48, 64, 96}) {
+    int64_t tiles = 0;
+    for (int g = 0; g < count; ++g) tiles += (n[g] + f - 1) / f;
+    const double cost = (double)((tiles * x.tiles_m + 255) / 256) * (f + 0.6 * (x.bm + x.rp));
+    if (cost < best) {
+      best = cost;
+      x.bn = f;
+      x.tiles_n = (int)tiles;
+    }
+  }
+  x.grid = (int64_t)x.tiles_m * x.tiles_n;
+  x.block = 512;
+  x.col_end = count == 1 ? n[0] : 0;   // (as the grouped tiles: no single column range)
+  p.add(x);
+  return p;
+}
+
 // Forward GEMM launch(es) for output columns [cb, ce) with tile t.  `first`:
 // the launch whose range starts at column 0 (it writes U, or the U pass runs
 // before it).  U comes from the U pass for single projections of rank above
@@ -95,17 +145,7 @@ inline void plan_fwd_part(Plan& p, GemmTile t, int64_t m, int64_t k, int64_t r, 
                           bool first, bool drop, bool grp, int tiles_n) {
   const bool kfull = k % 64 == 0;
   const bool upre = !grp && (drop || fwd_rank(r) >= 32 || t == TILE_256x256);
-  if (upre && first) {
-    Launch u = blank_launch(K_UPASS);
-    u.rp = fwd_rank(r);
-    u.drop = drop;
-    // 32 tokens per workgroup (A read half as often) unless that leaves
-    // compute units idle, then 16, then 8
-    u.tpw = (m + 31) / 32 >= 256 ? 32 : ((m + 15) / 16 >= 256 ? 16 : 8);
-    u.grid = (m + u.tpw - 1) / u.tpw;
-    u.block = 256;
-    p.add(u);
-  }
+  if (upre && first) p.add(upass_launch(1, m, r, drop));
   Launch x = gemm_launch(K_FWD, t, m, cb, ce, tiles_n);
   x.grp = grp;
   x.upre = upre;
@@ -126,6 +166,7 @@ inline void plan_fwd_part(Plan& p, GemmTile t, int64_t m, int64_t k, int64_t r, 
 // lora_linear_fwd / lora_linear_fwd_dropout (the same tiles and column split;
 // under dropout the U pass applies the mask).
 inline Plan plan_fwd(int64_t m, int64_t n, int64_t k, int64_t r, bool drop) {
+  if (m <= kSkinnyTokens) return plan_fwd_skinny(1, &n, m, k, r, drop);
   Plan p;
   const GemmSplit s = plan_gemm_split(m, n);
   plan_fwd_part(p, s.t1, m, k, r, 0, s.n1, true, drop, false, -1);
@@ -137,6 +178,7 @@ inline Plan plan_fwd(int64_t m, int64_t n, int64_t k, int64_t r, bool drop) {
 // tile chosen for m x (sum of n).  A group of one is the single projection.
 inline Plan plan_group_fwd(int count, const int64_t* n, int64_t m, int64_t k, int64_t r) {
   if (count == 1) return plan_fwd(m, n[0], k, r, false);
+  if (m <= kSkinnyTokens) return plan_fwd_skinny(count, n, m, k, r, false);
   int64_t ntot = 0;
   for (int g = 0; g < count; ++g) ntot += n[g];
   const GemmTile t = choose_gemm_tile(m, ntot);
@@ -331,6 +373,9 @@ inline void launch_name(const Launch& x, char* buf, size_t len) {
     case K_FINALIZE: snprintf(buf, len, "lora::lora_finalize_kernel"); break;
     case K_MERGE: snprintf(buf, len, "lora::lora_merge_kernel<%d, %d>", x.rp, kMergeRows); break;
     case K_MASK: snprintf(buf, len, "lora::lora_keep_mask_kernel"); break;
+    case K_FWD_SKINNY:
+      snprintf(buf, len, "lora::lora_fwd_skinny_ks_kernel<%d, %d, %d, %s>", x.bm, x.bn, x.rp, b(x.upre));
+      break;
   }
 }
 

@@ -76,6 +76,11 @@ CASES = [  # (ns, m, k, r, alpha)
     ([264, 392], 2000, 5120, 8, 16.0),             # 2.5 rounds of 128x256 dX tiles
     ([264, 392], 4096, 4096, 8, 16.0),             # the 256x256 dX tile for a group
     ([264, 520, 136, 72], 300, 448, 13, 26.0),     # four members share one dA reduction (stacked rank 64)
+    # few tokens: several members' columns in one launch, U beside W and from one U pass over the members
+    ([520, 136, 1032], 24, 328, 13, 26.0), ([4096, 1024, 1024], 3, 200, 16, 32.0),
+    ([13824, 13824], 40, 136, 8, 16.0), ([136, 392, 64], 61, 264, 40, 80.0), ([5120, 5120, 5120], 16, 72, 24, 48.0),
+    ([64, 64], 70, 72, 24, 48.0), ([64, 64], 70, 72, 33, 66.0),
+    ([4096, 4096, 4096], 7, 64, 33, 66.0), ([4096, 4096, 4096], 7, 64, 5, 10.0), ([5120, 5120, 5120], 7, 64, 5, 10.0),
 ] + [
     # the remaining grouped tiles a plan can name, at padded ranks 16 .. 64 with and without whole k stages:
     # the 128 x 128 forward and dX (few tokens), the 128 x 256 forward and k-split forward (130 tokens over

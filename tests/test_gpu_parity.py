@@ -68,6 +68,13 @@ RAGGED = [
     Shape("ragged", 300, 11008, 72, 24, 48.0, 134), Shape("ragged", 300, 11008, 64, 33, 66.0, 135),
     Shape("ragged", 2048, 11008, 72, 24, 48.0, 136), Shape("ragged", 2048, 11008, 64, 24, 48.0, 137),
     Shape("ragged", 2048, 11008, 72, 33, 66.0, 138),
+] + [
+    # few tokens: every token block (16, 32, 64 rows) and feature count (16, 32, 48, 64, 96) of the few-token
+    # forward, with U formed beside W (rank at most 16) and from the U pass, k with and without a partial stage
+    Shape("few", m, n, k, r, 2.0 * r, 140 + i)
+    for i, (m, k, r) in enumerate([(5, 520, 8), (16, 72, 16), (13, 264, 64), (17, 648, 3), (31, 200, 33),
+                                   (33, 1096, 16), (64, 328, 24)])
+    for n in (4088, 5120, 11008, 13824, 16392)
 ]
 
 
