@@ -102,6 +102,9 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
+// s_waitcnt lgkmcnt(0) alone: every LDS access of this wave is done.
+__device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4)); }
+
 // Workgroup barrier for pipelines fed by global -> LDS copies: waits until at
 // most N of this wave's copies are outstanding and all of its LDS accesses
 // are done, then s_barrier.  (__syncthreads would also wait for the copies
@@ -264,6 +267,39 @@ __device__ __forceinline__ void store_block_32x64(const floatx16& v0, const floa
 #pragma unroll
     for (int p = 0; p < 4; ++p)
       if (8 * p + r8 < nrows) *reinterpret_cast<int4v*>(dst + (size_t)(8 * p + r8) * ld + 8 * ch) = v[p];
+  }
+}
+
+// The same for a block of 32 rows x 32 NF columns (v[f]: columns 32 f ..),
+// with whole rows of the block per store.  The caller has synchronised the
+// region.
+template <int NF>
+constexpr int out_block_bytes() { return 32 * (64 * NF + 16); }
+template <int NF>
+__device__ __forceinline__ void store_out_block(const floatx16 (&v)[NF], char* ys, u16* dst, size_t ld, int nrows,
+                                                int ncols, int lane) {
+  constexpr int PITCH = 64 * NF + 16, CH = 4 * NF;   // bytes and 16-byte chunks per row
+  const int g = lane >> 5, c = lane & 31;
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+#pragma unroll
+    for (int qq = 0; qq < 4; ++qq) {
+      const uint32_t lo = (uint32_t)f32_to_bf16(v[f][4 * qq]) | ((uint32_t)f32_to_bf16(v[f][4 * qq + 1]) << 16);
+      const uint32_t hi = (uint32_t)f32_to_bf16(v[f][4 * qq + 2]) | ((uint32_t)f32_to_bf16(v[f][4 * qq + 3]) << 16);
+      *reinterpret_cast<uint2*>(ys + c * PITCH + (32 * f + 8 * qq + 4 * g) * 2) = uint2{lo, hi};
+    }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  int4v w[2 * NF];
+#pragma unroll
+  for (int p = 0; p < 2 * NF; ++p) {
+    const int e = lane + 64 * p, row = e / CH, ch = e - row * CH;
+    w[p] = *reinterpret_cast<const int4v*>(ys + row * PITCH + ch * 16);
+  }
+#pragma unroll
+  for (int p = 0; p < 2 * NF; ++p) {
+    const int e = lane + 64 * p, row = e / CH, ch = e - row * CH;
+    if (row < nrows && 8 * ch < ncols) *reinterpret_cast<int4v*>(dst + (size_t)row * ld + 8 * ch) = w[p];
   }
 }
 

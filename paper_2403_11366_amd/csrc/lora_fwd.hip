@@ -4,11 +4,12 @@
 // Kernels (one launch per call; a U pass before it for rank > 16, on the
 // 256 x 256 tile and under dropout, and a second GEMM launch when the columns
 // are split between two tiles):
-//   lora_fwd_ks_kernel  the 128 x 256 tile for rank <= 16 (the 7B q_proj
-//                       shape): wave pairs split the k substeps of each
-//                       stage, see its own comment.
-//   lora_fwd_kernel     the other tiles (256 x 256, 128 x 256, 128 x 128)
-//                       and grouped launches; described below.
+//   lora_fwd_kernel     the 256 x 256 tile (below), and the 128-token tiles of
+//                       lora_fwd_ks.hpp: 128 x 128, 128 x 192 and, beyond rank
+//                       16, 128 x 256.
+//   lora_fwd_ks_kernel  the 128 x 256 tile up to rank 16 (the 7B q_proj shape).
+//   lora_fwd_pair_ks_kernel  128 x 128 tiles, each computed by a pair of
+//                       workgroups of 64 tokens (lora_fwd_ks.hpp).
 //   lora_u_kernel       U = X A^T on its own (under dropout with the keep
 //                       mask applied; for a group, of every projection in one
 //                       launch), followed by a GEMM tile without U columns.
@@ -16,92 +17,52 @@
 // A launch covers the output columns from n_begin on (plan_gemm_split);
 // the launch whose range starts at column 0 writes U.
 //
-// lora_fwd_kernel: each workgroup owns a BM x BN tile of Y (BM tokens x BN output
-// features) and walks k in stages of 64.  Per stage it stages three
-// k-contiguous tiles in LDS -- X[BM rows], W[BN rows] and the LoRA
-// down-projection A padded to RP rows -- so each X tile is read once and
-// feeds both the W columns and the r extra "U columns".  Global loads run two
-// stages ahead in registers and are stored to the free LDS buffer piece by
-// piece during the stage before their use (one barrier per stage).
+// Every tile walks k in stages of 64.  Per stage it stages k-contiguous tiles
+// in LDS -- X rows, W rows and, where U is formed beside W, A padded to 16
+// rows -- so each X tile is read once for both products.
 //
 // Matrix-core products use v_mfma_f32_32x32x16_bf16 and are formed transposed
-// (W and A as the A operand, X as the B operand), so each lane's accumulator
-// holds runs of 4 consecutive output features of one token.
-//
-// The U columns of a token fragment are accumulated by the waves that share
-// it (each wave owns fixed fragments and k substeps, so the U products are
-// branch-free).  After the k loop the epilogue parks U in LDS, writes it out
-// (first tile column only), and adds s U B^T to the accumulators with a
-// short matrix-core pass over t in which s U enters as a bf16 high part and
-// a bf16 low part, then rounds Y to bf16 and stores it through a per-wave
-// LDS block (store_block_32x64) so that stores write whole 128-byte rows.
+// (W as the A operand, X as the B operand), so each lane's accumulator holds
+// runs of 4 consecutive output features of one token.  After the k loop the
+// epilogue adds s U B^T to the accumulators with a short matrix-core pass over
+// t in which s U enters as a bf16 high part and a bf16 low part, then rounds Y
+// to bf16 and stores it through a per-wave LDS block so that stores write
+// whole row pieces.
 #include <type_traits>
 
 #include "lora_device.hpp"
+#include "lora_fwd_ks.hpp"
 #include "lora_launch.hpp"
 #include "lora_plan.hpp"
 
 namespace lora {
 
-// With GRP the grid covers the output tiles of a group of projections that
-// read the same X (FwdGroup): each workgroup first selects its projection's
-// W, A, B, Y, U and n, then runs exactly the single-projection tile.
-//
-// With UPRE, U = X A^T has been computed by lora_u_kernel: the k loop stages
-// no A rows and runs no U products, and the epilogue reads U back.
-//
-// KFULL (k a multiple of 64): the loads carry no k-bound checks, and below the
-// 256 x 256 tile the stages run in pairs with compile-time LDS buffers.
-//
-// DMA (the 256 x 256 tile with KFULL): each stage is copied from
+constexpr int kBigStage = 512 * 128;   // bytes of a 64-wide stage of the 256 x 256 tile
+
+// The 256 x 256 tile: eight waves of 128 x 64, two 64-wide stages in LDS, U
+// from the U pass (read back in the epilogue).  Each stage is copied from
 // global memory straight into the free LDS buffer at the top of the stage
 // before it (one 16-byte chunk per lane per copy instruction, the swizzle
 // applied to the global addresses), with no staging registers; the stage's
-// closing barrier waits for those copies (copy_barrier).  With UPRE as well,
-// the fragment reads are issued as inline assembly, two register sets deep
-// (see the loop below).
-template <int BM, int BN, int WM, int WN, int RP, bool GRP, bool UPRE, bool KFULL, bool DMA>
-__global__ __launch_bounds__(64 * WM * WN) void lora_fwd_kernel(
-    const u16* __restrict__ X, const u16* __restrict__ W, const u16* __restrict__ A,
-    const u16* __restrict__ B, u16* __restrict__ Y,
-    float* __restrict__ U, int m, int n, int k, int r, float s, int tiles_m, int tiles_n,
-    int n_begin, FwdGroup grp) {
+// closing barrier waits for those copies (copy_barrier).  KFULL: k a multiple
+// of 64 (otherwise each copy checks its k bound).  With GRP the grid covers
+// the output tiles of a group of projections that read the same X (FwdGroup):
+// each workgroup first selects its projection's W, B, Y, U and n.
+template <int RP, bool GRP, bool KFULL>
+__device__ __forceinline__ void fwd_big_tile(const u16* __restrict__ X, const u16* __restrict__ W,
+                                             const u16* __restrict__ B, u16* __restrict__ Y,
+                                             const float* __restrict__ U, int m, int n, int k, int r, float s, int tm,
+                                             int tn, int n_begin, const FwdGroup& grp, char* smem) {
+  constexpr int BM = 256, BN = 256, WM = 2, WN = 4;
   constexpr int NW = WM * WN;
   constexpr int NT = 64 * NW;
   constexpr int WTI = BM / WM, WTJ = BN / WN;   // tokens, features per wave
   constexpr int FI = WTI / 32;                   // token fragments (B operand)
   constexpr int FJ = WTJ / 32;                   // feature fragments (A operand)
-  // U work.  For RP = 16 (rank <= 16) U runs on v_mfma_f32_16x16x32_bf16: a
-  // wave row's WTI tokens form WTI/16 groups of 16, GPW per wave, each over
-  // the 32-wide halves of the stage (substeps 0-1 and 2-3).  For RP >= 32 it
-  // runs on the 32x32x16 form: the FI token fragments of a wave row are shared
-  // by its WN waves; with FI >= WN each wave owns FUW fragments, with FI < WN
-  // NDUP waves share a fragment and split its k substeps (partial sums added in
-  // the epilogue).
-  constexpr bool U16 = RP == 16;
-  constexpr int FT = U16 ? 1 : RP / 32;          // U row fragments (A operand)
-  constexpr int FUW = U16 ? 1 : (FI >= WN ? FI / WN : 1);
-  constexpr int NDUP = U16 ? 1 : (FI >= WN ? 1 : WN / FI);
-  constexpr int GPW = U16 ? (WTI / 16) / WN : 1;
-  constexpr int RPS = UPRE ? 0 : RP;             // A rows staged per stage
-  constexpr int ROWS = BM + BN + RPS;            // 128-byte rows per 64-wide stage
-  constexpr int STAGE = ROWS * 128;
-  constexpr int CX = BM * 8, CW = BN * 8, CA = RPS * 8;  // 16-byte chunks per region
-  constexpr int LX = (CX + NT - 1) / NT, LW = (CW + NT - 1) / NT, LA = UPRE ? 1 : (CA + NT - 1) / NT;
-  static_assert(WTI % 32 == 0 && WTJ % 32 == 0 && (U16 || RP % 32 == 0), "32x32 fragments");
-  static_assert(!U16 || ((WTI / 16) % WN == 0 && GPW >= 1), "U groups split evenly");
-  static_assert(CX % 64 == 0 && CW % 64 == 0 && CA % 64 == 0, "regions end on wave boundaries");
-  static_assert(U16 || (FI >= WN ? FI % WN == 0 : WN % FI == 0), "U fragments split evenly");
-  static_assert(4 % NDUP == 0, "U substeps split evenly");
-  static_assert(2 * STAGE <= 160 * 1024, "LDS budget");
+  constexpr int STAGE = kBigStage;
+  static_assert(STAGE == (BM + BN) * 128 && 2 * STAGE <= 160 * 1024, "128-byte rows per 64-wide stage");
   constexpr int RPU = RP + 4, RPB = RP + 8;     // padded row lengths of the epilogue's U and B copies
-  constexpr int NUS = UPRE ? 1 : NDUP;           // U copies in the epilogue
-  static_assert(NUS * BM * RPU * 4 + BN * RPB * 2 <= 2 * STAGE, "epilogue LDS reuse");
-
-  __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
-
-  int tm, tn;
-  tile_coords(tiles_m, tiles_n, 8, (int)blockIdx.x, tm, tn);
+  static_assert(BM * RPU * 4 + BN * RPB * 2 <= 2 * STAGE, "epilogue LDS reuse");
   if (GRP) {   // projection of this column tile (uniform; compile-time indices only)
     int sel = 0;
 #pragma unroll
@@ -110,7 +71,7 @@ __global__ __launch_bounds__(64 * WM * WN) void lora_fwd_kernel(
 #pragma unroll
     for (int q = 0; q < kMaxGroup; ++q)
       if (q == sel) {
-        W = grp.W[q]; A = grp.A[q]; B = grp.B[q]; Y = grp.Y[q]; U = grp.U[q];
+        W = grp.W[q]; B = grp.B[q]; Y = grp.Y[q]; U = grp.U[q];
         n = grp.n[q];
         tn -= grp.tile0[q];
       }
@@ -120,330 +81,111 @@ __global__ __launch_bounds__(64 * WM * WN) void lora_fwd_kernel(
   const int wave = uniform(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int g = lane >> 5, c32 = lane & 31;
-  const int g16 = lane >> 4, c16 = lane & 15;
-  const int udup = NDUP > 1 ? wn / FI : 0;       // which share of the U substeps
 
   const uint32_t rowbytes = (uint32_t)k * 2;
   const __amdgpu_buffer_rsrc_t rsX = make_rsrc(X + (size_t)m0 * k, (uint64_t)min(BM, m - m0) * rowbytes);
   const __amdgpu_buffer_rsrc_t rsW = make_rsrc(W + (size_t)n0 * k, (uint64_t)min(BN, n - n0) * rowbytes);
-  const __amdgpu_buffer_rsrc_t rsA = make_rsrc(A, (uint64_t)r * rowbytes);
-
-  // Register staging of one k-block of the three regions: thread chunk
-  // q = tid + i NT of a region is row q/8, k-chunk q%8 (coalesced 128-byte
-  // rows).  The block moves in four pieces, one per 16-wide substep of the
-  // stage that stores it: 0 = X rows, 1 and 2 = the two halves of the W rows,
-  // 3 = A rows.
-  constexpr int LW1 = (LW + 1) / 2;
-  int4v gx[LX], gw[LW], ga[LA];
-  auto gload = [&](int kb, int piece) LORA_INLINE {
-    const int k0 = kb * 64;
-    if (piece == 0) {
-#pragma unroll
-      for (int i = 0; i < LX; ++i) {
-        const int q = tid + i * NT;
-        if (CX % NT != 0 && wave * 64 + i * NT >= CX) break;   // wave-uniform
-        const int kk = k0 + 8 * (q & 7);
-        gx[i] = buf_load16(rsX, (KFULL || kk < k) ? (uint32_t)(q >> 3) * rowbytes + (uint32_t)kk * 2 : kOOB);
-      }
-    } else if (piece <= 2) {
-#pragma unroll
-      for (int i = piece == 1 ? 0 : LW1; i < (piece == 1 ? LW1 : LW); ++i) {
-        const int q = tid + i * NT;
-        if (CW % NT != 0 && wave * 64 + i * NT >= CW) break;   // wave-uniform
-        const int kk = k0 + 8 * (q & 7);
-        gw[i] = buf_load16(rsW, (KFULL || kk < k) ? (uint32_t)(q >> 3) * rowbytes + (uint32_t)kk * 2 : kOOB);
-      }
-    } else if (!UPRE) {
-#pragma unroll
-      for (int i = 0; i < LA; ++i) {
-        const int q = tid + i * NT;
-        if (CA % NT != 0 && wave * 64 + i * NT >= CA) break;   // wave-uniform
-        const int kk = k0 + 8 * (q & 7);
-        ga[i] = buf_load16(rsA, (KFULL || kk < k) ? (uint32_t)(q >> 3) * rowbytes + (uint32_t)kk * 2 : kOOB);
-      }
-    }
-  };
-  auto swrite = [&](int buf, int piece) LORA_INLINE {
-    char* sb = smem + buf * STAGE;
-    if (piece == 0) {
-#pragma unroll
-      for (int i = 0; i < LX; ++i) {
-        const int q = tid + i * NT;
-        if (CX % NT != 0 && wave * 64 + i * NT >= CX) break;   // wave-uniform
-        *reinterpret_cast<int4v*>(sb + kc_offset(q >> 3, q & 7)) = gx[i];
-      }
-    } else if (piece <= 2) {
-#pragma unroll
-      for (int i = piece == 1 ? 0 : LW1; i < (piece == 1 ? LW1 : LW); ++i) {
-        const int q = tid + i * NT;
-        if (CW % NT != 0 && wave * 64 + i * NT >= CW) break;   // wave-uniform
-        *reinterpret_cast<int4v*>(sb + BM * 128 + kc_offset(q >> 3, q & 7)) = gw[i];
-      }
-    } else if (!UPRE) {
-#pragma unroll
-      for (int i = 0; i < LA; ++i) {
-        const int q = tid + i * NT;
-        if (CA % NT != 0 && wave * 64 + i * NT >= CA) break;   // wave-uniform
-        *reinterpret_cast<int4v*>(sb + (BM + BN) * 128 + kc_offset(q >> 3, q & 7)) = ga[i];
-      }
-    }
-  };
 
   floatx16 acc[FJ][FI];
-  floatx16 uacc[FT][FUW];      // U on the 32x32x16 form (RP >= 32)
-  floatx4 uacc16[GPW];         // U on the 16x16x32 form (RP = 16)
-#pragma unroll
-  for (int a = 0; a < GPW; ++a) uacc16[a] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int a = 0; a < FJ; ++a)
 #pragma unroll
     for (int b = 0; b < FI; ++b) acc[a][b] = floatx16{};
+  short8 fw[2][FJ], fx[2][FI];
+  const int nkb = (k + 63) / 64;
+  using B0 = std::integral_constant<int, 0>;
+  using B1 = std::integral_constant<int, 1>;
+  // Copy i of a region fills its rows 64 i + 8 wave .. + 7: lane l takes
+  // position l % 8 of row l / 8 of the eight, which holds logical chunk
+  // (l % 8) ^ kc_swz(row) (the same for every i).
+  const int r8 = 8 * wave + (lane >> 3);
+  const int kcol = 8 * ((lane & 7) ^ kc_swz(r8));
+  const uint32_t voff = (uint32_t)r8 * rowbytes + (uint32_t)kcol * 2;
+  auto dload = [&](int kb, int buf) LORA_INLINE {
+    const uint32_t k0b = (uint32_t)kb * 128;
+    char* sb = smem + buf * STAGE + wave * 1024;
+    const bool ok = KFULL || kb * 64 + kcol < k;
 #pragma unroll
-  for (int a = 0; a < FT; ++a)
+    for (int i = 0; i < BM / 64; ++i)
+      dma16(rsX, ok ? voff + (uint32_t)(64 * i) * rowbytes : kOOB, k0b, sb + i * 8192);
 #pragma unroll
-    for (int b = 0; b < FUW; ++b) uacc[a][b] = floatx16{};
-  int urow[FUW];
-#pragma unroll
-  for (int fu = 0; fu < FUW; ++fu) urow[fu] = wm * WTI + 32 * ((wn + WN * fu) % FI) + c32;
-  int urow16[GPW];
-#pragma unroll
-  for (int gg = 0; gg < GPW; ++gg) urow16[gg] = wm * WTI + 16 * (wn * GPW + gg) + c16;
-
-  // Fragments of the next 16-wide substep are read while the current one
-  // multiplies (two register sets, p = substep parity).  The U products of a
-  // shared token fragment run on substeps ks % NDUP == 0 only: there share
-  // udup multiplies the k columns of substep ks + udup, so every wave executes
-  // the same instruction stream.
-  short8 fw[2][FJ], fx[2][FI], fa[2][FT], fxu[2][FUW];
-  short8 fa16[2], fxu16[2][GPW];
-  auto read_frags = [&](const char* sb, int ks, int p) LORA_INLINE {
-    const char* Xs = sb;
-    const char* Ws = sb + BM * 128;
-    const char* As = sb + (BM + BN) * 128;
-    const int ch = 2 * ks + g;
-#pragma unroll
-    for (int fj = 0; fj < FJ; ++fj) fw[p][fj] = kc_read(Ws, wn * WTJ + 32 * fj + c32, ch);
-#pragma unroll
-    for (int fi = 0; fi < FI; ++fi) fx[p][fi] = kc_read(Xs, wm * WTI + 32 * fi + c32, ch);
-    if (UPRE) {
-    } else if (U16) {
-      if (ks % 2 == 0) {   // the 32-wide half starting at substep ks: chunks 2 ks + g16
-        fa16[p] = kc_read(As, c16, 2 * ks + g16);
-#pragma unroll
-        for (int gg = 0; gg < GPW; ++gg) fxu16[p][gg] = kc_read(Xs, urow16[gg], 2 * ks + g16);
-      }
-    } else if (ks % NDUP == 0) {
-      const int uch = ch + 2 * udup;
-#pragma unroll
-      for (int ft = 0; ft < FT; ++ft) fa[p][ft] = kc_read(As, 32 * ft + c32, uch);
-#pragma unroll
-      for (int fu = 0; fu < FUW; ++fu) fxu[p][fu] = kc_read(Xs, urow[fu], uch);
-    }
+    for (int i = 0; i < BN / 64; ++i)
+      dma16(rsW, ok ? voff + (uint32_t)(64 * i) * rowbytes : kOOB, k0b, sb + BM * 128 + i * 8192);
   };
-  auto multiply = [&](int p, int ks) LORA_INLINE {
+  dload(0, 0);
+  copy_barrier<0>();
+  // Fragment reads as inline assembly, two register sets deep: the reads
+  // of substep ks+1 are issued before the products of substep ks, which
+  // wait (s_waitcnt lgkmcnt) only for their own six reads.  (Left to
+  // itself the compiler folds the two sets into one and waits for each
+  // pair of reads right before its products.)  Chunk c of row p sits at
+  // p*128 | ((c ^ kc_swz(p)) << 4); for the lane's chunk 2ks + g that is
+  // base ^ (ks << 5) with base = p*128 | ((kc_swz(p) ^ g) << 4), and the
+  // fragments of a wave are 32 rows (4096 bytes) apart with the same
+  // swizzle, so one address register per operand and buffer suffices.
+  static_assert(FJ == 2 && FI == 4, "reads per substep");
+  const uint32_t sg = (uint32_t)((kc_swz(c32) ^ g) << 4);
+  const uint32_t wb0 = lds_addr(smem + BM * 128 + (wn * WTJ + c32) * 128) | sg;
+  const uint32_t xb0 = lds_addr(smem + (wm * WTI + c32) * 128) | sg;
+  auto areads = [&](int buf, int ks, int p) LORA_INLINE {   // (ks, buf, p: constants after inlining)
+    const uint32_t wb = wb0 + (uint32_t)buf * STAGE, xb = xb0 + (uint32_t)buf * STAGE;
+    uint32_t ta, tb;
+    asm volatile(
+        "v_xor_b32 %[ta], %[kx], %[wb]\n\t"
+        "v_xor_b32 %[tb], %[kx], %[xb]\n\t"
+        "ds_read_b128 %[w0], %[ta]\n\t"
+        "ds_read_b128 %[w1], %[ta] offset:4096\n\t"
+        "ds_read_b128 %[x0], %[tb]\n\t"
+        "ds_read_b128 %[x1], %[tb] offset:4096\n\t"
+        "ds_read_b128 %[x2], %[tb] offset:8192\n\t"
+        "ds_read_b128 %[x3], %[tb] offset:12288"
+        : [w0] "=v"(fw[p][0]), [w1] "=v"(fw[p][1]), [x0] "=v"(fx[p][0]), [x1] "=v"(fx[p][1]),
+          [x2] "=v"(fx[p][2]), [x3] "=v"(fx[p][3]), [ta] "=&v"(ta), [tb] "=&v"(tb)
+        : [wb] "v"(wb), [xb] "v"(xb), [kx] "i"(ks << 5));
+  };
+  auto amult = [&](int p, bool last) LORA_INLINE {
+    if (last)
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : "+v"(fw[p][0]), "+v"(fw[p][1]), "+v"(fx[p][0]), "+v"(fx[p][1]), "+v"(fx[p][2]),
+                     "+v"(fx[p][3]));
+    else
+      asm volatile("s_waitcnt lgkmcnt(6)"
+                   : "+v"(fw[p][0]), "+v"(fw[p][1]), "+v"(fx[p][0]), "+v"(fx[p][1]), "+v"(fx[p][2]),
+                     "+v"(fx[p][3]));
 #pragma unroll
     for (int fi = 0; fi < FI; ++fi)
 #pragma unroll
       for (int fj = 0; fj < FJ; ++fj) acc[fj][fi] = mfma32x32x16(fw[p][fj], fx[p][fi], acc[fj][fi]);
-    if (UPRE) {
-    } else if (U16) {
-      if (ks % 2 == 0) {
-#pragma unroll
-        for (int gg = 0; gg < GPW; ++gg) uacc16[gg] = mfma16x16x32(fa16[p], fxu16[p][gg], uacc16[gg]);
-      }
-    } else if (ks % NDUP == 0) {
-#pragma unroll
-      for (int fu = 0; fu < FUW; ++fu)
-#pragma unroll
-        for (int ft = 0; ft < FT; ++ft) uacc[ft][fu] = mfma32x32x16(fa[p][ft], fxu[p][fu], uacc[ft][fu]);
-    }
   };
-
-  // Pipeline.  At the top of stage kb the staging registers hold k-block
-  // kb+1 (loaded one stage earlier); piece ks of it is stored to the free LDS
-  // buffer at substep ks, and its registers are then reloaded with block kb+2.
-  // With ROT the loop is rotated by one substep: the products of substep 3 of
-  // stage kb-1 are issued after the barrier, while the first fragments of
-  // stage kb are being read (their operands are zeroed for stage 0, adding
-  // exact zeros).  The 256 x 256 tile has no registers to spare for it.  The k
-  // loop is peeled so the steady state carries no conditionals.
-  constexpr bool ROT = BM * BN < 256 * 256;
-  if (ROT) {
-#pragma unroll
-    for (int j = 0; j < FJ; ++j) fw[1][j] = short8{};
-#pragma unroll
-    for (int j = 0; j < FI; ++j) fx[1][j] = short8{};
-#pragma unroll
-    for (int j = 0; j < FT; ++j) fa[1][j] = short8{};
-#pragma unroll
-    for (int j = 0; j < FUW; ++j) fxu[1][j] = short8{};
-    fa16[1] = short8{};
-#pragma unroll
-    for (int j = 0; j < GPW; ++j) fxu16[1][j] = short8{};
-  }
-  // bufc: the stage's LDS buffer as a compile-time constant, or -1 for the
-  // parity of kb at run time
-  auto stage = [&](int kb, auto bufc, bool write_next, bool load_next) LORA_INLINE {
+  auto astage = [&](int kb, auto bufc, bool load_next) LORA_INLINE {
     constexpr int BUF = decltype(bufc)::value;
-    const int cur = BUF >= 0 ? BUF : (kb & 1);
-    const char* sb = smem + cur * STAGE;
-    read_frags(sb, 0, 0);
-    if (ROT) multiply(1, 3);
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      if (write_next) swrite(cur ^ 1, ks);
-      if (load_next) gload(kb + 2, ks);
-      if (ks < 3) read_frags(sb, ks + 1, (ks + 1) & 1);
-      if (ks < 3 || !ROT) multiply(ks & 1, ks);
-    }
-    __syncthreads();
-  };
-  const int nkb = (k + 63) / 64;
-  using B0 = std::integral_constant<int, 0>;
-  using B1 = std::integral_constant<int, 1>;
-  using BR = std::integral_constant<int, -1>;
-  if constexpr (DMA) {
-    static_assert(KFULL && !ROT, "copy pipeline shape");
-    // Copy instruction j of a region covers its rows 8j .. 8j+7: lane l takes
-    // position l % 8 of row 8j + l / 8, i.e. logical chunk (l % 8) ^ kc_swz(row).
-    constexpr int JX = BM / 8, JW = BN / 8, JA = RPS / 8;
-    static_assert(JX % NW == 0 && JW % NW == 0, "copies split evenly");
-    const int dl_row = lane >> 3, dl_cp = lane & 7;
-    auto voff = [&](int j) LORA_INLINE {
-      const int row = 8 * j + dl_row;
-      return (uint32_t)row * rowbytes + (uint32_t)((dl_cp ^ kc_swz(row)) << 4);
-    };
-    auto dload = [&](int kb, int buf) LORA_INLINE {
-      const uint32_t k0b = (uint32_t)kb * 128;
-      char* sb = smem + buf * STAGE;
-#pragma unroll
-      for (int i = 0; i < JX / NW; ++i) dma16(rsX, voff(wave + NW * i), k0b, sb + (wave + NW * i) * 1024);
-#pragma unroll
-      for (int i = 0; i < JW / NW; ++i)
-        dma16(rsW, voff(wave + NW * i), k0b, sb + BM * 128 + (wave + NW * i) * 1024);
-#pragma unroll
-      for (int i = 0; i < (JA + NW - 1) / NW; ++i)
-        if (wave + NW * i < JA) dma16(rsA, voff(wave + NW * i), k0b, sb + (BM + BN) * 128 + (wave + NW * i) * 1024);
-    };
-    dload(0, 0);
+    if (load_next) dload(kb + 1, BUF ^ 1);   // read in stage kb-1, free since its barrier
+    areads(BUF, 0, 0);
+    areads(BUF, 1, 1);
+    amult(0, false);
+    areads(BUF, 2, 0);
+    amult(1, false);
+    areads(BUF, 3, 1);
+    amult(0, false);
+    amult(1, true);
     copy_barrier<0>();
-    if constexpr (UPRE) {
-      // Fragment reads as inline assembly, two register sets deep: the reads
-      // of substep ks+1 are issued before the products of substep ks, which
-      // wait (s_waitcnt lgkmcnt) only for their own six reads.  (Left to
-      // itself the compiler folds the two sets into one and waits for each
-      // pair of reads right before its products.)  Chunk c of row p sits at
-      // p*128 | ((c ^ kc_swz(p)) << 4); for the lane's chunk 2ks + g that is
-      // base ^ (ks << 5) with base = p*128 | ((kc_swz(p) ^ g) << 4), and the
-      // fragments of a wave are 32 rows (4096 bytes) apart with the same
-      // swizzle, so one address register per operand and buffer suffices.
-      static_assert(FJ == 2 && FI == 4, "reads per substep");
-      const uint32_t sg = (uint32_t)((kc_swz(c32) ^ g) << 4);
-      const uint32_t wb0 = lds_addr(smem + BM * 128 + (wn * WTJ + c32) * 128) | sg;
-      const uint32_t xb0 = lds_addr(smem + (wm * WTI + c32) * 128) | sg;
-      auto areads = [&](int buf, int ks, int p) LORA_INLINE {   // (ks, buf, p: constants after inlining)
-        const uint32_t wb = wb0 + (uint32_t)buf * STAGE, xb = xb0 + (uint32_t)buf * STAGE;
-        uint32_t ta, tb;
-        asm volatile(
-            "v_xor_b32 %[ta], %[kx], %[wb]\n\t"
-            "v_xor_b32 %[tb], %[kx], %[xb]\n\t"
-            "ds_read_b128 %[w0], %[ta]\n\t"
-            "ds_read_b128 %[w1], %[ta] offset:4096\n\t"
-            "ds_read_b128 %[x0], %[tb]\n\t"
-            "ds_read_b128 %[x1], %[tb] offset:4096\n\t"
-            "ds_read_b128 %[x2], %[tb] offset:8192\n\t"
-            "ds_read_b128 %[x3], %[tb] offset:12288"
-            : [w0] "=v"(fw[p][0]), [w1] "=v"(fw[p][1]), [x0] "=v"(fx[p][0]), [x1] "=v"(fx[p][1]),
-              [x2] "=v"(fx[p][2]), [x3] "=v"(fx[p][3]), [ta] "=&v"(ta), [tb] "=&v"(tb)
-            : [wb] "v"(wb), [xb] "v"(xb), [kx] "i"(ks << 5));
-      };
-      auto amult = [&](int p, bool last) LORA_INLINE {
-        if (last)
-          asm volatile("s_waitcnt lgkmcnt(0)"
-                       : "+v"(fw[p][0]), "+v"(fw[p][1]), "+v"(fx[p][0]), "+v"(fx[p][1]), "+v"(fx[p][2]),
-                         "+v"(fx[p][3]));
-        else
-          asm volatile("s_waitcnt lgkmcnt(6)"
-                       : "+v"(fw[p][0]), "+v"(fw[p][1]), "+v"(fx[p][0]), "+v"(fx[p][1]), "+v"(fx[p][2]),
-                         "+v"(fx[p][3]));
-#pragma unroll
-        for (int fi = 0; fi < FI; ++fi)
-#pragma unroll
-          for (int fj = 0; fj < FJ; ++fj) acc[fj][fi] = mfma32x32x16(fw[p][fj], fx[p][fi], acc[fj][fi]);
-      };
-      auto astage = [&](int kb, auto bufc, bool load_next) LORA_INLINE {
-        constexpr int BUF = decltype(bufc)::value;
-        if (load_next) dload(kb + 1, BUF ^ 1);   // read in stage kb-1, free since its barrier
-        areads(BUF, 0, 0);
-        areads(BUF, 1, 1);
-        amult(0, false);
-        areads(BUF, 2, 0);
-        amult(1, false);
-        areads(BUF, 3, 1);
-        amult(0, false);
-        amult(1, true);
-        copy_barrier<0>();
-      };
-      int kb = 0;
-      for (; kb + 2 < nkb; kb += 2) {
-        astage(kb, B0{}, true);
-        astage(kb + 1, B1{}, true);
-      }
-      if (kb < nkb) astage(kb, B0{}, kb + 1 < nkb);
-      if (kb + 1 < nkb) astage(kb + 1, B1{}, false);
-    } else {
-      auto dstage = [&](int kb, auto bufc, bool load_next) LORA_INLINE {
-        constexpr int BUF = decltype(bufc)::value;
-        if (load_next) dload(kb + 1, BUF ^ 1);   // read in stage kb-1, free since its barrier
-        const char* sb = smem + BUF * STAGE;
-        read_frags(sb, 0, 0);
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          if (ks < 3) read_frags(sb, ks + 1, (ks + 1) & 1);
-          multiply(ks & 1, ks);
-        }
-        copy_barrier<0>();
-      };
-      int kb = 0;
-      for (; kb + 2 < nkb; kb += 2) {
-        dstage(kb, B0{}, true);
-        dstage(kb + 1, B1{}, true);
-      }
-      if (kb < nkb) dstage(kb, B0{}, kb + 1 < nkb);
-      if (kb + 1 < nkb) dstage(kb + 1, B1{}, false);
-    }
-  } else {
-#pragma unroll
-    for (int pc = 0; pc < 4; ++pc) gload(0, pc);
-#pragma unroll
-    for (int pc = 0; pc < 4; ++pc) swrite(0, pc);
-    __syncthreads();
-    if (nkb > 1) {
-#pragma unroll
-      for (int pc = 0; pc < 4; ++pc) gload(1, pc);
-    }
-    int kb = 0;
-    if constexpr (KFULL && BM * BN < 256 * 256) {
-      for (; kb + 3 < nkb; kb += 2) {
-        stage(kb, B0{}, true, true);
-        stage(kb + 1, B1{}, true, true);
-      }
-    }
-    for (; kb + 2 < nkb; ++kb) stage(kb, BR{}, true, true);
-    if (kb + 1 < nkb) stage(kb++, BR{}, true, false);
-    stage(kb, BR{}, false, false);
-    if (ROT) multiply(1, 3);
+  };
+  int kb = 0;
+  for (; kb + 2 < nkb; kb += 2) {
+    astage(kb, B0{}, true);
+    astage(kb + 1, B1{}, true);
   }
+  if (kb < nkb) astage(kb, B0{}, kb + 1 < nkb);
+  if (kb + 1 < nkb) astage(kb + 1, B1{}, false);
 
   // ---- epilogue ------------------------------------------------------------
-  // LDS reuse: Us [NUS][BM][RPU] fp32 partial U (summed in fixed order below),
-  // then Bs [BN][RPB] bf16 (B rows of this tile, zero beyond r and n).  The
+  // LDS reuse: Us [BM][RPU] fp32 U, then Bs [BN][RPB] bf16 (B rows of this tile, zero beyond r and n).  The
   // rows are padded by 16 bytes so that the 16 lanes of a read group, which
   // read 16 consecutive rows, fall in different banks.  Rows n0 .. n0+jn-1 of
   // B are contiguous, so they are fetched as 16-byte chunks of 8 elements, all
   // issued before the first wait, and scattered into Bs.
   float* Us = reinterpret_cast<float*>(smem);
-  u16* Bs = reinterpret_cast<u16*>(smem + NUS * BM * RPU * 4);
+  u16* Bs = reinterpret_cast<u16*>(smem + BM * RPU * 4);
   constexpr int BCH = (BN * RP / 8 + NT - 1) / NT;   // chunks per thread (r <= RP)
   const int jn = min(BN, n - n0);
   const int nch = jn * r / 8;                       // exact: n and n0 are multiples of 8
@@ -454,7 +196,7 @@ __global__ __launch_bounds__(64 * WM * WN) void lora_fwd_kernel(
     const int q = tid + i * NT;
     bv[i] = buf_load16(rsB, q < nch ? (uint32_t)q * 16 : kOOB);
   }
-  if (UPRE) {   // U of the tile's tokens from the U pass (zero beyond r and m), all loads issued before the first use
+  {   // U of the tile's tokens from the U pass (zero beyond r and m), all loads issued before the first use
     constexpr int UPT = BM * RP / NT;
     static_assert(BM * RP % NT == 0, "U values per thread");
     const __amdgpu_buffer_rsrc_t rsU = make_rsrc(U + (size_t)m0 * r, (uint64_t)min(BM, m - m0) * r * 4);
@@ -468,23 +210,6 @@ __global__ __launch_bounds__(64 * WM * WN) void lora_fwd_kernel(
     for (int i = 0; i < UPT; ++i) {
       const int e = tid + i * NT, il = e / RP, t = e - il * RP;
       Us[il * RPU + t] = uv[i];
-    }
-  } else if (U16) {   // lane holds token column c16 of its group, U rows t = 4 g16 .. +3
-#pragma unroll
-    for (int gg = 0; gg < GPW; ++gg)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) Us[urow16[gg] * RPU + 4 * g16 + q] = uacc16[gg][q];
-  } else {
-#pragma unroll
-    for (int fu = 0; fu < FUW; ++fu) {
-      const int il = urow[fu];
-#pragma unroll
-      for (int ft = 0; ft < FT; ++ft)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          const int t = 32 * ft + 8 * (q >> 2) + 4 * g + (q & 3);
-          Us[(udup * BM + il) * RPU + t] = uacc[ft][fu][q];
-        }
     }
   }
   for (int e = tid; e < BN * RPB / 8; e += NT) reinterpret_cast<int4v*>(Bs)[e] = int4v{0, 0, 0, 0};
@@ -507,22 +232,7 @@ __global__ __launch_bounds__(64 * WM * WN) void lora_fwd_kernel(
       }
     }
   }
-  if (NDUP > 1 && !UPRE) {  // fold the partial U sums into copy 0 (fixed order)
-    for (int e = tid; e < BM * RP; e += NT) {
-      const int o = (e / RP) * RPU + e % RP;
-      float v = Us[o];
-#pragma unroll
-      for (int d = 1; d < NDUP; ++d) v += Us[d * BM * RPU + o];
-      Us[o] = v;
-    }
-  }
   __syncthreads();
-  if (n0 == 0 && !UPRE) {   // U output: the first tile column writes it
-    for (int e = tid; e < BM * RP; e += NT) {
-      const int il = e / RP, t = e - il * RP;
-      if (m0 + il < m && t < r) U[(size_t)(m0 + il) * r + t] = Us[il * RPU + t];
-    }
-  }
 
   // acc += s U B^T, formed as Y^T += B (sU)^T over t in blocks of 16, each
   // block once with the high and once with the low bf16 part of sU.
@@ -566,6 +276,51 @@ __global__ __launch_bounds__(64 * WM * WN) void lora_fwd_kernel(
     store_block_32x64(acc[0][fi], acc[1][fi], smem + wave * kYsBytes, Y + (size_t)i0 * n + j0, (size_t)n, m - i0,
                       n - j0, lane);
   }
+}
+
+// One kernel template for the 256 x 256 tile (BIG) and the 128-token tiles that
+// lora_fwd_ks_kernel does not serve.
+template <int BM, int BN, int WM, int WN, int RP, bool GRP, bool UPRE, bool KFULL, bool BIG>
+__global__ __launch_bounds__(512) void lora_fwd_kernel(
+    const u16* __restrict__ X, const u16* __restrict__ W, const u16* __restrict__ A, const u16* __restrict__ B,
+    u16* __restrict__ Y, float* __restrict__ U, int m, int n, int k, int r, float s, int tiles_m, int tiles_n,
+    int n_begin, FwdGroup grp) {
+  static_assert(BIG == (BM == 256) && (BM == 256 ? BN == 256 && UPRE : BM == 128), "tile shapes");
+  int tm, tn;
+  tile_coords(tiles_m, tiles_n, 8, (int)blockIdx.x, tm, tn);
+  if constexpr (BIG) {
+    __shared__ __attribute__((aligned(1024))) char smem[2 * kBigStage];
+    fwd_big_tile<RP, GRP, KFULL>(X, W, B, Y, U, m, n, k, r, s, tm, tn, n_begin, grp, smem);
+  } else {
+    __shared__ __attribute__((aligned(1024))) char smem[fwd_ks_smem<128, BN, RP, UPRE>()];
+    fwd_ks_tile<128, BN, RP, GRP, UPRE, KFULL>(X, W, A, B, Y, U, m, n, k, r, s, tm * 128, tn, n_begin, grp, smem);
+  }
+}
+
+// 128 x 128 tiles, each computed by a pair of workgroups of 64 tokens, for
+// outputs of too few tiles to fill the chip.  Pair p's workgroups are 8 apart
+// (the last few, when the tiles are no multiple of 8, at most 7 apart), so
+// both run on the same XCD and share the tile's W rows in its L2.
+template <int RP, bool GRP, bool KFULL, bool UPRE>
+__global__ __launch_bounds__(512) void lora_fwd_pair_ks_kernel(
+    const u16* __restrict__ X, const u16* __restrict__ W, const u16* __restrict__ A, const u16* __restrict__ B,
+    u16* __restrict__ Y, float* __restrict__ U, int m, int n, int k, int r, float s, int tiles_m, int tiles_n,
+    int n_begin, FwdGroup grp) {
+  __shared__ __attribute__((aligned(1024))) char smem[fwd_ks_smem<64, 128, RP, UPRE>()];
+  const int b = (int)blockIdx.x, tiles = tiles_m * tiles_n, whole = tiles & ~7, rest = tiles & 7;
+  int p, h;
+  if (b < 2 * whole) {
+    p = (b >> 4) * 8 + (b & 7);
+    h = (b >> 3) & 1;
+  } else {
+    h = (b - 2 * whole) / rest;
+    p = whole + (b - 2 * whole) - h * rest;
+  }
+  int tm, tn;
+  tile_coords(tiles_m, tiles_n, 8, p, tm, tn);
+  const int m0 = tm * 128 + 64 * h;
+  if (m0 >= m) return;   // (uniform) the second half of a ragged last tile row
+  fwd_ks_tile<64, 128, RP, GRP, UPRE, KFULL>(X, W, A, B, Y, U, m, n, k, r, s, m0, tn, n_begin, grp, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -719,31 +474,15 @@ __global__ __launch_bounds__(256) void lora_u_kernel(const u16* __restrict__ X, 
 }
 
 // ---------------------------------------------------------------------------
-// The 128 x 256 tile for rank <= 16 with the k substeps split between wave
-// pairs.  Eight waves: wave (wk, wm, wn) multiplies the 64 tokens wm and the
-// 128 features wn of the tile over substeps 2 wk and 2 wk + 1 of every 64-wide
-// stage (the 32-wide k half wk).  Per stage a wave issues as many products as
-// in the 2 x 4 layout of 64 x 64 wave tiles but reads 12 operand fragments
-// instead of 16, and two waves still share each SIMD.  The U columns run on
-// v_mfma_f32_16x16x32_bf16: wave (wk, wm, wn) owns the 16-token groups
-// 2 wn, 2 wn + 1 of its token half, over its k half.
-//
-// After the k loop the two k-half partial sums of each output are added in
-// fixed order through LDS: wave wk keeps feature fragments 2 wk, 2 wk + 1 and
-// sends the other two to its partner, so each wave then holds a complete
-// 64 x 64 block (features wn 128 + 64 wk ..) for the epilogue, which is the one
-// of the 2 x 4 layout.  GRP selects the projection of a grouped launch as in
-// lora_fwd_kernel.
-//
-// DMA (k a multiple of 64; used for launches of at most one round): the
-// stages go from global memory straight into three LDS buffers (one 16-byte
-// chunk per lane per copy instruction, the chunk swizzle applied to the
-// global addresses), two stages ahead and without staging registers; each
-// stage ends with a barrier that waits only for this wave's copies of the
-// next stage (copy_barrier).
-//
-// UPRE (LoRA dropout: U from the masked U pass): the stages hold no A rows,
-// the loop runs no U products, and the epilogue reads U back.
+// The 128 x 256 tile for rank <= 16, the k substeps of each stage split between
+// wave pairs.  DMA (single-round launches with whole stages): fwd_ks_tile.
+// Otherwise the same split with both halves of a pair in step and the stages
+// staged in registers two ahead, stored to the free one of two LDS buffers
+// during the stage before their use.  Wave (wk, wm, wn) multiplies the 64
+// tokens wm and the 128 features wn of the tile over substeps 2 wk and 2 wk + 1
+// of every 64-wide stage; U as in fwd_ks_tile.  After the k loop wave wk keeps
+// feature fragments 2 wk, 2 wk + 1 and sends the other two to its partner, so
+// each wave then holds a complete 64 x 64 block (features wn 128 + 64 wk ..).
 template <bool GRP, bool KFULL, bool DMA, bool UPRE>
 __global__ __launch_bounds__(512) void lora_fwd_ks_kernel(
     const u16* __restrict__ X, const u16* __restrict__ W, const u16* __restrict__ A,
@@ -759,15 +498,17 @@ __global__ __launch_bounds__(512) void lora_fwd_ks_kernel(
   constexpr int LX = CX / NT, LW = CW / NT, LA = UPRE ? 1 : (CA + NT - 1) / NT;
   static_assert(!(UPRE && GRP), "U from the U pass only for single projections");
   constexpr int XCH = 8 * 16 * 1024;              // exchange: 8 waves x 32 fragments x 64 lanes x 4 B
-  static_assert(!DMA || KFULL, "the copies carry no k-bound checks");
-  constexpr int NBUF = DMA ? 3 : 2;                       // LDS stage buffers
-  constexpr int BS_OFF = DMA ? NBUF * STAGE : XCH + 2 * BM * RP * 4;
-  constexpr int EPI = (BS_OFF > XCH + 2 * BM * RP * 4 ? BS_OFF : XCH + 2 * BM * RP * 4) + BN * RP * 2;
-  constexpr int SMEM = EPI > NBUF * STAGE ? EPI : NBUF * STAGE;
+  constexpr int BS_OFF = XCH + 2 * BM * RP * 4;
+  constexpr int EPI = BS_OFF + BN * RP * 2;
+  constexpr int SMEM = DMA ? fwd_ks_smem<128, 256, 16, UPRE>() : (EPI > 2 * STAGE ? EPI : 2 * STAGE);
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
   int tm, tn;
   tile_coords(tiles_m, tiles_n, 8, (int)blockIdx.x, tm, tn);
+  if constexpr (DMA) {
+    fwd_ks_tile<128, 256, 16, GRP, UPRE, KFULL>(X, W, A, B, Y, U, m, n, k, r, s, tm * 128, tn, n_begin, grp, smem);
+    return;
+  } else {
   if (GRP) {
     int sel = 0;
 #pragma unroll
@@ -908,83 +649,6 @@ __global__ __launch_bounds__(512) void lora_fwd_ks_kernel(
   using B1 = std::integral_constant<int, 1>;
   using BR = std::integral_constant<int, -1>;
   u16* Bs = reinterpret_cast<u16*>(smem + BS_OFF);   // B rows for the epilogue, staged in the prologue
-  if constexpr (DMA) {
-  const int nkb = (k + 63) / 64;
-  // Copies straight into LDS: instruction j of a tile covers its rows 8j ..
-  // 8j + 7, lane l position l % 8 of row 8j + l / 8, which holds the row's
-  // logical chunk (l % 8) ^ kc_swz(row) (the swizzle is applied on the global
-  // side).  Per stage a wave issues 2 X, 4 W and (waves 0, 1) 1 A copies.
-  const int dl_row = lane >> 3, dl_cp = lane & 7;
-  auto voff = [&](int j) LORA_INLINE {
-    const int row = 8 * j + dl_row;
-    return (uint32_t)row * rowbytes + (uint32_t)((dl_cp ^ kc_swz(row)) << 4);
-  };
-  auto dload = [&](int kb, int buf) LORA_INLINE {
-    const uint32_t k0b = (uint32_t)kb * 128;
-    char* sb = smem + buf * STAGE;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) dma16(rsX, voff(wave + 8 * i), k0b, sb + (wave + 8 * i) * 1024);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) dma16(rsW, voff(wave + 8 * i), k0b, sb + BM * 128 + (wave + 8 * i) * 1024);
-    if (!UPRE && wave < 2) dma16(rsA, voff(wave), k0b, sb + (BM + BN) * 128 + wave * 1024);
-  };
-  constexpr int NDMA_MIN = 6;   // fewest copies any wave issues per stage
-  dload(0, 0);
-  if (nkb > 1) dload(1, 1);
-  // B rows of the tile for the epilogue, staged once beside the pipeline's
-  // buffers: Bs [BN][RP] bf16, zero beyond r and n; thread tid fills entries
-  // t0b .. t0b + 7 of row tid / (RP / 8).
-  {
-    static_assert(BN * RP / 8 == NT, "one chunk of Bs per thread");
-    const int j = tid / (RP / 8), t0b = 8 * (tid % (RP / 8));
-    int4v v = int4v{0, 0, 0, 0};
-    if (j < min(BN, n - n0) && t0b < r) {
-      const u16* brow = B + (size_t)(n0 + j) * r;
-      if ((r & 7) == 0) {
-        v = *reinterpret_cast<const int4v*>(brow + t0b);
-      } else {
-        uint32_t w[4];
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-          const uint32_t lo = t0b + 2 * x < r ? brow[t0b + 2 * x] : 0u;
-          const uint32_t hi = t0b + 2 * x + 1 < r ? brow[t0b + 2 * x + 1] : 0u;
-          w[x] = lo | (hi << 16);
-        }
-        v = int4v{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-      }
-    }
-    *reinterpret_cast<int4v*>(Bs + j * RP + t0b) = v;
-  }
-  copy_barrier<0>();   // every copy and load of the prologue has landed
-  // Stage kb reads buffer kb % 3; at its top the copies of stage kb+2 go to
-  // buffer (kb+2) % 3, which every wave finished reading in stage kb-1; at
-  // its end each wave waits for its copies of stage kb+1 before the barrier.
-  auto dstage = [&](int kb, auto bufc, bool load_next) LORA_INLINE {
-    constexpr int BUF = decltype(bufc)::value;
-    if (load_next) dload(kb + 2, (BUF + 2) % 3);
-    const char* sb = smem + BUF * STAGE;
-    read_frags(sb, 0, 0);
-    read_frags(sb, 1, 1);
-    multiply(0, 0);
-    multiply(1, 1);
-    if (load_next) copy_barrier<NDMA_MIN>();
-    else copy_barrier<0>();
-  };
-  using D0 = std::integral_constant<int, 0>;
-  using D1 = std::integral_constant<int, 1>;
-  using D2 = std::integral_constant<int, 2>;
-  int kb = 0;
-  for (; kb + 5 < nkb; kb += 3) {
-    dstage(kb, D0{}, true);
-    dstage(kb + 1, D1{}, true);
-    dstage(kb + 2, D2{}, true);
-  }
-  if (kb < nkb) dstage(kb, D0{}, kb + 2 < nkb);
-  if (kb + 1 < nkb) dstage(kb + 1, D1{}, kb + 3 < nkb);
-  if (kb + 2 < nkb) dstage(kb + 2, D2{}, kb + 4 < nkb);
-  if (kb + 3 < nkb) dstage(kb + 3, D0{}, false);
-  if (kb + 4 < nkb) dstage(kb + 4, D1{}, false);
-  } else {
   const int nkb = (k + 63) / 64;
   gload(0, 0);
   gload(0, 1);
@@ -1036,8 +700,6 @@ __global__ __launch_bounds__(512) void lora_fwd_ks_kernel(
     for (; kb + 2 < nkb; ++kb) stage(kb, BR{}, true, true);
     if (kb + 1 < nkb) stage(kb++, BR{}, true, false);
     stage(kb, BR{}, false, false);
-  }
-
   }
   // The epilogue's lane-derived values are recomputed from the lane index
   // rather than kept live across the k loop (which runs at the register limit).
@@ -1165,21 +827,11 @@ __global__ __launch_bounds__(512) void lora_fwd_ks_kernel(
   if (wk == 0) finish(acc[0], acc[1]);
   else finish(acc[2], acc[3]);
   }
+  }
 }
 
 // ---------------------------------------------------------------------------
 // Launchers: execute the plans of lora_plan.hpp.
-
-// Instantiations a plan can name (any other combination is refused): U from
-// the U pass for single projections of rank above 16, on the 256 x 256 tile
-// and under dropout (where the pass applies the keep mask), in the tile for
-// groups and rank 16 otherwise; the 128 x 256 tile at rank 16 is the k-split
-// kernel's.
-template <int BM, int BN, int RP, bool GRP, bool UPRE, bool KFULL, bool DMA>
-constexpr bool fwd_instantiated() {
-  return !(BM == 128 && BN == 256 && RP == 16) && (UPRE ? !GRP : (RP == 16 || GRP)) &&
-         DMA == (KFULL && BM == 256 && BN == 256);
-}
 
 static hipError_t run_fwd_launch(const Launch& L, const FwdArgs& a, const FwdGroup& grp, hipStream_t st) {
   const dim3 grid((unsigned)L.grid), block((unsigned)L.block);
@@ -1201,7 +853,7 @@ static hipError_t run_fwd_launch(const Launch& L, const FwdArgs& a, const FwdGro
           return with_bool(L.upre, [&](auto uc) {
             constexpr bool G = decltype(gc)::value, F = decltype(fc)::value, D = decltype(dc)::value,
                            UP = decltype(uc)::value;
-            if constexpr ((D && (G || !F)) || (UP && (G || !F))) {   // (dropout: k a multiple of 64)
+            if constexpr ((D && !F) || (UP && (G || !F))) {   // (U from the pass: dropout, k a multiple of 64)
               return hipErrorInvalidValue;
             } else {
               hipLaunchKernelGGL((lora_fwd_ks_kernel<G, F, D, UP>), grid, block, 0, st, a.X, a.W, a.A, a.B, a.Y,
@@ -1215,27 +867,33 @@ static hipError_t run_fwd_launch(const Launch& L, const FwdArgs& a, const FwdGro
     });
   }
   if (L.id == K_FWD_SKINNY) return launch_fwd_skinny(L, a, grp, st);
-  if (L.id != K_FWD) return hipErrorInvalidValue;
-  return with_int<0, 1, 2>(tile_code(L), [&](auto tc) {
+  if (L.id != K_FWD && L.id != K_FWD_PAIR) return hipErrorInvalidValue;
+  // U comes from the tile only at rank 16 and below the 256 x 256 tile, 128 x
+  // 192 serves single projections, and 128 x 256 at rank 16 is K_FWD_KS's.
+  const int tile = L.id == K_FWD_PAIR ? 64 : L.bn + (L.bm == 256 ? 1 : 0);
+  return with_int<64, 128, 192, 256, 257>(tile, [&](auto tc) {
     constexpr int T = decltype(tc)::value;
-    constexpr int BM = T == 0 ? 256 : 128, BN = T == 2 ? 128 : 256, WN = T == 2 ? 2 : 4;
     return with_int<16, 32, 64>(L.rp, [&](auto rc) {
       return with_bool(L.grp, [&](auto gr) {
         return with_bool(L.upre, [&](auto up) {
           return with_bool(L.full, [&](auto kf) {
-            return with_bool(L.dma, [&](auto dm) {
-              constexpr int RP = decltype(rc)::value;
-              constexpr bool GRP = decltype(gr)::value, UPRE = decltype(up)::value, KF = decltype(kf)::value,
-                             DMA = decltype(dm)::value;
-              if constexpr (!fwd_instantiated<BM, BN, RP, GRP, UPRE, KF, DMA>()) {
-                return hipErrorInvalidValue;
-              } else {
-                hipLaunchKernelGGL((lora_fwd_kernel<BM, BN, 2, WN, RP, GRP, UPRE, KF, DMA>), grid, block, 0, st,
-                                   a.X, a.W, a.A, a.B, a.Y, a.U, (int)a.m, (int)a.n, (int)a.k, (int)a.r, a.s,
-                                   L.tiles_m, L.tiles_n, (int)L.col_begin, grp);
-                return hipGetLastError();
-              }
-            });
+            constexpr int RP = decltype(rc)::value;
+            constexpr bool GRP = decltype(gr)::value, UPRE = decltype(up)::value, KF = decltype(kf)::value;
+            if constexpr ((!UPRE && (RP != 16 || T == 257)) || (T == 256 && RP == 16) || (T == 192 && GRP) ||
+                          (UPRE && RP == 16 && T != 257 && (GRP || !KF))) {
+              return hipErrorInvalidValue;
+            } else if constexpr (T == 64) {
+              hipLaunchKernelGGL((lora_fwd_pair_ks_kernel<RP, GRP, KF, UPRE>), grid, block, 0, st, a.X, a.W, a.A, a.B,
+                                 a.Y, a.U, (int)a.m, (int)a.n, (int)a.k, (int)a.r, a.s, L.tiles_m, L.tiles_n,
+                                 (int)L.col_begin, grp);
+              return hipGetLastError();
+            } else {
+              constexpr bool BIG = T == 257;
+              hipLaunchKernelGGL((lora_fwd_kernel<BIG ? 256 : 128, BIG ? 256 : T, 2, BIG ? 4 : 2, RP, GRP, UPRE, KF, BIG>),
+                                 grid, block, 0, st, a.X, a.W, a.A, a.B, a.Y, a.U, (int)a.m, (int)a.n, (int)a.k,
+                                 (int)a.r, a.s, L.tiles_m, L.tiles_n, (int)L.col_begin, grp);
+              return hipGetLastError();
+            }
           });
         });
       });

@@ -1,0 +1,418 @@
+// Forward tiles of 128 tokens x 128, 192 or 256 features with the k substeps
+// of each stage split between wave pairs:
+//   Y = X W^T + s U B^T,   U = X A^T formed beside W or read back.
+#pragma once
+
+#include <type_traits>
+
+#include "lora_device.hpp"
+#include "lora_launch.hpp"
+
+namespace lora {
+
+// Eight waves: wave (wk, wm, wn) multiplies the 64 tokens wm and the BN / 2
+// features wn of the tile over substeps 2 wk and 2 wk + 1 of every 64-wide
+// stage (the 32-wide k half wk); waves w and w + 4, the two k halves of one
+// block, share a SIMD.  The stages (X[128 rows], W[BN rows] and, without UPRE,
+// A padded to 16 rows, 128 bytes a row with the kc_offset swizzle) are copied
+// straight into NBUF LDS buffers, NBUF - 1 stages ahead.
+//
+// The two halves take turns: while the waves wk = 0 multiply, the waves wk = 1
+// read the fragments of their half of the stage and issue the copies of a
+// later one, then they swap, with a workgroup barrier at each change (the
+// waves wk = 1 run one slot behind).  So one wave of every SIMD is always
+// multiplying and its partner's LDS latency is hidden, where the same loop
+// with both waves in step waits for the first fragments after each barrier.
+// Measured (weights rotated past the caches; forward kernel alone, U beside W,
+// against the same shapes on the previous tiles): 333 x 4096 x 4096, r = 8: 44
+// us on 96 workgroups of 128 x 128 with four waves in step, 37 with this loop,
+// 28.6 as 192 half tiles; 1024 x 5120 x 13824, r = 32: 174 us on 128 x 256
+// tiles, 154 on 128 x 192.  A slot lasts about as long as its LDS traffic: at
+// 128 x 128 44 KB of reads and 17 KB of copies, 0.24 us, against 0.12 us of
+// products.  Issuing the copies before the reads is 2 to 5% slower; s_setprio
+// around the products makes no difference here.
+//
+// Ordering.  Slot 2 kb holds the reads of half 0 and slot 2 kb + 1 those of
+// half 1 of stage kb.  Every wave waits for its LDS reads before the barrier
+// that ends its read slot, so a buffer is free once both read slots are over:
+// the copies of stage kb + NBUF - 1 go to the buffer of stage kb - 1 in the
+// read slots of stage kb.  Copies of stage kb + 1 are waited for (vmcnt,
+// leaving those of NBUF - 2 later stages in flight) before the barrier that
+// ends slot 2 kb + 1: by half 1 in its read slot, by half 0 after its products.
+//
+// After the k loop the two partial sums of each output are added in fixed
+// order through LDS: wave wk keeps token fragment wk of its 64 tokens and
+// sends the other, so each wave finishes 32 tokens x BN / 2 features.  U on
+// 16x16x32 products: wave (wk, wm, wn) owns the 16-token groups 2 wn, 2 wn + 1
+// of its token half, over its k half; the first tile column writes U.  s U B^T
+// is added as in lora_fwd_kernel.  GRP selects the projection of a grouped
+// launch; UPRE reads U from the U pass.  KFULL: k a multiple of 64 (otherwise
+// each copy checks its k bound).
+template <int BM, int BN, int RP, bool GRP, bool UPRE, bool KFULL>
+__device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16* __restrict__ W,
+                                            const u16* __restrict__ A, const u16* __restrict__ B,
+                                            u16* __restrict__ Y, float* __restrict__ U, int m, int n, int k, int r,
+                                            float s, int m0, int tn, int n_begin, const FwdGroup& grp, char* smem) {
+  constexpr int NT = 512, FI = 2, FJ = BN / 64, WTJ = BN / 2;
+  constexpr int WM = BM / 64, NK = 4 / WM;        // waves along the tokens, k shares
+  constexpr int KP = NK / 2;                      // 64-wide k pieces per stage
+  constexpr int ROWS = BM + BN + (UPRE ? 0 : 16);
+  constexpr int PIECE = ROWS * 128, STAGE = KP * PIECE;
+  constexpr bool EARLY_B = RP == 16;              // B staged beside the pipeline's buffers
+  constexpr int BS_EARLY = EARLY_B ? BN * RP * 2 : 0;
+  constexpr int NBUF = (160 * 1024 - BS_EARLY) / STAGE < 4 ? (160 * 1024 - BS_EARLY) / STAGE : 4;
+  constexpr int NCOPY = KP * (BM / 64 + BN / 64);  // copies per wave and stage
+  constexpr int NA = UPRE ? 0 : 2 * KP;           // waves 0 .. NA - 1: one more, for A
+  constexpr int XCH = NK == 2 ? 8 * FJ * 4096 : 8 * 4 * 4096;   // exchanged fragments of 64 lanes x 16 floats
+  static_assert((BM == 128 || (BM == 64 && BN == 128)), "tile shapes");
+  static_assert(NBUF >= 3 && (UPRE || RP == 16), "pipeline depth; U beside W only up to rank 16");
+
+  if (GRP) {
+    int sel = 0;
+#pragma unroll
+    for (int q = 1; q < kMaxGroup; ++q)
+      if (q < grp.count && tn >= grp.tile0[q]) sel = q;
+#pragma unroll
+    for (int q = 0; q < kMaxGroup; ++q)
+      if (q == sel) {
+        W = grp.W[q]; A = grp.A[q]; B = grp.B[q]; Y = grp.Y[q]; U = grp.U[q];
+        n = grp.n[q];
+        tn -= grp.tile0[q];
+      }
+  }
+  const int n0 = n_begin + tn * BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = uniform(tid >> 6);
+  const int wk = wave / (2 * WM), wm = (wave >> 1) % WM, wn = wave & 1;
+  const bool second = wave >= 4;                   // the waves that run one slot behind
+  const int g = lane >> 5, c32 = lane & 31;
+  const int g16 = lane >> 4, c16 = lane & 15;
+
+  const uint32_t rowbytes = (uint32_t)k * 2;
+  const __amdgpu_buffer_rsrc_t rsX = make_rsrc(X + (size_t)m0 * k, (uint64_t)min(BM, m - m0) * rowbytes);
+  const __amdgpu_buffer_rsrc_t rsW = make_rsrc(W + (size_t)n0 * k, (uint64_t)min(BN, n - n0) * rowbytes);
+  const __amdgpu_buffer_rsrc_t rsA = make_rsrc(A, (uint64_t)r * rowbytes);
+  const int nkb = (k + 64 * KP - 1) / (64 * KP);
+
+  // Copy i of a region fills its rows 64 i + 8 wave .. + 7: lane l takes
+  // position l % 8 of row l / 8 of the eight, which holds logical chunk
+  // (l % 8) ^ kc_swz(row) (the same for every i).
+  const int r8 = 8 * wave + (lane >> 3);
+  const int kcol = 8 * ((lane & 7) ^ kc_swz(r8));
+  const uint32_t voff = (uint32_t)r8 * rowbytes + (uint32_t)kcol * 2;
+  auto dload = [&](int kb, int boff) LORA_INLINE {
+#pragma unroll
+    for (int p = 0; p < KP; ++p) {
+      const int k0 = (kb * KP + p) * 64;
+      const uint32_t k0b = (uint32_t)k0 * 2;
+      char* sb = smem + boff + p * PIECE + wave * 1024;
+      // (a piece that starts past the end has no byte in range either way)
+      const bool ok = (KFULL && KP == 1) || k0 + kcol < k;
+      const uint32_t so = KP == 1 || k0 < k ? k0b : 0;
+#pragma unroll
+      for (int i = 0; i < BM / 64; ++i)
+        dma16(rsX, ok ? voff + (uint32_t)(64 * i) * rowbytes : kOOB, so, sb + i * 8192);
+#pragma unroll
+      for (int i = 0; i < BN / 64; ++i)
+        dma16(rsW, ok ? voff + (uint32_t)(64 * i) * rowbytes : kOOB, so, sb + BM * 128 + i * 8192);
+    }
+    if (wave < NA) {   // A: rows 8 (wave % 2) .. + 7 of piece wave / 2
+      const int k0 = (kb * KP + (wave >> 1)) * 64, row = 8 * (wave & 1) + (lane >> 3);
+      const int kc = 8 * ((lane & 7) ^ kc_swz(row));
+      dma16(rsA, k0 + kc < k ? (uint32_t)row * rowbytes + (uint32_t)(k0 + kc) * 2 : kOOB, 0,
+            smem + boff + (wave >> 1) * PIECE + (BM + BN) * 128 + (wave & 1) * 1024);
+    }
+  };
+  // Wait until only the copies of the `later` newest stages are in flight.
+  auto wait_copies = [&](auto later) LORA_INLINE {
+    constexpr int N = decltype(later)::value;
+    if (wave < NA) wait_vmcnt<N * (NCOPY + 1)>();
+    else wait_vmcnt<N * NCOPY>();
+  };
+  using All = std::integral_constant<int, 0>;
+  using Deep = std::integral_constant<int, NBUF - 2>;
+
+#pragma unroll
+  for (int st = 0; st < NBUF - 1; ++st)
+    if (st < nkb) dload(st, st * STAGE);
+
+  u16* Bs = reinterpret_cast<u16*>(smem + NBUF * STAGE);   // EARLY_B: [BN][RP] bf16, zero beyond r and n
+  if constexpr (EARLY_B) {
+    if (tid < BN * 2) {
+      const int j = tid >> 1, t0b = 8 * (tid & 1);
+      int4v v = int4v{0, 0, 0, 0};
+      if (j < min(BN, n - n0) && t0b < r) {
+        const u16* brow = B + (size_t)(n0 + j) * r;
+        if ((r & 7) == 0) {
+          v = *reinterpret_cast<const int4v*>(brow + t0b);
+        } else {
+          uint32_t w[4];
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            const uint32_t lo = t0b + 2 * x < r ? brow[t0b + 2 * x] : 0u;
+            const uint32_t hi = t0b + 2 * x + 1 < r ? brow[t0b + 2 * x + 1] : 0u;
+            w[x] = lo | (hi << 16);
+          }
+          v = int4v{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+        }
+      }
+      *reinterpret_cast<int4v*>(Bs + j * RP + t0b) = v;
+    }
+  }
+
+  floatx16 acc[FJ][FI];
+#pragma unroll
+  for (int a = 0; a < FJ; ++a)
+#pragma unroll
+    for (int b = 0; b < FI; ++b) acc[a][b] = floatx16{};
+  floatx4 uacc16[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+
+  short8 fw[2][FJ], fx[2][FI], fa16, fxu16[2];
+  auto reads = [&](int boff) LORA_INLINE {
+    const char* Xs = smem + boff + (wk >> 1) * PIECE;
+    const char* Ws = Xs + BM * 128;
+    const char* As = Xs + (BM + BN) * 128;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int ch = 2 * (2 * (wk & 1) + j) + g;
+#pragma unroll
+      for (int fi = 0; fi < FI; ++fi) fx[j][fi] = kc_read(Xs, wm * 64 + 32 * fi + c32, ch);
+#pragma unroll
+      for (int fj = 0; fj < FJ; ++fj) fw[j][fj] = kc_read(Ws, wn * WTJ + 32 * fj + c32, ch);
+    }
+    if (!UPRE) {
+      fa16 = kc_read(As, c16, 4 * (wk & 1) + g16);
+#pragma unroll
+      for (int gg = 0; gg < 2; ++gg) fxu16[gg] = kc_read(Xs, wm * 64 + 16 * (2 * wn + gg) + c16, 4 * (wk & 1) + g16);
+    }
+  };
+  auto multiply = [&]() LORA_INLINE {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int fi = 0; fi < FI; ++fi)
+#pragma unroll
+        for (int fj = 0; fj < FJ; ++fj) acc[fj][fi] = mfma32x32x16(fw[j][fj], fx[j][fi], acc[fj][fi]);
+    if (!UPRE) {
+#pragma unroll
+      for (int gg = 0; gg < 2; ++gg) uacc16[gg] = mfma16x16x32(fa16, fxu16[gg], uacc16[gg]);
+    }
+  };
+  auto slot_end = [&]() LORA_INLINE {
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  copy_barrier<0>();             // the first stages and B are staged
+  if (second) slot_end();        // half 1 runs one slot behind
+  int rb = 0, wb = (NBUF - 1) * STAGE;
+  for (int kb = 0; kb < nkb; ++kb) {
+    const bool more = kb + NBUF - 1 < nkb;
+    reads(rb);
+    if (more) dload(kb + NBUF - 1, wb);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_lgkm0();
+    if (second) {
+      if (more) wait_copies(Deep{});
+      else wait_copies(All{});
+    }
+    slot_end();
+    multiply();
+    __builtin_amdgcn_sched_barrier(0);
+    if (!second) {
+      if (more) wait_copies(Deep{});
+      else wait_copies(All{});
+    }
+    slot_end();
+    rb = rb + STAGE == NBUF * STAGE ? 0 : rb + STAGE;
+    wb = wb + STAGE == NBUF * STAGE ? 0 : wb + STAGE;
+  }
+  if (!second) slot_end();
+
+  // ---- epilogue (LDS is free of copies and reads after the last barrier).
+  // Lane-derived values are recomputed rather than kept live across the loop.
+  const int lane_e = lane_fresh();
+  {
+    const int lane = lane_e, tid = wave * 64 + lane_e;
+    const int g = lane >> 5, c32 = lane & 31;
+    const int g16 = lane >> 4, c16 = lane & 15;
+    // Regions: [0, XCH) the exchange, later the per-wave output staging; Us fp32
+    // [BM][RPU] (twice at RP = 16: the two k-half partials) and Bs bf16
+    // [BN][RPB].  At RP = 16 they lie beside the exchange; for larger ranks they
+    // reuse it once it has been read.
+    constexpr int RPU = RP == 16 ? RP : RP + 4, RPB = RP == 16 ? RP : RP + 8;
+    constexpr int UPT = BM * RP / NT, BCH = (BN * RP / 8 + NT - 1) / NT;
+    float* Us = reinterpret_cast<float*>(smem + (EARLY_B ? XCH : 0));
+    u16* Bs2 = EARLY_B ? Bs : reinterpret_cast<u16*>(smem + BM * RPU * 4);
+    float uv[UPT];
+    int4v bv[EARLY_B ? 1 : BCH];
+    const int nch = min(BN, n - n0) * r / 8;       // 16-byte chunks of the tile's B rows (exact)
+    if constexpr (UPRE) {                          // U, and B beyond rank 16: all loads issued before the first use
+      const __amdgpu_buffer_rsrc_t rsU = make_rsrc(U + (size_t)m0 * r, (uint64_t)min(BM, m - m0) * r * 4);
+#pragma unroll
+      for (int i = 0; i < UPT; ++i) {
+        const int e = tid + i * NT, il = e / RP, t = e - il * RP;
+        uv[i] = buf_load4f(rsU, t < r ? (uint32_t)(il * r + t) * 4 : kOOB);
+      }
+      if constexpr (!EARLY_B) {
+        const __amdgpu_buffer_rsrc_t rsB = make_rsrc(B + (size_t)n0 * r, (uint64_t)nch * 16);
+#pragma unroll
+        for (int i = 0; i < BCH; ++i) {
+          const int q = tid + i * NT;
+          bv[i] = buf_load16(rsB, q < nch ? (uint32_t)q * 16 : kOOB);
+        }
+      }
+    }
+    // The wave finishes token fragment ofi, feature fragments ofj .. ofj + NO - 1
+    // of its block: with two k shares one token fragment, with four one
+    // 32 x 32 fragment.  Partial sums are added in k-share order.
+    constexpr int NO = NK == 2 ? FJ : 1;
+    const int ofi = NK == 2 ? wk : wk >> 1, ofj = NK == 2 ? 0 : wk & 1;
+    floatx16 own[NO];
+    float4* xb = reinterpret_cast<float4*>(smem);
+    if constexpr (NK == 2) {
+      float4* dst = xb + (size_t)(wave ^ 4) * FJ * 4 * 64;   // the partner's region
+#pragma unroll
+      for (int fj = 0; fj < FJ; ++fj) {
+        const floatx16 a0 = acc[fj][0], a1 = acc[fj][1];
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          float4 o;
+          o.x = wk == 0 ? a1[4 * q4] : a0[4 * q4];
+          o.y = wk == 0 ? a1[4 * q4 + 1] : a0[4 * q4 + 1];
+          o.z = wk == 0 ? a1[4 * q4 + 2] : a0[4 * q4 + 2];
+          o.w = wk == 0 ? a1[4 * q4 + 3] : a0[4 * q4 + 3];
+          dst[(fj * 4 + q4) * 64 + lane] = o;
+        }
+      }
+    } else {   // [wn][fragment 2 fi + fj][k share]
+#pragma unroll
+      for (int f = 0; f < 4; ++f) {
+        const floatx16 v = acc[f & 1][f >> 1];
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+          xb[(size_t)(((wn * 4 + f) * 4 + wk) * 4 + q4) * 64 + lane] =
+              float4{v[4 * q4], v[4 * q4 + 1], v[4 * q4 + 2], v[4 * q4 + 3]};
+      }
+    }
+    if (!UPRE) {
+#pragma unroll
+      for (int gg = 0; gg < 2; ++gg)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          Us[(wk * BM + wm * 64 + 16 * (2 * wn + gg) + c16) * RP + 4 * g16 + q] = uacc16[gg][q];
+    }
+    __syncthreads();
+    if constexpr (NK == 2) {
+      const float4* src = xb + (size_t)wave * FJ * 4 * 64;
+#pragma unroll
+      for (int fj = 0; fj < FJ; ++fj) {
+        const floatx16 a0 = acc[fj][0], a1 = acc[fj][1];
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const float4 o = src[(fj * 4 + q4) * 64 + lane];
+          own[fj][4 * q4] = (wk == 0 ? a0[4 * q4] : a1[4 * q4]) + o.x;
+          own[fj][4 * q4 + 1] = (wk == 0 ? a0[4 * q4 + 1] : a1[4 * q4 + 1]) + o.y;
+          own[fj][4 * q4 + 2] = (wk == 0 ? a0[4 * q4 + 2] : a1[4 * q4 + 2]) + o.z;
+          own[fj][4 * q4 + 3] = (wk == 0 ? a0[4 * q4 + 3] : a1[4 * q4 + 3]) + o.w;
+        }
+      }
+    } else {
+      const float4* src = xb + (size_t)((wn * 4 + wk) * 4) * 4 * 64;
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        float4 o = src[q4 * 64 + lane];
+#pragma unroll
+        for (int q = 1; q < 4; ++q) {
+          const float4 x = src[(q * 4 + q4) * 64 + lane];
+          o.x += x.x; o.y += x.y; o.z += x.z; o.w += x.w;
+        }
+        own[0][4 * q4] = o.x; own[0][4 * q4 + 1] = o.y; own[0][4 * q4 + 2] = o.z; own[0][4 * q4 + 3] = o.w;
+      }
+    }
+    if constexpr (!EARLY_B) {
+      __syncthreads();                             // the exchange has been read
+      for (int e = tid; e < BN * RPB / 8; e += NT) reinterpret_cast<int4v*>(Bs2)[e] = int4v{0, 0, 0, 0};
+      __syncthreads();
+      // element idx of the chunks is B row idx / r, column idx % r; the quotient
+      // comes from a float product that stays at least 0.5/r away from an integer
+      const float rinv = 1.0f / (float)r;
+#pragma unroll
+      for (int i = 0; i < BCH; ++i) {
+        const int q = tid + i * NT;
+        if (q < nch) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int idx = 8 * q + e;
+            const int j = (int)(((float)idx + 0.5f) * rinv);
+            const int t = idx - j * r;
+            Bs2[j * RPB + t] = (u16)((uint32_t)bv[i][e >> 1] >> (16 * (e & 1)));
+          }
+        }
+      }
+    }
+    if (UPRE) {
+#pragma unroll
+      for (int i = 0; i < UPT; ++i) {
+        const int e = tid + i * NT, il = e / RP, t = e - il * RP;
+        Us[il * RPU + t] = uv[i];
+      }
+    } else {
+      for (int e = tid; e < BM * RP; e += NT) {   // the k shares' partials, written before the barrier above
+        float v = Us[e];
+#pragma unroll
+        for (int q = 1; q < NK; ++q) v += Us[q * BM * RP + e];
+        Us[e] = v;
+      }
+    }
+    __syncthreads();
+    if (n0 == 0 && !UPRE) {
+      for (int e = tid; e < BM * RP; e += NT) {
+        const int il = e / RP, t = e - il * RP;
+        if (m0 + il < m && t < r) U[(size_t)(m0 + il) * r + t] = Us[e];
+      }
+    }
+    // acc += s U B^T (high and low bf16 parts of s U) on the wave's 32 tokens
+    const int il = wm * 64 + 32 * ofi + c32;
+    const int tblocks = RP == 16 ? 1 : (r + 15) / 16;
+    for (int tb = 0; tb < tblocks; ++tb) {
+      const int t0 = 16 * tb + 8 * g;
+      const float* up = Us + il * RPU + t0;
+      short8 uh, ul;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float v = s * up[e];
+        const u16 hi = f32_to_bf16(v);
+        uh[e] = (short)hi;
+        ul[e] = (short)f32_to_bf16(v - bf16_to_f32(hi));
+      }
+#pragma unroll
+      for (int fj = 0; fj < NO; ++fj) {
+        const short8 bfr = *reinterpret_cast<const short8*>(Bs2 + (wn * WTJ + 32 * (ofj + fj) + c32) * RPB + t0);
+        own[fj] = mfma32x32x16(bfr, uh, own[fj]);
+        own[fj] = mfma32x32x16(bfr, ul, own[fj]);
+      }
+    }
+    // Y rounded to bf16, through a wave-private LDS region (at RP = 16 the
+    // exchange region, read before the last barrier)
+    if constexpr (!EARLY_B) __syncthreads();
+    const int i0 = m0 + wm * 64 + 32 * ofi, j0 = n0 + wn * WTJ + 32 * ofj;
+    static_assert(8 * out_block_bytes<NO>() <= (EARLY_B ? XCH : 160 * 1024), "output staging");
+    store_out_block<NO>(own, smem + wave * out_block_bytes<NO>(), Y + (size_t)i0 * n + j0, (size_t)n, m - i0, n - j0,
+                        lane);
+  }
+}
+
+template <int BM, int BN, int RP, bool UPRE>
+constexpr int fwd_ks_smem() {
+  constexpr int nk = BM == 128 ? 2 : 4;
+  constexpr int stage = (BM + BN + (UPRE ? 0 : 16)) * 128 * (nk / 2), early = RP == 16 ? BN * RP * 2 : 0;
+  constexpr int nbuf = (160 * 1024 - early) / stage < 4 ? (160 * 1024 - early) / stage : 4;
+  constexpr int loop = nbuf * stage + early, xch = nk == 2 ? 8 * (BN / 64) * 4096 : 8 * 4 * 4096;
+  constexpr int epi = RP == 16 ? xch + nk * BM * RP * 4 : BM * (RP + 4) * 4 + BN * (RP + 8) * 2;
+  constexpr int e1 = epi > xch ? epi : xch;
+  static_assert(loop <= 160 * 1024 && e1 <= (RP == 16 ? nbuf * stage : 160 * 1024), "LDS budget");
+  return loop > e1 ? loop : e1;
+}
+
+}  // namespace lora

@@ -14,65 +14,80 @@ inline int pad_rank(int64_t r) { return (int)((r + 15) / 16) * 16; }
 // Token count padded to the 64-token chunk of the split-K reductions.
 inline int64_t pad_tokens(int64_t m) { return (m + 63) / 64 * 64; }
 
-// Output tiles of the two large GEMMs (tokens x features): 256x256 and 128x256
-// run 8 waves (two per SIMD) as 2 x 4 waves of 128 x 64 and 64 x 64;
-// 128x128 runs 4 waves of 64 x 64.
-enum GemmTile { TILE_256x256 = 0, TILE_128x256 = 1, TILE_128x128 = 2 };
+// Output tiles of the two large GEMMs (tokens x features): 256x256 runs 8
+// waves (two per SIMD) as 2 x 4 waves of 128 x 64; the tiles of 128 tokens run
+// 8 waves (128x128 dX: 4).  Forward only: 128x192, and 128x128 shared by a
+// pair of workgroups of 64 tokens each.
+enum GemmTile { TILE_256x256 = 0, TILE_128x256 = 1, TILE_128x128 = 2, TILE_128x192 = 3, TILE_PAIR = 4 };
 
-// Pick the output tile of the two large GEMMs for an M x N output.  Every
-// workgroup of these kernels fills one compute unit (LDS-limited), so the
-// kernel runs in ceil(tiles / 256) rounds on 256 CUs; the estimate is rounds
-// times the per-tile work divided by a relative per-tile efficiency (larger
-// tiles read less LDS and L2 per flop).
-inline GemmTile choose_gemm_tile(int64_t M, int64_t N) {
-  struct C { GemmTile t; int bm, bn; double eff; };
-  const C cands[3] = {{TILE_256x256, 256, 256, 1.0}, {TILE_128x256, 128, 256, 0.9},
-                      {TILE_128x128, 128, 128, 0.75}};
-  GemmTile best = TILE_256x256;
-  double best_cost = 1e300;
-  for (const C& c : cands) {
-    const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-    const double rounds = (double)((tiles + 255) / 256);
-    const double cost = rounds * c.bm * c.bn / c.eff;
-    if (cost < best_cost) { best_cost = cost; best = c.t; }
-  }
-  return best;
+// A candidate tile: the output area a workgroup computes, and the workgroup's
+// relative efficiency (larger tiles read less LDS and L2 per flop).  Every
+// workgroup of these kernels fills one compute unit (LDS-limited), so a launch
+// runs in ceil(workgroups / 256) rounds on 256 CUs, and its estimated cost is
+// rounds x area / efficiency.
+struct TileCost { GemmTile t; int bm, bn, wgs; double eff; };
+
+// Forward tiles.  Time per 64-wide k stage with the chip full, measured at k =
+// 4096 to 13824: 256x256 1.70 us, 128x256 0.94, 128x192 0.74, 128x128 0.58, a
+// half of a pair 0.42.  128x192 serves single projections of k >= 2048 (with
+// fewer stages a launch is mostly its fixed cost).
+constexpr TileCost kFwdTiles[5] = {{TILE_256x256, 256, 256, 1, 1.0}, {TILE_128x256, 128, 256, 1, 0.9},
+                                   {TILE_128x128, 128, 128, 1, 0.73}, {TILE_128x192, 128, 192, 1, 0.85},
+                                   {TILE_PAIR, 128, 128, 2, 0.5}};
+// dX tiles (measured at 4096 x 5120 x 5120 and 4096 x 13824 x 5120).
+constexpr TileCost kDxTiles[3] = {{TILE_256x256, 256, 256, 1, 1.0}, {TILE_128x256, 128, 256, 1, 0.9},
+                                  {TILE_128x128, 128, 128, 1, 0.75}};
+
+inline int64_t tile_workgroups(const TileCost& c, int64_t M, int64_t N) {
+  return (M + c.bm - 1) / c.bm * ((N + c.bn - 1) / c.bn) * c.wgs;
+}
+inline double tile_cost(const TileCost& c, int64_t M, int64_t N) {
+  return (double)((tile_workgroups(c, M, N) + 255) / 256) * (c.bm * c.bn / c.wgs) / c.eff;
+}
+
+// The cheapest tile for an M x N output (the first of equal ones); mid: 128x192
+// is a candidate.
+template <int NT>
+inline const TileCost& cheapest_tile(const TileCost (&cands)[NT], int64_t M, int64_t N, bool mid) {
+  const TileCost* best = &cands[0];
+  for (const TileCost& c : cands)
+    if ((mid || c.t != TILE_128x192) && tile_cost(c, M, N) < tile_cost(*best, M, N)) best = &c;
+  return *best;
 }
 
 // Column split of one large GEMM with an M x N output: columns [0, n1) with
 // tile t1, then columns [n1, N) with tile t2 in a second launch.  Taken when
 // the split, whose second part is at most one round of 256 workgroups, is
-// estimated more than 5% faster than the single tiling (estimate: rounds x
-// tile area / relative efficiency, 1.0, 0.9 and 0.72 for 256x256, 128x256
-// and 128x128, measured at 4096 x 5120 x 5120 and 4096 x 13824 x 5120).
+// estimated more than 5% faster than the single tiling.
 // Typical cases: 4096 x 5120, where 640 tiles of 128x256 take three rounds
 // and 256 tiles of 256x256 plus 256 tiles of 128x128 take two; 4096 x 13824,
 // where 1728 tiles of 128x256 take seven rounds and 768 tiles of 256x256 plus
-// 192 of 128x256 take four (forward 607-616 -> 537 us).  Among equal
-// estimates the largest n1 wins.
-// n1 == N: no split.
+// 192 of 128x256 take four (forward 607-616 -> 537 us).  The first part's cost
+// depends on its rounds alone, so for each tile and number of rounds only the
+// largest n1 is looked at.  n1 == N: no split.
 struct GemmSplit { GemmTile t1, t2; int64_t n1; };
-inline GemmSplit plan_gemm_split(int64_t M, int64_t N) {
-  struct C { GemmTile t; int bm, bn; double eff; };
-  const C cands[3] = {{TILE_256x256, 256, 256, 1.0}, {TILE_128x256, 128, 256, 0.9},
-                      {TILE_128x128, 128, 128, 0.72}};
-  auto tiles = [&](const C& c, int64_t n) { return ((M + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn); };
-  auto cost = [&](const C& c, int64_t n) { return (double)((tiles(c, n) + 255) / 256) * c.bm * c.bn / c.eff; };
-  const GemmTile t0 = choose_gemm_tile(M, N);
-  GemmSplit best{t0, t0, N};
-  double best_cost = 0.95 * cost(cands[(int)t0], N);
-  bool found = false;
-  for (const C& c1 : cands)
-    for (int64_t n1 = c1.bn; n1 < N; n1 += c1.bn)
-      for (const C& c2 : cands) {
-        if (tiles(c2, N - n1) > 256) continue;
-        const double c = cost(c1, n1) + cost(c2, N - n1);
-        if (c < best_cost || (found && c == best_cost && n1 > best.n1)) {
+template <int NT>
+inline GemmSplit plan_gemm_split(const TileCost (&cands)[NT], int64_t M, int64_t N, bool mid) {
+  const TileCost& c0 = cheapest_tile(cands, M, N, mid);
+  GemmSplit best{c0.t, c0.t, N};
+  double best_cost = 0.95 * tile_cost(c0, M, N);
+  for (const TileCost& c1 : cands) {
+    if (!mid && c1.t == TILE_128x192) continue;
+    const int64_t per_col = tile_workgroups(c1, M, 1);   // workgroups per column of tiles
+    const int64_t rounds = (tile_workgroups(c1, M, N) + 255) / 256;
+    for (int64_t R = 1; R <= rounds; ++R) {
+      const int64_t n1 = 256 * R / per_col * c1.bn;
+      if (n1 < c1.bn || n1 >= N) continue;
+      for (const TileCost& c2 : cands) {
+        if ((!mid && c2.t == TILE_128x192) || tile_workgroups(c2, M, N - n1) > 256) continue;
+        const double c = tile_cost(c1, M, n1) + tile_cost(c2, M, N - n1);
+        if (c < best_cost || (c == best_cost && best.n1 < N && n1 > best.n1)) {
           best_cost = c;
           best = GemmSplit{c1.t, c2.t, n1};
-          found = true;
         }
       }
+    }
+  }
   return best;
 }
 

@@ -16,8 +16,8 @@ namespace lora {
 
 enum KernelId : int {
   K_UPASS = 0,     // lora_u_kernel<RP, TPW, KEEP>: U = X A^T on its own (rank > 16, and under dropout)
-  K_FWD = 1,       // lora_fwd_kernel<BM, BN, WM, WN, RP, GRP, UPRE, KFULL, DMA>
-  K_FWD_KS = 2,    // lora_fwd_ks_kernel<GRP, KFULL, DMA, UPRE>
+  K_FWD = 1,       // lora_fwd_kernel<BM, BN, WM, WN, RP, GRP, UPRE, KFULL, BIG>
+  K_FWD_KS = 2,    // lora_fwd_ks_kernel<GRP, KFULL, DMA, UPRE>: 128 x 256 up to rank 16
   K_DU = 3,        // lora_bwd_du_dma_kernel<RP, TPW> (r a multiple of 8), else lora_bwd_du_kernel<RP, TPW>
   K_TOKRED = 4,    // lora_tokred_dma_kernel<RP>, or lora_tokred_kernel<RP, true> with a keep mask
   K_DX = 5,        // lora_bwd_dx_kernel<BM, BN, WM, WN, RP, DROP, GRP, FULL>
@@ -25,6 +25,7 @@ enum KernelId : int {
   K_FINALIZE = 7,  // lora_finalize_kernel
   K_MERGE = 8,     // lora_merge_kernel<RP, 64>
   K_MASK = 9,      // lora_keep_mask_kernel: the dropout keep mask from the counter-based generator
+  K_FWD_PAIR = 11,     // lora_fwd_pair_ks_kernel<RP, GRP, KFULL, UPRE>: 128 x 128 tiles, two workgroups each
   K_FWD_SKINNY = 10,   // lora_fwd_skinny_ks_kernel<XR, F, AR, UPRE>: forward of few tokens
 };
 
@@ -68,6 +69,7 @@ inline void tile_dims(GemmTile t, int& bm, int& bn, int& wm, int& wn) {
   switch (t) {
     case TILE_256x256: bm = 256; bn = 256; wm = 2; wn = 4; break;
     case TILE_128x256: bm = 128; bn = 256; wm = 2; wn = 4; break;
+    case TILE_128x192: bm = 128; bn = 192; wm = 2; wn = 2; break;
     default: bm = 128; bn = 128; wm = 2; wn = 2; break;
   }
 }
@@ -135,42 +137,51 @@ inline Plan plan_fwd_skinny(int count, const int64_t* n, int64_t m, int64_t k, i
 
 // Forward GEMM launch(es) for output columns [cb, ce) with tile t.  `first`:
 // the launch whose range starts at column 0 (it writes U, or the U pass runs
-// before it).  U comes from the U pass for single projections of rank above
-// 16, on the 256 x 256 tile (where recomputing rank 16 in every tile costs
-// more than the pass: 7B up_proj forward 387 -> 371 us), and under dropout
-// (drop: the pass applies the keep mask, and the GEMM then runs exactly as
-// without dropout); otherwise the tile computes it.  For a group, tiles_n is
-// the summed column tiles.
+// before it).  U comes from the U pass for ranks above 16 (in the tile it
+// would be recomputed by every output tile), on the 256 x 256 tile (where
+// recomputing rank 16 in every tile costs more than the pass: 7B up_proj
+// forward 387 -> 371 us), and under dropout (drop: the pass applies the keep
+// mask, and the GEMM then runs exactly as without dropout); otherwise the tile
+// computes it.  For a group, tiles_n is the summed column tiles.
 inline void plan_fwd_part(Plan& p, GemmTile t, int64_t m, int64_t k, int64_t r, int64_t cb, int64_t ce,
-                          bool first, bool drop, bool grp, int tiles_n) {
+                          bool first, bool drop, bool grp, int count, int tiles_n) {
   const bool kfull = k % 64 == 0;
-  const bool upre = !grp && (drop || fwd_rank(r) >= 32 || t == TILE_256x256);
-  if (upre && first) p.add(upass_launch(1, m, r, drop));
+  const bool upre = drop || fwd_rank(r) >= 32 || t == TILE_256x256;
+  if (upre && first) p.add(upass_launch(count, m, r, drop));
   Launch x = gemm_launch(K_FWD, t, m, cb, ce, tiles_n);
   x.grp = grp;
   x.upre = upre;
   x.full = kfull;
-  if (t == TILE_128x256 && r <= 16) {
-    // k-split tile; single-round launches copy their stages straight into LDS
-    x.id = K_FWD_KS;
-    x.rp = 16;
-    x.dma = kfull && !grp && x.grid <= 256;
-    p.add(x);
-    return;
-  }
   x.rp = fwd_rank(r);
-  x.dma = t == TILE_256x256 && kfull;
+  x.block = 512;
+  if (t == TILE_128x256 && r <= 16) {
+    // Single-round launches with whole stages copy them straight into LDS and
+    // let the wave halves take turns (7B q_proj 73 -> 63 us); with more rounds
+    // or a partial stage the register-staged loop is as fast or faster (2048 x
+    // 11008 x 4096 182 and 186 us, 1531 x 4104 x 3208 64.5 and 67.8).
+    x.id = K_FWD_KS;
+    x.dma = kfull && x.grid <= 256;
+  } else if (t == TILE_PAIR) {
+    x.id = K_FWD_PAIR;
+    x.grid *= 2;
+  } else if (t == TILE_256x256) {
+    x.dma = true;
+  } else {
+    x.wm = x.wn = 2;
+  }
   p.add(x);
 }
+
+constexpr int64_t kMidTileDepth = 2048;   // least k of the 128 x 192 tile
 
 // lora_linear_fwd / lora_linear_fwd_dropout (the same tiles and column split;
 // under dropout the U pass applies the mask).
 inline Plan plan_fwd(int64_t m, int64_t n, int64_t k, int64_t r, bool drop) {
   if (m <= kSkinnyTokens) return plan_fwd_skinny(1, &n, m, k, r, drop);
   Plan p;
-  const GemmSplit s = plan_gemm_split(m, n);
-  plan_fwd_part(p, s.t1, m, k, r, 0, s.n1, true, drop, false, -1);
-  if (s.n1 < n) plan_fwd_part(p, s.t2, m, k, r, s.n1, n, false, drop, false, -1);
+  const GemmSplit s = plan_gemm_split(kFwdTiles, m, n, k >= kMidTileDepth);
+  plan_fwd_part(p, s.t1, m, k, r, 0, s.n1, true, drop, false, 1, -1);
+  if (s.n1 < n) plan_fwd_part(p, s.t2, m, k, r, s.n1, n, false, drop, false, 1, -1);
   return p;
 }
 
@@ -181,13 +192,13 @@ inline Plan plan_group_fwd(int count, const int64_t* n, int64_t m, int64_t k, in
   if (m <= kSkinnyTokens) return plan_fwd_skinny(count, n, m, k, r, false);
   int64_t ntot = 0;
   for (int g = 0; g < count; ++g) ntot += n[g];
-  const GemmTile t = choose_gemm_tile(m, ntot);
+  const GemmTile t = cheapest_tile(kFwdTiles, m, ntot, false).t;
   int bm, bn, wm, wn;
   tile_dims(t, bm, bn, wm, wn);
   int tiles_n = 0;
   for (int g = 0; g < count; ++g) tiles_n += (int)((n[g] + bn - 1) / bn);
   Plan p;
-  plan_fwd_part(p, t, m, k, r, 0, 0, true, false, true, tiles_n);
+  plan_fwd_part(p, t, m, k, r, 0, 0, true, false, true, count, tiles_n);
   return p;
 }
 
@@ -254,11 +265,11 @@ inline Plan plan_bwd(int64_t m, int64_t n, int64_t k, int64_t r, bool drop) {
   p.add(tokred_launch(L, drop, 0));
   const bool n_whole = n % 64 == 0;
   if (drop) {
-    const GemmTile t = choose_gemm_tile(m, k) == TILE_128x128 ? TILE_128x128 : TILE_128x256;
+    const GemmTile t = cheapest_tile(kDxTiles, m, k, false).t == TILE_128x128 ? TILE_128x128 : TILE_128x256;
     plan_dx_part(p, t, m, L.rp, 0, k, n_whole, true, false, true);
     return p;
   }
-  const GemmSplit s = plan_gemm_split(m, k);
+  const GemmSplit s = plan_gemm_split(kDxTiles, m, k, false);
   plan_dx_part(p, s.t1, m, L.rp, 0, s.n1, n_whole, false, false, true);
   if (s.n1 < k) plan_dx_part(p, s.t2, m, L.rp, s.n1, k, n_whole, false, false, false);
   return p;
@@ -289,7 +300,7 @@ inline Plan plan_group_bwd(int count, const int64_t* n, int64_t m, int64_t k, in
     p.add(x);
   }
   const int rp = G.L[0].rp;
-  const GemmSplit s = plan_gemm_split(m, k);
+  const GemmSplit s = plan_gemm_split(kDxTiles, m, k, false);
   plan_dx_part(p, s.t1, m, rp, 0, s.n1, n_whole, false, true, true);
   if (s.n1 < k) plan_dx_part(p, s.t2, m, rp, s.n1, k, n_whole, false, true, false);
   return p;
@@ -373,6 +384,9 @@ inline void launch_name(const Launch& x, char* buf, size_t len) {
     case K_FINALIZE: snprintf(buf, len, "lora::lora_finalize_kernel"); break;
     case K_MERGE: snprintf(buf, len, "lora::lora_merge_kernel<%d, %d>", x.rp, kMergeRows); break;
     case K_MASK: snprintf(buf, len, "lora::lora_keep_mask_kernel"); break;
+    case K_FWD_PAIR:
+      snprintf(buf, len, "lora::lora_fwd_pair_ks_kernel<%d, %s, %s, %s>", x.rp, b(x.grp), b(x.full), b(x.upre));
+      break;
     case K_FWD_SKINNY:
       snprintf(buf, len, "lora::lora_fwd_skinny_ks_kernel<%d, %d, %d, %s>", x.bm, x.bn, x.rp, b(x.upre));
       break;

@@ -80,6 +80,11 @@ CASES = [  # (ns, m, k, r, alpha)
     ([520, 136, 1032], 24, 328, 13, 26.0), ([4096, 1024, 1024], 3, 200, 16, 32.0),
     ([13824, 13824], 40, 136, 8, 16.0), ([136, 392, 64], 61, 264, 40, 80.0), ([5120, 5120, 5120], 16, 72, 24, 48.0),
     ([64, 64], 70, 72, 24, 48.0), ([64, 64], 70, 72, 33, 66.0),
+    # 128 x 128 forward tiles, one workgroup each, U beside W and from the U pass; the single-round k-split tile;
+    # a group of one on the 128 x 192 tile
+    ([4096, 4096, 4096], 130, 72, 1, 2.0), ([4096, 4096, 4096], 130, 72, 24, 48.0),
+    ([4096, 4096, 4096], 130, 64, 24, 48.0), ([4096, 4096, 4096], 130, 72, 33, 66.0),
+    ([4096, 4096, 4096], 130, 64, 33, 66.0), ([13824, 13824], 130, 64, 1, 2.0), ([11008], 300, 2048, 24, 48.0),
     ([4096, 4096, 4096], 7, 64, 33, 66.0), ([4096, 4096, 4096], 7, 64, 5, 10.0), ([5120, 5120, 5120], 7, 64, 5, 10.0),
 ] + [
     # the remaining grouped tiles a plan can name, at padded ranks 16 .. 64 with and without whole k stages:

@@ -75,6 +75,10 @@ RAGGED = [
     for i, (m, k, r) in enumerate([(5, 520, 8), (16, 72, 16), (13, 264, 64), (17, 648, 3), (31, 200, 33),
                                    (33, 1096, 16), (64, 328, 24)])
     for n in (4088, 5120, 11008, 13824, 16392)
+] + [
+    # the 128 x 192 forward tile with U from the pass, with and without a partial last stage
+    Shape("mid", 300, 11008, 2056, 24, 48.0, 180), Shape("mid", 300, 11008, 2048, 24, 48.0, 181),
+    Shape("mid", 300, 11008, 2056, 33, 66.0, 182), Shape("mid", 300, 11008, 2048, 33, 66.0, 183),
 ]
 
 
@@ -124,6 +128,11 @@ SPLIT_EDGE = [
     Shape("edge", 4096, 4000, 4096, 64, 128.0, 502),
     Shape("edge", 4096, 1024, 4096, 24, 48.0, 503),
     Shape("edge", 4096, 1024, 4096, 40, 80.0, 504),
+    # forward tiles shared by pairs of workgroups (an empty and a nearly empty second half, a number of tiles that
+    # is no multiple of 8), and the 128 x 192 tile, U beside W and from the pass, whole and partial last stages
+    Shape("edge", 300, 1096, 1096, 8, 16.0, 505), Shape("edge", 333, 520, 1088, 13, 26.0, 506),
+    Shape("edge", 193, 1032, 320, 40, 80.0, 507), Shape("edge", 300, 11008, 2056, 8, 16.0, 508),
+    Shape("edge", 300, 10816, 2048, 24, 48.0, 509),
 ]
 
 
