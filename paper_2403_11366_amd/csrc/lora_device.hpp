@@ -270,34 +270,42 @@ __device__ __forceinline__ void store_block_32x64(const floatx16& v0, const floa
   }
 }
 
-// The same for a block of 32 rows x 32 NF columns (v[f]: columns 32 f ..),
-// with whole rows of the block per store.  The caller has synchronised the
-// region.
-template <int NF>
-constexpr int out_block_bytes() { return 32 * (64 * NF + 16); }
-template <int NF>
-__device__ __forceinline__ void store_out_block(const floatx16 (&v)[NF], char* ys, u16* dst, size_t ld, int nrows,
-                                                int ncols, int lane) {
-  constexpr int PITCH = 64 * NF + 16, CH = 4 * NF;   // bytes and 16-byte chunks per row
-  const int g = lane >> 5, c = lane & 31;
+// Output block of 16x16x32 results: v[a][b] holds features 16 a + 4 g .. + 3 of
+// token 16 b + c (lane l: g = l / 16, c = l % 16).  The 16 NB tokens x 16 NA
+// features go through a wave-private LDS region (out16_bytes<NA, NB>(), which
+// no other wave touches meanwhile; the fences order this wave's accesses) and
+// are written back with 16 bytes per lane in whole row pieces.  dst points at
+// the block's (row 0, column 0), ld is the row pitch in elements; rows >= nrows
+// and columns >= ncols (a multiple of 8) are not written.
+template <int NA, int NB>
+constexpr int out16_bytes() { return 16 * NB * (32 * NA + 16); }
+template <int NA, int NB>
+__device__ __forceinline__ void store_out16(const floatx4 (&v)[NA][NB], char* ys, u16* dst, size_t ld, int nrows,
+                                            int ncols, int lane) {
+  constexpr int PITCH = 32 * NA + 16, CH = 2 * NA;   // bytes and 16-byte chunks per row
+  constexpr int NP = (16 * NB * CH + 63) / 64;
+  const int g = lane >> 4, c = lane & 15;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // earlier reads of the region
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 #pragma unroll
-  for (int f = 0; f < NF; ++f)
+  for (int b = 0; b < NB; ++b)
 #pragma unroll
-    for (int qq = 0; qq < 4; ++qq) {
-      const uint32_t lo = (uint32_t)f32_to_bf16(v[f][4 * qq]) | ((uint32_t)f32_to_bf16(v[f][4 * qq + 1]) << 16);
-      const uint32_t hi = (uint32_t)f32_to_bf16(v[f][4 * qq + 2]) | ((uint32_t)f32_to_bf16(v[f][4 * qq + 3]) << 16);
-      *reinterpret_cast<uint2*>(ys + c * PITCH + (32 * f + 8 * qq + 4 * g) * 2) = uint2{lo, hi};
+    for (int a = 0; a < NA; ++a) {
+      const uint32_t lo = (uint32_t)f32_to_bf16(v[a][b][0]) | ((uint32_t)f32_to_bf16(v[a][b][1]) << 16);
+      const uint32_t hi = (uint32_t)f32_to_bf16(v[a][b][2]) | ((uint32_t)f32_to_bf16(v[a][b][3]) << 16);
+      *reinterpret_cast<uint2*>(ys + (16 * b + c) * PITCH + (16 * a + 4 * g) * 2) = uint2{lo, hi};
     }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  int4v w[2 * NF];
+  static_assert(16 * NB * CH % 64 == 0, "whole waves of chunks");
+  int4v w[NP];
 #pragma unroll
-  for (int p = 0; p < 2 * NF; ++p) {
+  for (int p = 0; p < NP; ++p) {
     const int e = lane + 64 * p, row = e / CH, ch = e - row * CH;
     w[p] = *reinterpret_cast<const int4v*>(ys + row * PITCH + ch * 16);
   }
 #pragma unroll
-  for (int p = 0; p < 2 * NF; ++p) {
+  for (int p = 0; p < NP; ++p) {
     const int e = lane + 64 * p, row = e / CH, ch = e - row * CH;
     if (row < nrows && 8 * ch < ncols) *reinterpret_cast<int4v*>(dst + (size_t)row * ld + 8 * ch) = w[p];
   }

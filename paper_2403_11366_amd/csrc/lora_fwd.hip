@@ -21,7 +21,7 @@
 // in LDS -- X rows, W rows and, where U is formed beside W, A padded to 16
 // rows -- so each X tile is read once for both products.
 //
-// Matrix-core products use v_mfma_f32_32x32x16_bf16 and are formed transposed
+// Matrix-core products are formed transposed
 // (W as the A operand, X as the B operand), so each lane's accumulator holds
 // runs of 4 consecutive output features of one token.  After the k loop the
 // epilogue adds s U B^T to the accumulators with a short matrix-core pass over
@@ -40,14 +40,32 @@ namespace lora {
 constexpr int kBigStage = 512 * 128;   // bytes of a 64-wide stage of the 256 x 256 tile
 
 // The 256 x 256 tile: eight waves of 128 x 64, two 64-wide stages in LDS, U
-// from the U pass (read back in the epilogue).  Each stage is copied from
-// global memory straight into the free LDS buffer at the top of the stage
-// before it (one 16-byte chunk per lane per copy instruction, the swizzle
-// applied to the global addresses), with no staging registers; the stage's
-// closing barrier waits for those copies (copy_barrier).  KFULL: k a multiple
-// of 64 (otherwise each copy checks its k bound).  With GRP the grid covers
-// the output tiles of a group of projections that read the same X (FwdGroup):
-// each workgroup first selects its projection's W, B, Y, U and n.
+// from the U pass (read back in the epilogue).  The stages are copied from
+// global memory straight into LDS (one 16-byte chunk per lane per copy
+// instruction, the swizzle applied to the global addresses).
+//
+// The two wave rows take turns: waves w and w + 4 share a SIMD, and while one
+// multiplies, the other reads its next fragments and issues copies; a workgroup
+// barrier ends each slot, and the second row runs one slot behind.  A stage is
+// four phases, each a slot of reads and a slot of sixteen products: (W half 0, X
+// half 0), (W 1, X 0), (W 0, X 1), (W 1, X 1), reading X half 0, W half 1, X
+// half 1 and the next stage's W half 0.  Every wave waits for its reads before
+// the barrier that ends its read slot, so the quarter of a stage read in phase
+// P is free from the read slots of phase P + 1 on, which refill it for the
+// stage after next (seven phases before its use).  The quarter read in phase
+// P + 1 is waited for (six newer ones stay in flight) in the read slot of P.
+//
+// Bound by power: with all eight waves in step (reads of the next substep
+// under the products, one barrier per stage) the matrix cores were 65% busy,
+// waiting after every barrier.  8192 x 4096 x 11008 at rank 64 (U pass
+// included) takes 620 us so, 582 taking turns on 32x32x16 products and 533 on
+// the 16x16x32 ones used here; 4096 x 11008 x 4096 at rank 16 303, 292 and 275;
+// 4096 x 4096 x 5120 143, 137 and 126 (one process, in turn).  s_setprio around
+// the products: no difference.
+// KFULL: k a multiple of 64 (otherwise each copy checks its k bound).  With GRP
+// the grid covers the output tiles of a group of projections that read the
+// same X (FwdGroup): each workgroup first selects its projection's W, B, Y, U
+// and n.
 template <int RP, bool GRP, bool KFULL>
 __device__ __forceinline__ void fwd_big_tile(const u16* __restrict__ X, const u16* __restrict__ W,
                                              const u16* __restrict__ B, u16* __restrict__ Y,
@@ -57,8 +75,7 @@ __device__ __forceinline__ void fwd_big_tile(const u16* __restrict__ X, const u1
   constexpr int NW = WM * WN;
   constexpr int NT = 64 * NW;
   constexpr int WTI = BM / WM, WTJ = BN / WN;   // tokens, features per wave
-  constexpr int FI = WTI / 32;                   // token fragments (B operand)
-  constexpr int FJ = WTJ / 32;                   // feature fragments (A operand)
+  static_assert(WTI == 128 && WTJ == 64, "wave tile");
   constexpr int STAGE = kBigStage;
   static_assert(STAGE == (BM + BN) * 128 && 2 * STAGE <= 160 * 1024, "128-byte rows per 64-wide stage");
   constexpr int RPU = RP + 4, RPB = RP + 8;     // padded row lengths of the epilogue's U and B copies
@@ -80,103 +97,124 @@ __device__ __forceinline__ void fwd_big_tile(const u16* __restrict__ X, const u1
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = uniform(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
-  const int g = lane >> 5, c32 = lane & 31;
+  const int g = lane >> 4, c16 = lane & 15;
 
   const uint32_t rowbytes = (uint32_t)k * 2;
   const __amdgpu_buffer_rsrc_t rsX = make_rsrc(X + (size_t)m0 * k, (uint64_t)min(BM, m - m0) * rowbytes);
   const __amdgpu_buffer_rsrc_t rsW = make_rsrc(W + (size_t)n0 * k, (uint64_t)min(BN, n - n0) * rowbytes);
 
-  floatx16 acc[FJ][FI];
+  floatx4 acc[4][8];           // 16 x 16 fragments: [features 16 a ..][tokens 16 b ..] of the wave's 64 x 128
 #pragma unroll
-  for (int a = 0; a < FJ; ++a)
+  for (int a = 0; a < 4; ++a)
 #pragma unroll
-    for (int b = 0; b < FI; ++b) acc[a][b] = floatx16{};
-  short8 fw[2][FJ], fx[2][FI];
+    for (int b = 0; b < 8; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+  short8 fw[2][2][2], fx[2][4];   // W halves [half][32-wide k][fragment], the current X half [32-wide k][fragment]
   const int nkb = (k + 63) / 64;
-  using B0 = std::integral_constant<int, 0>;
-  using B1 = std::integral_constant<int, 1>;
-  // Copy i of a region fills its rows 64 i + 8 wave .. + 7: lane l takes
-  // position l % 8 of row l / 8 of the eight, which holds logical chunk
-  // (l % 8) ^ kc_swz(row) (the same for every i).
-  const int r8 = 8 * wave + (lane >> 3);
-  const int kcol = 8 * ((lane & 7) ^ kc_swz(r8));
-  const uint32_t voff = (uint32_t)r8 * rowbytes + (uint32_t)kcol * 2;
-  auto dload = [&](int kb, int buf) LORA_INLINE {
-    const uint32_t k0b = (uint32_t)kb * 128;
-    char* sb = smem + buf * STAGE + wave * 1024;
+  // Quarters of a stage, 16 KB each: X half h = tokens 64 h .. + 63 of both
+  // wave rows (tile rows 64 h .. and 128 + 64 h ..), W half h = features 32 h ..
+  // + 31 of all four wave columns (rows 64 j + 32 h ..).
+  // A wave copies 8 rows per instruction, two instructions per quarter: lane l
+  // takes position l % 8 of row l / 8 of the eight, which holds logical chunk
+  // (l % 8) ^ kc_swz(row) (the same for all of a wave's copies).
+  const int l8 = lane >> 3;
+  const int xrow = 8 * wave, wrow = 64 * (wave >> 2) + 8 * (wave & 3);
+  const int kcol = 8 * ((lane & 7) ^ kc_swz(xrow + l8));
+  const uint32_t xoff = (uint32_t)(xrow + l8) * rowbytes + (uint32_t)kcol * 2;
+  const uint32_t woff = (uint32_t)(wrow + l8) * rowbytes + (uint32_t)kcol * 2;
+  auto copy_x = [&](int kb, int h) LORA_INLINE {
+    char* sb = smem + (kb & 1) * STAGE + xrow * 128 + h * 8192;
     const bool ok = KFULL || kb * 64 + kcol < k;
 #pragma unroll
-    for (int i = 0; i < BM / 64; ++i)
-      dma16(rsX, ok ? voff + (uint32_t)(64 * i) * rowbytes : kOOB, k0b, sb + i * 8192);
+    for (int i = 0; i < 2; ++i)
+      dma16(rsX, ok ? xoff + (uint32_t)(64 * h + 128 * i) * rowbytes : kOOB, (uint32_t)kb * 128, sb + i * 16384);
+  };
+  auto copy_w = [&](int kb, int h) LORA_INLINE {
+    char* sb = smem + (kb & 1) * STAGE + BM * 128 + wrow * 128 + h * 4096;
+    const bool ok = KFULL || kb * 64 + kcol < k;
 #pragma unroll
-    for (int i = 0; i < BN / 64; ++i)
-      dma16(rsW, ok ? voff + (uint32_t)(64 * i) * rowbytes : kOOB, k0b, sb + BM * 128 + i * 8192);
+    for (int i = 0; i < 2; ++i)
+      dma16(rsW, ok ? woff + (uint32_t)(32 * h + 128 * i) * rowbytes : kOOB, (uint32_t)kb * 128, sb + i * 16384);
   };
-  dload(0, 0);
-  copy_barrier<0>();
-  // Fragment reads as inline assembly, two register sets deep: the reads
-  // of substep ks+1 are issued before the products of substep ks, which
-  // wait (s_waitcnt lgkmcnt) only for their own six reads.  (Left to
-  // itself the compiler folds the two sets into one and waits for each
-  // pair of reads right before its products.)  Chunk c of row p sits at
-  // p*128 | ((c ^ kc_swz(p)) << 4); for the lane's chunk 2ks + g that is
-  // base ^ (ks << 5) with base = p*128 | ((kc_swz(p) ^ g) << 4), and the
-  // fragments of a wave are 32 rows (4096 bytes) apart with the same
-  // swizzle, so one address register per operand and buffer suffices.
-  static_assert(FJ == 2 && FI == 4, "reads per substep");
-  const uint32_t sg = (uint32_t)((kc_swz(c32) ^ g) << 4);
-  const uint32_t wb0 = lds_addr(smem + BM * 128 + (wn * WTJ + c32) * 128) | sg;
-  const uint32_t xb0 = lds_addr(smem + (wm * WTI + c32) * 128) | sg;
-  auto areads = [&](int buf, int ks, int p) LORA_INLINE {   // (ks, buf, p: constants after inlining)
-    const uint32_t wb = wb0 + (uint32_t)buf * STAGE, xb = xb0 + (uint32_t)buf * STAGE;
-    uint32_t ta, tb;
-    asm volatile(
-        "v_xor_b32 %[ta], %[kx], %[wb]\n\t"
-        "v_xor_b32 %[tb], %[kx], %[xb]\n\t"
-        "ds_read_b128 %[w0], %[ta]\n\t"
-        "ds_read_b128 %[w1], %[ta] offset:4096\n\t"
-        "ds_read_b128 %[x0], %[tb]\n\t"
-        "ds_read_b128 %[x1], %[tb] offset:4096\n\t"
-        "ds_read_b128 %[x2], %[tb] offset:8192\n\t"
-        "ds_read_b128 %[x3], %[tb] offset:12288"
-        : [w0] "=v"(fw[p][0]), [w1] "=v"(fw[p][1]), [x0] "=v"(fx[p][0]), [x1] "=v"(fx[p][1]),
-          [x2] "=v"(fx[p][2]), [x3] "=v"(fx[p][3]), [ta] "=&v"(ta), [tb] "=&v"(tb)
-        : [wb] "v"(wb), [xb] "v"(xb), [kx] "i"(ks << 5));
-  };
-  auto amult = [&](int p, bool last) LORA_INLINE {
-    if (last)
-      asm volatile("s_waitcnt lgkmcnt(0)"
-                   : "+v"(fw[p][0]), "+v"(fw[p][1]), "+v"(fx[p][0]), "+v"(fx[p][1]), "+v"(fx[p][2]),
-                     "+v"(fx[p][3]));
-    else
-      asm volatile("s_waitcnt lgkmcnt(6)"
-                   : "+v"(fw[p][0]), "+v"(fw[p][1]), "+v"(fx[p][0]), "+v"(fx[p][1]), "+v"(fx[p][2]),
-                     "+v"(fx[p][3]));
+  auto read_x = [&](int kb, int h) LORA_INLINE {
+    const char* Xs = smem + (kb & 1) * STAGE;
 #pragma unroll
-    for (int fi = 0; fi < FI; ++fi)
+    for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-      for (int fj = 0; fj < FJ; ++fj) acc[fj][fi] = mfma32x32x16(fw[p][fj], fx[p][fi], acc[fj][fi]);
+      for (int b = 0; b < 4; ++b) fx[kk][b] = kc_read(Xs, wm * WTI + 64 * h + 16 * b + c16, 4 * kk + g);
   };
-  auto astage = [&](int kb, auto bufc, bool load_next) LORA_INLINE {
-    constexpr int BUF = decltype(bufc)::value;
-    if (load_next) dload(kb + 1, BUF ^ 1);   // read in stage kb-1, free since its barrier
-    areads(BUF, 0, 0);
-    areads(BUF, 1, 1);
-    amult(0, false);
-    areads(BUF, 2, 0);
-    amult(1, false);
-    areads(BUF, 3, 1);
-    amult(0, false);
-    amult(1, true);
-    copy_barrier<0>();
+  auto read_w = [&](int kb, int h) LORA_INLINE {
+    const char* Ws = smem + (kb & 1) * STAGE + BM * 128;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) fw[h][kk][a] = kc_read(Ws, wn * WTJ + 32 * h + 16 * a + c16, 4 * kk + g);
   };
-  int kb = 0;
-  for (; kb + 2 < nkb; kb += 2) {
-    astage(kb, B0{}, true);
-    astage(kb + 1, B1{}, true);
+  auto slot_end = [&]() LORA_INLINE {
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto products = [&](int hw, int hx) LORA_INLINE {
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          acc[2 * hw + a][4 * hx + b] = mfma16x16x32(fw[hw][kk][a], fx[kk][b], acc[2 * hw + a][4 * hx + b]);
+    __builtin_amdgcn_sched_barrier(0);
+    slot_end();
+  };
+  auto ready = [&](auto left) LORA_INLINE {   // reads done; at most `left` quarters' copies in flight
+    __builtin_amdgcn_sched_barrier(0);
+    wait_lgkm0();
+    wait_vmcnt<2 * decltype(left)::value>();
+    slot_end();
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+  using I4 = std::integral_constant<int, 4>;
+  using I5 = std::integral_constant<int, 5>;
+  using I6 = std::integral_constant<int, 6>;
+  auto stage = [&](int kb, auto mode) LORA_INLINE {   // 0: steady, 1: the last but one, 2: the last
+    constexpr int MODE = decltype(mode)::value;
+    read_x(kb, 0);
+    if constexpr (MODE == 0) { copy_w(kb + 2, 0); ready(I6{}); }
+    else if constexpr (MODE == 1) ready(I5{});
+    else ready(I1{});
+    products(0, 0);
+    read_w(kb, 1);
+    if constexpr (MODE == 0) { copy_x(kb + 2, 0); ready(I6{}); }
+    else if constexpr (MODE == 1) ready(I4{});
+    else ready(I0{});
+    products(1, 0);
+    read_x(kb, 1);
+    if constexpr (MODE == 0) { copy_w(kb + 2, 1); ready(I6{}); }
+    else if constexpr (MODE == 1) ready(I3{});
+    else ready(I0{});
+    products(0, 1);
+    if constexpr (MODE < 2) read_w(kb + 1, 0);
+    if constexpr (MODE == 0) { copy_x(kb + 2, 1); ready(I6{}); }
+    else if constexpr (MODE == 1) ready(I2{});
+    else ready(I0{});
+    products(1, 1);
+  };
+  copy_w(0, 0); copy_x(0, 0); copy_w(0, 1); copy_x(0, 1);
+  if (nkb > 1) {
+    copy_w(1, 0); copy_x(1, 0); copy_w(1, 1); copy_x(1, 1);
+    wait_vmcnt<12>();
+  } else {
+    wait_vmcnt<0>();
   }
-  if (kb < nkb) astage(kb, B0{}, kb + 1 < nkb);
-  if (kb + 1 < nkb) astage(kb + 1, B1{}, false);
+  slot_end();
+  read_w(0, 0);
+  if (wm == 1) slot_end();       // the second wave row runs one slot behind
+  int kb = 0;
+  for (; kb + 2 < nkb; ++kb) stage(kb, I0{});
+  if (nkb > 1) stage(kb++, I1{});
+  stage(kb, I2{});
+  if (wm == 0) slot_end();
 
   // ---- epilogue ------------------------------------------------------------
   // LDS reuse: Us [BM][RPU] fp32 U, then Bs [BN][RPB] bf16 (B rows of this tile, zero beyond r and n).  The
@@ -234,47 +272,47 @@ __device__ __forceinline__ void fwd_big_tile(const u16* __restrict__ X, const u1
   }
   __syncthreads();
 
-  // acc += s U B^T, formed as Y^T += B (sU)^T over t in blocks of 16, each
-  // block once with the high and once with the low bf16 part of sU.
+  // acc += s U B^T, formed as Y^T += B (sU)^T over t in blocks of 16: one
+  // product of 32 k holds the block twice, against the high bf16 part of sU in
+  // its lower half (lanes g = 0, 1) and the low part in its upper half.
   const int tblocks = (r + 15) / 16;
   for (int tb = 0; tb < tblocks; ++tb) {
-    const int t0 = 16 * tb + 8 * g;
-    short8 bfr[FJ];
+    const int t0 = 16 * tb + 8 * (g & 1);
+    short8 bfr[4];
 #pragma unroll
-    for (int fj = 0; fj < FJ; ++fj) {
-      const int jl = wn * WTJ + 32 * fj + c32;
-      bfr[fj] = *reinterpret_cast<const short8*>(Bs + jl * RPB + t0);
-    }
+    for (int a = 0; a < 4; ++a)
+      bfr[a] = *reinterpret_cast<const short8*>(Bs + (wn * WTJ + 16 * a + c16) * RPB + t0);
 #pragma unroll
-    for (int fi = 0; fi < FI; ++fi) {
-      const int il = wm * WTI + 32 * fi + c32;
-      const float* up = Us + il * RPU + t0;
-      short8 uh, ul;
+    for (int b = 0; b < 8; ++b) {
+      const float* up = Us + (wm * WTI + 16 * b + c16) * RPU + t0;
+      short8 uf;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const float v = s * up[e];
         const u16 hi = f32_to_bf16(v);
-        uh[e] = (short)hi;
-        ul[e] = (short)f32_to_bf16(v - bf16_to_f32(hi));
+        uf[e] = (short)(g < 2 ? hi : f32_to_bf16(v - bf16_to_f32(hi)));
       }
 #pragma unroll
-      for (int fj = 0; fj < FJ; ++fj) {
-        acc[fj][fi] = mfma32x32x16(bfr[fj], uh, acc[fj][fi]);
-        acc[fj][fi] = mfma32x32x16(bfr[fj], ul, acc[fj][fi]);
-      }
+      for (int a = 0; a < 4; ++a) acc[a][b] = mfma16x16x32(bfr[a], uf, acc[a][b]);
     }
   }
 
-  // store Y: each wave's 32-token blocks of its 64 features through a
+  // store Y: each wave's blocks of 32 tokens x 64 features through a
   // wave-private LDS region (free once every wave is past the reads above)
-  static_assert(FJ == 2 && NW * kYsBytes <= 2 * STAGE, "output staging");
+  constexpr int OUT = out16_bytes<4, 2>();
+  static_assert(NW * OUT <= 2 * STAGE, "output staging");
   __syncthreads();
   const int j0 = n0 + wn * WTJ;
 #pragma unroll
-  for (int fi = 0; fi < FI; ++fi) {
+  for (int fi = 0; fi < 4; ++fi) {
     const int i0 = m0 + wm * WTI + 32 * fi;
-    store_block_32x64(acc[0][fi], acc[1][fi], smem + wave * kYsBytes, Y + (size_t)i0 * n + j0, (size_t)n, m - i0,
-                      n - j0, lane);
+    floatx4 v[4][2];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      v[a][0] = acc[a][2 * fi];
+      v[a][1] = acc[a][2 * fi + 1];
+    }
+    store_out16<4, 2>(v, smem + wave * OUT, Y + (size_t)i0 * n + j0, (size_t)n, m - i0, n - j0, lane);
   }
 }
 

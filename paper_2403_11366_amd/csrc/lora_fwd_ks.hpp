@@ -24,13 +24,15 @@ namespace lora {
 // multiplying and its partner's LDS latency is hidden, where the same loop
 // with both waves in step waits for the first fragments after each barrier.
 // Measured (weights rotated past the caches; forward kernel alone, U beside W,
-// against the same shapes on the previous tiles): 333 x 4096 x 4096, r = 8: 44
-// us on 96 workgroups of 128 x 128 with four waves in step, 37 with this loop,
-// 28.6 as 192 half tiles; 1024 x 5120 x 13824, r = 32: 174 us on 128 x 256
-// tiles, 154 on 128 x 192.  A slot lasts about as long as its LDS traffic: at
-// 128 x 128 44 KB of reads and 17 KB of copies, 0.24 us, against 0.12 us of
-// products.  Issuing the copies before the reads is 2 to 5% slower; s_setprio
-// around the products makes no difference here.
+// against the same shapes on the previous tiles): 2048 x 4096 x 4096, r = 8: 73
+// -> 68 us with the halves taking turns on 32x32x16 products, 63.7 on the
+// 16x16x32 ones used here, whose X fragments also feed the U products; 333 x
+// 4096 x 4096: 44 us on 96 workgroups of 128 x 128 with four waves in step, 37
+// with this loop, 28.8 as 192 half tiles; 1024 x 5120 x 13824, r = 32: 174 us on
+// 128 x 256 tiles, 153 on 128 x 192.  A slot lasts about as long as its LDS
+// traffic: at 128 x 128 36 KB of reads and 17 KB of copies, 0.23 us, against
+// 0.13 us of products.  Issuing the copies before the reads is 2 to 5% slower;
+// s_setprio around the products makes no difference here.
 //
 // Ordering.  Slot 2 kb holds the reads of half 0 and slot 2 kb + 1 those of
 // half 1 of stage kb.  Every wave waits for its LDS reads before the barrier
@@ -40,12 +42,14 @@ namespace lora {
 // leaving those of NBUF - 2 later stages in flight) before the barrier that
 // ends slot 2 kb + 1: by half 1 in its read slot, by half 0 after its products.
 //
-// After the k loop the two partial sums of each output are added in fixed
-// order through LDS: wave wk keeps token fragment wk of its 64 tokens and
-// sends the other, so each wave finishes 32 tokens x BN / 2 features.  U on
-// 16x16x32 products: wave (wk, wm, wn) owns the 16-token groups 2 wn, 2 wn + 1
-// of its token half, over its k half; the first tile column writes U.  s U B^T
-// is added as in lora_fwd_kernel.  GRP selects the projection of a grouped
+// BM = 64 (half of a paired 128 x 128 tile): four k shares instead of two, the
+// stages 128 wide (two 64-wide pieces), waves 0 .. 3 on the first piece.
+//
+// After the k loop the partial sums of each output are added in k-share order
+// through LDS, every wave finishing a share of the tokens of its block.  U:
+// wave (wk, wm, wn) multiplies A with its own X fragments of the tokens 32 wn ..
+// + 31 of its block, over its k share; the first tile column writes U.  s U B^T
+// is added as in the 256 x 256 tile.  GRP selects the projection of a grouped
 // launch; UPRE reads U from the U pass.  KFULL: k a multiple of 64 (otherwise
 // each copy checks its k bound).
 template <int BM, int BN, int RP, bool GRP, bool UPRE, bool KFULL>
@@ -53,7 +57,7 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
                                             const u16* __restrict__ A, const u16* __restrict__ B,
                                             u16* __restrict__ Y, float* __restrict__ U, int m, int n, int k, int r,
                                             float s, int m0, int tn, int n_begin, const FwdGroup& grp, char* smem) {
-  constexpr int NT = 512, FI = 2, FJ = BN / 64, WTJ = BN / 2;
+  constexpr int NT = 512, WTJ = BN / 2, NA = WTJ / 16;   // features per wave, in fragments of 16
   constexpr int WM = BM / 64, NK = 4 / WM;        // waves along the tokens, k shares
   constexpr int KP = NK / 2;                      // 64-wide k pieces per stage
   constexpr int ROWS = BM + BN + (UPRE ? 0 : 16);
@@ -62,8 +66,9 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
   constexpr int BS_EARLY = EARLY_B ? BN * RP * 2 : 0;
   constexpr int NBUF = (160 * 1024 - BS_EARLY) / STAGE < 4 ? (160 * 1024 - BS_EARLY) / STAGE : 4;
   constexpr int NCOPY = KP * (BM / 64 + BN / 64);  // copies per wave and stage
-  constexpr int NA = UPRE ? 0 : 2 * KP;           // waves 0 .. NA - 1: one more, for A
-  constexpr int XCH = NK == 2 ? 8 * FJ * 4096 : 8 * 4 * 4096;   // exchanged fragments of 64 lanes x 16 floats
+  constexpr int NCA = UPRE ? 0 : 2 * KP;          // waves 0 .. NCA - 1: one more, for A
+  constexpr int NOB = 4 / NK;                     // token fragments a wave finishes
+  constexpr int XCH = 8 * (NK == 2 ? 2 : 4) * NA * 1024;   // exchanged fragments of 64 lanes x 4 floats
   static_assert((BM == 128 || (BM == 64 && BN == 128)), "tile shapes");
   static_assert(NBUF >= 3 && (UPRE || RP == 16), "pipeline depth; U beside W only up to rank 16");
 
@@ -85,8 +90,7 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
   const int wave = uniform(tid >> 6);
   const int wk = wave / (2 * WM), wm = (wave >> 1) % WM, wn = wave & 1;
   const bool second = wave >= 4;                   // the waves that run one slot behind
-  const int g = lane >> 5, c32 = lane & 31;
-  const int g16 = lane >> 4, c16 = lane & 15;
+  const int g = lane >> 4, c16 = lane & 15;
 
   const uint32_t rowbytes = (uint32_t)k * 2;
   const __amdgpu_buffer_rsrc_t rsX = make_rsrc(X + (size_t)m0 * k, (uint64_t)min(BM, m - m0) * rowbytes);
@@ -116,7 +120,7 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
       for (int i = 0; i < BN / 64; ++i)
         dma16(rsW, ok ? voff + (uint32_t)(64 * i) * rowbytes : kOOB, so, sb + BM * 128 + i * 8192);
     }
-    if (wave < NA) {   // A: rows 8 (wave % 2) .. + 7 of piece wave / 2
+    if (wave < NCA) {   // A: rows 8 (wave % 2) .. + 7 of piece wave / 2
       const int k0 = (kb * KP + (wave >> 1)) * 64, row = 8 * (wave & 1) + (lane >> 3);
       const int kc = 8 * ((lane & 7) ^ kc_swz(row));
       dma16(rsA, k0 + kc < k ? (uint32_t)row * rowbytes + (uint32_t)(k0 + kc) * 2 : kOOB, 0,
@@ -126,7 +130,7 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
   // Wait until only the copies of the `later` newest stages are in flight.
   auto wait_copies = [&](auto later) LORA_INLINE {
     constexpr int N = decltype(later)::value;
-    if (wave < NA) wait_vmcnt<N * (NCOPY + 1)>();
+    if (wave < NCA) wait_vmcnt<N * (NCOPY + 1)>();
     else wait_vmcnt<N * NCOPY>();
   };
   using All = std::integral_constant<int, 0>;
@@ -160,42 +164,35 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
     }
   }
 
-  floatx16 acc[FJ][FI];
+  // acc[a][b]: features 16 a .. of the wave's block, tokens 16 (b ^ 2 wn) .. (in
+  // this order a wave's share of U is always its fragments b = 0, 1).
+  floatx4 acc[NA][4];
 #pragma unroll
-  for (int a = 0; a < FJ; ++a)
+  for (int a = 0; a < NA; ++a)
 #pragma unroll
-    for (int b = 0; b < FI; ++b) acc[a][b] = floatx16{};
-  floatx4 uacc16[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+    for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+  floatx4 uacc[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
 
-  short8 fw[2][FJ], fx[2][FI], fa16, fxu16[2];
+  short8 fw[NA], fx[4], fa;
   auto reads = [&](int boff) LORA_INLINE {
     const char* Xs = smem + boff + (wk >> 1) * PIECE;
     const char* Ws = Xs + BM * 128;
     const char* As = Xs + (BM + BN) * 128;
+    const int ch = 4 * (wk & 1) + g;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int ch = 2 * (2 * (wk & 1) + j) + g;
+    for (int b = 0; b < 4; ++b) fx[b] = kc_read(Xs, wm * 64 + 16 * (b ^ (2 * wn)) + c16, ch);
 #pragma unroll
-      for (int fi = 0; fi < FI; ++fi) fx[j][fi] = kc_read(Xs, wm * 64 + 32 * fi + c32, ch);
-#pragma unroll
-      for (int fj = 0; fj < FJ; ++fj) fw[j][fj] = kc_read(Ws, wn * WTJ + 32 * fj + c32, ch);
-    }
-    if (!UPRE) {
-      fa16 = kc_read(As, c16, 4 * (wk & 1) + g16);
-#pragma unroll
-      for (int gg = 0; gg < 2; ++gg) fxu16[gg] = kc_read(Xs, wm * 64 + 16 * (2 * wn + gg) + c16, 4 * (wk & 1) + g16);
-    }
+    for (int a = 0; a < NA; ++a) fw[a] = kc_read(Ws, wn * WTJ + 16 * a + c16, ch);
+    if (!UPRE) fa = kc_read(As, c16, ch);
   };
   auto multiply = [&]() LORA_INLINE {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int a = 0; a < NA; ++a)
 #pragma unroll
-      for (int fi = 0; fi < FI; ++fi)
-#pragma unroll
-        for (int fj = 0; fj < FJ; ++fj) acc[fj][fi] = mfma32x32x16(fw[j][fj], fx[j][fi], acc[fj][fi]);
+      for (int b = 0; b < 4; ++b) acc[a][b] = mfma16x16x32(fw[a], fx[b], acc[a][b]);
     if (!UPRE) {
-#pragma unroll
-      for (int gg = 0; gg < 2; ++gg) uacc16[gg] = mfma16x16x32(fa16, fxu16[gg], uacc16[gg]);
+      uacc[0] = mfma16x16x32(fa, fx[0], uacc[0]);
+      uacc[1] = mfma16x16x32(fa, fx[1], uacc[1]);
     }
   };
   auto slot_end = [&]() LORA_INLINE {
@@ -234,8 +231,7 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
   const int lane_e = lane_fresh();
   {
     const int lane = lane_e, tid = wave * 64 + lane_e;
-    const int g = lane >> 5, c32 = lane & 31;
-    const int g16 = lane >> 4, c16 = lane & 15;
+    const int g = lane >> 4, c16 = lane & 15;
     // Regions: [0, XCH) the exchange, later the per-wave output staging; Us fp32
     // [BM][RPU] (twice at RP = 16: the two k-half partials) and Bs bf16
     // [BN][RPB].  At RP = 16 they lie beside the exchange; for larger ranks they
@@ -263,71 +259,52 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
         }
       }
     }
-    // The wave finishes token fragment ofi, feature fragments ofj .. ofj + NO - 1
-    // of its block: with two k shares one token fragment, with four one
-    // 32 x 32 fragment.  Partial sums are added in k-share order.
-    constexpr int NO = NK == 2 ? FJ : 1;
-    const int ofi = NK == 2 ? wk : wk >> 1, ofj = NK == 2 ? 0 : wk & 1;
-    floatx16 own[NO];
-    float4* xb = reinterpret_cast<float4*>(smem);
+    // The wave finishes fragments b = NOB wk .. + NOB - 1 of its block.
+    // Partial sums are added in k-share order.
+    floatx4 own[NA][NOB];
+    floatx4* xb = reinterpret_cast<floatx4*>(smem);
     if constexpr (NK == 2) {
-      float4* dst = xb + (size_t)(wave ^ 4) * FJ * 4 * 64;   // the partner's region
+      floatx4* dst = xb + (size_t)(wave ^ 4) * NA * 2 * 64;   // the partner's region
 #pragma unroll
-      for (int fj = 0; fj < FJ; ++fj) {
-        const floatx16 a0 = acc[fj][0], a1 = acc[fj][1];
+      for (int a = 0; a < NA; ++a)
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          float4 o;
-          o.x = wk == 0 ? a1[4 * q4] : a0[4 * q4];
-          o.y = wk == 0 ? a1[4 * q4 + 1] : a0[4 * q4 + 1];
-          o.z = wk == 0 ? a1[4 * q4 + 2] : a0[4 * q4 + 2];
-          o.w = wk == 0 ? a1[4 * q4 + 3] : a0[4 * q4 + 3];
-          dst[(fj * 4 + q4) * 64 + lane] = o;
+        for (int b = 0; b < 2; ++b) {
+          const floatx4 lo = acc[a][b], hi = acc[a][2 + b];
+          floatx4 o;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            o[q] = wk == 0 ? hi[q] : lo[q];
+            own[a][b][q] = wk == 0 ? lo[q] : hi[q];
+          }
+          dst[(a * 2 + b) * 64 + lane] = o;
         }
-      }
-    } else {   // [wn][fragment 2 fi + fj][k share]
+    } else {   // [wn][token fragment][k share][feature fragment]
 #pragma unroll
-      for (int f = 0; f < 4; ++f) {
-        const floatx16 v = acc[f & 1][f >> 1];
+      for (int a = 0; a < NA; ++a)
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4)
-          xb[(size_t)(((wn * 4 + f) * 4 + wk) * 4 + q4) * 64 + lane] =
-              float4{v[4 * q4], v[4 * q4 + 1], v[4 * q4 + 2], v[4 * q4 + 3]};
-      }
+        for (int b = 0; b < 4; ++b) xb[(size_t)(((wn * 4 + b) * 4 + wk) * NA + a) * 64 + lane] = acc[a][b];
     }
     if (!UPRE) {
 #pragma unroll
       for (int gg = 0; gg < 2; ++gg)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          Us[(wk * BM + wm * 64 + 16 * (2 * wn + gg) + c16) * RP + 4 * g16 + q] = uacc16[gg][q];
+          Us[(wk * BM + wm * 64 + 16 * (2 * wn + gg) + c16) * RP + 4 * g + q] = uacc[gg][q];
     }
     __syncthreads();
     if constexpr (NK == 2) {
-      const float4* src = xb + (size_t)wave * FJ * 4 * 64;
+      const floatx4* src = xb + (size_t)wave * NA * 2 * 64;
 #pragma unroll
-      for (int fj = 0; fj < FJ; ++fj) {
-        const floatx16 a0 = acc[fj][0], a1 = acc[fj][1];
+      for (int a = 0; a < NA; ++a)
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const float4 o = src[(fj * 4 + q4) * 64 + lane];
-          own[fj][4 * q4] = (wk == 0 ? a0[4 * q4] : a1[4 * q4]) + o.x;
-          own[fj][4 * q4 + 1] = (wk == 0 ? a0[4 * q4 + 1] : a1[4 * q4 + 1]) + o.y;
-          own[fj][4 * q4 + 2] = (wk == 0 ? a0[4 * q4 + 2] : a1[4 * q4 + 2]) + o.z;
-          own[fj][4 * q4 + 3] = (wk == 0 ? a0[4 * q4 + 3] : a1[4 * q4 + 3]) + o.w;
-        }
-      }
+        for (int b = 0; b < 2; ++b) own[a][b] += src[(a * 2 + b) * 64 + lane];
     } else {
-      const float4* src = xb + (size_t)((wn * 4 + wk) * 4) * 4 * 64;
+      const floatx4* src = xb + (size_t)(wn * 4 + wk) * 4 * NA * 64;
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        float4 o = src[q4 * 64 + lane];
+      for (int a = 0; a < NA; ++a) {
+        own[a][0] = src[a * 64 + lane];
 #pragma unroll
-        for (int q = 1; q < 4; ++q) {
-          const float4 x = src[(q * 4 + q4) * 64 + lane];
-          o.x += x.x; o.y += x.y; o.z += x.z; o.w += x.w;
-        }
-        own[0][4 * q4] = o.x; own[0][4 * q4 + 1] = o.y; own[0][4 * q4 + 2] = o.z; own[0][4 * q4 + 3] = o.w;
+        for (int q = 1; q < 4; ++q) own[a][0] += src[(q * NA + a) * 64 + lane];
       }
     }
     if constexpr (!EARLY_B) {
@@ -372,34 +349,37 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
         if (m0 + il < m && t < r) U[(size_t)(m0 + il) * r + t] = Us[e];
       }
     }
-    // acc += s U B^T (high and low bf16 parts of s U) on the wave's 32 tokens
-    const int il = wm * 64 + 32 * ofi + c32;
+    // own += s U B^T: one product of 32 k holds a block of 16 t twice, against
+    // the high bf16 part of s U (lanes g = 0, 1) and the low part (g = 2, 3)
+    const int i1 = wm * 64 + 16 * ((NOB * wk) ^ (2 * wn));   // the wave's first token in the tile
     const int tblocks = RP == 16 ? 1 : (r + 15) / 16;
     for (int tb = 0; tb < tblocks; ++tb) {
-      const int t0 = 16 * tb + 8 * g;
-      const float* up = Us + il * RPU + t0;
-      short8 uh, ul;
+      const int t0 = 16 * tb + 8 * (g & 1);
+      short8 uf[NOB];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float v = s * up[e];
-        const u16 hi = f32_to_bf16(v);
-        uh[e] = (short)hi;
-        ul[e] = (short)f32_to_bf16(v - bf16_to_f32(hi));
+      for (int b = 0; b < NOB; ++b) {
+        const float* up = Us + (i1 + 16 * b + c16) * RPU + t0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float v = s * up[e];
+          const u16 hi = f32_to_bf16(v);
+          uf[b][e] = (short)(g < 2 ? hi : f32_to_bf16(v - bf16_to_f32(hi)));
+        }
       }
 #pragma unroll
-      for (int fj = 0; fj < NO; ++fj) {
-        const short8 bfr = *reinterpret_cast<const short8*>(Bs2 + (wn * WTJ + 32 * (ofj + fj) + c32) * RPB + t0);
-        own[fj] = mfma32x32x16(bfr, uh, own[fj]);
-        own[fj] = mfma32x32x16(bfr, ul, own[fj]);
+      for (int a = 0; a < NA; ++a) {
+        const short8 bfr = *reinterpret_cast<const short8*>(Bs2 + (wn * WTJ + 16 * a + c16) * RPB + t0);
+#pragma unroll
+        for (int b = 0; b < NOB; ++b) own[a][b] = mfma16x16x32(bfr, uf[b], own[a][b]);
       }
     }
     // Y rounded to bf16, through a wave-private LDS region (at RP = 16 the
     // exchange region, read before the last barrier)
     if constexpr (!EARLY_B) __syncthreads();
-    const int i0 = m0 + wm * 64 + 32 * ofi, j0 = n0 + wn * WTJ + 32 * ofj;
-    static_assert(8 * out_block_bytes<NO>() <= (EARLY_B ? XCH : 160 * 1024), "output staging");
-    store_out_block<NO>(own, smem + wave * out_block_bytes<NO>(), Y + (size_t)i0 * n + j0, (size_t)n, m - i0, n - j0,
-                        lane);
+    constexpr int OUT = out16_bytes<NA, NOB>();
+    static_assert(8 * OUT <= (EARLY_B ? XCH : 96 * 1024), "output staging");
+    store_out16<NA, NOB>(own, smem + wave * OUT, Y + (size_t)(m0 + i1) * n + n0 + wn * WTJ, (size_t)n, m - m0 - i1,
+                         n - n0 - wn * WTJ, lane);
   }
 }
 
@@ -408,7 +388,7 @@ constexpr int fwd_ks_smem() {
   constexpr int nk = BM == 128 ? 2 : 4;
   constexpr int stage = (BM + BN + (UPRE ? 0 : 16)) * 128 * (nk / 2), early = RP == 16 ? BN * RP * 2 : 0;
   constexpr int nbuf = (160 * 1024 - early) / stage < 4 ? (160 * 1024 - early) / stage : 4;
-  constexpr int loop = nbuf * stage + early, xch = nk == 2 ? 8 * (BN / 64) * 4096 : 8 * 4 * 4096;
+  constexpr int loop = nbuf * stage + early, xch = 8 * (nk == 2 ? 2 : 4) * (BN / 32) * 1024;
   constexpr int epi = RP == 16 ? xch + nk * BM * RP * 4 : BM * (RP + 4) * 4 + BN * (RP + 8) * 2;
   constexpr int e1 = epi > xch ? epi : xch;
   static_assert(loop <= 160 * 1024 && e1 <= (RP == 16 ? nbuf * stage : 160 * 1024), "LDS budget");

@@ -155,12 +155,14 @@ inline void plan_fwd_part(Plan& p, GemmTile t, int64_t m, int64_t k, int64_t r, 
   x.rp = fwd_rank(r);
   x.block = 512;
   if (t == TILE_128x256 && r <= 16) {
-    // Single-round launches with whole stages copy them straight into LDS and
-    // let the wave halves take turns (7B q_proj 73 -> 63 us); with more rounds
-    // or a partial stage the register-staged loop is as fast or faster (2048 x
-    // 11008 x 4096 182 and 186 us, 1531 x 4104 x 3208 64.5 and 67.8).
+    // With whole stages the stages are copied straight into LDS and the wave
+    // halves take turns (7B q_proj 73 -> 61 us; 2431 x 6656 x 4096, two rounds,
+    // 136 -> 122).  The register-staged loop stays for several rounds of few
+    // stages (2431 x 6656 x 128: 20.4 us, copies 21.1; x 256 equal) and for a
+    // partial last stage, whose rows lie unaligned (1531 x 4104 x 3208 64.5 us,
+    // copies 67.1).
     x.id = K_FWD_KS;
-    x.dma = kfull && x.grid <= 256;
+    x.dma = kfull && (x.grid <= 256 || k >= 512);
   } else if (t == TILE_PAIR) {
     x.id = K_FWD_PAIR;
     x.grid *= 2;
