@@ -15,10 +15,8 @@
 //             n and then over the 2 RP wide slab (high and low part of dU
 //             against the same A rows).  W is read through LDS with the
 //             transposing ds_read_b64_tr_b16, since the product contracts
-//             W over its rows.  The 128 x 256 and 256 x 256 tiles with whole
-//             stages copy them straight into LDS and issue their fragment
-//             reads as inline assembly with explicit waits.  After its tile, each workgroup of this launch
-//             (the first one of a split) sums a slice of the dB and dA
+//             W over its rows.  After its tile, each workgroup of this
+//             launch (the first one of a split) sums a slice of the dB and dA
 //             partials in a fixed order (no atomics, so results are
 //             bit-identical from run to run) and applies s to dB.
 #include <mutex>
@@ -846,14 +844,14 @@ struct DxGroup {
 };
 
 // ---------------------------------------------------------------------------
-// dX tile of BM tokens x BN input features, formed as dX^T = W^T dY^T with
-// v_mfma_f32_32x32x16_bf16 (W as the A operand, dY as the B operand).  Stages
-// of 64 along n: dY [BM rows][64] (k-contiguous) and W [64 rows of n][BN]
-// (mn-contiguous, read with the transposing LDS read).  After the n stages,
-// NSLAB stages cover the 2 RP wide slab: dU2 [BM][2RP] against A's rows, once
-// for the high and once for the low part.  Global loads run two stages ahead
-// in registers and are stored to the free LDS buffer piece by piece during
-// the stage before their use (one barrier per stage).
+// dX tiles, formed as dX^T = W^T dY^T with v_mfma_f32_16x16x32_bf16 (W as the A
+// operand, dY as the B operand).  Stages of 64 along n: dY [BM rows][64]
+// (k-contiguous) and W [64 rows of n][BN] (mn-contiguous, read with the
+// transposing LDS read, which is issued as inline assembly: the compiler would
+// otherwise wait for every copy in flight before each), copied from global
+// memory straight into LDS.  After the n stages, NSLAB stages cover the 2 RP
+// wide slab: dU2 [BM][2RP] against A's rows, once for the high and once for the
+// low part.
 //
 // With dropout (DROP) the LoRA term is keep * (dU A) / (1 - p): the mask acts
 // after the rank-r product, so it cannot ride in the k loop.  The slab stages
@@ -866,560 +864,605 @@ struct DxGroup {
 // stages are skipped and each dU_g A_g is added after the loop from LDS.
 //
 // FULL (every n a multiple of 64 and the launch's columns a multiple of BN):
-// the n-stage loads carry no bound checks.  With BN = 256 the stages are then
-// copied straight into LDS (DMA below); on the 128 x 128 tile they keep the
-// register staging and run in pairs with compile-time LDS buffers.
-template <int BM, int BN, int WM, int WN, int RP, bool DROP, bool GRP, bool FULL>
-__global__ __launch_bounds__(64 * WM * WN) void lora_bwd_dx_kernel(
-    const u16* __restrict__ dY, const u16* __restrict__ W, const u16* __restrict__ dU2,
-    const u16* __restrict__ A, const uint8_t* __restrict__ keep, u16* __restrict__ dX, int m, int n, int k,
-    int r, int mp, float inv_keep, int tiles_m, int tiles_n, int l_begin, FinalizeArgs fin, DxGroup grp) {
-  constexpr int NW = WM * WN;
-  constexpr int NT = 64 * NW;
-  constexpr int WTI = BM / WM, WTJ = BN / WN;
+// the copies carry no bound checks.
+constexpr int dx_ks_bufs(int bn) { return bn == 256 ? 3 : 4; }   // LDS stages of the 128-token tiles
 
-  constexpr int FI = WTI / 32, FJ = WTJ / 32;
-  constexpr int STAGE = BM * 128 + 64 * BN * 2;
-  constexpr int KS2 = 2 * RP;
-  constexpr int NSLAB = (KS2 + 63) / 64;
-  constexpr int CPR = BN / 8;                       // 16-byte chunks per W tile row
-  constexpr int CY = BM * 8, CW = 64 * CPR;          // chunks per stage
-  constexpr int LY = (CY + NT - 1) / NT, LW = (CW + NT - 1) / NT;
-  static_assert(WTI % 32 == 0 && WTJ % 32 == 0, "32x32 fragments");
-  static_assert(BN == 128 || BN == 256, "W tile rows of 256 or 512 bytes");
-  static_assert(NSLAB == 1 || NSLAB == 2, "slab stages of the unrolled tail");
-  // DMA: the 256-wide tiles with FULL copy their stages straight into
-  // LDS (128 x 256: three buffers, two stages ahead; 256 x 256: two buffers,
-  // one stage ahead), see the k loop below.  (The 128 x 128 tile with two
-  // buffers measured slower than with register staging: 13B q_proj step
-  // 462 -> 467 us.)
-  constexpr bool DMA = FULL && BN == 256;
-  constexpr int NBUF = DMA && BM == 128 ? 3 : 2;
-  static_assert(NBUF * STAGE <= 160 * 1024, "LDS budget");
-  __shared__ __attribute__((aligned(1024))) char smem[NBUF * STAGE];
+struct DxArgs {
+  const u16 *dY, *W, *dU2, *A;
+  const uint8_t* keep;
+  u16* dX;
+  int m, n, k, r, mp;
+  float inv_keep;
+};
 
-  int tm, tn;
-  tile_coords(tiles_m, tiles_n, 8, (int)blockIdx.x, tm, tn);
-  const int m0 = tm * BM, l0 = l_begin + tn * BN;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = uniform(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
-  const int g = lane >> 5, c32 = lane & 31;
-  const uint32_t yrow = (uint32_t)n * 2, wrow = (uint32_t)k * 2, urow = (uint32_t)KS2 * 2;
-  const __amdgpu_buffer_rsrc_t rsY = make_rsrc(dY + (size_t)m0 * n, (uint64_t)min(BM, m - m0) * yrow);
+// Source of the n stages, in order: projection, its stage, its dY rows (a
+// single projection's are the arguments').
+template <bool GRP>
+struct DxCursor {
+  int g = 0, sl = -1, n;
+  const u16* W;
+  uint32_t yr;
+  __amdgpu_buffer_rsrc_t rsY;
+  int m0, rows;
+  __device__ __forceinline__ DxCursor(const DxArgs& p, const DxGroup& grp, int m0_, int bm)
+      : n(GRP ? grp.n[0] : p.n), W(GRP ? grp.W[0] : p.W), yr((uint32_t)n * 2),
+        rsY(make_rsrc((GRP ? grp.dY[0] : p.dY) + (size_t)m0_ * n, (uint64_t)min(bm, p.m - m0_) * yr)), m0(m0_),
+        rows(min(bm, p.m - m0_)) {}
+  __device__ __forceinline__ void advance(const DxGroup& grp) {
+    ++sl;
+    if (GRP && sl * 64 >= n) {   // next projection (uniform)
+      ++g;
+      sl = 0;
+      n = pick(grp.n, g);
+      W = pick(grp.W, g);
+      yr = (uint32_t)n * 2;
+      rsY = make_rsrc(pick(grp.dY, g) + (size_t)m0 * n, (uint64_t)rows * yr);
+    }
+  }
+};
+
+// 16x16x32 A operand (16 columns x 32 k) of the rank-r rows in LDS: tile As
+// [RP][BN] mn-contiguous (mc16 swizzle), k rows 32 kk + 8 g .. + 7 of [A; A].
+template <int BN, int RP>
+__device__ __forceinline__ short8 slab_frag(const char* As, int kk, int col0, int lane) {
+  const int g = lane >> 4, c = lane & 15;
+  const int r0 = (32 * kk + 8 * g) % RP + (c >> 2), col = col0 + 4 * (c & 3);   // RP is a multiple of 16
+  const char* p0 = As + mc16_offset<BN>(r0, col >> 3) + (col & 7) * 2;
+  const char* p1 = As + mc16_offset<BN>(r0 + 4, col >> 3) + (col & 7) * 2;
+  return join4(__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4v*)p0),
+               __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4v*)p1));
+}
+
+// Stage a tile's dU2 rows (Us [BM][2 RP + 8] bf16) and A columns (As [RP][BN]
+// mn-contiguous, zero beyond r and k) for the rank-r term after the k loop.
+template <int BM, int BN, int RP, int NT>
+__device__ __forceinline__ void stage_rank_operands(const u16* dU2, const u16* A, u16* Us, char* As, int m0, int l0,
+                                                    int mp, int k, int r, int tid) {
+  constexpr int KS2 = 2 * RP, UP = KS2 + 8;
+  const uint32_t urow = (uint32_t)KS2 * 2, wrow = (uint32_t)k * 2;
   const __amdgpu_buffer_rsrc_t rsU = make_rsrc(dU2 + (size_t)m0 * KS2, (uint64_t)min(BM, mp - m0) * urow);
   const __amdgpu_buffer_rsrc_t rsA = make_rsrc(A, (uint64_t)r * wrow);
-  const int nkb = GRP ? grp.nkb : (n + 63) / 64;
-
-  // Staging registers move in pieces, one per 16-wide substep of the stage
-  // that stores them: 0 = the dY (or dU2) rows, 1 and 2 = the two halves of
-  // the W (or A) rows.
-  constexpr int LW1 = (LW + 1) / 2;
-  int4v gy[LY], gw[LW];
-  // Loads of W stage st (dY columns and W rows st*64 ..) and of slab stage sl
-  // (dU2 columns and the matching A rows, high part then low part).
-  // With GRP the stages are loaded in order (piece 0 of a stage first), so a
-  // load cursor -- projection, its stage, its dY rows -- advances by one stage
-  // at each piece 0 and switches projection only at a boundary.
-  int cur_g = 0, cur_sl = -1, cur_n = GRP ? grp.n[0] : n;
-  const u16* cur_W = GRP ? grp.W[0] : W;
-  uint32_t cur_yr = GRP ? (uint32_t)grp.n[0] * 2 : yrow;
-  __amdgpu_buffer_rsrc_t cur_rsY =
-      GRP ? make_rsrc(grp.dY[0] + (size_t)m0 * grp.n[0], (uint64_t)min(BM, m - m0) * cur_yr) : rsY;
-  auto gload_w = [&](int st, int piece) LORA_INLINE {
-    const u16* Wp = W;
-    int ns = n, sl = st;
-    if (GRP) {
-      if (piece == 0) {
-        ++cur_sl;
-        if (cur_sl * 64 >= cur_n) {   // next projection (uniform, taken count - 1 times)
-          ++cur_g;
-          cur_sl = 0;
-          cur_n = pick(grp.n, cur_g);
-          cur_W = pick(grp.W, cur_g);
-          cur_yr = (uint32_t)cur_n * 2;
-          cur_rsY = make_rsrc(pick(grp.dY, cur_g) + (size_t)m0 * cur_n, (uint64_t)min(BM, m - m0) * cur_yr);
-        }
-      }
-      Wp = cur_W;
-      ns = cur_n;
-      sl = cur_sl;
-    }
-    const int n0 = sl * 64;
-    if (piece == 0) {
-      const uint32_t yr = GRP ? cur_yr : yrow;
-      const __amdgpu_buffer_rsrc_t rsYs = GRP ? cur_rsY : rsY;
-#pragma unroll
-      for (int i = 0; i < LY; ++i) {
-        const int q = tid + i * NT;
-        if (CY % NT != 0 && wave * 64 + i * NT >= CY) break;   // wave-uniform
-        const int nn = n0 + 8 * (q & 7);
-        gy[i] = buf_load16(rsYs, (FULL || nn < ns) ? (uint32_t)(q >> 3) * yr + (uint32_t)nn * 2 : kOOB);
-      }
-    } else if (piece <= 2) {
-      const __amdgpu_buffer_rsrc_t rsW = make_rsrc(Wp + (size_t)n0 * k, (uint64_t)min(64, ns - n0) * wrow);
-#pragma unroll
-      for (int i = piece == 1 ? 0 : LW1; i < (piece == 1 ? LW1 : LW); ++i) {
-        const int q = tid + i * NT;
-        if (CW % NT != 0 && wave * 64 + i * NT >= CW) break;   // wave-uniform
-        const int ll = l0 + 8 * (q % CPR);
-        gw[i] = buf_load16(rsW, (FULL || ll < k) ? (uint32_t)(q / CPR) * wrow + (uint32_t)ll * 2 : kOOB);
-      }
-    }
-  };
-  auto gload_s = [&](int sl, int piece) LORA_INLINE {
-    const int kk0 = sl * 64;
-    if (piece == 0) {
-#pragma unroll
-      for (int i = 0; i < LY; ++i) {
-        const int q = tid + i * NT;
-        if (CY % NT != 0 && wave * 64 + i * NT >= CY) break;   // wave-uniform
-        const int kk = kk0 + 8 * (q & 7);
-        gy[i] = buf_load16(rsU, kk < KS2 ? (uint32_t)(q >> 3) * urow + (uint32_t)kk * 2 : kOOB);
-      }
-    } else if (piece <= 2) {
-#pragma unroll
-      for (int i = piece == 1 ? 0 : LW1; i < (piece == 1 ? LW1 : LW); ++i) {
-        const int q = tid + i * NT;
-        if (CW % NT != 0 && wave * 64 + i * NT >= CW) break;   // wave-uniform
-        const int kk = kk0 + q / CPR;
-        const int t = kk % RP;
-        const int ll = l0 + 8 * (q % CPR);
-        const bool ok = kk < KS2 && t < r && ll < k;
-        gw[i] = buf_load16(rsA, ok ? (uint32_t)t * wrow + (uint32_t)ll * 2 : kOOB);
-      }
-    }
-  };
-  auto swrite = [&](int buf, int piece) LORA_INLINE {
-    char* sb = smem + buf * STAGE;
-    if (piece == 0) {
-#pragma unroll
-      for (int i = 0; i < LY; ++i) {
-        const int q = tid + i * NT;
-        if (CY % NT != 0 && wave * 64 + i * NT >= CY) break;
-        *reinterpret_cast<int4v*>(sb + kc_offset(q >> 3, q & 7)) = gy[i];
-      }
-    } else if (piece <= 2) {
-#pragma unroll
-      for (int i = piece == 1 ? 0 : LW1; i < (piece == 1 ? LW1 : LW); ++i) {
-        const int q = tid + i * NT;
-        if (CW % NT != 0 && wave * 64 + i * NT >= CW) break;
-        *reinterpret_cast<int4v*>(sb + BM * 128 + mc32_offset<BN>(q / CPR, q % CPR)) = gw[i];
-      }
-    }
-  };
-
-  floatx16 acc[FJ][FI];
-#pragma unroll
-  for (int a = 0; a < FJ; ++a)
-#pragma unroll
-    for (int b = 0; b < FI; ++b) acc[a][b] = floatx16{};
-
-  // Fragments of the next 16-wide substep are read while the current one
-  // multiplies (two register sets, p = substep parity).
-  short8 fw[2][FJ], fy[2][FI];
-  auto read_frags = [&](const char* sb, int ks, int p) LORA_INLINE {
-    const char* Ys = sb;
-    const char* Ws = sb + BM * 128;
-#pragma unroll
-    for (int fj = 0; fj < FJ; ++fj) fw[p][fj] = mc32_read_tr<BN>(Ws, 16 * ks, wn * WTJ + 32 * fj, lane);
-#pragma unroll
-    for (int fi = 0; fi < FI; ++fi) fy[p][fi] = kc_read(Ys, wm * WTI + 32 * fi + c32, 2 * ks + g);
-  };
-  auto multiply = [&](int p) LORA_INLINE {
-#pragma unroll
-    for (int fi = 0; fi < FI; ++fi)
-#pragma unroll
-      for (int fj = 0; fj < FJ; ++fj) acc[fj][fi] = mfma32x32x16(fw[p][fj], fy[p][fi], acc[fj][fi]);
-  };
-
-  if constexpr (DMA) {
-    // Stages 0 .. nkb-1 over n, then the NSLAB slab stages; each stage is
-    // copied from global memory straight into an LDS buffer without staging
-    // registers (three or two buffers, two stages or one ahead): copy
-    // instruction j of a wave fills 1 KB of the
-    // buffer (dY region: rows 8j .. 8j+7; W region: rows WRK j ..), lane l its
-    // 16-byte position l, which holds the logical chunk given by the tile's
-    // swizzle (applied to the global address).  The fragment reads are issued
-    // as inline assembly with explicit lgkmcnt waits: the compiler would
-    // otherwise wait for every copy still in flight (s_waitcnt vmcnt(0))
-    // before each transposing read, which undoes the prefetch.  Per substep a
-    // wave issues NRD LDS reads (2 FJ transposing reads of W, FI of dY); the
-    // products of substep ks wait until only the reads of substep ks+1 are
-    // outstanding.  Each stage ends with a barrier that waits only for this
-    // wave's copies of the next stage (copy_barrier).
-    constexpr int NRD = 2 * FJ + FI;
-    constexpr int CYW = BM / 8 / NW;        // dY-region copies per wave and stage
-    constexpr int CWW = BN / 8 / NW;        // W-region copies per wave and stage
-    constexpr int WRK = 512 / BN;           // W rows per 1 KB copy
-    constexpr int WRB = BN * 2;             // bytes of a W tile row
-    static_assert(CYW * NW * 8 == BM && CWW * NW * 8 == BN, "copies per stage");
-    const int T = nkb + ((GRP || DROP) ? 0 : NSLAB);   // (group and dropout epilogues add dU A)
-    // With GRP the copies walk the projections' stages in order (dload is
-    // called once per stage, in stage order): cursor = projection, its stage,
-    // its dY rows.
-    int dc_g = 0, dc_sl = -1, dc_n = GRP ? grp.n[0] : n;
-    const u16* dc_W = GRP ? grp.W[0] : W;
-    uint32_t dc_yr = GRP ? (uint32_t)grp.n[0] * 2 : yrow;
-    __amdgpu_buffer_rsrc_t dc_rsY =
-        GRP ? make_rsrc(grp.dY[0] + (size_t)m0 * grp.n[0], (uint64_t)min(BM, m - m0) * dc_yr) : rsY;
-    const int dl_r8 = lane >> 3, dl_c8 = lane & 7, dl_rw = lane / (BN / 8), dl_cw = lane % (BN / 8);
-    auto dload = [&](int kb, int buf) LORA_INLINE {
-      char* sb = smem + buf * STAGE;
-      if (kb < nkb) {
-        const u16* Wp = W;
-        uint32_t yr = yrow;
-        __amdgpu_buffer_rsrc_t rsYs = rsY;
-        int sl = kb;
-        if (GRP) {
-          ++dc_sl;
-          if (dc_sl * 64 >= dc_n) {   // next projection (uniform)
-            ++dc_g;
-            dc_sl = 0;
-            dc_n = pick(grp.n, dc_g);
-            dc_W = pick(grp.W, dc_g);
-            dc_yr = (uint32_t)dc_n * 2;
-            dc_rsY = make_rsrc(pick(grp.dY, dc_g) + (size_t)m0 * dc_n, (uint64_t)min(BM, m - m0) * dc_yr);
-          }
-          Wp = dc_W;
-          yr = dc_yr;
-          rsYs = dc_rsY;
-          sl = dc_sl;
-        }
-        const __amdgpu_buffer_rsrc_t rsW = make_rsrc(Wp + (size_t)sl * 64 * k, (uint64_t)64 * wrow);
-#pragma unroll
-        for (int i = 0; i < CYW; ++i) {
-          const int j = wave + NW * i, row = 8 * j + dl_r8;
-          dma16(rsYs, (uint32_t)row * yr + (uint32_t)((dl_c8 ^ kc_swz(row)) << 4), (uint32_t)sl * 128,
-                sb + j * 1024);
-        }
-#pragma unroll
-        for (int i = 0; i < CWW; ++i) {
-          const int j = wave + NW * i, row = WRK * j + dl_rw;
-          const int c = dl_cw ^ mc32_swz(row);
-          dma16(rsW, (uint32_t)row * wrow + (uint32_t)(l0 + 8 * c) * 2, 0, sb + BM * 128 + j * 1024);
-        }
-      } else {
-        const int kk0 = (kb - nkb) * 64;
-#pragma unroll
-        for (int i = 0; i < CYW; ++i) {
-          const int j = wave + NW * i, row = 8 * j + dl_r8;
-          const int kk = kk0 + 8 * (dl_c8 ^ kc_swz(row));
-          dma16(rsU, kk < KS2 ? (uint32_t)row * urow + (uint32_t)kk * 2 : kOOB, 0, sb + j * 1024);
-        }
-#pragma unroll
-        for (int i = 0; i < CWW; ++i) {
-          const int j = wave + NW * i, row = WRK * j + dl_rw;
-          const int c = dl_cw ^ mc32_swz(row);
-          const int kk = kk0 + row, t = kk % RP;
-          dma16(rsA, (kk < KS2 && t < r) ? (uint32_t)t * wrow + (uint32_t)(l0 + 8 * c) * 2 : kOOB, 0,
-                sb + BM * 128 + j * 1024);
-        }
-      }
-    };
-    constexpr int NCOPY = CYW + CWW;   // copies per wave and stage
-    // Lane addresses of the fragment reads in buffer 0, substep 0: W fragment
-    // fj (the second read of a pair is 4 rows further; substep ks adds 16
-    // rows, the swizzle depending only on row % 4), dY fragment fi at substep
-    // ks (fi adds 32 rows = 4096 bytes).
-    uint32_t wa[FJ], ya[4];
-    {
-      const int h = (lane >> 4) & 1, j = lane & 15, e = j >> 2, q = j & 3;
-#pragma unroll
-      for (int fj = 0; fj < FJ; ++fj) {
-        const int col = wn * WTJ + 32 * fj + 16 * h + 4 * q;
-        wa[fj] = lds_addr(smem + BM * 128 + mc32_offset<BN>(8 * g + e, col >> 3) + (col & 7) * 2);
-      }
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) ya[ks] = lds_addr(smem + kc_offset(wm * WTI + c32, 2 * ks + g));
-    }
-    short4v fwl[2][FJ], fwh[2][FJ];
-    auto reads = [&](uint32_t boff, int ks, int p) LORA_INLINE {
-#pragma unroll
-      for (int fj = 0; fj < FJ; ++fj) {
-        const uint32_t a0 = wa[fj] + boff + (uint32_t)(16 * WRB) * ks;
-        ds_read_tr_b64_asm<0>(fwl[p][fj], a0);
-        ds_read_tr_b64_asm<4 * WRB>(fwh[p][fj], a0);
-      }
-      const uint32_t y0 = ya[ks] + boff;
-      ds_read_b128_asm<0>(fy[p][0], y0);
-      ds_read_b128_asm<4096>(fy[p][1], y0);
-      if constexpr (FI == 4) {
-        ds_read_b128_asm<8192>(fy[p][2], y0);
-        ds_read_b128_asm<12288>(fy[p][3], y0);
-      }
-    };
-    static_assert(FJ == 2 && (FI == 2 || FI == 4), "reads per substep");
-    auto mult = [&](int p, bool last) LORA_INLINE {
-      if constexpr (FI == 2) {
-        if (last)
-          asm volatile("s_waitcnt lgkmcnt(0)"
-                       : "+v"(fwl[p][0]), "+v"(fwh[p][0]), "+v"(fwl[p][1]), "+v"(fwh[p][1]), "+v"(fy[p][0]),
-                         "+v"(fy[p][1]));
-        else
-          asm volatile("s_waitcnt lgkmcnt(6)"
-                       : "+v"(fwl[p][0]), "+v"(fwh[p][0]), "+v"(fwl[p][1]), "+v"(fwh[p][1]), "+v"(fy[p][0]),
-                         "+v"(fy[p][1]));
-      } else {
-        if (last)
-          asm volatile("s_waitcnt lgkmcnt(0)"
-                       : "+v"(fwl[p][0]), "+v"(fwh[p][0]), "+v"(fwl[p][1]), "+v"(fwh[p][1]), "+v"(fy[p][0]),
-                         "+v"(fy[p][1]), "+v"(fy[p][2]), "+v"(fy[p][3]));
-        else
-          asm volatile("s_waitcnt lgkmcnt(8)"
-                       : "+v"(fwl[p][0]), "+v"(fwh[p][0]), "+v"(fwl[p][1]), "+v"(fwh[p][1]), "+v"(fy[p][0]),
-                         "+v"(fy[p][1]), "+v"(fy[p][2]), "+v"(fy[p][3]));
-      }
-      static_assert(NRD == (FI == 2 ? 6 : 8), "wait counts above");
-#pragma unroll
-      for (int fj = 0; fj < FJ; ++fj) {
-        const short8 w8 = join4(fwl[p][fj], fwh[p][fj]);
-#pragma unroll
-        for (int fi = 0; fi < FI; ++fi) acc[fj][fi] = mfma32x32x16(w8, fy[p][fi], acc[fj][fi]);
-      }
-    };
-    auto compute = [&](uint32_t boff) LORA_INLINE {
-      reads(boff, 0, 0);
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        if (ks < 3) reads(boff, ks + 1, (ks + 1) & 1);
-        mult(ks & 1, ks == 3);
-      }
-    };
-    using D0 = std::integral_constant<int, 0>;
-    using D1 = std::integral_constant<int, 1>;
-    using D2 = std::integral_constant<int, 2>;
-    if constexpr (NBUF == 3) {
-      auto dstage = [&](int kb, auto bufc, bool load_next) LORA_INLINE {
-        constexpr int BUF = decltype(bufc)::value;
-        if (load_next) dload(kb + 2, (BUF + 2) % 3);
-        compute((uint32_t)BUF * STAGE);
-        if (load_next) copy_barrier<NCOPY>();
-        else copy_barrier<0>();
-      };
-      dload(0, 0);
-      if (T > 1) dload(1, 1);
-      copy_barrier<0>();
-      int kb = 0;
-      for (; kb + 5 < T; kb += 3) {
-        dstage(kb, D0{}, true);
-        dstage(kb + 1, D1{}, true);
-        dstage(kb + 2, D2{}, true);
-      }
-      if (kb < T) dstage(kb, D0{}, kb + 2 < T);
-      if (kb + 1 < T) dstage(kb + 1, D1{}, kb + 3 < T);
-      if (kb + 2 < T) dstage(kb + 2, D2{}, kb + 4 < T);
-      if (kb + 3 < T) dstage(kb + 3, D0{}, false);
-      if (kb + 4 < T) dstage(kb + 4, D1{}, false);
-    } else {
-      // two buffers: stage kb+1 is copied into the other buffer (read in
-      // stage kb-1, before the last barrier) while stage kb multiplies
-      auto dstage = [&](int kb, auto bufc, bool load_next) LORA_INLINE {
-        constexpr int BUF = decltype(bufc)::value;
-        if (load_next) dload(kb + 1, BUF ^ 1);
-        compute((uint32_t)BUF * STAGE);
-        copy_barrier<0>();
-      };
-      dload(0, 0);
-      copy_barrier<0>();
-      int kb = 0;
-      for (; kb + 1 < T; kb += 2) {
-        dstage(kb, D0{}, true);
-        dstage(kb + 1, D1{}, kb + 2 < T);
-      }
-      if (kb < T) dstage(kb, D0{}, false);
-    }
-  } else {
-  // Same pipeline as the forward GEMM: at the top of stage st the registers
-  // hold stage st+1; piece ks goes to the free LDS buffer at substep ks and
-  // its registers then receive the loads of stage st+2.  With ROT the
-  // products of substep 3 run after the barrier (zero operands before stage
-  // 0).  Stages 0 .. nkb-1 run over n, the NSLAB (1 or 2) slab stages follow;
-  // the tail is unrolled so every load is of a known kind.
-  constexpr bool ROT = BM * BN < 256 * 256;
-  if (ROT) {
-#pragma unroll
-    for (int j = 0; j < FJ; ++j) fw[1][j] = short8{};
-#pragma unroll
-    for (int j = 0; j < FI; ++j) fy[1][j] = short8{};
+  for (int q = tid; q < BM * (RP / 4); q += NT) {
+    const int i = q / (RP / 4), c = q % (RP / 4);
+    *reinterpret_cast<int4v*>(Us + i * UP + 8 * c) = buf_load16(rsU, (uint32_t)i * urow + (uint32_t)c * 16);
   }
-  enum { LD_NONE, LD_W, LD_S0, LD_S1 };
-  // bufc: the stage's LDS buffer as a compile-time constant, or -1 for the
-  // parity of st at run time
-  auto stage = [&](int st, auto bufc, bool write_next, int load) LORA_INLINE {
-    constexpr int BUF = decltype(bufc)::value;
-    const int cur = BUF >= 0 ? BUF : (st & 1);
-    const char* sb = smem + cur * STAGE;
-    read_frags(sb, 0, 0);
-    if (ROT) multiply(1);
+  for (int q = tid; q < RP * (BN / 8); q += NT) {
+    const int t = q / (BN / 8), c = q % (BN / 8);
+    const int ll = l0 + 8 * c;
+    *reinterpret_cast<int4v*>(As + mc16_offset<BN>(t, c)) =
+        buf_load16(rsA, (t < r && ll < k) ? (uint32_t)t * wrow + (uint32_t)ll * 2 : kOOB);
+  }
+}
+
+// 128 x BN tiles.  Eight waves: wave (wk, wn) multiplies all 128 tokens with BN
+// / 4 columns over the 32-wide n half wk of every stage (so each W column is
+// read by one wave per half: the transposing reads run at half the rate of the
+// plain ones), three or four stages in LDS.  The two halves take turns reading
+// and multiplying exactly as in the forward's 128-token tiles, with the same
+// ordering of copies, waits and barriers; after the loop the halves' partial
+// sums are exchanged through LDS, each wave finishing 64 tokens.
+// Measured (whole backward call, against 64 x 64 wave tiles in step on 32x32x16
+// products, register-staged for partial stages and 128 x 128): 2048 x 4096 x
+// 4096 (tokens x n x k), r = 8: 76 -> 70 us; 333 x 4096 x 4096 51 -> 40; 1531 x
+// 4104 x 3208, r = 12: 83 -> 71; 2000 x 512 x 4096 24.8 -> 25.6 (the exchange;
+// even at n = 1024).  The reads come before the copies: 5 us slower the other
+// way round at 2048 x 4096 x 4096.
+template <int BN, int RP, bool DROP, bool GRP, bool FULL>
+__device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, int m0, int l0, char* smem) {
+  constexpr int BM = 128, NT = 512, NA = BN / 64;  // 16-column fragments per wave
+  constexpr int STAGE = BM * 128 + 64 * BN * 2;
+  constexpr int NBUF = dx_ks_bufs(BN);
+  constexpr int KS2 = 2 * RP, NSLAB = (KS2 + 63) / 64;
+  constexpr int CPR = BN / 8;                      // 16-byte chunks per W tile row
+  constexpr int NCOPY = BM / 64 + BN / 64;         // copies per wave and stage
+  static_assert(BN == 128 || BN == 192 || BN == 256, "W tile rows");
+  const int m = p.m, n = p.n, k = p.k, r = p.r;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = uniform(tid >> 6);
+  const int wk = wave >> 2, wn = wave & 3;
+  const int g = lane >> 4, c16 = lane & 15;
+  const uint32_t wrow = (uint32_t)k * 2, urow = (uint32_t)KS2 * 2;
+  const __amdgpu_buffer_rsrc_t rsU = make_rsrc(p.dU2 + (size_t)m0 * KS2, (uint64_t)min(BM, p.mp - m0) * urow);
+  const __amdgpu_buffer_rsrc_t rsA = make_rsrc(p.A, (uint64_t)r * wrow);
+  const int nkb = GRP ? grp.nkb : (n + 63) / 64;
+  const int T = nkb + ((GRP || DROP) ? 0 : NSLAB);
+  DxCursor<GRP> cur(p, grp, m0, BM);
+
+  // dY copy i: rows 64 i + 8 wave + lane / 8; W copy i: the tile's 16-byte
+  // positions 64 (8 i + wave) + lane.  The lane's position holds the logical
+  // chunk of the tile's swizzle (dY: the same for every i).
+  const int yr0 = 8 * wave + (lane >> 3);
+  const int ycol = 8 * ((lane & 7) ^ kc_swz(yr0));
+  int wr[BN / 64], wcol[BN / 64];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      if (write_next) swrite(cur ^ 1, ks);
-      if (load == LD_W) gload_w(st + 2, ks);
-      if (load == LD_S0) gload_s(0, ks);
-      if (load == LD_S1) gload_s(1, ks);
-      if (ks < 3) read_frags(sb, ks + 1, (ks + 1) & 1);
-      if (ks < 3 || !ROT) multiply(ks & 1);
+  for (int i = 0; i < BN / 64; ++i) {
+    const int pos = 64 * (8 * i + wave) + lane;
+    wr[i] = pos / CPR;
+    wcol[i] = l0 + 8 * ((pos % CPR) ^ mc16_swz_of<BN>(wr[i]));
+  }
+  auto copy_main = [&](int boff) LORA_INLINE {       // the cursor's stage
+    char* sb = smem + boff + wave * 1024;
+    const int n0 = cur.sl * 64;
+    const bool yok = FULL || n0 + ycol < cur.n;
+    const uint32_t yoff = (uint32_t)yr0 * cur.yr + (uint32_t)ycol * 2;
+#pragma unroll
+    for (int i = 0; i < BM / 64; ++i)
+      dma16(cur.rsY, yok ? yoff + (uint32_t)(64 * i) * cur.yr : kOOB, (uint32_t)n0 * 2, sb + i * 8192);
+    const __amdgpu_buffer_rsrc_t rsW =
+        make_rsrc(cur.W + (size_t)n0 * k, (uint64_t)(FULL ? 64 : min(64, cur.n - n0)) * wrow);
+#pragma unroll
+    for (int i = 0; i < BN / 64; ++i)
+      dma16(rsW, FULL || wcol[i] < k ? (uint32_t)wr[i] * wrow + (uint32_t)wcol[i] * 2 : kOOB, 0,
+            sb + BM * 128 + i * 8192);
+  };
+  auto copy_slab = [&](int kb, int boff) LORA_INLINE {
+    char* sb = smem + boff + wave * 1024;
+    const int kk0 = (kb - nkb) * 64;
+    const uint32_t uoff = (uint32_t)(kk0 + ycol) * 2;
+#pragma unroll
+    for (int i = 0; i < BM / 64; ++i)
+      dma16(rsU, uoff < urow ? (uint32_t)(yr0 + 64 * i) * urow + uoff : kOOB, 0, sb + i * 8192);
+#pragma unroll
+    for (int i = 0; i < BN / 64; ++i) {
+      const int kk = kk0 + wr[i], t = kk % RP;
+      dma16(rsA, ((FULL || wcol[i] < k) && kk < KS2 && t < r) ? (uint32_t)t * wrow + (uint32_t)wcol[i] * 2 : kOOB, 0,
+            sb + BM * 128 + i * 8192);
+    }
+  };
+  // Fragment addresses in buffer 0: W rows 32 wk + 8 g + e (second read of a
+  // pair 4 rows further), columns wn BN / 4 + 16 a + 4 q; dY as kc_read.
+  uint32_t wa[NA];
+  {
+    const int e = c16 >> 2, q = c16 & 3;
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+      wa[a] = lds_addr(smem + BM * 128 +
+                       mc16_offset<BN>(32 * wk + 8 * g + e, (wn * (BN / 4) + 16 * a) / 8 + (q >> 1)) + (q & 1) * 8);
+  }
+  floatx4 acc[NA][8];
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b < 8; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+  short8 fy[8];
+  short4v wl[NA], wh[NA];
+  auto slot_end = [&]() LORA_INLINE {
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int st = 0; st < NBUF - 1; ++st) {
+    if (st < nkb) {
+      cur.advance(grp);
+      copy_main(st * STAGE);
+    } else if (st < T) {
+      copy_slab(st, st * STAGE);
+    }
+  }
+  if (T >= NBUF - 1) wait_vmcnt<(NBUF - 2) * NCOPY>();
+  else wait_vmcnt<0>();
+  slot_end();                    // stage 0 has landed
+  if (wk == 1) slot_end();       // half 1 runs one slot behind
+  int rb = 0, wb = (NBUF - 1) * STAGE;
+  // Stage kb; mode 0: refills a buffer with an n stage, 1: with a slab stage,
+  // 2: with none.  Nothing branches between the assembly reads and their wait.
+  auto stage = [&](int kb, auto mode) LORA_INLINE {
+    constexpr int MODE = decltype(mode)::value;
+    if constexpr (MODE == 0) cur.advance(grp);
+    const char* Ys = smem + rb;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) fy[b] = kc_read(Ys, 16 * b + c16, 4 * wk + g);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      ds_read_tr_b64_asm<0>(wl[a], wa[a] + (uint32_t)rb);
+      ds_read_tr_b64_asm<4 * BN * 2>(wh[a], wa[a] + (uint32_t)rb);
+    }
+    if constexpr (MODE == 0) copy_main(wb);
+    if constexpr (MODE == 1) copy_slab(kb + NBUF - 1, wb);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (NA == 4)
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : "+v"(wl[0]), "+v"(wh[0]), "+v"(wl[1]), "+v"(wh[1]), "+v"(wl[2]), "+v"(wh[2]), "+v"(wl[3]),
+                     "+v"(wh[3]));
+    else if constexpr (NA == 3)
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : "+v"(wl[0]), "+v"(wh[0]), "+v"(wl[1]), "+v"(wh[1]), "+v"(wl[2]), "+v"(wh[2]));
+    else
+      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(wl[0]), "+v"(wh[0]), "+v"(wl[1]), "+v"(wh[1]));
+    static_assert(NA >= 2 && NA <= 4, "fragments of the wait");
+    if (wk == 1) wait_vmcnt<MODE == 2 ? 0 : (NBUF - 2) * NCOPY>();
+    slot_end();
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      const short8 w8 = join4(wl[a], wh[a]);
+#pragma unroll
+      for (int b = 0; b < 8; ++b) acc[a][b] = mfma16x16x32(w8, fy[b], acc[a][b]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (wk == 0) wait_vmcnt<MODE == 2 ? 0 : (NBUF - 2) * NCOPY>();
+    slot_end();
+    rb = rb + STAGE == NBUF * STAGE ? 0 : rb + STAGE;
+    wb = wb + STAGE == NBUF * STAGE ? 0 : wb + STAGE;
+  };
+  int kb = 0;
+  for (; kb + NBUF - 1 < nkb; ++kb) stage(kb, std::integral_constant<int, 0>{});
+  if constexpr (!GRP && !DROP)
+    for (; kb + NBUF - 1 < T; ++kb) stage(kb, std::integral_constant<int, 1>{});
+  for (; kb < T; ++kb) stage(kb, std::integral_constant<int, 2>{});
+  if (wk == 0) slot_end();
+
+  // Exchange: wave wk keeps the token fragments 4 wk .. + 3, moved to own[..][0
+  // .. 3], and sends the others (branches on wk: selects of every element cost
+  // a microsecond).
+  auto& own = acc;
+  floatx4* xin = reinterpret_cast<floatx4*>(smem) + (size_t)wave * NA * 4 * 64;   // from the partner
+  {
+    floatx4* dst = reinterpret_cast<floatx4*>(smem) + (size_t)(wave ^ 4) * NA * 4 * 64;
+    if (wk == 0) {
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) dst[(a * 4 + b) * 64 + lane] = acc[a][4 + b];
+    } else {
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          dst[(a * 4 + b) * 64 + lane] = acc[a][b];
+          own[a][b] = acc[a][4 + b];
+        }
     }
     __syncthreads();
-  };
 #pragma unroll
-  for (int pc = 0; pc < 3; ++pc) gload_w(0, pc);
+    for (int a = 0; a < NA; ++a)
 #pragma unroll
-  for (int pc = 0; pc < 3; ++pc) swrite(0, pc);
-  __syncthreads();
-  constexpr int NSL = (DROP || GRP) ? 0 : NSLAB;   // slab stages in the k loop
-  using B0 = std::integral_constant<int, 0>;
-  using B1 = std::integral_constant<int, 1>;
-  using BR = std::integral_constant<int, -1>;
-  int st = 0;
-  if (nkb >= 2) {
-#pragma unroll
-    for (int pc = 0; pc < 3; ++pc) gload_w(1, pc);
-    if constexpr (FULL) {
-      for (; st + 3 < nkb; st += 2) {
-        stage(st, B0{}, true, LD_W);
-        stage(st + 1, B1{}, true, LD_W);
-      }
-    }
-    for (; st + 2 < nkb; ++st) stage(st, BR{}, true, LD_W);
-    stage(st, BR{}, true, NSL > 0 ? LD_S0 : LD_NONE);   // st = nkb - 2
-    ++st;
-  } else if (NSL > 0) {
-#pragma unroll
-    for (int pc = 0; pc < 3; ++pc) gload_s(0, pc);
+      for (int b = 0; b < 4; ++b) own[a][b] += xin[(a * 4 + b) * 64 + lane];
   }
-  if (NSL > 0) stage(st++, BR{}, true, NSL > 1 ? LD_S1 : LD_NONE);   // writes slab 0
-  if (NSL > 1) stage(st++, BR{}, true, LD_NONE);                     // writes slab 1
-  stage(st, BR{}, false, LD_NONE);
-  if (ROT) multiply(1);
-  }
+  const int i1 = 64 * wk, j1 = wn * (BN / 4);      // the wave's first token and column in the tile
 
-  if (GRP) {
-    // LDS after the k loop, per projection: Us2 [BM][UP] bf16 (dU_g high |
-    // low of the tile's tokens), As2 [RP][BN] bf16 mn-contiguous (A_g rows,
-    // zero beyond r and k).  acc += [dU_hi | dU_lo] [A_g; A_g].
-    constexpr int UP = 2 * RP + 8;
+  if constexpr (GRP || DROP) {
+    constexpr int UP = KS2 + 8;                    // Us row pitch in elements (16-byte multiple)
     constexpr int US_BYTES = BM * UP * 2, AS_BYTES = RP * BN * 2;
-    static_assert(US_BYTES + AS_BYTES <= 2 * STAGE, "group epilogue fits the stage LDS");
-    u16* Us2 = reinterpret_cast<u16*>(smem);
-    char* As2 = smem + US_BYTES;
-    for (int pq = 0; pq < grp.count; ++pq) {
-      if (pq > 0) __syncthreads();                  // the previous projection's reads are done
-      const __amdgpu_buffer_rsrc_t rsU2 =
-          make_rsrc(pick(grp.dU2, pq) + (size_t)m0 * KS2, (uint64_t)min(BM, mp - m0) * urow);
-      const __amdgpu_buffer_rsrc_t rsAq = make_rsrc(pick(grp.A, pq), (uint64_t)r * wrow);
-      constexpr int UCH = BM * (RP / 4);            // 16-byte chunks of the dU2 rows
-      for (int q = tid; q < UCH; q += NT) {
-        const int i = q / (RP / 4), c = q % (RP / 4);
-        *reinterpret_cast<int4v*>(Us2 + i * UP + 8 * c) = buf_load16(rsU2, (uint32_t)i * urow + (uint32_t)c * 16);
-      }
-      constexpr int ACH = RP * (BN / 8);
-      for (int q = tid; q < ACH; q += NT) {
-        const int t = q / (BN / 8), c = q % (BN / 8);
-        const int ll = l0 + 8 * c;
-        *reinterpret_cast<int4v*>(As2 + mc32_offset<BN>(t, c)) =
-            buf_load16(rsAq, (t < r && ll < k) ? (uint32_t)t * wrow + (uint32_t)ll * 2 : kOOB);
-      }
-      __syncthreads();
-      // (kk unrolled by two only: fully unrolled, the fragment reads of all
-      // 2 RP / 16 steps are issued ahead and spill beside the accumulators)
+    static_assert(US_BYTES + AS_BYTES + BM * BN / 8 <= NBUF * STAGE, "the rank-r operands fit the stage LDS");
+    u16* Us = reinterpret_cast<u16*>(smem);
+    char* As = smem + US_BYTES;
+    if constexpr (GRP) {
+      for (int pq = 0; pq < grp.count; ++pq) {
+        __syncthreads();                           // the exchange, or the previous projection's reads, are done
+        stage_rank_operands<BM, BN, RP, NT>(pick(grp.dU2, pq), pick(grp.A, pq), Us, As, m0, l0, p.mp, k, r, tid);
+        __syncthreads();
+#pragma unroll 1
+        for (int kk = 0; kk < KS2 / 32; ++kk) {
+          short8 uf[4];
 #pragma unroll
-      for (int fj = 0; fj < FJ; ++fj)
-#pragma unroll 2
-        for (int kk = 0; kk < KS2 / 16; ++kk) {
-          const short8 af = mc32_read_tr<BN>(As2, (16 * kk) % RP, wn * WTJ + 32 * fj, lane);
+          for (int b = 0; b < 4; ++b)
+            uf[b] = *reinterpret_cast<const short8*>(Us + (i1 + 16 * b + c16) * UP + 32 * kk + 8 * g);
 #pragma unroll
-          for (int fi = 0; fi < FI; ++fi) {
-            const short8 bf =
-                *reinterpret_cast<const short8*>(Us2 + (wm * WTI + 32 * fi + c32) * UP + 16 * kk + 8 * g);
-            acc[fj][fi] = mfma32x32x16(af, bf, acc[fj][fi]);
+          for (int a = 0; a < NA; ++a) {
+            const short8 af = slab_frag<BN, RP>(As, kk, j1 + 16 * a, lane);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) own[a][b] = mfma16x16x32(af, uf[b], own[a][b]);
           }
         }
-    }
-  }
-
-  if (DROP) {
-    // LDS after the k loop: Us2 [BM][UP] bf16 (dU high | low of the tile's
-    // tokens), As2 [RP][BN] bf16 mn-contiguous (A rows, zero beyond r and k),
-    // Kb [BM][BN/8] keep bytes of the tile.
-    constexpr int UP = 2 * RP + 8;                  // Us2 row pitch in elements (16-byte multiple)
-    constexpr int US_BYTES = BM * UP * 2, AS_BYTES = RP * BN * 2;
-    static_assert(US_BYTES + AS_BYTES + BM * BN / 8 <= 2 * STAGE, "dropout epilogue fits the stage LDS");
-    u16* Us2 = reinterpret_cast<u16*>(smem);
-    char* As2 = smem + US_BYTES;
-    uint8_t* Kb = reinterpret_cast<uint8_t*>(smem + US_BYTES + AS_BYTES);
-    const uint32_t kb8 = (uint32_t)k / 8;
-    {
-      constexpr int UCH = BM * (RP / 4);            // 16-byte chunks of the dU2 rows
-      const __amdgpu_buffer_rsrc_t rsU2 = make_rsrc(dU2 + (size_t)m0 * KS2, (uint64_t)min(BM, mp - m0) * urow);
-      for (int q = tid; q < UCH; q += NT) {
-        const int i = q / (RP / 4), c = q % (RP / 4);
-        *reinterpret_cast<int4v*>(Us2 + i * UP + 8 * c) = buf_load16(rsU2, (uint32_t)i * urow + (uint32_t)c * 16);
       }
-      constexpr int ACH = RP * (BN / 8);
-      for (int q = tid; q < ACH; q += NT) {
-        const int t = q / (BN / 8), c = q % (BN / 8);
-        const int ll = l0 + 8 * c;
-        *reinterpret_cast<int4v*>(As2 + mc32_offset<BN>(t, c)) =
-            buf_load16(rsA, (t < r && ll < k) ? (uint32_t)t * wrow + (uint32_t)ll * 2 : kOOB);
-      }
-      constexpr int KCH = BM * (BN / 64);           // 8-byte chunks of keep bits
-      const __amdgpu_buffer_rsrc_t rsK = make_rsrc(keep + (size_t)m0 * kb8, (uint64_t)min(BM, m - m0) * kb8);
-      for (int q = tid; q < KCH; q += NT) {
+    } else {
+      __syncthreads();                             // the exchange has been read
+      stage_rank_operands<BM, BN, RP, NT>(p.dU2, p.A, Us, As, m0, l0, p.mp, k, r, tid);
+      uint8_t* Kb = reinterpret_cast<uint8_t*>(smem + US_BYTES + AS_BYTES);   // keep bytes of the tile [BM][BN / 8]
+      const uint32_t kb8 = (uint32_t)k / 8;
+      const __amdgpu_buffer_rsrc_t rsK = make_rsrc(p.keep + (size_t)m0 * kb8, (uint64_t)min(BM, m - m0) * kb8);
+      for (int q = tid; q < BM * (BN / 64); q += NT) {
         const int i = q / (BN / 64), c = q % (BN / 64);
         *reinterpret_cast<uint2*>(Kb + i * (BN / 8) + 8 * c) =
             buf_load8(rsK, (uint32_t)i * kb8 + (uint32_t)l0 / 8 + 8 * c);
       }
+      __syncthreads();
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        floatx4 tmp[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) tmp[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < KS2 / 32; ++kk) {
+          const short8 af = slab_frag<BN, RP>(As, kk, j1 + 16 * a, lane);
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+            tmp[b] = mfma16x16x32(
+                af, *reinterpret_cast<const short8*>(Us + (i1 + 16 * b + c16) * UP + 32 * kk + 8 * g), tmp[b]);
+        }
+        // lane: token c16 of fragment b, columns 16 a + 4 g + q
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const uint32_t bits = (uint32_t)Kb[(i1 + 16 * b + c16) * (BN / 8) + (j1 + 16 * a) / 8 + (g >> 1)] >> (4 * (g & 1));
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if ((bits >> q) & 1u) own[a][b][q] += p.inv_keep * tmp[b][q];
+        }
+      }
+    }
+  }
+  // Stored through the wave's own exchange region, which nobody else touches
+  // after the exchange; the rank-r operands of a group or dropout lie there too.
+  if constexpr (GRP || DROP) __syncthreads();
+  constexpr int OUT = out16_bytes<NA, 4>();
+  static_assert(OUT <= NA * 4 * 1024 && 8 * NA * 4 * 1024 <= NBUF * STAGE, "output staging and exchange");
+  floatx4 v[NA][4];
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) v[a][b] = own[a][b];
+  store_out16<NA, 4>(v, reinterpret_cast<char*>(xin), p.dX + (size_t)(m0 + i1) * k + l0 + j1, (size_t)k, m - m0 - i1,
+                     k - l0 - j1, lane);
+}
+
+// The 256 x 256 tile (whole stages and columns).
+// Stages 0 .. nkb-1 over n, then the NSLAB slab stages, two in LDS.  The
+// wave rows take turns as in the forward's 256 x 256 tile: per stage four
+// phases of sixteen products -- (W half 0, dY half 0), (W 1, dY 0), (W 0, dY
+// 1), (W 1, dY 1) -- and while one row multiplies, the other reads the dY
+// half 0, W half 1, dY half 1, or the next stage's W half 0, and refills
+// the quarter that both rows read in the phase before for the stage after
+// next.  dY half h: tokens 64 h .. + 63 of both wave rows.  W half h:
+// columns 128 h .. + 127 of the tile as [64][128] (wave column wn takes
+// columns 128 h + 32 wn .. + 31), so that a copy takes whole 256-byte row
+// pieces.  Nothing branches between the assembly reads and their wait.
+// Measured (whole backward call, against all waves in step on 32x32x16
+// products): 8192 x 4096 x 11008 (tokens x n x k), r = 64: 712 -> 650 us taking
+// turns, 628 on the 16x16x32 products used here; 4096 x 11008 x 4096, r = 16:
+// 305, 305 and 292.
+template <int RP, bool GRP>
+__device__ __forceinline__ void dx_big_tile(const DxArgs& p, const DxGroup& grp, int m0, int l0, char* smem) {
+  constexpr int BM = 256, BN = 256, NT = 512, WTI = 128;
+  constexpr int STAGE = BM * 128 + 64 * BN * 2;
+  constexpr int KS2 = 2 * RP, NSLAB = (KS2 + 63) / 64;
+  const int m = p.m, k = p.k, r = p.r;
+  u16* dX = p.dX;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = uniform(tid >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
+  const int g16 = lane >> 4, c16 = lane & 15;
+  const uint32_t wrow = (uint32_t)k * 2, urow = (uint32_t)KS2 * 2;
+  const __amdgpu_buffer_rsrc_t rsU = make_rsrc(p.dU2 + (size_t)m0 * KS2, (uint64_t)min(BM, p.mp - m0) * urow);
+  const __amdgpu_buffer_rsrc_t rsA = make_rsrc(p.A, (uint64_t)r * wrow);
+  const int nkb = GRP ? grp.nkb : (p.n + 63) / 64;
+  // acc[a][b]: columns big_col(a) .. + 15 of the tile, tokens 16 b .. of the wave row.
+  floatx4 acc[4][8];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 8; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto big_col = [&](int a) LORA_INLINE { return 128 * (a >> 1) + 32 * wn + 16 * (a & 1); };
+  const int T = nkb + (GRP ? 0 : NSLAB);   // (group epilogues add dU A)
+  DxCursor<GRP> cur(p, grp, m0, BM);   // advanced once per stage
+  const int l8 = lane >> 3, l16 = lane >> 4;
+  const int yr0 = 8 * wave + l8;                            // dY row of this lane in copy 0 (+ 64 h + 128 i)
+  const uint32_t ych = (uint32_t)(((lane & 7) ^ kc_swz(yr0)) << 4);
+  const int wr0 = 4 * wave + l16;                           // W row (+ 32 i)
+  const int wc = (lane & 15) ^ mc16_swz(wr0);               // logical 8-column chunk of the half
+  using Slab = std::true_type;
+  using Main = std::false_type;
+  // Quarters of stage kb (Main: the cursor's stage).
+  auto copy_y = [&](int kb, int h, auto slab) LORA_INLINE {
+    char* sb = smem + (kb & 1) * STAGE + wave * 1024 + h * 8192;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uint32_t row = (uint32_t)(yr0 + 64 * h + 128 * i);
+      if constexpr (decltype(slab)::value) {
+        const uint32_t off = (uint32_t)(kb - nkb) * 128 + ych;
+        dma16(rsU, off < urow ? row * urow + off : kOOB, 0, sb + i * 16384);
+      } else {
+        dma16(cur.rsY, row * cur.yr + ych, (uint32_t)cur.sl * 128, sb + i * 16384);
+      }
+    }
+  };
+  auto copy_w = [&](int kb, int h, auto slab) LORA_INLINE {
+    char* sb = smem + (kb & 1) * STAGE + BM * 128 + h * 16384 + wave * 1024;
+    const uint32_t col = (uint32_t)(l0 + 128 * h + 8 * wc) * 2;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = wr0 + 32 * i;
+      if constexpr (decltype(slab)::value) {
+        const int kk = (kb - nkb) * 64 + row, t = kk % RP;
+        dma16(rsA, (kk < KS2 && t < r) ? (uint32_t)t * wrow + col : kOOB, 0, sb + i * 8192);
+      } else {
+        const __amdgpu_buffer_rsrc_t rsW = make_rsrc(cur.W + (size_t)cur.sl * 64 * k, (uint64_t)64 * wrow);
+        dma16(rsW, (uint32_t)row * wrow + col, 0, sb + i * 8192);
+      }
+    }
+  };
+  // Fragment addresses in buffer 0: W half 0, k rows 0 .. 31 (half 1 + 16384,
+  // rows 32 .. 63 + 8192, second read of a pair + 1024), dY as kc_read.
+  uint32_t wa[2];
+  {
+    const int e = c16 >> 2, q = c16 & 3;
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+      wa[a] = lds_addr(smem + BM * 128 + mc16_offset<128>(8 * g16 + e, 4 * wn + 2 * a + (q >> 1)) + (q & 1) * 8);
+  }
+  short8 fyq[2][4];                    // the current dY half: [32-wide k][token fragment]
+  short4v wl[2][4], wh[2][4];          // W halves: [half][2 (32-wide k) + fragment], rows 0..3 and 4..7 of eight
+  auto read_y = [&](int kb, int h) LORA_INLINE {
+    const char* Ys = smem + (kb & 1) * STAGE;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) fyq[kk][b] = kc_read(Ys, wm * WTI + 64 * h + 16 * b + c16, 4 * kk + g16);
+  };
+  auto read_w = [&](int kb, auto hc) LORA_INLINE {
+    constexpr int H = decltype(hc)::value;
+    const uint32_t a0 = wa[0] + (uint32_t)((kb & 1) * STAGE), a1 = wa[1] + (uint32_t)((kb & 1) * STAGE);
+    ds_read_tr_b64_asm<H * 16384>(wl[H][0], a0);
+    ds_read_tr_b64_asm<H * 16384 + 1024>(wh[H][0], a0);
+    ds_read_tr_b64_asm<H * 16384>(wl[H][1], a1);
+    ds_read_tr_b64_asm<H * 16384 + 1024>(wh[H][1], a1);
+    ds_read_tr_b64_asm<H * 16384 + 8192>(wl[H][2], a0);
+    ds_read_tr_b64_asm<H * 16384 + 9216>(wh[H][2], a0);
+    ds_read_tr_b64_asm<H * 16384 + 8192>(wl[H][3], a1);
+    ds_read_tr_b64_asm<H * 16384 + 9216>(wh[H][3], a1);
+  };
+  auto slot_end = [&]() LORA_INLINE {
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Reads done (the W fragments pass through the wait, so their products
+  // stay behind it); at most `left` quarters' copies in flight.
+  auto ready = [&](auto left, auto hc) LORA_INLINE {
+    constexpr int H = decltype(hc)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (H >= 0)
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : "+v"(wl[H][0]), "+v"(wh[H][0]), "+v"(wl[H][1]), "+v"(wh[H][1]), "+v"(wl[H][2]), "+v"(wh[H][2]),
+                     "+v"(wl[H][3]), "+v"(wh[H][3]));
+    else
+      wait_lgkm0();
+    wait_vmcnt<2 * decltype(left)::value>();
+    slot_end();
+  };
+  auto products = [&](int hw, int hy) LORA_INLINE {
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        const short8 w8 = join4(wl[hw][2 * kk + a], wh[hw][2 * kk + a]);
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          acc[2 * hw + a][4 * hy + b] = mfma16x16x32(w8, fyq[kk][b], acc[2 * hw + a][4 * hy + b]);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    slot_end();
+  };
+  using N1 = std::integral_constant<int, -1>;
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+  using I4 = std::integral_constant<int, 4>;
+  using I5 = std::integral_constant<int, 5>;
+  using I6 = std::integral_constant<int, 6>;
+  // mode 0: refill with n stages, 3: with slab stages, 1: the last stage but
+  // one, 2: the last.
+  auto stage = [&](int kb, auto mode) LORA_INLINE {
+    constexpr int MODE = decltype(mode)::value;
+    constexpr bool FILL = MODE == 0 || MODE == 3;
+    using S = std::integral_constant<bool, MODE == 3>;
+    if constexpr (MODE == 0) cur.advance(grp);
+    read_y(kb, 0);
+    if constexpr (FILL) { copy_w(kb + 2, 0, S{}); ready(I6{}, N1{}); }
+    else if constexpr (MODE == 1) ready(I5{}, N1{});
+    else ready(I1{}, N1{});
+    products(0, 0);
+    read_w(kb, I1{});
+    if constexpr (FILL) { copy_y(kb + 2, 0, S{}); ready(I6{}, I1{}); }
+    else if constexpr (MODE == 1) ready(I4{}, I1{});
+    else ready(I0{}, I1{});
+    products(1, 0);
+    read_y(kb, 1);
+    if constexpr (FILL) { copy_w(kb + 2, 1, S{}); ready(I6{}, N1{}); }
+    else if constexpr (MODE == 1) ready(I3{}, N1{});
+    else ready(I0{}, N1{});
+    products(0, 1);
+    if constexpr (MODE != 2) read_w(kb + 1, I0{});
+    if constexpr (FILL) { copy_y(kb + 2, 1, S{}); ready(I6{}, I0{}); }
+    else if constexpr (MODE == 1) ready(I2{}, I0{});
+    else ready(I0{}, N1{});
+    products(1, 1);
+  };
+  auto fill = [&](int kb) LORA_INLINE {
+    if (kb < nkb) {
+      cur.advance(grp);
+      copy_w(kb, 0, Main{}); copy_y(kb, 0, Main{}); copy_w(kb, 1, Main{}); copy_y(kb, 1, Main{});
+    } else {
+      copy_w(kb, 0, Slab{}); copy_y(kb, 0, Slab{}); copy_w(kb, 1, Slab{}); copy_y(kb, 1, Slab{});
+    }
+  };
+  fill(0);
+  if (T > 1) {
+    fill(1);
+    wait_vmcnt<12>();
+  } else {
+    wait_vmcnt<0>();
+  }
+  slot_end();
+  read_w(0, I0{});
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(wl[0][0]), "+v"(wh[0][0]), "+v"(wl[0][1]), "+v"(wh[0][1]), "+v"(wl[0][2]), "+v"(wh[0][2]),
+                 "+v"(wl[0][3]), "+v"(wh[0][3]));
+  if (wm == 1) slot_end();       // the second wave row runs one slot behind
+  int kb = 0;
+  for (; kb + 2 < nkb; ++kb) stage(kb, I0{});
+  if constexpr (!GRP)
+    for (; kb + 2 < T; ++kb) stage(kb, I3{});
+  if (T > 1) stage(kb++, I1{});
+  stage(kb, I2{});
+  if (wm == 0) slot_end();
+
+  if constexpr (GRP) {
+    // LDS after the k loop, per projection: dU_g rows (high | low) and A_g rows;
+    // acc += [dU_hi | dU_lo] [A_g; A_g].
+    constexpr int UP = KS2 + 8;
+    constexpr int US_BYTES = BM * UP * 2, AS_BYTES = RP * BN * 2;
+    static_assert(US_BYTES + AS_BYTES <= 2 * STAGE, "the rank-r operands fit the stage LDS");
+    u16* Us = reinterpret_cast<u16*>(smem);
+    char* As = smem + US_BYTES;
+    for (int pq = 0; pq < grp.count; ++pq) {
+      if (pq > 0) __syncthreads();                  // the previous projection's reads are done
+      stage_rank_operands<BM, BN, RP, NT>(pick(grp.dU2, pq), pick(grp.A, pq), Us, As, m0, l0, p.mp, k, r, tid);
+      __syncthreads();
+#pragma unroll 1
+      for (int kk = 0; kk < KS2 / 32; ++kk) {
+        short8 uf[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b)
+          uf[b] = *reinterpret_cast<const short8*>(Us + (wm * WTI + 16 * b + c16) * UP + 32 * kk + 8 * g16);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          const short8 af = slab_frag<BN, RP>(As, kk, big_col(a), lane);
+#pragma unroll
+          for (int b = 0; b < 8; ++b) acc[a][b] = mfma16x16x32(af, uf[b], acc[a][b]);
+        }
+      }
     }
     __syncthreads();
-#pragma unroll
-    for (int fj = 0; fj < FJ; ++fj) {
-      floatx16 tmp[FI];
-#pragma unroll
-      for (int fi = 0; fi < FI; ++fi) tmp[fi] = floatx16{};
-#pragma unroll
-      for (int kk = 0; kk < KS2 / 16; ++kk) {        // k = t of [dU_hi | dU_lo] against [A; A]
-        const short8 af = mc32_read_tr<BN>(As2, (16 * kk) % RP, wn * WTJ + 32 * fj, lane);
-#pragma unroll
-        for (int fi = 0; fi < FI; ++fi) {
-          const short8 bf = *reinterpret_cast<const short8*>(Us2 + (wm * WTI + 32 * fi + c32) * UP + 16 * kk + 8 * g);
-          tmp[fi] = mfma32x32x16(af, bf, tmp[fi]);
-        }
-      }
-      // lane: token column c32 of fragment fi, features 8 qq + 4 g + q4 of
-      // fragment fj -> keep byte (wn WTJ + 32 fj) / 8 + qq, bit 4 g + q4
-#pragma unroll
-      for (int fi = 0; fi < FI; ++fi) {
-        const uint8_t* kr = Kb + (wm * WTI + 32 * fi + c32) * (BN / 8) + (wn * WTJ + 32 * fj) / 8;
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-          const uint32_t byte = kr[qq];
-#pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4)
-            if ((byte >> (4 * g + q4)) & 1u) acc[fj][fi][4 * qq + q4] += inv_keep * tmp[fi][4 * qq + q4];
-        }
-      }
-    }
   }
 
-  // store dX: each wave's 32-token blocks of its 64 features through a
-  // wave-private LDS region (the k loop ended with a barrier; the group and
-  // dropout epilogues read LDS until here)
-  static_assert(FJ == 2 && NW * kYsBytes <= 2 * STAGE, "output staging");
-  if (GRP || DROP) __syncthreads();
-  {
-    const int j0 = l0 + wn * WTJ;
+  // The wave's columns lie in two pieces: the tile goes through LDS as bf16 and
+  // is stored in whole rows.
+  static_assert(2 * STAGE >= 256 * 512, "the bf16 tile fits the stage LDS");
 #pragma unroll
-    for (int fi = 0; fi < FI; ++fi) {
-      const int i0 = m0 + wm * WTI + 32 * fi;
-      store_block_32x64(acc[0][fi], acc[1][fi], smem + wave * kYsBytes, dX + (size_t)i0 * k + j0, (size_t)k,
-                        m - i0, k - j0, lane);
+  for (int b = 0; b < 8; ++b)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const int row = wm * WTI + 16 * b + c16, col = big_col(a) + 4 * g16;
+      const floatx4 v = acc[a][b];
+      const uint32_t lo = (uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16);
+      const uint32_t hi = (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16);
+      // 16-byte chunk col / 8 at position (col / 8) ^ (row % 32)
+      *reinterpret_cast<uint2*>(smem + row * 512 + (((col >> 3) ^ (row & 31)) << 4) + (col & 7) * 2) = uint2{lo, hi};
     }
+  __syncthreads();
+  for (int e = tid; e < BM * 32; e += NT) {   // (whole column tiles: FULL)
+    const int row = e >> 5, ch = e & 31;
+    const int4v v = *reinterpret_cast<const int4v*>(smem + row * 512 + ((ch ^ (row & 31)) << 4));
+    if (m0 + row < m) *reinterpret_cast<int4v*>(dX + (size_t)(m0 + row) * k + l0 + 8 * ch) = v;
   }
-  // After its tile, every workgroup sums a slice of the dA, dB partials
-  // (complete: the token reductions ran before this launch in stream order).
-  const int first = (int)blockIdx.x * NT + (int)threadIdx.x, stride = (int)gridDim.x * NT;
+}
+
+// After its tile, every workgroup sums a slice of the dA, dB partials
+// (complete: the token reductions ran before this launch in stream order).
+template <int BM, int BN, int WM, int WN, int RP, bool DROP, bool GRP, bool FULL>
+__global__ __launch_bounds__(512) void lora_bwd_dx_kernel(
+    const u16* __restrict__ dY, const u16* __restrict__ W, const u16* __restrict__ dU2,
+    const u16* __restrict__ A, const uint8_t* __restrict__ keep, u16* __restrict__ dX, int m, int n, int k,
+    int r, int mp, float inv_keep, int tiles_m, int tiles_n, int l_begin, FinalizeArgs fin, DxGroup grp) {
+  static_assert(BM == 128 || (BM == 256 && BN == 256 && FULL && !DROP), "tile shapes");
+  __shared__ __attribute__((aligned(1024))) char smem[BM == 256 ? 2 * 65536 : dx_ks_bufs(BN) * (BM * 128 + BN * 128)];
+  int tm, tn;
+  tile_coords(tiles_m, tiles_n, 8, (int)blockIdx.x, tm, tn);
+  const DxArgs p{dY, W, dU2, A, keep, dX, m, n, k, r, mp, inv_keep};
+  if constexpr (BM == 256) dx_big_tile<RP, GRP>(p, grp, tm * BM, l_begin + tn * BN, smem);
+  else dx_ks_tile<BN, RP, DROP, GRP, FULL>(p, grp, tm * BM, l_begin + tn * BN, smem);
+  const int first = (int)blockIdx.x * 512 + (int)threadIdx.x, stride = (int)gridDim.x * 512;
   if (GRP) {
     for (int pq = 0; pq < grp.count; ++pq) finalize_partials(pick(grp.fin, pq), first, stride);
   } else {
@@ -1733,19 +1776,19 @@ __global__ __launch_bounds__(256) void lora_finalize_kernel(FinalizeArgs f) {
 // ---------------------------------------------------------------------------
 // Launchers: execute the plans of lora_plan.hpp.
 
-// dX instantiations a plan can name: no dropout in groups or on the 256 x 256
-// tile, and the 256 x 256 tile only with whole stages (FULL).
+// Instantiations a plan can name: the 256 x 256 tile only with whole stages and
+// without dropout, 128 x 192 for single projections.
 template <int BM, int BN, int RP, bool DROP, bool GRP, bool FULL>
 constexpr bool dx_instantiated() {
-  return !(DROP && GRP) && !(DROP && BM == 256) && !(BM == 256 && !FULL);
+  return !(DROP && GRP) && (BM == 128 || (FULL && !DROP)) && !(BN == 192 && GRP);
 }
 
 static hipError_t run_dx(const Launch& L, const BwdArgs& a, const u16* dU2, int mp, const FinalizeArgs& fin,
                          const DxGroup& grp, hipStream_t st) {
   const dim3 grid((unsigned)L.grid), block((unsigned)L.block);
-  return with_int<0, 1, 2>(tile_code(L), [&](auto tc) {
+  return with_int<128, 192, 256, 257>(tile_code(L), [&](auto tc) {
     constexpr int T = decltype(tc)::value;
-    constexpr int BM = T == 0 ? 256 : 128, BN = T == 2 ? 128 : 256, WN = T == 2 ? 2 : 4;
+    constexpr int BM = T == 257 ? 256 : 128, BN = T == 257 ? 256 : T, WN = BN == 256 ? 4 : 2;
     return with_int<16, 32, 48, 64>(L.rp, [&](auto rc) {
       return with_bool(L.drop, [&](auto dr) {
         return with_bool(L.grp, [&](auto gr) {

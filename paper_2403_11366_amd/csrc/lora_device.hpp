@@ -185,9 +185,15 @@ __device__ __forceinline__ short8 kc_read(const char* tile, int row, int chunk) 
 __device__ __forceinline__ int mc16_swz(int row) { return 2 * (row & 3) + 8 * ((row >> 3) & 1); }
 __device__ __forceinline__ int mc32_swz(int row) { return 4 * (row & 3); }
 
+// Rows of 192 (384 bytes): consecutive rows already fall in different halves of
+// the banks, and the swizzle has to stay within 8 chunks of 24.
+template <int COLS>
+__device__ __forceinline__ int mc16_swz_of(int row) {
+  return COLS == 192 ? 2 * ((row >> 1) & 1) + 4 * ((row >> 3) & 1) : mc16_swz(row);
+}
 template <int COLS>
 __device__ __forceinline__ uint32_t mc16_offset(int row, int chunk) {
-  return (uint32_t)(row * (COLS * 2) + ((chunk ^ mc16_swz(row)) << 4));
+  return (uint32_t)(row * (COLS * 2) + ((chunk ^ mc16_swz_of<COLS>(row)) << 4));
 }
 template <int COLS>
 __device__ __forceinline__ uint32_t mc32_offset(int row, int chunk) {

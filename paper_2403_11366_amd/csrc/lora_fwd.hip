@@ -908,7 +908,7 @@ static hipError_t run_fwd_launch(const Launch& L, const FwdArgs& a, const FwdGro
   if (L.id != K_FWD && L.id != K_FWD_PAIR) return hipErrorInvalidValue;
   // U comes from the tile only at rank 16 and below the 256 x 256 tile, 128 x
   // 192 serves single projections, and 128 x 256 at rank 16 is K_FWD_KS's.
-  const int tile = L.id == K_FWD_PAIR ? 64 : L.bn + (L.bm == 256 ? 1 : 0);
+  const int tile = L.id == K_FWD_PAIR ? 64 : tile_code(L);
   return with_int<64, 128, 192, 256, 257>(tile, [&](auto tc) {
     constexpr int T = decltype(tc)::value;
     return with_int<16, 32, 64>(L.rp, [&](auto rc) {

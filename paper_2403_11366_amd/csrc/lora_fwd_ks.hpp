@@ -200,7 +200,10 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  copy_barrier<0>();             // the first stages and B are staged
+  if (nkb >= NBUF - 1) wait_copies(Deep{});
+  else wait_copies(All{});
+  wait_lgkm0();
+  slot_end();                    // stage 0 and B are staged
   if (second) slot_end();        // half 1 runs one slot behind
   int rb = 0, wb = (NBUF - 1) * STAGE;
   for (int kb = 0; kb < nkb; ++kb) {

@@ -15,9 +15,9 @@ inline int pad_rank(int64_t r) { return (int)((r + 15) / 16) * 16; }
 inline int64_t pad_tokens(int64_t m) { return (m + 63) / 64 * 64; }
 
 // Output tiles of the two large GEMMs (tokens x features): 256x256 runs 8
-// waves (two per SIMD) as 2 x 4 waves of 128 x 64; the tiles of 128 tokens run
-// 8 waves (128x128 dX: 4).  Forward only: 128x192, and 128x128 shared by a
-// pair of workgroups of 64 tokens each.
+// waves (two per SIMD) as 2 x 4 waves of 128 x 64, the others 8 waves that
+// split k.  Forward only: 128x128 shared by a pair of workgroups of 64 tokens
+// each.
 enum GemmTile { TILE_256x256 = 0, TILE_128x256 = 1, TILE_128x128 = 2, TILE_128x192 = 3, TILE_PAIR = 4 };
 
 // A candidate tile: the output area a workgroup computes, and the workgroup's
@@ -28,15 +28,19 @@ enum GemmTile { TILE_256x256 = 0, TILE_128x256 = 1, TILE_128x128 = 2, TILE_128x1
 struct TileCost { GemmTile t; int bm, bn, wgs; double eff; };
 
 // Forward tiles.  Time per 64-wide k stage with the chip full, measured at k =
-// 4096 to 13824: 256x256 1.70 us, 128x256 0.94, 128x192 0.74, 128x128 0.58, a
-// half of a pair 0.42.  128x192 serves single projections of k >= 2048 (with
-// fewer stages a launch is mostly its fixed cost).
-constexpr TileCost kFwdTiles[5] = {{TILE_256x256, 256, 256, 1, 1.0}, {TILE_128x256, 128, 256, 1, 0.9},
-                                   {TILE_128x128, 128, 128, 1, 0.73}, {TILE_128x192, 128, 192, 1, 0.85},
-                                   {TILE_PAIR, 128, 128, 2, 0.5}};
-// dX tiles (measured at 4096 x 5120 x 5120 and 4096 x 13824 x 5120).
-constexpr TileCost kDxTiles[3] = {{TILE_256x256, 256, 256, 1, 1.0}, {TILE_128x256, 128, 256, 1, 0.9},
-                                  {TILE_128x128, 128, 128, 1, 0.75}};
+// 4096 to 13824: 256x256 1.34 us, 128x256 0.85, 128x192 0.72, 128x128 0.55, a
+// half of a pair 0.42.
+constexpr TileCost kFwdTiles[5] = {{TILE_256x256, 256, 256, 1, 1.0}, {TILE_128x256, 128, 256, 1, 0.8},
+                                   {TILE_128x128, 128, 128, 1, 0.61}, {TILE_128x192, 128, 192, 1, 0.71},
+                                   {TILE_PAIR, 128, 128, 2, 0.4}};
+// dX tiles (per 64-wide n stage: 1.39 us, 0.77, 0.48, 0.61).
+constexpr TileCost kDxTiles[4] = {{TILE_256x256, 256, 256, 1, 1.0}, {TILE_128x256, 128, 256, 1, 0.9},
+                                  {TILE_128x128, 128, 128, 1, 0.72}, {TILE_128x192, 128, 192, 1, 0.82}};
+// The tiles that have the dropout epilogue.
+constexpr TileCost kDxDropTiles[3] = {kDxTiles[1], kDxTiles[2], kDxTiles[3]};
+// 128x192 serves single projections of at least kMidTileDepth contraction
+// steps (with fewer stages a launch is mostly its fixed cost).
+constexpr int64_t kMidTileDepth = 3072;
 
 inline int64_t tile_workgroups(const TileCost& c, int64_t M, int64_t N) {
   return (M + c.bm - 1) / c.bm * ((N + c.bn - 1) / c.bn) * c.wgs;

@@ -174,8 +174,6 @@ inline void plan_fwd_part(Plan& p, GemmTile t, int64_t m, int64_t k, int64_t r, 
   p.add(x);
 }
 
-constexpr int64_t kMidTileDepth = 2048;   // least k of the 128 x 192 tile
-
 // lora_linear_fwd / lora_linear_fwd_dropout (the same tiles and column split;
 // under dropout the U pass applies the mask).
 inline Plan plan_fwd(int64_t m, int64_t n, int64_t k, int64_t r, bool drop) {
@@ -204,11 +202,9 @@ inline Plan plan_group_fwd(int count, const int64_t* n, int64_t m, int64_t k, in
   return p;
 }
 
-// dX GEMM launch over columns [cb, ce).  FULL (no bound checks on the n-stage
-// loads) needs every n a multiple of 64 and whole column tiles; the 256-wide
-// FULL tiles copy their stages straight into LDS.  The 256 x 256 tile runs
-// only FULL: its register-staged variant keeps values in scratch beside the
-// 128 accumulators, so without FULL the range takes the 128 x 256 tile.
+// dX GEMM launch over columns [cb, ce).  FULL (no bound checks on the copies)
+// needs every n a multiple of 64 and whole column tiles.  The 256 x 256 tile
+// runs only FULL; otherwise the range takes the 128 x 256 tile.
 inline void plan_dx_part(Plan& p, GemmTile t, int64_t m, int rp, int64_t cb, int64_t ce, bool n_whole, bool drop,
                          bool grp, bool finalize) {
   int bm, bn, wm, wn;
@@ -223,8 +219,8 @@ inline void plan_dx_part(Plan& p, GemmTile t, int64_t m, int rp, int64_t cb, int
   x.rp = rp;
   x.drop = drop;
   x.grp = grp;
+  x.block = 512;
   x.full = full;
-  x.dma = full && bn == 256;
   x.finalize = finalize;
   p.add(x);
 }
@@ -267,11 +263,11 @@ inline Plan plan_bwd(int64_t m, int64_t n, int64_t k, int64_t r, bool drop) {
   p.add(tokred_launch(L, drop, 0));
   const bool n_whole = n % 64 == 0;
   if (drop) {
-    const GemmTile t = cheapest_tile(kDxTiles, m, k, false).t == TILE_128x128 ? TILE_128x128 : TILE_128x256;
+    const GemmTile t = cheapest_tile(kDxDropTiles, m, k, n >= kMidTileDepth).t;
     plan_dx_part(p, t, m, L.rp, 0, k, n_whole, true, false, true);
     return p;
   }
-  const GemmSplit s = plan_gemm_split(kDxTiles, m, k, false);
+  const GemmSplit s = plan_gemm_split(kDxTiles, m, k, n >= kMidTileDepth);
   plan_dx_part(p, s.t1, m, L.rp, 0, s.n1, n_whole, false, false, true);
   if (s.n1 < k) plan_dx_part(p, s.t2, m, L.rp, s.n1, k, n_whole, false, false, false);
   return p;
@@ -408,7 +404,7 @@ inline hipError_t with_int(int v, F&& f) {
   return e;
 }
 
-// The GEMM tile of a launch as one code: 0 = 256x256, 1 = 128x256, 2 = 128x128.
-inline int tile_code(const Launch& x) { return x.bm == 256 ? 0 : (x.bn == 256 ? 1 : 2); }
+// The GEMM tile of a launch as its width, 257 for 256x256.
+inline int tile_code(const Launch& x) { return x.bm == 256 ? 257 : x.bn; }
 
 }  // namespace lora

@@ -71,8 +71,11 @@ SHAPES = [Shape("drop_tiny", 256, 512, 512, 8, 16.0, 21), Shape("drop_ragged", 2
           # U pass with 16-token workgroups (4096 <= m < 8192; smaller m takes 8-token ones)
           Shape("drop_m4100", 4100, 136, 128, 8, 16.0, 51), Shape("drop_m4100_r24", 4100, 136, 128, 24, 48.0, 52),
           Shape("drop_m4096_r64", 4096, 128, 192, 64, 128.0, 53),
-          Shape("drop_mid", 300, 11008, 2048, 1, 2.0, 54),        # the 128 x 192 forward tile
-          Shape("drop_few", 40, 4096, 576, 13, 26.0, 55)]         # the few-token forward
+          Shape("drop_mid", 300, 11008, 3072, 1, 2.0, 54),        # the 128 x 192 forward tile
+          Shape("drop_few", 40, 4096, 576, 13, 26.0, 55)] + [     # the few-token forward
+    # the masked 128 x 192 dX tiles of every padded rank, with and without whole stages and columns
+    Shape(f"drop_dx192_n{n}_r{r}", 300, n, k, r, 2.0 * r, 60 + r) for n, k in ((3136, 10944), (3080, 11008))
+    for r in (1, 24, 33, 64)]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)

@@ -84,7 +84,7 @@ CASES = [  # (ns, m, k, r, alpha)
     # a group of one on the 128 x 192 tile
     ([4096, 4096, 4096], 130, 72, 1, 2.0), ([4096, 4096, 4096], 130, 72, 24, 48.0),
     ([4096, 4096, 4096], 130, 64, 24, 48.0), ([4096, 4096, 4096], 130, 72, 33, 66.0),
-    ([4096, 4096, 4096], 130, 64, 33, 66.0), ([13824, 13824], 130, 64, 1, 2.0), ([11008], 300, 2048, 24, 48.0),
+    ([4096, 4096, 4096], 130, 64, 33, 66.0), ([13824, 13824], 130, 64, 1, 2.0), ([11008], 300, 3072, 24, 48.0),
     ([4096, 4096, 4096], 2048, 64, 5, 10.0),         # several rounds of few stages: the register-staged k-split tile
     ([4096, 4096, 4096], 7, 64, 33, 66.0), ([4096, 4096, 4096], 7, 64, 5, 10.0), ([5120, 5120, 5120], 7, 64, 5, 10.0),
 ] + [

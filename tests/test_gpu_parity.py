@@ -76,9 +76,14 @@ RAGGED = [
                                    (33, 1096, 16), (64, 328, 24)])
     for n in (4088, 5120, 11008, 13824, 16392)
 ] + [
-    # the 128 x 192 forward tile with U from the pass, with and without a partial last stage
-    Shape("mid", 300, 11008, 2056, 24, 48.0, 180), Shape("mid", 300, 11008, 2048, 24, 48.0, 181),
-    Shape("mid", 300, 11008, 2056, 33, 66.0, 182), Shape("mid", 300, 11008, 2048, 33, 66.0, 183),
+    # the 128 x 192 tiles: forward with U from the pass, with and without a partial last stage, and dX at every
+    # padded rank, with and without whole stages and columns
+    Shape("mid", 300, 11008, 3080, 24, 48.0, 180), Shape("mid", 300, 11008, 3072, 24, 48.0, 181),
+    Shape("mid", 300, 11008, 3080, 33, 66.0, 182), Shape("mid", 300, 11008, 3072, 33, 66.0, 183),
+] + [
+    Shape("mid", 300, n, k, r, 2.0 * r, 184 + i)
+    for i, (n, k, r) in enumerate([(3136, 10944, 8), (3136, 10944, 24), (3136, 10944, 33), (3136, 10944, 64),
+                                   (3080, 11008, 13), (3080, 11008, 24), (3080, 11008, 33), (3080, 11008, 64)])
 ]
 
 
@@ -129,10 +134,10 @@ SPLIT_EDGE = [
     Shape("edge", 4096, 1024, 4096, 24, 48.0, 503),
     Shape("edge", 4096, 1024, 4096, 40, 80.0, 504),
     # forward tiles shared by pairs of workgroups (an empty and a nearly empty second half, a number of tiles that
-    # is no multiple of 8), and the 128 x 192 tile, U beside W and from the pass, whole and partial last stages
+    # is no multiple of 8), and the 128 x 192 tiles, whole and partial last stages
     Shape("edge", 300, 1096, 1096, 8, 16.0, 505), Shape("edge", 333, 520, 1088, 13, 26.0, 506),
-    Shape("edge", 193, 1032, 320, 40, 80.0, 507), Shape("edge", 300, 11008, 2056, 8, 16.0, 508),
-    Shape("edge", 300, 10816, 2048, 24, 48.0, 509),
+    Shape("edge", 193, 1032, 320, 40, 80.0, 507), Shape("edge", 300, 11008, 3080, 8, 16.0, 508),
+    Shape("edge", 300, 10816, 3072, 24, 48.0, 509), Shape("edge", 200, 3080, 10952, 13, 26.0, 510),
 ]
 
 
