@@ -105,20 +105,43 @@ def lora_linear_bwd_workspace_size(m: int, n: int, k: int, r: int) -> int:
 
 
 def _ptr(t) -> int:
-    return 0 if t is None else int(t.data_ptr())
+    return 0 if t is None else t.data_ptr()
+
+
+# torch.bfloat16, torch.float32 and the current stream's handle as a call (a
+# torch.cuda.Stream object per call costs a microsecond), looked up on the
+# first call that needs them: the host-only functions do without torch.
+_BF16 = _F32 = _current_stream = None
+
+
+def _bind_torch() -> None:
+    global _BF16, _F32, _current_stream
+    import torch
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is not None and device is not None:
+        _current_stream = lambda: raw(device())
+    else:
+        _current_stream = lambda: torch.cuda.current_stream().cuda_stream
+    _F32 = torch.float32
+    _BF16 = torch.bfloat16
 
 
 def _stream_handle(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if _current_stream is None:
+            _bind_torch()
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
 
 
+def _fits(t, dtype, shape) -> bool:
+    """The conditions of _check as one expression, for the calls that meet them."""
+    return t.dtype is dtype and t.shape == shape and t.is_cuda and t.is_contiguous()
+
+
 def _check(t, name, dtype, shape):
-    import torch
     if t.dtype != dtype:
         raise TypeError(f"{name}: expected {dtype}, got {t.dtype}")
     if tuple(t.shape) != tuple(shape):
@@ -127,20 +150,51 @@ def _check(t, name, dtype, shape):
         raise ValueError(f"{name}: must be contiguous (row-major)")
     if t.device.type != "cuda":
         raise ValueError(f"{name}: must be a device tensor")
-    return torch
+
+
+def _check_fwd(X, W, A, B, Y, U):
+    """Checks the forward's tensors; returns m, n, k, r."""
+    if _BF16 is None:
+        _bind_torch()
+    bf16, f32 = _BF16, _F32
+    m, k = X.shape
+    n, r = W.shape[0], A.shape[0]
+    if not (_fits(X, bf16, (m, k)) and _fits(W, bf16, (n, k)) and _fits(A, bf16, (r, k)) and _fits(B, bf16, (n, r))
+            and _fits(Y, bf16, (m, n)) and _fits(U, f32, (m, r))):
+        for t, name, dt, shp in ((X, "X", bf16, (m, k)), (W, "W", bf16, (n, k)), (A, "A", bf16, (r, k)),
+                                 (B, "B", bf16, (n, r)), (Y, "Y", bf16, (m, n)), (U, "U", f32, (m, r))):
+            _check(t, name, dt, shp)
+    return m, n, k, r
+
+
+def _check_bwd(dY, X, W, A, B, U, dX, dA, dB):
+    """Checks the backward's tensors; returns m, n, k, r."""
+    if _BF16 is None:
+        _bind_torch()
+    bf16, f32 = _BF16, _F32
+    m, n = dY.shape
+    k, r = X.shape[1], A.shape[0]
+    if not (_fits(dY, bf16, (m, n)) and _fits(X, bf16, (m, k)) and _fits(W, bf16, (n, k)) and _fits(A, bf16, (r, k))
+            and _fits(B, bf16, (n, r)) and _fits(U, f32, (m, r)) and _fits(dX, bf16, (m, k))
+            and _fits(dA, f32, (r, k)) and _fits(dB, f32, (n, r))):
+        for t, name, dt, shp in ((dY, "dY", bf16, (m, n)), (X, "X", bf16, (m, k)), (W, "W", bf16, (n, k)),
+                                 (A, "A", bf16, (r, k)), (B, "B", bf16, (n, r)), (U, "U", f32, (m, r)),
+                                 (dX, "dX", bf16, (m, k)), (dA, "dA", f32, (r, k)), (dB, "dB", f32, (n, r))):
+            _check(t, name, dt, shp)
+    return m, n, k, r
+
+
+def _workspace_bytes(workspace) -> int:
+    if not workspace.is_cuda or not workspace.is_contiguous():
+        raise ValueError("workspace: must be a contiguous device tensor")
+    return workspace.numel() * workspace.element_size()
 
 
 def lora_linear_fwd(X, W, A, B, Y, U, alpha: float, stream=None) -> None:
     """Y = X W^T + (alpha/r) (X A^T) B^T and U = X A^T (see include/lora_linear.h).
 
     X [m,k], W [n,k], A [r,k], B [n,r], Y [m,n]: torch.bfloat16; U [m,r]: torch.float32."""
-    import torch
-    m, k = X.shape
-    n, r = W.shape[0], A.shape[0]
-    for t, name, dt, shp in ((X, "X", torch.bfloat16, (m, k)), (W, "W", torch.bfloat16, (n, k)),
-                             (A, "A", torch.bfloat16, (r, k)), (B, "B", torch.bfloat16, (n, r)),
-                             (Y, "Y", torch.bfloat16, (m, n)), (U, "U", torch.float32, (m, r))):
-        _check(t, name, dt, shp)
+    m, n, k, r = _check_fwd(X, W, A, B, Y, U)
     st = load_library().lora_linear_fwd(_ptr(X), _ptr(W), _ptr(A), _ptr(B), _ptr(Y), _ptr(U),
                                         m, n, k, r, float(alpha), _stream_handle(stream))
     if st != 0:
@@ -166,15 +220,7 @@ NOALLOC_SCRATCH_BYTES = 32 << 20   # LORA_NOALLOC_SCRATCH_BYTES of include/lora_
 def lora_linear_bwd_noalloc(dY, X, W, A, B, U, dX, dA, dB, alpha: float, stream=None) -> None:
     """lora_linear_bwd with the library's own per-GPU scratch array as the
     workspace (no allocation; calls that overlap on one GPU race on it)."""
-    import torch
-    m, n = dY.shape
-    k, r = X.shape[1], A.shape[0]
-    for t, name, dt, shp in ((dY, "dY", torch.bfloat16, (m, n)), (X, "X", torch.bfloat16, (m, k)),
-                             (W, "W", torch.bfloat16, (n, k)), (A, "A", torch.bfloat16, (r, k)),
-                             (B, "B", torch.bfloat16, (n, r)), (U, "U", torch.float32, (m, r)),
-                             (dX, "dX", torch.bfloat16, (m, k)), (dA, "dA", torch.float32, (r, k)),
-                             (dB, "dB", torch.float32, (n, r))):
-        _check(t, name, dt, shp)
+    m, n, k, r = _check_bwd(dY, X, W, A, B, U, dX, dA, dB)
     st = load_library().lora_linear_bwd_noalloc(_ptr(dY), _ptr(X), _ptr(W), _ptr(A), _ptr(B), _ptr(U),
                                                 _ptr(dX), _ptr(dA), _ptr(dB), m, n, k, r, float(alpha),
                                                 _stream_handle(stream))
@@ -189,18 +235,8 @@ def lora_linear_bwd_fused(dY, X, W, A, B, U, dX, dA, dB, workspace, alpha: float
 
 
 def _bwd_call(fn, dY, X, W, A, B, U, dX, dA, dB, workspace, alpha, stream):
-    import torch
-    m, n = dY.shape
-    k, r = X.shape[1], A.shape[0]
-    for t, name, dt, shp in ((dY, "dY", torch.bfloat16, (m, n)), (X, "X", torch.bfloat16, (m, k)),
-                             (W, "W", torch.bfloat16, (n, k)), (A, "A", torch.bfloat16, (r, k)),
-                             (B, "B", torch.bfloat16, (n, r)), (U, "U", torch.float32, (m, r)),
-                             (dX, "dX", torch.bfloat16, (m, k)), (dA, "dA", torch.float32, (r, k)),
-                             (dB, "dB", torch.float32, (n, r))):
-        _check(t, name, dt, shp)
-    if workspace.device.type != "cuda" or not workspace.is_contiguous():
-        raise ValueError("workspace: must be a contiguous device tensor")
-    ws_bytes = workspace.numel() * workspace.element_size()
+    m, n, k, r = _check_bwd(dY, X, W, A, B, U, dX, dA, dB)
+    ws_bytes = _workspace_bytes(workspace)
     st = getattr(load_library(), fn)(_ptr(dY), _ptr(X), _ptr(W), _ptr(A), _ptr(B), _ptr(U),
                                      _ptr(dX), _ptr(dA), _ptr(dB), _ptr(workspace), ws_bytes,
                                      m, n, k, r, float(alpha), _stream_handle(stream))
@@ -212,12 +248,13 @@ def lora_linear_merge(W, A, B, W_out, alpha: float, sign: int = 1, stream=None) 
     """W_out = W + sign (alpha/r) B A, rounded to bf16 (sign +1 merges, -1 unmerges).
 
     W, W_out [n,k], A [r,k], B [n,r]: torch.bfloat16.  W_out may be W itself."""
-    import torch
+    if _BF16 is None:
+        _bind_torch()
     n, k = W.shape
     r = A.shape[0]
-    for t, name, dt, shp in ((W, "W", torch.bfloat16, (n, k)), (A, "A", torch.bfloat16, (r, k)),
-                             (B, "B", torch.bfloat16, (n, r)), (W_out, "W_out", torch.bfloat16, (n, k))):
-        _check(t, name, dt, shp)
+    for t, name, shp in ((W, "W", (n, k)), (A, "A", (r, k)), (B, "B", (n, r)), (W_out, "W_out", (n, k))):
+        if not _fits(t, _BF16, shp):
+            _check(t, name, _BF16, shp)
     st = load_library().lora_linear_merge(_ptr(W), _ptr(A), _ptr(B), _ptr(W_out), n, k, r, float(alpha),
                                           int(sign), _stream_handle(stream))
     if st != 0:
@@ -236,6 +273,8 @@ def lora_dropout_keep_mask(seed: int, offset: int, p: float, keep, stream=None) 
     counters offset .. offset + keep.numel() - 1; see include/lora_linear.h).
     keep: contiguous uint8 device tensor [m, k/8], written."""
     import torch
+    if _BF16 is None:
+        _bind_torch()
     if keep.dtype != torch.uint8 or keep.dim() != 2 or not keep.is_contiguous() or keep.device.type != "cuda":
         raise ValueError("keep: expected a contiguous uint8 device tensor [m, k/8]")
     m, k = keep.shape[0], keep.shape[1] * 8
@@ -249,13 +288,7 @@ def lora_linear_fwd_dropout(X, W, A, B, keep, p: float, Y, U, alpha: float, stre
     """Forward with dropout on the adapter input: D = keep * X / (1 - p),
     U = D A^T, Y = X W^T + (alpha/r) U B^T.  keep: uint8 [m, k/8] packed bits
     (bit l % 8 of byte l // 8 keeps element l)."""
-    import torch
-    m, k = X.shape
-    n, r = W.shape[0], A.shape[0]
-    for t, name, dt, shp in ((X, "X", torch.bfloat16, (m, k)), (W, "W", torch.bfloat16, (n, k)),
-                             (A, "A", torch.bfloat16, (r, k)), (B, "B", torch.bfloat16, (n, r)),
-                             (Y, "Y", torch.bfloat16, (m, n)), (U, "U", torch.float32, (m, r))):
-        _check(t, name, dt, shp)
+    m, n, k, r = _check_fwd(X, W, A, B, Y, U)
     _check_keep(keep, m, k)
     st = load_library().lora_linear_fwd_dropout(_ptr(X), _ptr(W), _ptr(A), _ptr(B), _ptr(keep), float(p), _ptr(Y),
                                                 _ptr(U), m, n, k, r, float(alpha), _stream_handle(stream))
@@ -266,19 +299,9 @@ def lora_linear_fwd_dropout(X, W, A, B, keep, p: float, Y, U, alpha: float, stre
 def lora_linear_bwd_dropout(dY, X, W, A, B, U, keep, p: float, dX, dA, dB, workspace, alpha: float,
                             stream=None) -> None:
     """Backward of lora_linear_fwd_dropout for the same keep mask and rate p."""
-    import torch
-    m, n = dY.shape
-    k, r = X.shape[1], A.shape[0]
-    for t, name, dt, shp in ((dY, "dY", torch.bfloat16, (m, n)), (X, "X", torch.bfloat16, (m, k)),
-                             (W, "W", torch.bfloat16, (n, k)), (A, "A", torch.bfloat16, (r, k)),
-                             (B, "B", torch.bfloat16, (n, r)), (U, "U", torch.float32, (m, r)),
-                             (dX, "dX", torch.bfloat16, (m, k)), (dA, "dA", torch.float32, (r, k)),
-                             (dB, "dB", torch.float32, (n, r))):
-        _check(t, name, dt, shp)
+    m, n, k, r = _check_bwd(dY, X, W, A, B, U, dX, dA, dB)
     _check_keep(keep, m, k)
-    if workspace.device.type != "cuda" or not workspace.is_contiguous():
-        raise ValueError("workspace: must be a contiguous device tensor")
-    ws_bytes = workspace.numel() * workspace.element_size()
+    ws_bytes = _workspace_bytes(workspace)
     st = load_library().lora_linear_bwd_dropout(_ptr(dY), _ptr(X), _ptr(W), _ptr(A), _ptr(B), _ptr(U), _ptr(keep),
                                                 float(p), _ptr(dX), _ptr(dA), _ptr(dB), _ptr(workspace), ws_bytes,
                                                 m, n, k, r, float(alpha), _stream_handle(stream))
@@ -302,18 +325,22 @@ def lora_linear_group_fwd(X, Ws, As, Bs, Ys, Us, alpha: float, stream=None) -> N
     """Projections g that read one X: U_g = X A_g^T, Y_g = X W_g^T + (alpha/r) U_g B_g^T,
     in one launch.  X [m,k], W_g [n_g,k], A_g [r,k], B_g [n_g,r], Y_g [m,n_g]:
     torch.bfloat16; U_g [m,r]: torch.float32."""
-    import torch
+    if _BF16 is None:
+        _bind_torch()
+    bf16, f32 = _BF16, _F32
     m, k = X.shape
     r = As[0].shape[0]
     ns = [W.shape[0] for W in Ws]
     if not (len(Ws) == len(As) == len(Bs) == len(Ys) == len(Us)):
         raise ValueError("group: W, A, B, Y, U lists must have the same length")
-    _check(X, "X", torch.bfloat16, (m, k))
+    if not _fits(X, bf16, (m, k)):
+        _check(X, "X", bf16, (m, k))
     for g, n in enumerate(ns):
-        for t, name, dt, shp in ((Ws[g], "W", torch.bfloat16, (n, k)), (As[g], "A", torch.bfloat16, (r, k)),
-                                 (Bs[g], "B", torch.bfloat16, (n, r)), (Ys[g], "Y", torch.bfloat16, (m, n)),
-                                 (Us[g], "U", torch.float32, (m, r))):
-            _check(t, f"{name}[{g}]", dt, shp)
+        if not (_fits(Ws[g], bf16, (n, k)) and _fits(As[g], bf16, (r, k)) and _fits(Bs[g], bf16, (n, r))
+                and _fits(Ys[g], bf16, (m, n)) and _fits(Us[g], f32, (m, r))):
+            for t, name, dt, shp in ((Ws[g], "W", bf16, (n, k)), (As[g], "A", bf16, (r, k)), (Bs[g], "B", bf16, (n, r)),
+                                     (Ys[g], "Y", bf16, (m, n)), (Us[g], "U", f32, (m, r))):
+                _check(t, f"{name}[{g}]", dt, shp)
     st = load_library().lora_linear_group_fwd(_ptr(X), len(ns), _n_array(ns), _ptr_array(Ws), _ptr_array(As),
                                               _ptr_array(Bs), _ptr_array(Ys), _ptr_array(Us), m, k, r,
                                               float(alpha), _stream_handle(stream))
@@ -325,23 +352,26 @@ def lora_linear_group_bwd(dYs, X, Ws, As, Bs, Us, dX, dAs, dBs, workspace, alpha
     """Backward of lora_linear_group_fwd: dX = sum_g (dY_g W_g + dU_g A_g),
     dA_g = dU_g^T X, dB_g = s dY_g^T U_g with dU_g = s dY_g B_g.  workspace: a
     device tensor of at least lora_linear_group_bwd_workspace_size(n, m, k, r) bytes."""
-    import torch
+    if _BF16 is None:
+        _bind_torch()
+    bf16, f32 = _BF16, _F32
     m, k = X.shape
     r = As[0].shape[0]
     ns = [W.shape[0] for W in Ws]
     if not (len(dYs) == len(Ws) == len(As) == len(Bs) == len(Us) == len(dAs) == len(dBs)):
         raise ValueError("group: dY, W, A, B, U, dA, dB lists must have the same length")
-    _check(X, "X", torch.bfloat16, (m, k))
-    _check(dX, "dX", torch.bfloat16, (m, k))
+    for t, name in ((X, "X"), (dX, "dX")):
+        if not _fits(t, bf16, (m, k)):
+            _check(t, name, bf16, (m, k))
     for g, n in enumerate(ns):
-        for t, name, dt, shp in ((dYs[g], "dY", torch.bfloat16, (m, n)), (Ws[g], "W", torch.bfloat16, (n, k)),
-                                 (As[g], "A", torch.bfloat16, (r, k)), (Bs[g], "B", torch.bfloat16, (n, r)),
-                                 (Us[g], "U", torch.float32, (m, r)), (dAs[g], "dA", torch.float32, (r, k)),
-                                 (dBs[g], "dB", torch.float32, (n, r))):
-            _check(t, f"{name}[{g}]", dt, shp)
-    if workspace.device.type != "cuda" or not workspace.is_contiguous():
-        raise ValueError("workspace: must be a contiguous device tensor")
-    ws_bytes = workspace.numel() * workspace.element_size()
+        if not (_fits(dYs[g], bf16, (m, n)) and _fits(Ws[g], bf16, (n, k)) and _fits(As[g], bf16, (r, k))
+                and _fits(Bs[g], bf16, (n, r)) and _fits(Us[g], f32, (m, r)) and _fits(dAs[g], f32, (r, k))
+                and _fits(dBs[g], f32, (n, r))):
+            for t, name, dt, shp in ((dYs[g], "dY", bf16, (m, n)), (Ws[g], "W", bf16, (n, k)), (As[g], "A", bf16, (r, k)),
+                                     (Bs[g], "B", bf16, (n, r)), (Us[g], "U", f32, (m, r)), (dAs[g], "dA", f32, (r, k)),
+                                     (dBs[g], "dB", f32, (n, r))):
+                _check(t, f"{name}[{g}]", dt, shp)
+    ws_bytes = _workspace_bytes(workspace)
     st = load_library().lora_linear_group_bwd(_ptr_array(dYs), _ptr(X), len(ns), _n_array(ns), _ptr_array(Ws),
                                               _ptr_array(As), _ptr_array(Bs), _ptr_array(Us), _ptr(dX),
                                               _ptr_array(dAs), _ptr_array(dBs), _ptr(workspace), ws_bytes,
