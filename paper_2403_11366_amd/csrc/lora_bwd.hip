@@ -865,7 +865,9 @@ struct DxGroup {
 //
 // FULL (every n a multiple of 64 and the launch's columns a multiple of BN):
 // the copies carry no bound checks.
-constexpr int dx_ks_bufs(int bn) { return bn == 256 ? 3 : 4; }   // LDS stages of the 128-token tiles
+// LDS stages and bytes of the 128- and 64-token tiles.
+constexpr int dx_ks_bufs(int bm, int bn) { return bm == 128 ? (bn == 256 ? 3 : 4) : (bn == 128 ? 3 : 4); }
+constexpr int dx_ks_smem(int bm, int bn) { return dx_ks_bufs(bm, bn) * (bm * 128 + bn * 128) * (bm == 64 ? 2 : 1); }
 
 struct DxArgs {
   const u16 *dY, *W, *dU2, *A;
@@ -875,28 +877,31 @@ struct DxArgs {
   float inv_keep;
 };
 
-// Source of the n stages, in order: projection, its stage, its dY rows (a
-// single projection's are the arguments').
-template <bool GRP>
+// Source of every STEP-th 64-wide n piece, starting `STEP - first` before its
+// first one: projection, the piece's index there, its dY rows (a single
+// projection's are the arguments').  Past the last piece sl * 64 >= n.
+template <bool GRP, int STEP>
 struct DxCursor {
-  int g = 0, sl = -1, n;
+  int g = 0, sl, n;
   const u16* W;
   uint32_t yr;
   __amdgpu_buffer_rsrc_t rsY;
   int m0, rows;
-  __device__ __forceinline__ DxCursor(const DxArgs& p, const DxGroup& grp, int m0_, int bm)
-      : n(GRP ? grp.n[0] : p.n), W(GRP ? grp.W[0] : p.W), yr((uint32_t)n * 2),
+  __device__ __forceinline__ DxCursor(const DxArgs& p, const DxGroup& grp, int m0_, int bm, int first)
+      : sl(first - STEP), n(GRP ? grp.n[0] : p.n), W(GRP ? grp.W[0] : p.W), yr((uint32_t)n * 2),
         rsY(make_rsrc((GRP ? grp.dY[0] : p.dY) + (size_t)m0_ * n, (uint64_t)min(bm, p.m - m0_) * yr)), m0(m0_),
         rows(min(bm, p.m - m0_)) {}
   __device__ __forceinline__ void advance(const DxGroup& grp) {
-    ++sl;
-    if (GRP && sl * 64 >= n) {   // next projection (uniform)
-      ++g;
-      sl = 0;
-      n = pick(grp.n, g);
-      W = pick(grp.W, g);
-      yr = (uint32_t)n * 2;
-      rsY = make_rsrc(pick(grp.dY, g) + (size_t)m0 * n, (uint64_t)rows * yr);
+    sl += STEP;
+    if (GRP) {
+      while (sl * 64 >= n && g + 1 < grp.count) {   // next projection (uniform)
+        sl -= (n + 63) / 64;
+        ++g;
+        n = pick(grp.n, g);
+        W = pick(grp.W, g);
+        yr = (uint32_t)n * 2;
+        rsY = make_rsrc(pick(grp.dY, g) + (size_t)m0 * n, (uint64_t)rows * yr);
+      }
     }
   }
 };
@@ -934,39 +939,59 @@ __device__ __forceinline__ void stage_rank_operands(const u16* dU2, const u16* A
   }
 }
 
-// 128 x BN tiles.  Eight waves: wave (wk, wn) multiplies all 128 tokens with BN
-// / 4 columns over the 32-wide n half wk of every stage (so each W column is
-// read by one wave per half: the transposing reads run at half the rate of the
-// plain ones), three or four stages in LDS.  The two halves take turns reading
-// and multiplying exactly as in the forward's 128-token tiles, with the same
-// ordering of copies, waits and barriers; after the loop the halves' partial
-// sums are exchanged through LDS, each wave finishing 64 tokens.
+// Tiles of 128 tokens x 128, 192 or 256 columns.  Eight waves: wave (wk, wn)
+// multiplies all 128 tokens with BN / 4 columns over the 32-wide n half wk of
+// every stage (so each W column is read by one wave per half: the transposing
+// reads run at half the rate of the plain ones), three or four stages in LDS.
+// The two halves take turns reading and multiplying exactly as in the forward's
+// 128-token tiles, with the same ordering of copies, waits and barriers; after
+// the loop the halves' partial sums are exchanged through LDS, each wave
+// finishing 64 tokens.
+//
+// Tiles of 64 tokens x 64 or 128 columns, for few tokens (the larger tiles then
+// leave compute units idle): four n shares of 32 instead of two, stages of 128
+// n (two 64-wide pieces), two waves along the columns.
 // Measured (whole backward call, against 64 x 64 wave tiles in step on 32x32x16
 // products, register-staged for partial stages and 128 x 128): 2048 x 4096 x
 // 4096 (tokens x n x k), r = 8: 76 -> 70 us; 333 x 4096 x 4096 51 -> 40; 1531 x
 // 4104 x 3208, r = 12: 83 -> 71; 2000 x 512 x 4096 24.8 -> 25.6 (the exchange;
 // even at n = 1024).  The reads come before the copies: 5 us slower the other
 // way round at 2048 x 4096 x 4096.
-template <int BN, int RP, bool DROP, bool GRP, bool FULL>
+template <int BM, int BN, int RP, bool DROP, bool GRP, bool FULL>
 __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, int m0, int l0, char* smem) {
-  constexpr int BM = 128, NT = 512, NA = BN / 64;  // 16-column fragments per wave
-  constexpr int STAGE = BM * 128 + 64 * BN * 2;
-  constexpr int NBUF = dx_ks_bufs(BN);
+  constexpr int NT = 512, WN = BM == 128 ? 4 : 2;   // waves along the columns
+  constexpr int NK = 8 / WN, KP = NK / 2;           // n shares, 64-wide n pieces per stage
+  constexpr int NA = BN / WN / 16, NB = BM / 16;    // 16-column and 16-token fragments per wave
+  constexpr int NOB = NB / NK;                      // token fragments a wave finishes
+  constexpr int PIECE = BM * 128 + 64 * BN * 2, STAGE = KP * PIECE;
+  constexpr int NBUF = dx_ks_bufs(BM, BN);
   constexpr int KS2 = 2 * RP, NSLAB = (KS2 + 63) / 64;
   constexpr int CPR = BN / 8;                      // 16-byte chunks per W tile row
-  constexpr int NCOPY = BM / 64 + BN / 64;         // copies per wave and stage
-  static_assert(BN == 128 || BN == 192 || BN == 256, "W tile rows");
+  constexpr int NCOPY = KP * (BM / 64 + BN / 64);  // copies per wave and stage
+  static_assert(BM == 128 ? BN == 128 || BN == 192 || BN == 256 : BM == 64 && (BN == 64 || BN == 128), "tile shapes");
   const int m = p.m, n = p.n, k = p.k, r = p.r;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = uniform(tid >> 6);
-  const int wk = wave >> 2, wn = wave & 3;
+  const int wk = wave / WN, wn = wave % WN;
+  const bool second = wave >= 4;                    // the waves that run one slot behind
   const int g = lane >> 4, c16 = lane & 15;
   const uint32_t wrow = (uint32_t)k * 2, urow = (uint32_t)KS2 * 2;
   const __amdgpu_buffer_rsrc_t rsU = make_rsrc(p.dU2 + (size_t)m0 * KS2, (uint64_t)min(BM, p.mp - m0) * urow);
   const __amdgpu_buffer_rsrc_t rsA = make_rsrc(p.A, (uint64_t)r * wrow);
   const int nkb = GRP ? grp.nkb : (n + 63) / 64;
-  const int T = nkb + ((GRP || DROP) ? 0 : NSLAB);
-  DxCursor<GRP> cur(p, grp, m0, BM);
+  const int NM = (nkb + KP - 1) / KP;               // n stages, then the slab's
+  const int T = NM + ((GRP || DROP) ? 0 : (NSLAB + KP - 1) / KP);
+  using Cursor = DxCursor<GRP, KP>;
+  Cursor cur[2] = {Cursor(p, grp, m0, BM, 0), Cursor(p, grp, m0, BM, KP - 1)};   // (the second: with two pieces)
+  int pn0[2], pleft[2];   // per piece: first n, and its count of n (branches only here)
+  auto advance = [&]() LORA_INLINE {
+#pragma unroll
+    for (int q = 0; q < KP; ++q) {
+      cur[q].advance(grp);
+      pleft[q] = KP == 1 ? 64 : uniform(min(64, max(0, cur[q].n - cur[q].sl * 64)));   // (kept in scalar registers)
+      pn0[q] = pleft[q] > 0 ? cur[q].sl * 64 : 0;   // (past the last piece: no offset beyond the resource)
+    }
+  };
 
   // dY copy i: rows 64 i + 8 wave + lane / 8; W copy i: the tile's 16-byte
   // positions 64 (8 i + wave) + lane.  The lane's position holds the logical
@@ -980,51 +1005,60 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
     wr[i] = pos / CPR;
     wcol[i] = l0 + 8 * ((pos % CPR) ^ mc16_swz_of<BN>(wr[i]));
   }
-  auto copy_main = [&](int boff) LORA_INLINE {       // the cursor's stage
-    char* sb = smem + boff + wave * 1024;
-    const int n0 = cur.sl * 64;
-    const bool yok = FULL || n0 + ycol < cur.n;
-    const uint32_t yoff = (uint32_t)yr0 * cur.yr + (uint32_t)ycol * 2;
+  auto copy_main = [&](int boff) LORA_INLINE {       // the cursors' pieces
 #pragma unroll
-    for (int i = 0; i < BM / 64; ++i)
-      dma16(cur.rsY, yok ? yoff + (uint32_t)(64 * i) * cur.yr : kOOB, (uint32_t)n0 * 2, sb + i * 8192);
-    const __amdgpu_buffer_rsrc_t rsW =
-        make_rsrc(cur.W + (size_t)n0 * k, (uint64_t)(FULL ? 64 : min(64, cur.n - n0)) * wrow);
+    for (int q = 0; q < KP; ++q) {
+      const Cursor& c = cur[q];
+      char* sb = smem + boff + q * PIECE + wave * 1024;
+      const int n0 = pn0[q];
+      const bool yok = KP == 1 ? (FULL || n0 + ycol < c.n) : ycol < pleft[q];
+      const uint32_t yoff = (uint32_t)yr0 * c.yr + (uint32_t)ycol * 2;
 #pragma unroll
-    for (int i = 0; i < BN / 64; ++i)
-      dma16(rsW, FULL || wcol[i] < k ? (uint32_t)wr[i] * wrow + (uint32_t)wcol[i] * 2 : kOOB, 0,
-            sb + BM * 128 + i * 8192);
-  };
-  auto copy_slab = [&](int kb, int boff) LORA_INLINE {
-    char* sb = smem + boff + wave * 1024;
-    const int kk0 = (kb - nkb) * 64;
-    const uint32_t uoff = (uint32_t)(kk0 + ycol) * 2;
+      for (int i = 0; i < BM / 64; ++i)
+        dma16(c.rsY, yok ? yoff + (uint32_t)(64 * i) * c.yr : kOOB, (uint32_t)n0 * 2, sb + i * 8192);
+      const int wrows = KP == 1 ? (FULL ? 64 : uniform(min(64, c.n - n0))) : pleft[q];
+      const __amdgpu_buffer_rsrc_t rsW = make_rsrc(c.W + (size_t)n0 * k, (uint64_t)wrows * wrow);
 #pragma unroll
-    for (int i = 0; i < BM / 64; ++i)
-      dma16(rsU, uoff < urow ? (uint32_t)(yr0 + 64 * i) * urow + uoff : kOOB, 0, sb + i * 8192);
-#pragma unroll
-    for (int i = 0; i < BN / 64; ++i) {
-      const int kk = kk0 + wr[i], t = kk % RP;
-      dma16(rsA, ((FULL || wcol[i] < k) && kk < KS2 && t < r) ? (uint32_t)t * wrow + (uint32_t)wcol[i] * 2 : kOOB, 0,
-            sb + BM * 128 + i * 8192);
+      for (int i = 0; i < BN / 64; ++i)
+        dma16(rsW, FULL || wcol[i] < k ? (uint32_t)wr[i] * wrow + (uint32_t)wcol[i] * 2 : kOOB, 0,
+              sb + BM * 128 + i * 8192);
     }
   };
-  // Fragment addresses in buffer 0: W rows 32 wk + 8 g + e (second read of a
-  // pair 4 rows further), columns wn BN / 4 + 16 a + 4 q; dY as kc_read.
+  auto copy_slab = [&](int kb, int boff) LORA_INLINE {
+#pragma unroll
+    for (int q = 0; q < KP; ++q) {
+      char* sb = smem + boff + q * PIECE + wave * 1024;
+      const int kk0 = ((kb - NM) * KP + q) * 64;
+      const uint32_t uoff = (uint32_t)(kk0 + ycol) * 2;
+#pragma unroll
+      for (int i = 0; i < BM / 64; ++i)
+        dma16(rsU, uoff < urow ? (uint32_t)(yr0 + 64 * i) * urow + uoff : kOOB, 0, sb + i * 8192);
+#pragma unroll
+      for (int i = 0; i < BN / 64; ++i) {
+        const int kk = kk0 + wr[i], t = kk % RP;
+        dma16(rsA, ((FULL || wcol[i] < k) && kk < KS2 && t < r) ? (uint32_t)t * wrow + (uint32_t)wcol[i] * 2 : kOOB, 0,
+              sb + BM * 128 + i * 8192);
+      }
+    }
+  };
+  // Fragment addresses in buffer 0: W rows 32 (wk % 2) + 8 g + e of piece wk / 2
+  // (second read of a pair 4 rows further), columns j1 + 16 a + 4 q; dY as
+  // kc_read.
+  const int j1 = wn * (BN / WN);                    // the wave's first column in the tile
   uint32_t wa[NA];
   {
     const int e = c16 >> 2, q = c16 & 3;
 #pragma unroll
     for (int a = 0; a < NA; ++a)
-      wa[a] = lds_addr(smem + BM * 128 +
-                       mc16_offset<BN>(32 * wk + 8 * g + e, (wn * (BN / 4) + 16 * a) / 8 + (q >> 1)) + (q & 1) * 8);
+      wa[a] = lds_addr(smem + (wk >> 1) * PIECE + BM * 128 +
+                       mc16_offset<BN>(32 * (wk & 1) + 8 * g + e, (j1 + 16 * a) / 8 + (q >> 1)) + (q & 1) * 8);
   }
-  floatx4 acc[NA][8];
+  floatx4 acc[NA][NB];
 #pragma unroll
   for (int a = 0; a < NA; ++a)
 #pragma unroll
-    for (int b = 0; b < 8; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-  short8 fy[8];
+    for (int b = 0; b < NB; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+  short8 fy[NB];
   short4v wl[NA], wh[NA];
   auto slot_end = [&]() LORA_INLINE {
     asm volatile("s_barrier" ::: "memory");
@@ -1032,8 +1066,8 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
   };
 #pragma unroll
   for (int st = 0; st < NBUF - 1; ++st) {
-    if (st < nkb) {
-      cur.advance(grp);
+    if (st < NM) {
+      advance();
       copy_main(st * STAGE);
     } else if (st < T) {
       copy_slab(st, st * STAGE);
@@ -1042,16 +1076,16 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
   if (T >= NBUF - 1) wait_vmcnt<(NBUF - 2) * NCOPY>();
   else wait_vmcnt<0>();
   slot_end();                    // stage 0 has landed
-  if (wk == 1) slot_end();       // half 1 runs one slot behind
+  if (second) slot_end();        // half 1 runs one slot behind
   int rb = 0, wb = (NBUF - 1) * STAGE;
   // Stage kb; mode 0: refills a buffer with an n stage, 1: with a slab stage,
   // 2: with none.  Nothing branches between the assembly reads and their wait.
   auto stage = [&](int kb, auto mode) LORA_INLINE {
     constexpr int MODE = decltype(mode)::value;
-    if constexpr (MODE == 0) cur.advance(grp);
-    const char* Ys = smem + rb;
+    if constexpr (MODE == 0) advance();
+    const char* Ys = smem + rb + (wk >> 1) * PIECE;
 #pragma unroll
-    for (int b = 0; b < 8; ++b) fy[b] = kc_read(Ys, 16 * b + c16, 4 * wk + g);
+    for (int b = 0; b < NB; ++b) fy[b] = kc_read(Ys, 16 * b + c16, 4 * (wk & 1) + g);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int a = 0; a < NA; ++a) {
@@ -1071,33 +1105,32 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
     else
       asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(wl[0]), "+v"(wh[0]), "+v"(wl[1]), "+v"(wh[1]));
     static_assert(NA >= 2 && NA <= 4, "fragments of the wait");
-    if (wk == 1) wait_vmcnt<MODE == 2 ? 0 : (NBUF - 2) * NCOPY>();
+    if (second) wait_vmcnt<MODE == 2 ? 0 : (NBUF - 2) * NCOPY>();
     slot_end();
 #pragma unroll
     for (int a = 0; a < NA; ++a) {
       const short8 w8 = join4(wl[a], wh[a]);
 #pragma unroll
-      for (int b = 0; b < 8; ++b) acc[a][b] = mfma16x16x32(w8, fy[b], acc[a][b]);
+      for (int b = 0; b < NB; ++b) acc[a][b] = mfma16x16x32(w8, fy[b], acc[a][b]);
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (wk == 0) wait_vmcnt<MODE == 2 ? 0 : (NBUF - 2) * NCOPY>();
+    if (!second) wait_vmcnt<MODE == 2 ? 0 : (NBUF - 2) * NCOPY>();
     slot_end();
     rb = rb + STAGE == NBUF * STAGE ? 0 : rb + STAGE;
     wb = wb + STAGE == NBUF * STAGE ? 0 : wb + STAGE;
   };
   int kb = 0;
-  for (; kb + NBUF - 1 < nkb; ++kb) stage(kb, std::integral_constant<int, 0>{});
+  for (; kb + NBUF - 1 < NM; ++kb) stage(kb, std::integral_constant<int, 0>{});
   if constexpr (!GRP && !DROP)
     for (; kb + NBUF - 1 < T; ++kb) stage(kb, std::integral_constant<int, 1>{});
   for (; kb < T; ++kb) stage(kb, std::integral_constant<int, 2>{});
-  if (wk == 0) slot_end();
+  if (!second) slot_end();
 
-  // Exchange: wave wk keeps the token fragments 4 wk .. + 3, moved to own[..][0
-  // .. 3], and sends the others (branches on wk: selects of every element cost
-  // a microsecond).
+  // Exchange: wave wk finishes its token fragments NOB wk .., moved to own[..][0
+  // .. NOB - 1]; partial sums are added in n-share order.
   auto& own = acc;
-  floatx4* xin = reinterpret_cast<floatx4*>(smem) + (size_t)wave * NA * 4 * 64;   // from the partner
-  {
+  floatx4* xin = reinterpret_cast<floatx4*>(smem) + (size_t)(NK == 2 ? wave : wn * 4 + wk) * NA * 4 * 64;   // to this wave
+  if constexpr (NK == 2) {   // (branches on wk: selects of every element cost a microsecond)
     floatx4* dst = reinterpret_cast<floatx4*>(smem) + (size_t)(wave ^ 4) * NA * 4 * 64;
     if (wk == 0) {
 #pragma unroll
@@ -1118,8 +1151,21 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
     for (int a = 0; a < NA; ++a)
 #pragma unroll
       for (int b = 0; b < 4; ++b) own[a][b] += xin[(a * 4 + b) * 64 + lane];
+  } else {   // [wn][token fragment = finishing share][share][column fragment]
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        reinterpret_cast<floatx4*>(smem)[(size_t)(((wn * 4 + b) * 4 + wk) * NA + a) * 64 + lane] = acc[a][b];
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      own[a][0] = xin[a * 64 + lane];
+#pragma unroll
+      for (int q = 1; q < 4; ++q) own[a][0] += xin[(q * NA + a) * 64 + lane];
+    }
   }
-  const int i1 = 64 * wk, j1 = wn * (BN / 4);      // the wave's first token and column in the tile
+  const int i1 = 16 * NOB * wk;                     // the wave's first token in the tile
 
   if constexpr (GRP || DROP) {
     constexpr int UP = KS2 + 8;                    // Us row pitch in elements (16-byte multiple)
@@ -1134,15 +1180,15 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
         __syncthreads();
 #pragma unroll 1
         for (int kk = 0; kk < KS2 / 32; ++kk) {
-          short8 uf[4];
+          short8 uf[NOB];
 #pragma unroll
-          for (int b = 0; b < 4; ++b)
+          for (int b = 0; b < NOB; ++b)
             uf[b] = *reinterpret_cast<const short8*>(Us + (i1 + 16 * b + c16) * UP + 32 * kk + 8 * g);
 #pragma unroll
           for (int a = 0; a < NA; ++a) {
             const short8 af = slab_frag<BN, RP>(As, kk, j1 + 16 * a, lane);
 #pragma unroll
-            for (int b = 0; b < 4; ++b) own[a][b] = mfma16x16x32(af, uf[b], own[a][b]);
+            for (int b = 0; b < NOB; ++b) own[a][b] = mfma16x16x32(af, uf[b], own[a][b]);
           }
         }
       }
@@ -1160,20 +1206,20 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
       __syncthreads();
 #pragma unroll
       for (int a = 0; a < NA; ++a) {
-        floatx4 tmp[4];
+        floatx4 tmp[NOB];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) tmp[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < NOB; ++b) tmp[b] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kk = 0; kk < KS2 / 32; ++kk) {
           const short8 af = slab_frag<BN, RP>(As, kk, j1 + 16 * a, lane);
 #pragma unroll
-          for (int b = 0; b < 4; ++b)
+          for (int b = 0; b < NOB; ++b)
             tmp[b] = mfma16x16x32(
                 af, *reinterpret_cast<const short8*>(Us + (i1 + 16 * b + c16) * UP + 32 * kk + 8 * g), tmp[b]);
         }
         // lane: token c16 of fragment b, columns 16 a + 4 g + q
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
+        for (int b = 0; b < NOB; ++b) {
           const uint32_t bits = (uint32_t)Kb[(i1 + 16 * b + c16) * (BN / 8) + (j1 + 16 * a) / 8 + (g >> 1)] >> (4 * (g & 1));
 #pragma unroll
           for (int q = 0; q < 4; ++q)
@@ -1185,15 +1231,15 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
   // Stored through the wave's own exchange region, which nobody else touches
   // after the exchange; the rank-r operands of a group or dropout lie there too.
   if constexpr (GRP || DROP) __syncthreads();
-  constexpr int OUT = out16_bytes<NA, 4>();
+  constexpr int OUT = out16_bytes<NA, NOB>();
   static_assert(OUT <= NA * 4 * 1024 && 8 * NA * 4 * 1024 <= NBUF * STAGE, "output staging and exchange");
-  floatx4 v[NA][4];
+  floatx4 v[NA][NOB];
 #pragma unroll
   for (int a = 0; a < NA; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) v[a][b] = own[a][b];
-  store_out16<NA, 4>(v, reinterpret_cast<char*>(xin), p.dX + (size_t)(m0 + i1) * k + l0 + j1, (size_t)k, m - m0 - i1,
-                     k - l0 - j1, lane);
+    for (int b = 0; b < NOB; ++b) v[a][b] = own[a][b];
+  store_out16<NA, NOB>(v, reinterpret_cast<char*>(xin), p.dX + (size_t)(m0 + i1) * k + l0 + j1, (size_t)k, m - m0 - i1,
+                       k - l0 - j1, lane);
 }
 
 // The 256 x 256 tile (whole stages and columns).
@@ -1234,7 +1280,7 @@ __device__ __forceinline__ void dx_big_tile(const DxArgs& p, const DxGroup& grp,
     for (int b = 0; b < 8; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
   auto big_col = [&](int a) LORA_INLINE { return 128 * (a >> 1) + 32 * wn + 16 * (a & 1); };
   const int T = nkb + (GRP ? 0 : NSLAB);   // (group epilogues add dU A)
-  DxCursor<GRP> cur(p, grp, m0, BM);   // advanced once per stage
+  DxCursor<GRP, 1> cur(p, grp, m0, BM, 0);   // advanced once per stage
   const int l8 = lane >> 3, l16 = lane >> 4;
   const int yr0 = 8 * wave + l8;                            // dY row of this lane in copy 0 (+ 64 h + 128 i)
   const uint32_t ych = (uint32_t)(((lane & 7) ^ kc_swz(yr0)) << 4);
@@ -1455,13 +1501,13 @@ __global__ __launch_bounds__(512) void lora_bwd_dx_kernel(
     const u16* __restrict__ dY, const u16* __restrict__ W, const u16* __restrict__ dU2,
     const u16* __restrict__ A, const uint8_t* __restrict__ keep, u16* __restrict__ dX, int m, int n, int k,
     int r, int mp, float inv_keep, int tiles_m, int tiles_n, int l_begin, FinalizeArgs fin, DxGroup grp) {
-  static_assert(BM == 128 || (BM == 256 && BN == 256 && FULL && !DROP), "tile shapes");
-  __shared__ __attribute__((aligned(1024))) char smem[BM == 256 ? 2 * 65536 : dx_ks_bufs(BN) * (BM * 128 + BN * 128)];
+  static_assert(BM <= 128 || (BM == 256 && BN == 256 && FULL && !DROP), "tile shapes");
+  __shared__ __attribute__((aligned(1024))) char smem[BM == 256 ? 2 * 65536 : dx_ks_smem(BM, BN)];
   int tm, tn;
   tile_coords(tiles_m, tiles_n, 8, (int)blockIdx.x, tm, tn);
   const DxArgs p{dY, W, dU2, A, keep, dX, m, n, k, r, mp, inv_keep};
   if constexpr (BM == 256) dx_big_tile<RP, GRP>(p, grp, tm * BM, l_begin + tn * BN, smem);
-  else dx_ks_tile<BN, RP, DROP, GRP, FULL>(p, grp, tm * BM, l_begin + tn * BN, smem);
+  else dx_ks_tile<BM, BN, RP, DROP, GRP, FULL>(p, grp, tm * BM, l_begin + tn * BN, smem);
   const int first = (int)blockIdx.x * 512 + (int)threadIdx.x, stride = (int)gridDim.x * 512;
   if (GRP) {
     for (int pq = 0; pq < grp.count; ++pq) finalize_partials(pick(grp.fin, pq), first, stride);
@@ -1780,15 +1826,16 @@ __global__ __launch_bounds__(256) void lora_finalize_kernel(FinalizeArgs f) {
 // without dropout, 128 x 192 for single projections.
 template <int BM, int BN, int RP, bool DROP, bool GRP, bool FULL>
 constexpr bool dx_instantiated() {
-  return !(DROP && GRP) && (BM == 128 || (FULL && !DROP)) && !(BN == 192 && GRP);
+  return !(DROP && GRP) && (BM <= 128 || (FULL && !DROP)) && !(BN == 192 && GRP);
 }
 
 static hipError_t run_dx(const Launch& L, const BwdArgs& a, const u16* dU2, int mp, const FinalizeArgs& fin,
                          const DxGroup& grp, hipStream_t st) {
   const dim3 grid((unsigned)L.grid), block((unsigned)L.block);
-  return with_int<128, 192, 256, 257>(tile_code(L), [&](auto tc) {
+  return with_int<64, 65, 128, 192, 256, 257>(tile_code(L), [&](auto tc) {
     constexpr int T = decltype(tc)::value;
-    constexpr int BM = T == 257 ? 256 : 128, BN = T == 257 ? 256 : T, WN = BN == 256 ? 4 : 2;
+    constexpr int BM = T == 257 ? 256 : (T <= 65 ? 64 : 128), BN = T == 257 ? 256 : (T == 65 ? 128 : T);
+    constexpr int WM = BM == 64 ? 1 : 2, WN = BN == 256 ? 4 : 2;
     return with_int<16, 32, 48, 64>(L.rp, [&](auto rc) {
       return with_bool(L.drop, [&](auto dr) {
         return with_bool(L.grp, [&](auto gr) {
@@ -1798,7 +1845,7 @@ static hipError_t run_dx(const Launch& L, const BwdArgs& a, const u16* dU2, int 
             if constexpr (!dx_instantiated<BM, BN, RP, DROP, GRP, FULL>()) {
               return hipErrorInvalidValue;
             } else {
-              hipLaunchKernelGGL((lora_bwd_dx_kernel<BM, BN, 2, WN, RP, DROP, GRP, FULL>), grid, block, 0, st, a.dY,
+              hipLaunchKernelGGL((lora_bwd_dx_kernel<BM, BN, WM, WN, RP, DROP, GRP, FULL>), grid, block, 0, st, a.dY,
                                  a.W, dU2, a.A, a.keep, a.dX, (int)a.m, (int)a.n, (int)a.k, (int)a.r, mp, a.inv_keep,
                                  L.tiles_m, L.tiles_n, (int)L.col_begin, L.finalize ? fin : FinalizeArgs{}, grp);
               return hipGetLastError();

@@ -185,11 +185,11 @@ __device__ __forceinline__ short8 kc_read(const char* tile, int row, int chunk) 
 __device__ __forceinline__ int mc16_swz(int row) { return 2 * (row & 3) + 8 * ((row >> 3) & 1); }
 __device__ __forceinline__ int mc32_swz(int row) { return 4 * (row & 3); }
 
-// Rows of 192 (384 bytes): consecutive rows already fall in different halves of
-// the banks, and the swizzle has to stay within 8 chunks of 24.
+// Rows of 64 and 192 (128 and 384 bytes): consecutive rows already fall in
+// different halves of the banks, and the swizzle has to stay within 8 chunks.
 template <int COLS>
 __device__ __forceinline__ int mc16_swz_of(int row) {
-  return COLS == 192 ? 2 * ((row >> 1) & 1) + 4 * ((row >> 3) & 1) : mc16_swz(row);
+  return COLS == 192 || COLS == 64 ? 2 * ((row >> 1) & 1) + 4 * ((row >> 3) & 1) : mc16_swz(row);
 }
 template <int COLS>
 __device__ __forceinline__ uint32_t mc16_offset(int row, int chunk) {

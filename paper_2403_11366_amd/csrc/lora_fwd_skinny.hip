@@ -1,5 +1,5 @@
 // Forward for few tokens (generation with the adapter kept apart from W):
-//   U = X A^T,   Y = X W^T + s U B^T   with m at most kSkinnyTokens.
+//   U = X A^T,   Y = X W^T + s U B^T   for calls fwd_skinny() admits.
 #include <type_traits>
 
 #include "lora_device.hpp"

@@ -17,8 +17,10 @@ inline int64_t pad_tokens(int64_t m) { return (m + 63) / 64 * 64; }
 // Output tiles of the two large GEMMs (tokens x features): 256x256 runs 8
 // waves (two per SIMD) as 2 x 4 waves of 128 x 64, the others 8 waves that
 // split k.  Forward only: 128x128 shared by a pair of workgroups of 64 tokens
-// each.
-enum GemmTile { TILE_256x256 = 0, TILE_128x256 = 1, TILE_128x128 = 2, TILE_128x192 = 3, TILE_PAIR = 4 };
+// each.  dX only: 64x128 and 64x64.
+enum GemmTile {
+  TILE_256x256 = 0, TILE_128x256 = 1, TILE_128x128 = 2, TILE_128x192 = 3, TILE_PAIR = 4, TILE_64x128 = 5, TILE_64x64 = 6
+};
 
 // A candidate tile: the output area a workgroup computes, and the workgroup's
 // relative efficiency (larger tiles read less LDS and L2 per flop).  Every
@@ -33,14 +35,28 @@ struct TileCost { GemmTile t; int bm, bn, wgs; double eff; };
 constexpr TileCost kFwdTiles[5] = {{TILE_256x256, 256, 256, 1, 1.0}, {TILE_128x256, 128, 256, 1, 0.8},
                                    {TILE_128x128, 128, 128, 1, 0.61}, {TILE_128x192, 128, 192, 1, 0.71},
                                    {TILE_PAIR, 128, 128, 2, 0.4}};
-// dX tiles (per 64-wide n stage: 1.39 us, 0.77, 0.48, 0.61).
-constexpr TileCost kDxTiles[4] = {{TILE_256x256, 256, 256, 1, 1.0}, {TILE_128x256, 128, 256, 1, 0.9},
-                                  {TILE_128x128, 128, 128, 1, 0.72}, {TILE_128x192, 128, 192, 1, 0.82}};
+// dX tiles (per 64-wide n stage: 1.39 us, 0.77, 0.48, 0.61, about 0.27, 0.16).
+constexpr TileCost kDxTiles[6] = {{TILE_256x256, 256, 256, 1, 1.0}, {TILE_128x256, 128, 256, 1, 0.9},
+                                  {TILE_128x128, 128, 128, 1, 0.72}, {TILE_128x192, 128, 192, 1, 0.82},
+                                  {TILE_64x128, 64, 128, 1, 0.6},    {TILE_64x64, 64, 64, 1, 0.5}};
 // The tiles that have the dropout epilogue.
-constexpr TileCost kDxDropTiles[3] = {kDxTiles[1], kDxTiles[2], kDxTiles[3]};
-// 128x192 serves single projections of at least kMidTileDepth contraction
-// steps (with fewer stages a launch is mostly its fixed cost).
-constexpr int64_t kMidTileDepth = 3072;
+constexpr TileCost kDxDropTiles[5] = {kDxTiles[1], kDxTiles[2], kDxTiles[3], kDxTiles[4], kDxTiles[5]};
+// Tiles a call may take beside 256x256, 128x256, 128x128 and pairs.  128x192
+// serves single projections of at least kMidTileDepth contraction steps (with
+// fewer stages a launch is mostly its fixed cost).  The 64-token tiles serve
+// calls of few tokens, where the larger ones leave compute units idle: up to
+// kFewTokens at any depth, up to kShortTokens from kShortDepth steps on.  (Whole
+// backward call with the best of them against 128x128: 130 x 4096 x 4096 38 ->
+// 29 us, 333 x 4096 x 4096 41 -> 36, 1024 x 4096 x 2048 54 -> 47, 256 x 512 x 512
+// 16 -> 13; 257 x 1024 x 4096, outside, 19.6 and 18.1; above 1024 tokens an
+// output of so few tiles has few columns.)
+constexpr int64_t kMidTileDepth = 3072, kFewTokens = 256, kShortTokens = 1024, kShortDepth = 2048;
+enum TileSet { TILES_BASE = 0, TILES_MID = 1, TILES_SHORT = 2 };
+inline bool tile_allowed(GemmTile t, int set) {
+  if (t == TILE_128x192) return set & TILES_MID;
+  if (t == TILE_64x128 || t == TILE_64x64) return set & TILES_SHORT;
+  return true;
+}
 
 inline int64_t tile_workgroups(const TileCost& c, int64_t M, int64_t N) {
   return (M + c.bm - 1) / c.bm * ((N + c.bn - 1) / c.bn) * c.wgs;
@@ -49,13 +65,12 @@ inline double tile_cost(const TileCost& c, int64_t M, int64_t N) {
   return (double)((tile_workgroups(c, M, N) + 255) / 256) * (c.bm * c.bn / c.wgs) / c.eff;
 }
 
-// The cheapest tile for an M x N output (the first of equal ones); mid: 128x192
-// is a candidate.
+// The cheapest tile of a set for an M x N output (the first of equal ones).
 template <int NT>
-inline const TileCost& cheapest_tile(const TileCost (&cands)[NT], int64_t M, int64_t N, bool mid) {
+inline const TileCost& cheapest_tile(const TileCost (&cands)[NT], int64_t M, int64_t N, int set) {
   const TileCost* best = &cands[0];
   for (const TileCost& c : cands)
-    if ((mid || c.t != TILE_128x192) && tile_cost(c, M, N) < tile_cost(*best, M, N)) best = &c;
+    if (tile_allowed(c.t, set) && tile_cost(c, M, N) < tile_cost(*best, M, N)) best = &c;
   return *best;
 }
 
@@ -71,19 +86,19 @@ inline const TileCost& cheapest_tile(const TileCost (&cands)[NT], int64_t M, int
 // largest n1 is looked at.  n1 == N: no split.
 struct GemmSplit { GemmTile t1, t2; int64_t n1; };
 template <int NT>
-inline GemmSplit plan_gemm_split(const TileCost (&cands)[NT], int64_t M, int64_t N, bool mid) {
-  const TileCost& c0 = cheapest_tile(cands, M, N, mid);
+inline GemmSplit plan_gemm_split(const TileCost (&cands)[NT], int64_t M, int64_t N, int set) {
+  const TileCost& c0 = cheapest_tile(cands, M, N, set);
   GemmSplit best{c0.t, c0.t, N};
   double best_cost = 0.95 * tile_cost(c0, M, N);
   for (const TileCost& c1 : cands) {
-    if (!mid && c1.t == TILE_128x192) continue;
+    if (!tile_allowed(c1.t, set)) continue;
     const int64_t per_col = tile_workgroups(c1, M, 1);   // workgroups per column of tiles
     const int64_t rounds = (tile_workgroups(c1, M, N) + 255) / 256;
     for (int64_t R = 1; R <= rounds; ++R) {
       const int64_t n1 = 256 * R / per_col * c1.bn;
       if (n1 < c1.bn || n1 >= N) continue;
       for (const TileCost& c2 : cands) {
-        if ((!mid && c2.t == TILE_128x192) || tile_workgroups(c2, M, N - n1) > 256) continue;
+        if (!tile_allowed(c2.t, set) || tile_workgroups(c2, M, N - n1) > 256) continue;
         const double c = tile_cost(c1, M, n1) + tile_cost(c2, M, N - n1);
         if (c < best_cost || (c == best_cost && best.n1 < N && n1 > best.n1)) {
           best_cost = c;

@@ -70,6 +70,8 @@ inline void tile_dims(GemmTile t, int& bm, int& bn, int& wm, int& wn) {
     case TILE_256x256: bm = 256; bn = 256; wm = 2; wn = 4; break;
     case TILE_128x256: bm = 128; bn = 256; wm = 2; wn = 4; break;
     case TILE_128x192: bm = 128; bn = 192; wm = 2; wn = 2; break;
+    case TILE_64x128: bm = 64; bn = 128; wm = 1; wn = 2; break;
+    case TILE_64x64: bm = 64; bn = 64; wm = 1; wn = 2; break;
     default: bm = 128; bn = 128; wm = 2; wn = 2; break;
   }
 }
@@ -100,11 +102,20 @@ inline Launch upass_launch(int count, int64_t m, int64_t r, bool drop) {
   return u;
 }
 
-// Forward of few tokens.  Up to kSkinnyTokens tokens the GEMM tiles leave most
-// compute units idle (one row of 128 x 128 tiles) or multiply mostly padding,
-// and a kernel that streams W past blocks of up to 64 tokens is faster
-// (n = k = 4096: 4 tokens 39 -> 11 us, 64 tokens 40 -> 18 us).
-constexpr int64_t kSkinnyTokens = 64;
+// Forward of few tokens: up to kSkinnyTokens, and up to kFewTokens for outputs
+// of at most kSkinnyTiles tiles of 128 x 128.  There the GEMM tiles leave most
+// compute units idle or multiply mostly padding, and a kernel that streams W
+// past blocks of up to 64 tokens is faster (n = k = 4096: 4 tokens 39 -> 10 us,
+// 64 tokens 40 -> 18; against paired 128 x 128 tiles: 128 tokens 24.2 -> 18.2,
+// 256 x 2048 x 2048 14.7 -> 11.5, 256 x 512 x 512 7.4 -> 5.5; at 64 tiles, 192 x
+// 4096 x 4096, 24.4 and 24.2; at 86, 128 x 11008 x 4096, 25.6 and 37.5).
+constexpr int64_t kSkinnyTokens = 64, kSkinnyTiles = 32;
+inline bool fwd_skinny(int count, const int64_t* n, int64_t m) {
+  if (m <= kSkinnyTokens) return true;
+  int64_t tiles = 0;
+  for (int g = 0; g < count; ++g) tiles += (m + 127) / 128 * ((n[g] + 127) / 128);
+  return m <= kFewTokens && tiles <= kSkinnyTiles;
+}
 inline Plan plan_fwd_skinny(int count, const int64_t* n, int64_t m, int64_t k, int64_t r, bool drop) {
   Plan p;
   Launch x = blank_launch(K_FWD_SKINNY);
@@ -177,9 +188,9 @@ inline void plan_fwd_part(Plan& p, GemmTile t, int64_t m, int64_t k, int64_t r, 
 // lora_linear_fwd / lora_linear_fwd_dropout (the same tiles and column split;
 // under dropout the U pass applies the mask).
 inline Plan plan_fwd(int64_t m, int64_t n, int64_t k, int64_t r, bool drop) {
-  if (m <= kSkinnyTokens) return plan_fwd_skinny(1, &n, m, k, r, drop);
+  if (fwd_skinny(1, &n, m)) return plan_fwd_skinny(1, &n, m, k, r, drop);
   Plan p;
-  const GemmSplit s = plan_gemm_split(kFwdTiles, m, n, k >= kMidTileDepth);
+  const GemmSplit s = plan_gemm_split(kFwdTiles, m, n, k >= kMidTileDepth ? TILES_MID : TILES_BASE);
   plan_fwd_part(p, s.t1, m, k, r, 0, s.n1, true, drop, false, 1, -1);
   if (s.n1 < n) plan_fwd_part(p, s.t2, m, k, r, s.n1, n, false, drop, false, 1, -1);
   return p;
@@ -189,10 +200,10 @@ inline Plan plan_fwd(int64_t m, int64_t n, int64_t k, int64_t r, bool drop) {
 // tile chosen for m x (sum of n).  A group of one is the single projection.
 inline Plan plan_group_fwd(int count, const int64_t* n, int64_t m, int64_t k, int64_t r) {
   if (count == 1) return plan_fwd(m, n[0], k, r, false);
-  if (m <= kSkinnyTokens) return plan_fwd_skinny(count, n, m, k, r, false);
+  if (fwd_skinny(count, n, m)) return plan_fwd_skinny(count, n, m, k, r, false);
   int64_t ntot = 0;
   for (int g = 0; g < count; ++g) ntot += n[g];
-  const GemmTile t = cheapest_tile(kFwdTiles, m, ntot, false).t;
+  const GemmTile t = cheapest_tile(kFwdTiles, m, ntot, TILES_BASE).t;
   int bm, bn, wm, wn;
   tile_dims(t, bm, bn, wm, wn);
   int tiles_n = 0;
@@ -223,6 +234,11 @@ inline void plan_dx_part(Plan& p, GemmTile t, int64_t m, int rp, int64_t cb, int
   x.full = full;
   x.finalize = finalize;
   p.add(x);
+}
+
+// Tiles open to the dX GEMM of m tokens over `depth` output features.
+inline int dx_tile_set(int64_t m, int64_t depth, bool grp) {
+  return (!grp && depth >= kMidTileDepth ? TILES_MID : 0) | (m <= kFewTokens || (m <= kShortTokens && depth >= kShortDepth) ? TILES_SHORT : 0);
 }
 
 inline Launch du_launch(const BwdLayout& L, int64_t r, int member) {
@@ -263,11 +279,11 @@ inline Plan plan_bwd(int64_t m, int64_t n, int64_t k, int64_t r, bool drop) {
   p.add(tokred_launch(L, drop, 0));
   const bool n_whole = n % 64 == 0;
   if (drop) {
-    const GemmTile t = cheapest_tile(kDxDropTiles, m, k, n >= kMidTileDepth).t;
+    const GemmTile t = cheapest_tile(kDxDropTiles, m, k, dx_tile_set(m, n, false)).t;
     plan_dx_part(p, t, m, L.rp, 0, k, n_whole, true, false, true);
     return p;
   }
-  const GemmSplit s = plan_gemm_split(kDxTiles, m, k, n >= kMidTileDepth);
+  const GemmSplit s = plan_gemm_split(kDxTiles, m, k, dx_tile_set(m, n, false));
   plan_dx_part(p, s.t1, m, L.rp, 0, s.n1, n_whole, false, false, true);
   if (s.n1 < k) plan_dx_part(p, s.t2, m, L.rp, s.n1, k, n_whole, false, false, false);
   return p;
@@ -283,10 +299,12 @@ inline Plan plan_group_bwd(int count, const int64_t* n, int64_t m, int64_t k, in
   const GroupBwdLayout G = group_bwd_layout(count, n, m, k, r);
   Plan p;
   bool n_whole = true;
+  int64_t depth = 0;
   for (int g = 0; g < count; ++g) {
     p.add(du_launch(G.L[g], r, g));
     p.add(tokred_launch(G.L[g], false, g, G.stacked ? 1 : 0));
     n_whole = n_whole && n[g] % 64 == 0;
+    depth += n[g];
   }
   if (G.stacked) {
     Launch x = blank_launch(K_TOKRED);
@@ -298,7 +316,7 @@ inline Plan plan_group_bwd(int count, const int64_t* n, int64_t m, int64_t k, in
     p.add(x);
   }
   const int rp = G.L[0].rp;
-  const GemmSplit s = plan_gemm_split(kDxTiles, m, k, false);
+  const GemmSplit s = plan_gemm_split(kDxTiles, m, k, dx_tile_set(m, depth, true));
   plan_dx_part(p, s.t1, m, rp, 0, s.n1, n_whole, false, true, true);
   if (s.n1 < k) plan_dx_part(p, s.t2, m, rp, s.n1, k, n_whole, false, true, false);
   return p;
@@ -404,7 +422,7 @@ inline hipError_t with_int(int v, F&& f) {
   return e;
 }
 
-// The GEMM tile of a launch as its width, 257 for 256x256.
-inline int tile_code(const Launch& x) { return x.bm == 256 ? 257 : x.bn; }
+// The GEMM tile of a launch as its width, 257 for 256x256, 65 for 64x128.
+inline int tile_code(const Launch& x) { return x.bm == 256 ? 257 : (x.bm == 64 && x.bn == 128 ? 65 : x.bn); }
 
 }  // namespace lora

@@ -73,9 +73,13 @@ SHAPES = [Shape("drop_tiny", 256, 512, 512, 8, 16.0, 21), Shape("drop_ragged", 2
           Shape("drop_m4096_r64", 4096, 128, 192, 64, 128.0, 53),
           Shape("drop_mid", 300, 11008, 3072, 1, 2.0, 54),        # the 128 x 192 forward tile
           Shape("drop_few", 40, 4096, 576, 13, 26.0, 55)] + [     # the few-token forward
-    # the masked 128 x 192 dX tiles of every padded rank, with and without whole stages and columns
-    Shape(f"drop_dx192_n{n}_r{r}", 300, n, k, r, 2.0 * r, 60 + r) for n, k in ((3136, 10944), (3080, 11008))
-    for r in (1, 24, 33, 64)]
+    # the masked 128 x 192 and 64 x 128 dX tiles of every padded rank, with and without whole stages and columns
+    Shape(f"drop_dx_m{m}_n{n}_r{r}", m, n, k, r, 2.0 * r, 60 + r)
+    for m, n, k in ((1100, 3136, 4224), (1100, 3080, 4160), (70, 64, 11008), (70, 72, 10944)) for r in (1, 24, 33, 64)
+] + [Shape(f"drop_dx64_r{r}", 7, 136, 64, r, 2.0 * r, 130 + r) for r in (24, 64)] + [
+    # the masked 128 x 128 dX tiles
+    Shape("drop_dx128m_r33", 300, 64, 64, 33, 66.0, 210), Shape("drop_dx128m_r24f", 300, 64, 1024, 24, 48.0, 211),
+    Shape("drop_dx128m_r33f", 300, 64, 1024, 33, 66.0, 212), Shape("drop_dx128m_r64f", 300, 64, 1024, 64, 128.0, 213)]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)

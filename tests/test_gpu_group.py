@@ -86,6 +86,14 @@ CASES = [  # (ns, m, k, r, alpha)
     ([4096, 4096, 4096], 130, 64, 24, 48.0), ([4096, 4096, 4096], 130, 72, 33, 66.0),
     ([4096, 4096, 4096], 130, 64, 33, 66.0), ([13824, 13824], 130, 64, 1, 2.0), ([11008], 300, 3072, 24, 48.0),
     ([4096, 4096, 4096], 2048, 64, 5, 10.0),         # several rounds of few stages: the register-staged k-split tile
+    # the 64-token dX tiles over members of odd and even numbers of pieces, the 128 x 128 dX and forward pairs
+    ([136, 264, 72], 70, 13824, 5, 10.0), ([136, 264, 72], 70, 13824, 24, 48.0), ([136, 264, 72], 70, 13824, 33, 66.0),
+    ([136, 264, 72], 70, 13824, 64, 128.0), ([64, 64], 70, 13824, 1, 2.0), ([64, 192], 70, 13824, 24, 48.0),
+    ([64, 64], 70, 13824, 33, 66.0), ([64, 128], 70, 13824, 64, 128.0), ([64, 64], 7, 72, 64, 128.0),
+    ([1024, 1088, 64], 300, 1024, 8, 16.0), ([8, 8, 200, 8], 100, 264, 13, 26.0),
+    ([64, 64], 300, 64, 24, 48.0), ([64, 64], 300, 1024, 24, 48.0), ([64, 64], 300, 64, 33, 66.0),
+    ([64, 64], 300, 1024, 33, 66.0), ([64, 64], 300, 1024, 64, 128.0), ([64, 64], 300, 72, 24, 48.0),
+    ([64, 64], 300, 72, 33, 66.0),
     ([4096, 4096, 4096], 7, 64, 33, 66.0), ([4096, 4096, 4096], 7, 64, 5, 10.0), ([5120, 5120, 5120], 7, 64, 5, 10.0),
 ] + [
     # the remaining grouped tiles a plan can name, at padded ranks 16 .. 64 with and without whole k stages:

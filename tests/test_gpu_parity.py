@@ -81,9 +81,18 @@ RAGGED = [
     Shape("mid", 300, 11008, 3080, 24, 48.0, 180), Shape("mid", 300, 11008, 3072, 24, 48.0, 181),
     Shape("mid", 300, 11008, 3080, 33, 66.0, 182), Shape("mid", 300, 11008, 3072, 33, 66.0, 183),
 ] + [
-    Shape("mid", 300, n, k, r, 2.0 * r, 184 + i)
-    for i, (n, k, r) in enumerate([(3136, 10944, 8), (3136, 10944, 24), (3136, 10944, 33), (3136, 10944, 64),
-                                   (3080, 11008, 13), (3080, 11008, 24), (3080, 11008, 33), (3080, 11008, 64)])
+    Shape("mid", 1100, n, k, r, 2.0 * r, 184 + i)
+    for i, (n, k, r) in enumerate([(3136, 4224, 8), (3136, 4224, 24), (3136, 4224, 33), (3136, 4224, 64),
+                                   (3080, 4104, 13), (3080, 4104, 24), (3080, 4104, 33), (3080, 4104, 64)])
+] + [
+    # the 64-token dX tiles with whole stages and columns at every padded rank (two empty or half-empty pieces of
+    # the last stage among them), and the 128 x 128 dX beside them
+    Shape("short", m, n, k, r, 2.0 * r, 200 + i)
+    for i, (m, n, k, r) in enumerate([(70, 64, 11008, 5), (70, 192, 11008, 24), (70, 64, 11008, 33),
+                                      (70, 128, 11008, 64), (200, 320, 1024, 16), (600, 2112, 1024, 8),
+                                      (600, 2056, 1032, 24), (300, 64, 1024, 24), (300, 64, 1024, 64),
+                                      (70, 72, 11008, 3), (70, 136, 11008, 24), (70, 72, 11008, 33),
+                                      (70, 72, 11008, 64)])
 ]
 
 
@@ -137,7 +146,8 @@ SPLIT_EDGE = [
     # is no multiple of 8), and the 128 x 192 tiles, whole and partial last stages
     Shape("edge", 300, 1096, 1096, 8, 16.0, 505), Shape("edge", 333, 520, 1088, 13, 26.0, 506),
     Shape("edge", 193, 1032, 320, 40, 80.0, 507), Shape("edge", 300, 11008, 3080, 8, 16.0, 508),
-    Shape("edge", 300, 10816, 3072, 24, 48.0, 509), Shape("edge", 200, 3080, 10952, 13, 26.0, 510),
+    Shape("edge", 300, 10816, 3072, 24, 48.0, 509), Shape("edge", 1030, 3080, 4360, 13, 26.0, 510),
+    Shape("edge", 333, 2048, 2056, 13, 26.0, 511), Shape("edge", 100, 2120, 520, 8, 16.0, 512),
 ]
 
 
