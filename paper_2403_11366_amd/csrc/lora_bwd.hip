@@ -61,6 +61,29 @@ __device__ __forceinline__ void store_ut2(const float* __restrict__ U, u16* __re
   }
 }
 
+// Element q of a per-projection argument array (q uniform); compile-time
+// indices only, so the kernel argument is never indexed dynamically.
+template <typename T>
+__device__ __forceinline__ T pick(const T (&v)[kMaxGroup], int q) {
+  T x = v[0];
+#pragma unroll
+  for (int i = 1; i < kMaxGroup; ++i)
+    if (q == i) x = v[i];
+  return x;
+}
+
+// Kernel argument (by value) of the dU kernels: the projections of a group
+// (one for a single projection), each with `blocks` workgroups of its own.
+struct DuGroup {
+  const u16* dY[kMaxGroup];
+  const u16* B[kMaxGroup];
+  const float* U[kMaxGroup];
+  u16* dU2[kMaxGroup];
+  u16* dUt2[kMaxGroup];
+  u16* Ut2[kMaxGroup];
+  int n[kMaxGroup];
+};
+
 // ---------------------------------------------------------------------------
 // dU = s dY B for TPW (8, 16 or 32) tokens per workgroup, reducing over all
 // of n, plus the U^T high/low split of the same tokens.  The launch takes the
@@ -82,10 +105,8 @@ __device__ __forceinline__ void store_ut2(const float* __restrict__ U, u16* __re
 // stacked dU^T) and Ut2 (U^T rounded to bf16).  Index math is 32-bit:
 // validation bounds every index below 2^30.
 template <int RP, int TPW>
-__global__ __launch_bounds__(512) void lora_bwd_du_kernel(
-    const u16* __restrict__ dY, const u16* __restrict__ B, const float* __restrict__ U,
-    u16* __restrict__ dU2, u16* __restrict__ dUt2, u16* __restrict__ Ut2,
-    int m, int n, int r, int mp, float s) {
+__global__ __launch_bounds__(512) void lora_bwd_du_kernel(DuGroup grp, int blocks, int m, int r, int mp,
+                                                          float s) {
   constexpr int FT = RP / 16;
   constexpr int TG = TPW >= 16 ? TPW / 16 : 1;      // 16-token groups
   constexpr int NWV = 8;
@@ -99,7 +120,12 @@ __global__ __launch_bounds__(512) void lora_bwd_du_kernel(
   __shared__ __attribute__((aligned(1024))) char sm[STAGE_BYTES > RED_BYTES ? STAGE_BYTES : RED_BYTES];
   static_assert(TPW == 32 || TPW == 16 || TPW == 8, "tokens per workgroup");
   static_assert(TG * FT <= NWV, "one wave per output fragment in the epilogue");
-  const int i0 = blockIdx.x * TPW;
+  const int sel = (int)blockIdx.x / blocks;        // the projection
+  const u16 *dY = pick(grp.dY, sel), *B = pick(grp.B, sel);
+  const float* U = pick(grp.U, sel);
+  u16 *dU2 = pick(grp.dU2, sel), *dUt2 = pick(grp.dUt2, sel), *Ut2 = pick(grp.Ut2, sel);
+  const int n = pick(grp.n, sel);
+  const int i0 = ((int)blockIdx.x - sel * blocks) * TPW;
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int g = lane >> 4, c16 = lane & 15;
   const uint32_t rowbytes = (uint32_t)n * 2;
@@ -260,10 +286,8 @@ __device__ __forceinline__ void du_frag_wait(short8 (&y)[TG], short4v (&bl)[FT],
 // sums are added in wave order through LDS, then written as the register
 // kernel does (dU2, dUt2, Ut2).
 template <int RP, int TPW>
-__global__ __launch_bounds__(256) void lora_bwd_du_dma_kernel(
-    const u16* __restrict__ dY, const u16* __restrict__ B, const float* __restrict__ U,
-    u16* __restrict__ dU2, u16* __restrict__ dUt2, u16* __restrict__ Ut2,
-    int m, int n, int r, int mp, float s) {
+__global__ __launch_bounds__(256) void lora_bwd_du_dma_kernel(DuGroup grp, int blocks, int m, int r, int mp,
+                                                              float s) {
   constexpr int NWV = 4;
   constexpr int FT = RP / 16;
   constexpr int TG = TPW >= 16 ? TPW / 16 : 1;
@@ -280,7 +304,12 @@ __global__ __launch_bounds__(256) void lora_bwd_du_dma_kernel(
   static_assert(NSW >= 3 && CPW * (NSW - 2) < 64, "copies in flight fit the wait counter");
   static_assert(NRD <= 15, "reads of one substep fit the LDS wait counter");
   __shared__ __attribute__((aligned(1024))) char sm[SMEM];
-  const int i0 = blockIdx.x * TPW;
+  const int sel = (int)blockIdx.x / blocks;        // the projection
+  const u16 *dY = pick(grp.dY, sel), *B = pick(grp.B, sel);
+  const float* U = pick(grp.U, sel);
+  u16 *dU2 = pick(grp.dU2, sel), *dUt2 = pick(grp.dUt2, sel), *Ut2 = pick(grp.Ut2, sel);
+  const int n = pick(grp.n, sel);
+  const int i0 = ((int)blockIdx.x - sel * blocks) * TPW;
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int g = lane >> 4, c16 = lane & 15;
   const uint32_t rowbytes = (uint32_t)n * 2;
@@ -815,17 +844,6 @@ __device__ __forceinline__ void finalize_partials(const FinalizeArgs& f, int fir
       f.dA[g] = f.sa_scale * sum_partials(f.pa + (size_t)t * f.k + l, (size_t)f.rpa * f.k, f.sa);
     }
   }
-}
-
-// Element q of a per-projection argument array (q uniform); compile-time
-// indices only, so the kernel argument is never indexed dynamically.
-template <typename T>
-__device__ __forceinline__ T pick(const T (&v)[kMaxGroup], int q) {
-  T x = v[0];
-#pragma unroll
-  for (int i = 1; i < kMaxGroup; ++i)
-    if (q == i) x = v[i];
-  return x;
 }
 
 // Kernel argument (by value) of the grouped dX GEMM of projections that read
@@ -1857,22 +1875,30 @@ static hipError_t run_dx(const Launch& L, const BwdArgs& a, const u16* dU2, int 
   });
 }
 
-// dUt2: where dU^T goes (the projection's own region, or its rows of a
-// group's stacked region).
-static hipError_t run_du(const Launch& L, const BwdArgs& a, const BwdLayout& BL, hipStream_t st,
-                         u16* dUt2 = nullptr) {
-  u16* Ut2 = reinterpret_cast<u16*>(a.ws + BL.ut2);
-  u16* dU2 = reinterpret_cast<u16*>(a.ws + BL.du2);
-  if (!dUt2) dUt2 = reinterpret_cast<u16*>(a.ws + BL.dut2);
+// Projection a (workspace layout BL) as member g of a dU launch.  dUt2: where
+// dU^T goes (the projection's own region, or its rows of a group's stacked
+// region).
+static void set_du(DuGroup& grp, int g, const BwdArgs& a, const BwdLayout& BL, u16* dUt2) {
+  grp.dY[g] = a.dY;
+  grp.B[g] = a.B;
+  grp.U[g] = a.U;
+  grp.dU2[g] = reinterpret_cast<u16*>(a.ws + BL.du2);
+  grp.dUt2[g] = dUt2 ? dUt2 : reinterpret_cast<u16*>(a.ws + BL.dut2);
+  grp.Ut2[g] = reinterpret_cast<u16*>(a.ws + BL.ut2);
+  grp.n[g] = (int)a.n;
+}
+
+static hipError_t run_du(const Launch& L, const DuGroup& grp, int64_t m, int64_t r, int64_t mp, float s,
+                         hipStream_t st) {
   return with_int<16, 32, 48, 64>(L.rp, [&](auto rc) {
     return with_int<8, 16, 32>(L.tpw, [&](auto tc) {
       constexpr int RP = decltype(rc)::value, TPW = decltype(tc)::value;
       if (L.fastb)
         hipLaunchKernelGGL((lora_bwd_du_dma_kernel<RP, TPW>), dim3((unsigned)L.grid), dim3((unsigned)L.block), 0, st,
-                           a.dY, a.B, a.U, dU2, dUt2, Ut2, (int)a.m, (int)a.n, (int)a.r, (int)BL.mp, a.s);
+                           grp, L.tiles_m, (int)m, (int)r, (int)mp, s);
       else
-        hipLaunchKernelGGL((lora_bwd_du_kernel<RP, TPW>), dim3((unsigned)L.grid), dim3((unsigned)L.block), 0, st,
-                           a.dY, a.B, a.U, dU2, dUt2, Ut2, (int)a.m, (int)a.n, (int)a.r, (int)BL.mp, a.s);
+        hipLaunchKernelGGL((lora_bwd_du_kernel<RP, TPW>), dim3((unsigned)L.grid), dim3((unsigned)L.block), 0, st, grp,
+                           L.tiles_m, (int)m, (int)r, (int)mp, s);
       return hipGetLastError();
     });
   });
@@ -1921,7 +1947,12 @@ hipError_t launch_bwd(const BwdArgs& a, hipStream_t st) {
     const Launch& L = p.l[i];
     hipError_t e = hipErrorInvalidValue;
     switch (L.id) {
-      case K_DU: e = run_du(L, a, BL, st); break;
+      case K_DU: {
+        DuGroup one{};
+        set_du(one, 0, a, BL, nullptr);
+        e = run_du(L, one, a.m, a.r, BL.mp, a.s, st);
+        break;
+      }
       case K_TOKRED: e = run_tokred(L, a, BL, st); break;
       case K_DX: e = run_dx(L, a, dU2, (int)BL.mp, fin, none, st); break;
       default: break;
@@ -2074,9 +2105,10 @@ hipError_t launch_bwd_group(const GroupBwdArgs& a, hipStream_t st) {
         return hipGetLastError();
       });
     } else if (L.id == K_DU) {
-      const BwdArgs b = member_args(L.member, GL);
-      e = GL.stacked ? run_du(L, b, GL.L[L.member], st, dut_stack + (size_t)L.member * rp * GL.L[0].mp)
-                     : run_du(L, b, GL.L[L.member], st);
+      DuGroup dg{};
+      for (int g = 0; g < a.count; ++g)
+        set_du(dg, g, member_args(g, GL), GL.L[g], GL.stacked ? dut_stack + (size_t)g * rp * GL.L[0].mp : nullptr);
+      e = run_du(L, dg, a.m, a.r, GL.L[0].mp, a.s, st);
     } else if (L.id == K_TOKRED) {
       const BwdArgs b = member_args(L.member, GL);
       e = run_tokred(L, b, GL.L[L.member], st);
