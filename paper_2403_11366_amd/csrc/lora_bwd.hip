@@ -2046,8 +2046,8 @@ hipError_t launch_bwd_noalloc(const BwdArgs& a, hipStream_t st) {
   return launch_bwd(b, st);
 }
 
-// Grouped backward: per projection the dU and token-reduction launches (each
-// in its own workspace region), then one dX launch over the whole group whose
+// Grouped backward: one dU launch for all projections, per projection the
+// token reductions (each in its own workspace region), then one dX launch over the whole group whose
 // tails (of the first column range) finalize every projection's dA and dB.
 hipError_t launch_bwd_group(const GroupBwdArgs& a, hipStream_t st) {
   auto member_args = [&](int g, const GroupBwdLayout& GL) {
