@@ -18,6 +18,10 @@ that contains inline-asm LDS reads:
   * no LDS read is outstanding at a branch or a label (the check follows
     straight-line code only, so the pipelines must drain at stage ends).
 
+It also checks that the two-stage 256 x 256 forward tiles close the LDS reads of their
+prologue with a barrier before anything refills what was read
+(check_first_reads).
+
 Usage: python -m paper_2403_11366_amd.asm_check FILE.s [...]; build() calls
 check_files() on the saved assembly and fails the build on any finding.
 """
@@ -105,21 +109,59 @@ def check_function(name: str, lines: list) -> list:
     return errs
 
 
-def check_assembly(text: str) -> list:
-    lines = text.split("\n")
-    errs = []
+def check_first_reads(name: str, lines: list) -> list:
+    """Findings for one function whose waves take turns over two LDS stages:
+    the reads issued before its first matrix product load fragments from a
+    buffer that the first slot refills, in any wave, so they have to be
+    waited for (`lgkmcnt(0)`) and followed by an `s_barrier` that every wave
+    takes, i.e. before the next branch or label and the next copy into LDS."""
+    reads, waited = 0, False
+    for no, ln in enumerate(lines):
+        t = ln.strip()
+        s = t.split(";")[0].strip()
+        op, _, rest = s.partition(" ")
+        if op.startswith("ds_read"):
+            reads, waited = reads + 1, False
+        elif not reads or not s:
+            continue
+        elif op == "s_waitcnt":
+            m = _LGKM.search(rest)
+            waited = waited or bool(m and int(m.group(1)) == 0)
+        elif op == "s_barrier":
+            return [] if waited else [f"{name}: barrier at line {no} before the first LDS reads completed"]
+        elif op.startswith(("s_cbranch", "s_branch", "v_mfma")) or s.startswith(".LBB") or s.endswith(" lds"):
+            return [f"{name}: `{s}` at line {no} with no barrier since the first LDS reads"]
+    return [f"{name}: no barrier after its first LDS reads"] if reads else [f"{name}: no LDS reads"]
+
+
+# The 256 x 256 forward tile (two LDS stages, wave rows taking turns).
+_TWO_STAGE = re.compile(r"lora_fwd_kernel<256, 256,")
+
+
+def is_two_stage(name: str) -> bool:
+    return bool(_TWO_STAGE.search(name))
+
+
+def functions(text: str):
+    """(demangled name, assembly lines) of every function of a listing."""
     name, body = None, []
-    for ln in lines:
+    for ln in text.split("\n"):
         m = _FUNC.match(ln)
         if m:
             name, body = m.group(1), []
-            continue
-        if name and ln.strip().startswith(".Lfunc_end"):
-            errs += check_function(_demangle(name), body)
+        elif name and ln.strip().startswith(".Lfunc_end"):
+            yield _demangle(name), body
             name = None
-            continue
-        if name:
+        elif name:
             body.append(ln)
+
+
+def check_assembly(text: str) -> list:
+    errs = []
+    for name, body in functions(text):
+        errs += check_function(name, body)
+        if is_two_stage(name):
+            errs += check_first_reads(name, body)
     return errs
 
 

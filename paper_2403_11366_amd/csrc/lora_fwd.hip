@@ -54,6 +54,9 @@ constexpr int kBigStage = 512 * 128;   // bytes of a 64-wide stage of the 256 x 
 // P is free from the read slots of phase P + 1 on, which refill it for the
 // stage after next (seven phases before its use).  The quarter read in phase
 // P + 1 is waited for (six newer ones stay in flight) in the read slot of P.
+// The reads before the first slot (W half 0 of stage 0, whose quarter the first
+// row's first slot refills) are closed the same way: every wave waits for them
+// and all eight pass a barrier before the second row's extra one.
 //
 // Bound by power: with all eight waves in step (reads of the next substep
 // under the products, one barrier per stage) the matrix cores were 65% busy,
@@ -209,6 +212,9 @@ __device__ __forceinline__ void fwd_big_tile(const u16* __restrict__ X, const u1
   }
   slot_end();
   read_w(0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  wait_lgkm0();
+  slot_end();                    // every wave has read the quarter that the first read slot refills
   if (wm == 1) slot_end();       // the second wave row runs one slot behind
   int kb = 0;
   for (; kb + 2 < nkb; ++kb) stage(kb, I0{});

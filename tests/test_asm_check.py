@@ -97,3 +97,51 @@ def test_reads_after_address_arithmetic_in_one_block():
     bad = XOR_BLOCK.replace("\t;;#ASMSTART\n\ts_waitcnt lgkmcnt(0)", "\tv_mov_b32_e32 v50, v15\n\t;;#ASMSTART\n\ts_waitcnt lgkmcnt(0)", 1)
     errs = asm_check.check_assembly(_fn(bad))
     assert errs and "before its LDS read completed" in errs[0]
+
+
+# The prologue of a 256 x 256 tile: the first stage's copies, a barrier, the
+# first reads, a barrier of all waves, the extra barrier of the second wave row.
+PROLOGUE = """
+	buffer_load_dwordx4 v1, s[4:7], 0 offen lds
+	s_waitcnt vmcnt(12)
+	s_barrier
+	ds_read_b128 v[10:13], v1 offset:32768
+	ds_read_b128 v[14:17], v1 offset:34816
+	s_waitcnt lgkmcnt(0)
+	s_barrier
+	s_cbranch_scc1 .LBB0_2
+	s_barrier
+.LBB0_2:
+	ds_read_b128 v[18:21], v2
+	buffer_load_dwordx4 v1, s[4:7], 0 offen lds
+	s_waitcnt vmcnt(12) lgkmcnt(0)
+	s_barrier
+	v_mfma_f32_16x16x32_bf16 v[20:23], v[10:13], v[18:21], v[20:23]
+"""
+
+
+def test_first_reads_of_a_two_stage_tile_are_closed_by_a_barrier():
+    def check(body):
+        return asm_check.check_first_reads("f", body.split("\n"))
+    assert check(PROLOGUE) == []
+    closed = "\ts_waitcnt lgkmcnt(0)\n\ts_barrier\n\ts_cbranch"
+    # no barrier of all waves between the reads and the refill; one that does not wait for the reads
+    assert check(PROLOGUE.replace(closed, "\ts_cbranch", 1))
+    assert check(PROLOGUE.replace(closed, "\ts_waitcnt lgkmcnt(0)\n\ts_cbranch", 1))
+    assert check(PROLOGUE.replace(closed, "\ts_waitcnt lgkmcnt(1)\n\ts_barrier\n\ts_cbranch", 1))
+
+
+def test_built_two_stage_tiles_close_their_first_reads():
+    """Every compiled 256 x 256 forward tile."""
+    files = sorted(glob.glob(os.path.join(ROOT, "paper_2403_11366_amd", "_build", "*-hip-amdgcn-amd-amdhsa-gfx950.s")))
+    if not files:
+        pytest.skip("library not built here")
+    found, checked = [], 0
+    for f in files:
+        with open(f) as fh:
+            for name, body in asm_check.functions(fh.read()):
+                if asm_check.is_two_stage(name):
+                    checked += 1
+                    found += asm_check.check_first_reads(name, body)
+    assert checked >= 12, checked   # 3 ranks x group x whole stages
+    assert not found, found
