@@ -18,7 +18,7 @@ that contains inline-asm LDS reads:
   * no LDS read is outstanding at a branch or a label (the check follows
     straight-line code only, so the pipelines must drain at stage ends).
 
-It also checks that the two-stage 256 x 256 forward tiles close the LDS reads of their
+It also checks that the two-stage 256 x 256 tiles close the LDS reads of their
 prologue with a barrier before anything refills what was read
 (check_first_reads).
 
@@ -134,8 +134,8 @@ def check_first_reads(name: str, lines: list) -> list:
     return [f"{name}: no barrier after its first LDS reads"] if reads else [f"{name}: no LDS reads"]
 
 
-# The 256 x 256 forward tile (two LDS stages, wave rows taking turns).
-_TWO_STAGE = re.compile(r"lora_fwd_kernel<256, 256,")
+# The 256 x 256 tiles (two LDS stages, wave rows taking turns).
+_TWO_STAGE = re.compile(r"lora_(?:fwd|bwd_dx)_kernel<256, 256,")
 
 
 def is_two_stage(name: str) -> bool:

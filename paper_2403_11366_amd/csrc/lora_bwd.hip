@@ -1270,7 +1270,9 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
 // next.  dY half h: tokens 64 h .. + 63 of both wave rows.  W half h:
 // columns 128 h .. + 127 of the tile as [64][128] (wave column wn takes
 // columns 128 h + 32 wn .. + 31), so that a copy takes whole 256-byte row
-// pieces.  Nothing branches between the assembly reads and their wait.
+// pieces.  Nothing branches between the assembly reads and their wait.  The
+// reads before the first slot are closed by a barrier of all eight waves before
+// the second row's extra one.
 // Measured (whole backward call, against all waves in step on 32x32x16
 // products): 8192 x 4096 x 11008 (tokens x n x k), r = 64: 712 -> 650 us taking
 // turns, 628 on the 16x16x32 products used here; 4096 x 11008 x 4096, r = 16:
@@ -1452,6 +1454,7 @@ __device__ __forceinline__ void dx_big_tile(const DxArgs& p, const DxGroup& grp,
   asm volatile("s_waitcnt lgkmcnt(0)"
                : "+v"(wl[0][0]), "+v"(wh[0][0]), "+v"(wl[0][1]), "+v"(wh[0][1]), "+v"(wl[0][2]), "+v"(wh[0][2]),
                  "+v"(wl[0][3]), "+v"(wh[0][3]));
+  slot_end();                    // every wave has read the quarter that the first read slot refills
   if (wm == 1) slot_end();       // the second wave row runs one slot behind
   int kb = 0;
   for (; kb + 2 < nkb; ++kb) stage(kb, I0{});
