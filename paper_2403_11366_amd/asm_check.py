@@ -156,6 +156,13 @@ def functions(text: str):
             body.append(ln)
 
 
+def vgpr_spills(text: str):
+    """(demangled kernel name, spilled vector registers) of every kernel of a
+    listing, from its metadata."""
+    for name, count in re.findall(r"\.symbol:\s+(\S+)\.kd\n(?:\s+\.\w+:.*\n)*?\s+\.vgpr_spill_count:\s+(\d+)", text):
+        yield _demangle(name), int(count)
+
+
 def check_assembly(text: str) -> list:
     errs = []
     for name, body in functions(text):

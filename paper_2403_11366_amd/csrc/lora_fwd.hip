@@ -81,8 +81,8 @@ __device__ __forceinline__ void fwd_big_tile(const u16* __restrict__ X, const u1
   static_assert(WTI == 128 && WTJ == 64, "wave tile");
   constexpr int STAGE = kBigStage;
   static_assert(STAGE == (BM + BN) * 128 && 2 * STAGE <= 160 * 1024, "128-byte rows per 64-wide stage");
-  constexpr int RPU = RP + 4, RPB = RP + 8;     // padded row lengths of the epilogue's U and B copies
-  static_assert(BM * RPU * 4 + BN * RPB * 2 <= 2 * STAGE, "epilogue LDS reuse");
+  constexpr int RPU = 2 * RP + 8, RPB = RP + 8;   // padded row lengths of the epilogue's U and B copies
+  static_assert(BM * RPU * 2 + BN * RPB * 2 <= 2 * STAGE, "epilogue LDS reuse");
   if (GRP) {   // projection of this column tile (uniform; compile-time indices only)
     int sel = 0;
 #pragma unroll
@@ -223,81 +223,43 @@ __device__ __forceinline__ void fwd_big_tile(const u16* __restrict__ X, const u1
   if (wm == 0) slot_end();
 
   // ---- epilogue ------------------------------------------------------------
-  // LDS reuse: Us [BM][RPU] fp32 U, then Bs [BN][RPB] bf16 (B rows of this tile, zero beyond r and n).  The
-  // rows are padded by 16 bytes so that the 16 lanes of a read group, which
-  // read 16 consecutive rows, fall in different banks.  Rows n0 .. n0+jn-1 of
-  // B are contiguous, so they are fetched as 16-byte chunks of 8 elements, all
-  // issued before the first wait, and scattered into Bs.
-  float* Us = reinterpret_cast<float*>(smem);
-  u16* Bs = reinterpret_cast<u16*>(smem + BM * RPU * 4);
+  // LDS reuse: Us [BM][RPU] bf16, s U as its high parts (RP) and low parts (RP)
+  // a row, then Bs [BN][RPB] bf16 (B rows of this tile, zero beyond r and n).
+  // Split here, once a value: split by every wave that multiplies the token (each
+  // lane forming both parts) the conversions alone took 5 us a tile at rank 64.
+  // The rows are padded by 16 bytes so that the 16 lanes of a read group, which
+  // read 16 consecutive rows, fall in different banks.  Rows n0 .. n0+jn-1 of B
+  // are fetched as 16-byte chunks of 8 elements, all issued before the first
+  // wait.
+  u16* Us = reinterpret_cast<u16*>(smem);
+  u16* Bs = reinterpret_cast<u16*>(smem + BM * RPU * 2);
   constexpr int BCH = (BN * RP / 8 + NT - 1) / NT;   // chunks per thread (r <= RP)
   const int jn = min(BN, n - n0);
-  const int nch = jn * r / 8;                       // exact: n and n0 are multiples of 8
-  const __amdgpu_buffer_rsrc_t rsB = make_rsrc(B + (size_t)n0 * r, (uint64_t)nch * 16);
+  const __amdgpu_buffer_rsrc_t rsB = make_rsrc(B + (size_t)n0 * r, (uint64_t)jn * r * 2);
   int4v bv[BCH];
-#pragma unroll
-  for (int i = 0; i < BCH; ++i) {
-    const int q = tid + i * NT;
-    bv[i] = buf_load16(rsB, q < nch ? (uint32_t)q * 16 : kOOB);
-  }
+  load_b_rows<RP, NT>(rsB, r, jn, tid, bv);
   {   // U of the tile's tokens from the U pass (zero beyond r and m), all loads issued before the first use
-    constexpr int UPT = BM * RP / NT;
-    static_assert(BM * RP % NT == 0, "U values per thread");
     const __amdgpu_buffer_rsrc_t rsU = make_rsrc(U + (size_t)m0 * r, (uint64_t)min(BM, m - m0) * r * 4);
-    float uv[UPT];
-#pragma unroll
-    for (int i = 0; i < UPT; ++i) {
-      const int e = tid + i * NT, il = e / RP, t = e - il * RP;
-      uv[i] = buf_load4f(rsU, t < r ? (uint32_t)(il * r + t) * 4 : kOOB);
-    }
-#pragma unroll
-    for (int i = 0; i < UPT; ++i) {
-      const int e = tid + i * NT, il = e / RP, t = e - il * RP;
-      Us[il * RPU + t] = uv[i];
-    }
+    float uv[BM * RP / NT];
+    load_u_pairs<BM, RP, NT>(rsU, r, tid, uv);
+    split_u_pairs<BM, RP, NT>(uv, s, tid, Us);
   }
-  for (int e = tid; e < BN * RPB / 8; e += NT) reinterpret_cast<int4v*>(Bs)[e] = int4v{0, 0, 0, 0};
-  __syncthreads();
-  {
-    // element idx of the chunks is B row idx / r, column idx % r; the quotient
-    // comes from a float product that stays at least 0.5/r away from an integer
-    const float rinv = 1.0f / (float)r;
-#pragma unroll
-    for (int i = 0; i < BCH; ++i) {
-      const int q = tid + i * NT;
-      if (q < nch) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int idx = 8 * q + e;
-          const int j = (int)(((float)idx + 0.5f) * rinv);
-          const int t = idx - j * r;
-          Bs[j * RPB + t] = (u16)((uint32_t)bv[i][e >> 1] >> (16 * (e & 1)));
-        }
-      }
-    }
-  }
+  store_b_rows<BN, RP, NT>(bv, r, jn, tid, Bs);
   __syncthreads();
 
   // acc += s U B^T, formed as Y^T += B (sU)^T over t in blocks of 16: one
   // product of 32 k holds the block twice, against the high bf16 part of sU in
   // its lower half (lanes g = 0, 1) and the low part in its upper half.
   const int tblocks = (r + 15) / 16;
+  const u16* up = Us + (wm * WTI + c16) * RPU + (g < 2 ? 0 : RP) + 8 * (g & 1);
+  const u16* bp = Bs + (wn * WTJ + c16) * RPB + 8 * (g & 1);
   for (int tb = 0; tb < tblocks; ++tb) {
-    const int t0 = 16 * tb + 8 * (g & 1);
     short8 bfr[4];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
-      bfr[a] = *reinterpret_cast<const short8*>(Bs + (wn * WTJ + 16 * a + c16) * RPB + t0);
+    for (int a = 0; a < 4; ++a) bfr[a] = *reinterpret_cast<const short8*>(bp + 16 * a * RPB + 16 * tb);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
-      const float* up = Us + (wm * WTI + 16 * b + c16) * RPU + t0;
-      short8 uf;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float v = s * up[e];
-        const u16 hi = f32_to_bf16(v);
-        uf[e] = (short)(g < 2 ? hi : f32_to_bf16(v - bf16_to_f32(hi)));
-      }
+      const short8 uf = *reinterpret_cast<const short8*>(up + 16 * b * RPU + 16 * tb);
 #pragma unroll
       for (int a = 0; a < 4; ++a) acc[a][b] = mfma16x16x32(bfr[a], uf, acc[a][b]);
     }

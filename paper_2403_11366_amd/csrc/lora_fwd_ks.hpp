@@ -10,6 +10,83 @@
 
 namespace lora {
 
+// Epilogue operands of the forward tiles beyond rank 16 and of the 256 x 256
+// one.  U of BM tokens, in pairs of ranks (zero beyond r and the resource).
+template <int BM, int RP, int NT>
+__device__ __forceinline__ void load_u_pairs(__amdgpu_buffer_rsrc_t rsU, int r, int tid, float (&uv)[BM * RP / NT]) {
+  static_assert(BM * RP % (2 * NT) == 0, "pairs per thread");
+#pragma unroll
+  for (int i = 0; i < BM * RP / NT / 2; ++i) {
+    const int e = 2 * (tid + i * NT), il = e / RP, t = e - il * RP;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) uv[2 * i + h] = buf_load4f(rsU, t + h < r ? (uint32_t)(il * r + t + h) * 4 : kOOB);
+  }
+}
+// s U as bf16 high and low parts: Us rows of RP high, RP low and 8 unused.
+template <int BM, int RP, int NT>
+__device__ __forceinline__ void split_u_pairs(const float (&uv)[BM * RP / NT], float s, int tid, u16* Us) {
+#pragma unroll
+  for (int i = 0; i < BM * RP / NT / 2; ++i) {
+    const int e = 2 * (tid + i * NT), il = e / RP, t = e - il * RP;
+    uint32_t hi = 0, lo = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float v = s * uv[2 * i + h];
+      const u16 top = f32_to_bf16(v);
+      hi |= (uint32_t)top << (16 * h);
+      lo |= (uint32_t)f32_to_bf16(v - bf16_to_f32(top)) << (16 * h);
+    }
+    *reinterpret_cast<uint32_t*>(Us + il * (2 * RP + 8) + t) = hi;
+    *reinterpret_cast<uint32_t*>(Us + il * (2 * RP + 8) + RP + t) = lo;
+  }
+}
+// B rows of BN features in 16-byte chunks: the tile's rows (contiguous) in order,
+// or, for r a multiple of 8, where each chunk lies inside one row, by their place
+// in the padded [BN][RP] block.
+template <int RP, int NT, int BCH>
+__device__ __forceinline__ void load_b_rows(__amdgpu_buffer_rsrc_t rsB, int r, int jn, int tid, int4v (&bv)[BCH]) {
+  const bool whole = (r & 7) == 0;
+#pragma unroll
+  for (int i = 0; i < BCH; ++i) {
+    const int q = tid + i * NT, j = q / (RP / 8), t0 = 8 * (q % (RP / 8));
+    bv[i] = buf_load16(rsB, whole ? (t0 < r ? (uint32_t)(j * r + t0) * 2 : kOOB)
+                                  : (q < jn * r / 8 ? (uint32_t)q * 16 : kOOB));   // (exact: jn is a multiple of 8)
+  }
+}
+// The same into Bs [BN][RP + 8], zero beyond r and n.  Contains a barrier for
+// other ranks (uniform).
+template <int BN, int RP, int NT, int BCH>
+__device__ __forceinline__ void store_b_rows(const int4v (&bv)[BCH], int r, int jn, int tid, u16* Bs) {
+  constexpr int RPB = RP + 8;
+  if ((r & 7) == 0) {
+#pragma unroll
+    for (int i = 0; i < BCH; ++i) {
+      const int q = tid + i * NT;
+      if (q < BN * RP / 8) *reinterpret_cast<int4v*>(Bs + q / (RP / 8) * RPB + 8 * (q % (RP / 8))) = bv[i];
+    }
+    return;
+  }
+  for (int e = tid; e < BN * RPB / 8; e += NT) reinterpret_cast<int4v*>(Bs)[e] = int4v{0, 0, 0, 0};
+  __syncthreads();
+  // element idx of the chunks is B row idx / r, column idx % r; the quotient
+  // comes from a float product that stays at least 0.5/r away from an integer
+  const float rinv = 1.0f / (float)r;
+  const int nch = jn * r / 8;
+#pragma unroll
+  for (int i = 0; i < BCH; ++i) {
+    const int q = tid + i * NT;
+    if (q < nch) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int idx = 8 * q + e;
+        const int j = (int)(((float)idx + 0.5f) * rinv);
+        const int t = idx - j * r;
+        Bs[j * RPB + t] = (u16)((uint32_t)bv[i][e >> 1] >> (16 * (e & 1)));
+      }
+    }
+  }
+}
+
 // Eight waves: wave (wk, wm, wn) multiplies the 64 tokens wm and the BN / 2
 // features wn of the tile over substeps 2 wk and 2 wk + 1 of every 64-wide
 // stage (the 32-wide k half wk); waves w and w + 4, the two k halves of one
@@ -235,36 +312,25 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
   {
     const int lane = lane_e, tid = wave * 64 + lane_e;
     const int g = lane >> 4, c16 = lane & 15;
-    // Regions: [0, XCH) the exchange, later the per-wave output staging; Us fp32
-    // [BM][RPU] (twice at RP = 16: the two k-half partials) and Bs bf16
-    // [BN][RPB].  At RP = 16 they lie beside the exchange; for larger ranks they
-    // reuse it once it has been read.
-    constexpr int RPU = RP == 16 ? RP : RP + 4, RPB = RP == 16 ? RP : RP + 8;
+    // Regions: [0, XCH) the exchange, later the per-wave output staging; at RP =
+    // 16, beside it, Us fp32 [BM][RP] (once per k share) and Bs bf16 [BN][RP]; for
+    // larger ranks, over it once it has been read, Us bf16 [BM][RPU] (s U as high
+    // and low parts) and Bs [BN][RPB].
+    constexpr int RPU = RP == 16 ? RP : 2 * RP + 8, RPB = RP == 16 ? RP : RP + 8;
     constexpr int UPT = BM * RP / NT, BCH = (BN * RP / 8 + NT - 1) / NT;
     float* Us = reinterpret_cast<float*>(smem + (EARLY_B ? XCH : 0));
-    u16* Bs2 = EARLY_B ? Bs : reinterpret_cast<u16*>(smem + BM * RPU * 4);
+    u16* Bs2 = EARLY_B ? Bs : reinterpret_cast<u16*>(smem + BM * RPU * 2);
     float uv[UPT];
     int4v bv[EARLY_B ? 1 : BCH];
-    const int nch = min(BN, n - n0) * r / 8;       // 16-byte chunks of the tile's B rows (exact)
-    if constexpr (UPRE) {                          // U, and B beyond rank 16: all loads issued before the first use
-      const __amdgpu_buffer_rsrc_t rsU = make_rsrc(U + (size_t)m0 * r, (uint64_t)min(BM, m - m0) * r * 4);
-#pragma unroll
-      for (int i = 0; i < UPT; ++i) {
-        const int e = tid + i * NT, il = e / RP, t = e - il * RP;
-        uv[i] = buf_load4f(rsU, t < r ? (uint32_t)(il * r + t) * 4 : kOOB);
-      }
-      if constexpr (!EARLY_B) {
-        const __amdgpu_buffer_rsrc_t rsB = make_rsrc(B + (size_t)n0 * r, (uint64_t)nch * 16);
-#pragma unroll
-        for (int i = 0; i < BCH; ++i) {
-          const int q = tid + i * NT;
-          bv[i] = buf_load16(rsB, q < nch ? (uint32_t)q * 16 : kOOB);
-        }
-      }
-    }
+    const int jn = min(BN, n - n0);
     // The wave finishes fragments b = NOB wk .. + NOB - 1 of its block.
     // Partial sums are added in k-share order.
+    // The shares are pinned where they are formed: sunk to their next use, they
+    // would keep all of acc and the partner's sums in registers beside the U and B
+    // loads, which 128 x 256 at rank 64 then spills one by one as they arrive (1172
+    // x 5120 x 512, r = 54: 24.8 us, 17.1 without).
     floatx4 own[NA][NOB];
+    auto pin = [&](floatx4& v) LORA_INLINE { asm volatile("" : "+v"(v)); };
     floatx4* xb = reinterpret_cast<floatx4*>(smem);
     if constexpr (NK == 2) {
       floatx4* dst = xb + (size_t)(wave ^ 4) * NA * 2 * 64;   // the partner's region
@@ -279,6 +345,7 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
             o[q] = wk == 0 ? hi[q] : lo[q];
             own[a][b][q] = wk == 0 ? lo[q] : hi[q];
           }
+          pin(own[a][b]);
           dst[(a * 2 + b) * 64 + lane] = o;
         }
     } else {   // [wn][token fragment][k share][feature fragment]
@@ -286,6 +353,14 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
       for (int a = 0; a < NA; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b) xb[(size_t)(((wn * 4 + b) * 4 + wk) * NA + a) * 64 + lane] = acc[a][b];
+    }
+    if constexpr (UPRE) {   // U, and B beyond rank 16: all loads issued before the first use, acc half free
+      const __amdgpu_buffer_rsrc_t rsU = make_rsrc(U + (size_t)m0 * r, (uint64_t)min(BM, m - m0) * r * 4);
+      load_u_pairs<BM, RP, NT>(rsU, r, tid, uv);
+      if constexpr (!EARLY_B) {
+        const __amdgpu_buffer_rsrc_t rsB = make_rsrc(B + (size_t)n0 * r, (uint64_t)jn * r * 2);
+        load_b_rows<RP, NT>(rsB, r, jn, tid, bv);
+      }
     }
     if (!UPRE) {
 #pragma unroll
@@ -300,7 +375,10 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
 #pragma unroll
       for (int a = 0; a < NA; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) own[a][b] += src[(a * 2 + b) * 64 + lane];
+        for (int b = 0; b < 2; ++b) {
+          own[a][b] += src[(a * 2 + b) * 64 + lane];
+          pin(own[a][b]);
+        }
     } else {
       const floatx4* src = xb + (size_t)(wn * 4 + wk) * 4 * NA * 64;
 #pragma unroll
@@ -312,31 +390,12 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
     }
     if constexpr (!EARLY_B) {
       __syncthreads();                             // the exchange has been read
-      for (int e = tid; e < BN * RPB / 8; e += NT) reinterpret_cast<int4v*>(Bs2)[e] = int4v{0, 0, 0, 0};
-      __syncthreads();
-      // element idx of the chunks is B row idx / r, column idx % r; the quotient
-      // comes from a float product that stays at least 0.5/r away from an integer
-      const float rinv = 1.0f / (float)r;
+      store_b_rows<BN, RP, NT>(bv, r, jn, tid, Bs2);
+      split_u_pairs<BM, RP, NT>(uv, s, tid, reinterpret_cast<u16*>(Us));
+    } else if (UPRE) {
 #pragma unroll
-      for (int i = 0; i < BCH; ++i) {
-        const int q = tid + i * NT;
-        if (q < nch) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int idx = 8 * q + e;
-            const int j = (int)(((float)idx + 0.5f) * rinv);
-            const int t = idx - j * r;
-            Bs2[j * RPB + t] = (u16)((uint32_t)bv[i][e >> 1] >> (16 * (e & 1)));
-          }
-        }
-      }
-    }
-    if (UPRE) {
-#pragma unroll
-      for (int i = 0; i < UPT; ++i) {
-        const int e = tid + i * NT, il = e / RP, t = e - il * RP;
-        Us[il * RPU + t] = uv[i];
-      }
+      for (int i = 0; i < UPT / 2; ++i)
+        *reinterpret_cast<float2*>(Us + 2 * (tid + i * NT)) = float2{uv[2 * i], uv[2 * i + 1]};
     } else {
       for (int e = tid; e < BM * RP; e += NT) {   // the k shares' partials, written before the barrier above
         float v = Us[e];
@@ -361,12 +420,17 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
       short8 uf[NOB];
 #pragma unroll
       for (int b = 0; b < NOB; ++b) {
-        const float* up = Us + (i1 + 16 * b + c16) * RPU + t0;
+        if constexpr (!EARLY_B) {
+          uf[b] = *reinterpret_cast<const short8*>(reinterpret_cast<const u16*>(Us) + (i1 + 16 * b + c16) * RPU +
+                                                   (g < 2 ? 0 : RP) + t0);
+        } else {
+          const float* up = Us + (i1 + 16 * b + c16) * RPU + t0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float v = s * up[e];
-          const u16 hi = f32_to_bf16(v);
-          uf[b][e] = (short)(g < 2 ? hi : f32_to_bf16(v - bf16_to_f32(hi)));
+          for (int e = 0; e < 8; ++e) {
+            const float v = s * up[e];
+            const u16 hi = f32_to_bf16(v);
+            uf[b][e] = (short)(g < 2 ? hi : f32_to_bf16(v - bf16_to_f32(hi)));
+          }
         }
       }
 #pragma unroll

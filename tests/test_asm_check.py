@@ -4,6 +4,7 @@ listings are found, the safe pattern passes, and the built library's saved
 gfx950 assembly passes (when it has been built here)."""
 import glob
 import os
+import re
 
 import pytest
 
@@ -145,3 +146,21 @@ def test_built_two_stage_tiles_close_their_first_reads():
                     found += asm_check.check_first_reads(name, body)
     assert checked >= 12 + 8, checked   # forward: 3 ranks x group x whole stages; dX: 4 ranks x group
     assert not found, found
+
+
+def test_built_kernels_do_not_spill_vector_registers():
+    """A spill beside the copies into LDS waits for every copy and load issued
+    before it.  Only the register-staged k-split tile, which runs at the
+    register limit, keeps two values in scratch (before its loop)."""
+    files = sorted(glob.glob(os.path.join(ROOT, "paper_2403_11366_amd", "_build", "*-hip-amdgcn-amd-amdhsa-gfx950.s")))
+    if not files:
+        pytest.skip("library not built here")
+    seen, bad = 0, {}
+    for f in files:
+        with open(f) as fh:
+            for name, spills in asm_check.vgpr_spills(fh.read()):
+                seen += 1
+                if spills > (2 if re.search(r"lora_fwd_ks_kernel<\w+, true, false, false>", name) else 0):
+                    bad[name] = spills
+    assert seen >= 200, seen
+    assert not bad, bad
