@@ -325,12 +325,13 @@ __device__ __forceinline__ void fwd_ks_tile(const u16* __restrict__ X, const u16
     const int jn = min(BN, n - n0);
     // The wave finishes fragments b = NOB wk .. + NOB - 1 of its block.
     // Partial sums are added in k-share order.
-    // The shares are pinned where they are formed: sunk to their next use, they
-    // would keep all of acc and the partner's sums in registers beside the U and B
-    // loads, which 128 x 256 at rank 64 then spills one by one as they arrive (1172
-    // x 5120 x 512, r = 54: 24.8 us, 17.1 without).
+    // Beyond rank 16 the shares are pinned where they are formed: sunk to their next
+    // use, they keep all of acc and the partner's sums in registers beside the U and
+    // B loads, and 128 x 256 at rank 64 spills each U value as it arrives, one load
+    // after the other (1172 x 5120 x 512, r = 54: 24.8 us against 17.1).  At rank
+    // 16, where nothing is loaded here, the pins would cost 0.4 us.
     floatx4 own[NA][NOB];
-    auto pin = [&](floatx4& v) LORA_INLINE { asm volatile("" : "+v"(v)); };
+    auto pin = [&](floatx4& v) LORA_INLINE { if constexpr (!EARLY_B) asm volatile("" : "+v"(v)); };
     floatx4* xb = reinterpret_cast<floatx4*>(smem);
     if constexpr (NK == 2) {
       floatx4* dst = xb + (size_t)(wave ^ 4) * NA * 2 * 64;   // the partner's region
