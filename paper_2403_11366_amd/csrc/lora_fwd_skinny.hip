@@ -53,7 +53,10 @@ __global__ __launch_bounds__(512) void lora_fwd_skinny_ks_kernel(const u16* __re
   constexpr int RMAX = UPRE ? 64 : 16;
   constexpr int BCH = (F * RMAX / 8 + NT - 1) / NT;
   constexpr int UPT = UPRE ? (16 * TG * RMAX + NT - 1) / NT : 1;
-  constexpr int SMEM = NS * STAGE > PART + F * RMAX * 2 ? NS * STAGE : PART + F * RMAX * 2;
+  constexpr bool BT = UPRE || XR > 16;             // B^T in LDS (below, B as it lies in memory is 0.1 us faster)
+  constexpr int BP = F + 2;                        // its row pitch: a rank's features contiguous
+  constexpr int EPI = PART + RMAX * BP * 2;
+  constexpr int SMEM = NS * STAGE > EPI ? NS * STAGE : EPI;
   static_assert(NS >= 3 && CPW * (NS - 2) < 64, "copies in flight fit the wait counter");
   static_assert(SMEM <= 160 * 1024, "LDS budget");
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
@@ -177,7 +180,7 @@ __global__ __launch_bounds__(512) void lora_fwd_skinny_ks_kernel(const u16* __re
   }
   copy_barrier<0>();   // the trailing copies (zeros) have landed before the LDS is reused
   float* part = reinterpret_cast<float*>(smem);    // [KQ][PR][TP]
-  u16* Bs = reinterpret_cast<u16*>(smem + PART);   // [jn][r]
+  u16* Bt = reinterpret_cast<u16*>(smem + PART);   // B^T of the workgroup's features [r][BP], or B [jn][r]
 #pragma unroll
   for (int a = 0; a < GPW; ++a) {
     const int rg = rw + RW * a;
@@ -188,10 +191,22 @@ __global__ __launch_bounds__(512) void lora_fwd_skinny_ks_kernel(const u16* __re
         for (int j = 0; j < 4; ++j) part[(kq * PR + 16 * rg + 4 * g + j) * TP + 16 * tg + c16] = acc[a][tg][j];
     }
   }
+  // element 8 q of chunk q is B row 8 q / r, column 8 q % r; the quotient comes
+  // from a float product that stays at least 0.5/r away from an integer
+  const float rinv = 1.0f / (float)r;
 #pragma unroll
   for (int i = 0; i < BCH; ++i) {
     const int q = tid + i * NT;
-    if (q < nch) reinterpret_cast<int4v*>(Bs)[q] = bv[i];
+    if (q < nch && !BT) reinterpret_cast<int4v*>(Bt)[q] = bv[i];
+    if (q < nch && BT) {
+      const int f0 = (int)(((float)(8 * q) + 0.5f) * rinv);
+      int f = f0, t = 8 * q - f0 * r;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        Bt[t * BP + f] = (u16)((uint32_t)bv[i][e >> 1] >> (16 * (e & 1)));
+        if (++t == r) { t = 0; ++f; }
+      }
+    }
   }
   if (UPRE) {
 #pragma unroll
@@ -212,25 +227,43 @@ __global__ __launch_bounds__(512) void lora_fwd_skinny_ks_kernel(const u16* __re
     }
     __syncthreads();
   }
-  for (int e = tid; e < m * (F / 2); e += NT) {    // two features of one token
+  // Two features of TT tokens (i, i + XR / TT, ...) per thread, as many tokens as
+  // leave every thread work: per rank one read of B^T, contiguous over the lanes,
+  // and TT of U, shared by the lanes of a token.  (One token per thread with B as
+  // [feature][rank] read each value of B in as many LDS passes as lanes hit its
+  // bank, 32 at rank 64: 2 x 13824 x 64 x 1024, r = 64, 99 us against 33.)
+  constexpr int TW = XR * (F / 2) / NT;
+  constexpr int TT = TW >= 4 ? 4 : (TW >= 2 ? 2 : 1), TI = XR / TT;
+  for (int e = tid; e < TI * (F / 2); e += NT) {
     const int i = e / (F / 2), f = 2 * (e - i * (F / 2));
-    if (f >= jn) continue;
-    float y0 = part[f * TP + i], y1 = part[(f + 1) * TP + i];
+    if (f >= jn || i >= m) continue;
+    float y[TT][2], d[TT][2];
 #pragma unroll
-    for (int q = 1; q < KQ; ++q) {
-      y0 += part[(q * PR + f) * TP + i];
-      y1 += part[(q * PR + f + 1) * TP + i];
+    for (int x = 0; x < TT; ++x) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        y[x][h] = part[(f + h) * TP + i + TI * x];
+#pragma unroll
+        for (int q = 1; q < KQ; ++q) y[x][h] += part[(q * PR + f + h) * TP + i + TI * x];
+        d[x][h] = 0.f;
+      }
     }
-    float d0 = 0.f, d1 = 0.f;
     for (int t = 0; t < r; ++t) {
-      const float u = part[(F + t) * TP + i];
-      d0 += u * bf16_to_f32(Bs[f * r + t]);
-      d1 += u * bf16_to_f32(Bs[(f + 1) * r + t]);
+      const uint32_t b2 = BT ? *reinterpret_cast<const uint32_t*>(Bt + t * BP + f)
+                             : (uint32_t)Bt[f * r + t] | ((uint32_t)Bt[(f + 1) * r + t] << 16);
+      const float b0 = bf16_to_f32((u16)b2), b1 = bf16_to_f32((u16)(b2 >> 16));
+#pragma unroll
+      for (int x = 0; x < TT; ++x) {
+        const float u = part[(F + t) * TP + i + TI * x];
+        d[x][0] += u * b0;
+        d[x][1] += u * b1;
+      }
     }
-    y0 += s * d0;
-    y1 += s * d1;
-    *reinterpret_cast<uint32_t*>(Y + (size_t)i * n + n0 + f) =
-        (uint32_t)f32_to_bf16(y0) | ((uint32_t)f32_to_bf16(y1) << 16);
+#pragma unroll
+    for (int x = 0; x < TT; ++x)
+      if (i + TI * x < m)
+        *reinterpret_cast<uint32_t*>(Y + (size_t)(i + TI * x) * n + n0 + f) =
+            (uint32_t)f32_to_bf16(y[x][0] + s * d[x][0]) | ((uint32_t)f32_to_bf16(y[x][1] + s * d[x][1]) << 16);
   }
 }
 
