@@ -186,6 +186,15 @@ def test_group_suites_reach_every_plannable_kernel(lora):
     assert not missing, missing
 
 
+@pytest.mark.parametrize("m, tpw", [(1000, 8), (1366, 16), (2731, 32)])
+def test_grouped_u_pass_counts_the_tokens_of_all_members(lora, m, tpw):
+    """Tokens per workgroup of a group's one U pass: the most that still gives
+    every compute unit a workgroup, over the members together."""
+    u = lora.lora_linear_plan("group_fwd", m, [4096] * 3, 4096, 32)[0]
+    assert u["kernel"] == f"lora::lora_u_kernel<32, {tpw}, false>"
+    assert u["grid"] == 3 * -(-m // tpw)
+
+
 def test_ragged_n_avoids_the_register_staged_256_tile(lora):
     """n not a multiple of 64 on a shape whose dX would take the 256 x 256 tile:
     the 128 x 256 tile without the FULL loads serves it."""
