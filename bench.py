@@ -38,6 +38,7 @@ PEAK_BF16_TFLOPS = 2500.0    # MI355X dense bf16 matrix-core peak
 PEAK_HBM_GBS = 8000.0        # MI355X HBM3E
 MALL_BYTES = 256 << 20       # Infinity Cache
 KERNEL_SOURCES = ["paper_2403_11366_amd/csrc/lora_fwd.hip", "paper_2403_11366_amd/csrc/lora_fwd_ks.hpp",
+                  "paper_2403_11366_amd/csrc/lora_fwd_reg.hpp",
                   "paper_2403_11366_amd/csrc/lora_device.hpp",
                   "paper_2403_11366_amd/csrc/lora_plan.hpp", "paper_2403_11366_amd/csrc/lora_launch.hpp"]
 

@@ -14,6 +14,8 @@
 //                       mask applied; for a group, of every projection in one
 //                       launch), followed by a GEMM tile without U columns.
 //   lora_fwd_skinny_ks_kernel (lora_fwd_skinny.hip)  few tokens.
+//   lora_fwd_reg_kernel (lora_fwd_reg.hpp)  128 x 128 tiles of few stages, staged
+//                       in registers, two workgroups to a compute unit.
 // A launch covers the output columns from n_begin on (plan_gemm_split);
 // the launch whose range starts at column 0 writes U.
 //
@@ -32,6 +34,7 @@
 
 #include "lora_device.hpp"
 #include "lora_fwd_ks.hpp"
+#include "lora_fwd_reg.hpp"
 #include "lora_launch.hpp"
 #include "lora_plan.hpp"
 
@@ -874,6 +877,27 @@ static hipError_t run_fwd_launch(const Launch& L, const FwdArgs& a, const FwdGro
     });
   }
   if (L.id == K_FWD_SKINNY) return launch_fwd_skinny(L, a, grp, st);
+  if (L.id == K_FWD_REG) {
+    return with_int<16, 32, 64>(L.rp, [&](auto rc) {
+      return with_bool(L.grp, [&](auto gc) {
+        return with_bool(L.upre, [&](auto uc) {
+          return with_bool(L.full, [&](auto fc) {
+            constexpr int RP = decltype(rc)::value;
+            constexpr bool G = decltype(gc)::value, UP = decltype(uc)::value, F = decltype(fc)::value;
+            // U from the pass: single projections beyond rank 16, and under dropout (k a multiple of 64)
+            if constexpr (G ? UP : (UP ? RP == 16 && !F : RP != 16)) {
+              return hipErrorInvalidValue;
+            } else {
+              hipLaunchKernelGGL((lora_fwd_reg_kernel<128, 128, 2, 2, RP, G, UP, F>), grid, block, 0, st, a.X, a.W,
+                                 a.A, a.B, a.Y, a.U, (int)a.m, (int)a.n, (int)a.k, (int)a.r, a.s, L.tiles_m,
+                                 L.tiles_n, (int)L.col_begin, grp);
+              return hipGetLastError();
+            }
+          });
+        });
+      });
+    });
+  }
   if (L.id != K_FWD && L.id != K_FWD_PAIR) return hipErrorInvalidValue;
   // U comes from the tile only at rank 16 and below the 256 x 256 tile, 128 x
   // 192 serves single projections, and 128 x 256 at rank 16 is K_FWD_KS's.

@@ -17,9 +17,11 @@ inline int64_t pad_tokens(int64_t m) { return (m + 63) / 64 * 64; }
 // Output tiles of the two large GEMMs (tokens x features): 256x256 runs 8
 // waves (two per SIMD) as 2 x 4 waves of 128 x 64, the others 8 waves that
 // split k.  Forward only: 128x128 shared by a pair of workgroups of 64 tokens
-// each.  dX only: 64x128 and 64x64.
+// each, and 128x128 staged in registers by four waves, two workgroups to a
+// compute unit (TILE_REG).  dX only: 64x128 and 64x64.
 enum GemmTile {
-  TILE_256x256 = 0, TILE_128x256 = 1, TILE_128x128 = 2, TILE_128x192 = 3, TILE_PAIR = 4, TILE_64x128 = 5, TILE_64x64 = 6
+  TILE_256x256 = 0, TILE_128x256 = 1, TILE_128x128 = 2, TILE_128x192 = 3, TILE_PAIR = 4, TILE_64x128 = 5, TILE_64x64 = 6,
+  TILE_REG = 7
 };
 
 // A candidate tile: the output area a workgroup computes, and the workgroup's

@@ -27,6 +27,7 @@ enum KernelId : int {
   K_MASK = 9,      // lora_keep_mask_kernel: the dropout keep mask from the counter-based generator
   K_FWD_PAIR = 11,     // lora_fwd_pair_ks_kernel<RP, GRP, KFULL, UPRE>: 128 x 128 tiles, two workgroups each
   K_FWD_SKINNY = 10,   // lora_fwd_skinny_ks_kernel<XR, F, AR, UPRE>: forward of few tokens
+  K_FWD_REG = 12,      // lora_fwd_reg_kernel<128, 128, 2, 2, RP, GRP, UPRE, KFULL>: two workgroups to a compute unit
 };
 
 // One kernel launch.  Fields a kernel does not use stay zero / false.
@@ -155,12 +156,13 @@ inline Plan plan_fwd_skinny(int count, const int64_t* n, int64_t m, int64_t k, i
 // would be recomputed by every output tile), on the 256 x 256 tile (where
 // recomputing rank 16 in every tile costs more than the pass: 7B up_proj
 // forward 387 -> 371 us), and under dropout (drop: the pass applies the keep
-// mask, and the GEMM then runs exactly as without dropout); otherwise the tile
-// computes it.  For a group, tiles_n is the summed column tiles.
+// mask, and the GEMM then runs exactly as without dropout); otherwise, and for
+// a group on the register-staged tile, the tile computes it.  For a group,
+// tiles_n is the summed column tiles.
 inline void plan_fwd_part(Plan& p, GemmTile t, int64_t m, int64_t k, int64_t r, int64_t cb, int64_t ce,
                           bool first, bool drop, bool grp, int count, int tiles_n) {
   const bool kfull = k % 64 == 0;
-  const bool upre = drop || fwd_rank(r) >= 32 || t == TILE_256x256;
+  const bool upre = drop || t == TILE_256x256 || (fwd_rank(r) >= 32 && !(t == TILE_REG && grp));
   if (upre && first) p.add(upass_launch(count, m, r, drop));
   Launch x = gemm_launch(K_FWD, t, m, cb, ce, tiles_n);
   x.grp = grp;
@@ -180,6 +182,9 @@ inline void plan_fwd_part(Plan& p, GemmTile t, int64_t m, int64_t k, int64_t r, 
   } else if (t == TILE_PAIR) {
     x.id = K_FWD_PAIR;
     x.grid *= 2;
+  } else if (t == TILE_REG) {
+    x.id = K_FWD_REG;
+    x.block = 256;
   } else if (t == TILE_256x256) {
     x.dma = true;
   } else {
@@ -188,25 +193,84 @@ inline void plan_fwd_part(Plan& p, GemmTile t, int64_t m, int64_t k, int64_t r, 
   p.add(x);
 }
 
+// Estimated GPU time of the forward's kernels in us, for the choice between the
+// turn-taking and few-token kernels on one side and the register-staged tile on
+// the other.  A launch takes rounds of 256 workgroups (two half rounds of the
+// register-staged tile run together) of a fixed part -- the first stages from
+// memory, the exchange of sums, the epilogue, more of it beyond rank 16 -- and
+// a part per 64-wide stage, where rows lie unaligned (k no multiple of 64) a
+// longer one.  Fitted to 1900 calls drawn over the supported range up to k =
+// 2048, weights read from memory: 6 to 9% standard error, 10 to 13 unaligned.
+struct FwdTime { double fixed, wide[2], stage[2]; };   // wide: added at padded ranks 32, 64; stage: aligned, unaligned
+inline FwdTime fwd_tile_time(const Launch& x) {
+  if (x.id == K_FWD_PAIR) return {4.5, {0, 0.6}, {0.37, 0.43}};
+  if (x.bm == 256) return {11, {1, 1.8}, {0.85, 0.95}};
+  if (x.bn == 256) return {8.4, {2.5, 3.3}, {0.68, 0.90}};
+  if (x.bn == 192) return {7, {1.6, 2.4}, {0.58, 0.73}};
+  return {6, {0.1, 1}, {0.495, 0.58}};
+}
+inline double fwd_time(const Plan& p, int64_t k, int64_t r) {
+  const double stages = (double)((k + 63) / 64);
+  const int rag = k % 64 != 0, wide = fwd_rank(r) / 32;   // 0, 1, 2
+  double t = 0;
+  for (int i = 0; i < p.count; ++i) {
+    const Launch& x = p.l[i];
+    const double rounds = (double)((x.grid + 255) / 256);
+    if (x.id == K_UPASS) {
+      t += 2.3 + rounds * stages * (x.tpw + x.rp) * 0.0013;
+    } else if (x.id == K_FWD_SKINNY) {
+      const double ranks = (wide == 0 ? 0.45 : 0.85) * (double)r / 16;
+      t += rag ? rounds * (3.25 + ranks + stages * (0.0052 * x.bn + 0.00175 * x.bm))
+               : 0.24 + rounds * (3.28 + ranks + stages * (0.00474 * x.bn + 0.00117 * x.bm));
+    } else if (x.id == K_FWD_REG) {
+      const double both = (double)((x.grid + 255) / 256 / 2), one = rounds - 2 * both;
+      const double w = x.upre ? (wide == 0 ? 0 : (wide == 1 ? 0.8 : 2)) : (wide == 0 ? 0 : (wide == 1 ? 1 : 3.6));
+      const double f = x.upre || wide == 0 ? 1 : (wide == 1 ? 1.15 : 1.2);   // A rows and U products beside W
+      t += 2 + both * (3.7 + w + (rag ? 1.34 : 1.04) * f * stages) + one * (1.9 + 0.6 * w + (rag ? 0.71 : 0.64) * f * stages);
+    } else {
+      const FwdTime c = fwd_tile_time(x);
+      t += rounds * (c.fixed + (wide ? c.wide[wide - 1] : 0) + stages * c.stage[rag]);
+    }
+  }
+  return t;
+}
+// The plan p, or the register-staged tile where that is estimated at least 3%
+// faster.  Measured with the other kernels (forward calls, this tile second):
+// 5912 x 1240 x 512, r = 20 23.1 and 21.2 us; 842 x (2 x 11008) x 928, r = 4 76.6
+// and 61.4; 1735 x (2 x 5120) x 512, r = 32 50.7 and 39.2; 3663 x (512, 128, 128) x
+// 512, r = 32 18.7 and 13.9.  The few-token kernel keeps calls deeper than
+// kRegDepth, where its one pass over W wins even over wide outputs (5 x (2 x 13824)
+// x 13824 133 and 180; 39 x (3 x 13824) x 512, r = 32 26.5 and 18.2).
+constexpr int64_t kRegDepth = 1536;
+inline Plan faster_fwd(const Plan& p, const Plan& reg, int64_t k, int64_t r) {
+  if (p.l[p.count - 1].id == K_FWD_SKINNY && k > kRegDepth) return p;
+  return fwd_time(reg, k, r) < 0.97 * fwd_time(p, k, r) ? reg : p;
+}
+
 // lora_linear_fwd / lora_linear_fwd_dropout (the same tiles and column split;
 // under dropout the U pass applies the mask).
-inline Plan plan_fwd(int64_t m, int64_t n, int64_t k, int64_t r, bool drop) {
-  if (fwd_skinny(1, &n, m)) return plan_fwd_skinny(1, &n, m, k, r, drop);
+inline Plan plan_fwd_tiles(int64_t m, int64_t n, int64_t k, int64_t r, bool drop, bool reg) {
+  if (!reg && fwd_skinny(1, &n, m)) return plan_fwd_skinny(1, &n, m, k, r, drop);
   Plan p;
-  const GemmSplit s = plan_gemm_split(kFwdTiles, m, n, k >= kMidTileDepth ? TILES_MID : TILES_BASE);
+  const GemmSplit s = reg ? GemmSplit{TILE_REG, TILE_REG, n}
+                          : plan_gemm_split(kFwdTiles, m, n, k >= kMidTileDepth ? TILES_MID : TILES_BASE);
   plan_fwd_part(p, s.t1, m, k, r, 0, s.n1, true, drop, false, 1, -1);
   if (s.n1 < n) plan_fwd_part(p, s.t2, m, k, r, s.n1, n, false, drop, false, 1, -1);
   return p;
 }
+inline Plan plan_fwd(int64_t m, int64_t n, int64_t k, int64_t r, bool drop) {
+  const Plan p = plan_fwd_tiles(m, n, k, r, false, false), reg = plan_fwd_tiles(m, n, k, r, false, true);
+  const Plan best = faster_fwd(p, reg, k, r);
+  return drop ? plan_fwd_tiles(m, n, k, r, true, best.l[best.count - 1].id == K_FWD_REG) : best;
+}
 
-// lora_linear_group_fwd: one launch over the output tiles of all members, the
-// tile chosen for m x (sum of n).  A group of one is the single projection.
-inline Plan plan_group_fwd(int count, const int64_t* n, int64_t m, int64_t k, int64_t r) {
-  if (count == 1) return plan_fwd(m, n[0], k, r, false);
-  if (fwd_skinny(count, n, m)) return plan_fwd_skinny(count, n, m, k, r, false);
+// lora_linear_group_fwd: one GEMM launch over the output tiles of all members,
+// the tile chosen for m x (sum of n).  A group of one is the single projection.
+inline Plan plan_group_fwd_tiles(int count, const int64_t* n, int64_t m, int64_t k, int64_t r, bool reg) {
+  if (!reg && fwd_skinny(count, n, m)) return plan_fwd_skinny(count, n, m, k, r, false);
   int64_t ntot = 0;
   for (int g = 0; g < count; ++g) ntot += n[g];
-  const GemmTile t = cheapest_tile(kFwdTiles, m, ntot, TILES_BASE).t;
+  const GemmTile t = reg ? TILE_REG : cheapest_tile(kFwdTiles, m, ntot, TILES_BASE).t;
   int bm, bn, wm, wn;
   tile_dims(t, bm, bn, wm, wn);
   int tiles_n = 0;
@@ -214,6 +278,10 @@ inline Plan plan_group_fwd(int count, const int64_t* n, int64_t m, int64_t k, in
   Plan p;
   plan_fwd_part(p, t, m, k, r, 0, 0, true, false, true, count, tiles_n);
   return p;
+}
+inline Plan plan_group_fwd(int count, const int64_t* n, int64_t m, int64_t k, int64_t r) {
+  if (count == 1) return plan_fwd(m, n[0], k, r, false);
+  return faster_fwd(plan_group_fwd_tiles(count, n, m, k, r, false), plan_group_fwd_tiles(count, n, m, k, r, true), k, r);
 }
 
 // dX GEMM launch over columns [cb, ce).  FULL (no bound checks on the copies)
@@ -410,6 +478,10 @@ inline void launch_name(const Launch& x, char* buf, size_t len) {
     case K_MASK: snprintf(buf, len, "lora::lora_keep_mask_kernel"); break;
     case K_FWD_PAIR:
       snprintf(buf, len, "lora::lora_fwd_pair_ks_kernel<%d, %s, %s, %s>", x.rp, b(x.grp), b(x.full), b(x.upre));
+      break;
+    case K_FWD_REG:
+      snprintf(buf, len, "lora::lora_fwd_reg_kernel<%d, %d, %d, %d, %d, %s, %s, %s>", x.bm, x.bn, x.wm, x.wn, x.rp,
+               b(x.grp), b(x.upre), b(x.full));
       break;
     case K_FWD_SKINNY:
       snprintf(buf, len, "lora::lora_fwd_skinny_ks_kernel<%d, %d, %d, %s>", x.bm, x.bn, x.rp, b(x.upre));

@@ -79,7 +79,10 @@ SHAPES = [Shape("drop_tiny", 256, 512, 512, 8, 16.0, 21), Shape("drop_ragged", 2
 ] + [Shape(f"drop_dx64_r{r}", 7, 136, 64, r, 2.0 * r, 130 + r) for r in (24, 64)] + [
     # the masked 128 x 128 dX tiles
     Shape("drop_dx128m_r33", 300, 64, 64, 33, 66.0, 210), Shape("drop_dx128m_r24f", 300, 64, 1024, 24, 48.0, 211),
-    Shape("drop_dx128m_r33f", 300, 64, 1024, 33, 66.0, 212), Shape("drop_dx128m_r64f", 300, 64, 1024, 64, 128.0, 213)]
+    Shape("drop_dx128m_r33f", 300, 64, 1024, 33, 66.0, 212), Shape("drop_dx128m_r64f", 300, 64, 1024, 64, 128.0, 213),
+    # the register-staged forward tiles reading U back: 128 x 128, and the k-split one over several rounds
+    Shape("drop_reg", 1100, 13824, 64, 8, 16.0, 214), Shape("drop_reg_r24", 300, 11008, 192, 24, 48.0, 215),
+    Shape("drop_ks_staged", 1538, 18944, 384, 8, 16.0, 216)]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)

@@ -110,6 +110,15 @@ CASES = [  # (ns, m, k, r, alpha)
         ([64, 64], 2048, 2304, 24), ([64, 64], 2048, 2304, 33), ([64, 64], 2048, 2304, 64),
         ([136, 264, 72], 2048, 2304, 24), ([136, 264, 72], 2048, 2304, 33), ([136, 264, 72], 2048, 2304, 64),
         ([64, 64], 3000, 4096, 24), ([64, 64], 3000, 4096, 33), ([64, 64], 3000, 4096, 64))
+] + [
+    # the grouped forward tiles of more stages than the register-staged tile takes, every padded rank, with and
+    # without whole stages
+    (ns, m, k, r, 2.0 * r) for ns, m, k, r in (
+        ([4096] * 3, 130, 1032, 1), ([4096] * 3, 130, 2056, 24), ([4096] * 3, 130, 1536, 24), ([4096] * 3, 130, 1032, 33),
+        ([4096] * 3, 130, 1024, 33), ([13824] * 2, 130, 520, 1), ([13824] * 2, 130, 1032, 24), ([13824] * 2, 130, 1024, 24),
+        ([13824] * 2, 130, 520, 33), ([13824] * 2, 130, 1024, 33), ([4096] * 3, 1100, 136, 1), ([4096] * 3, 1100, 256, 1),
+        ([4096] * 3, 1100, 72, 24), ([4096] * 3, 1100, 256, 24), ([4096] * 3, 1100, 64, 33), ([64, 64], 300, 520, 24),
+        ([64, 64], 300, 200, 33), ([2048] * 2, 4096, 136, 1))
 ]
 
 

@@ -93,6 +93,18 @@ RAGGED = [
                                       (600, 2056, 1032, 24), (300, 64, 1024, 24), (300, 64, 1024, 64),
                                       (70, 72, 11008, 3), (70, 136, 11008, 24), (70, 72, 11008, 33),
                                       (70, 72, 11008, 64)])
+] + [
+    # the register-staged 128 x 128 tile: one to five stages (every tail of its paired loop) and a partial last one,
+    # U beside W and from the U pass
+    Shape("reg", 1100, 13824, k, r, 2.0 * r, 220 + i)
+    for i, (k, r) in enumerate([(64, 8), (128, 13), (192, 8), (256, 16), (320, 3), (72, 5), (200, 16), (264, 24), (256, 64)])
+] + [
+    # tiles that calls of few stages no longer reach: 128 x 256 and 256 x 256 with U from the pass, the register-staged
+    # k-split tile over several rounds
+    Shape("stages", m, n, k, r, 2.0 * r, 230 + i)
+    for i, (m, n, k, r) in enumerate([(300, 11008, 520, 24), (300, 11008, 1024, 33), (1100, 11008, 72, 24),
+                                      (1100, 11008, 64, 24), (8200, 1024, 72, 33), (8200, 1024, 512, 1),
+                                      (1538, 18944, 384, 8), (1538, 18944, 448, 13)])
 ]
 
 

@@ -186,6 +186,26 @@ def test_group_suites_reach_every_plannable_kernel(lora):
     assert not missing, missing
 
 
+@pytest.mark.parametrize("op, m, ns, k, r, kernel", [
+    # few stages: two register-staged tiles to a compute unit, U beside W (a single projection's from the pass)
+    ("group_fwd", 3663, [512, 128, 128], 512, 32, "lora_fwd_reg_kernel<128, 128, 2, 2, 32, true, false, true>"),
+    ("group_fwd", 1735, [5120, 5120], 512, 32, "lora_fwd_reg_kernel<128, 128, 2, 2, 32, true, false, true>"),
+    ("fwd", 678, 10816, 848, 16, "lora_fwd_reg_kernel<128, 128, 2, 2, 16, false, false, false>"),
+    ("fwd", 5912, 1240, 512, 20, "lora_fwd_reg_kernel<128, 128, 2, 2, 32, false, true, true>"),
+    # few tokens over outputs too wide for the few-token kernel
+    ("group_fwd", 64, [13824, 13824], 1024, 64, "lora_fwd_reg_kernel<128, 128, 2, 2, 64, true, false, true>"),
+    ("group_fwd", 39, [13824] * 3, 512, 32, "lora_fwd_reg_kernel<128, 128, 2, 2, 32, true, false, true>"),
+    ("fwd", 64, 32000, 1024, 16, "lora_fwd_reg_kernel<128, 128, 2, 2, 16, false, false, true>"),
+    # and the calls that stay: the few-token kernel's one pass over W, the turn-taking tiles' many stages
+    ("fwd", 4, 4096, 4096, 8, "lora_fwd_skinny_ks_kernel<16, 16, 16, false>"),
+    ("group_fwd", 5, [13824, 13824], 13824, 8, "lora_fwd_skinny_ks_kernel<16, 64, 16, false>"),
+    ("fwd", 2048, 4096, 4096, 8, "lora_fwd_ks_kernel<false, true, true, false>"),
+    ("group_fwd", 4096, [5120] * 3, 5120, 8, "lora_fwd_kernel<256, 256, 2, 4, 16, true, true, true, true>")])
+def test_forward_kernel_of_measured_calls(lora, op, m, ns, k, r, kernel):
+    """The forward kernel each of these calls was measured to be fastest on."""
+    assert lora.lora_linear_plan(op, m, ns, k, r)[-1]["kernel"] == "lora::" + kernel
+
+
 @pytest.mark.parametrize("m, tpw", [(1000, 8), (1366, 16), (2731, 32)])
 def test_grouped_u_pass_counts_the_tokens_of_all_members(lora, m, tpw):
     """Tokens per workgroup of a group's one U pass: the most that still gives
