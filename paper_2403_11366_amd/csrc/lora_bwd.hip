@@ -975,11 +975,20 @@ __device__ __forceinline__ void stage_rank_operands(const u16* dU2, const u16* A
 // 4104 x 3208, r = 12: 83 -> 71; 2000 x 512 x 4096 24.8 -> 25.6 (the exchange;
 // even at n = 1024).  The reads come before the copies: 5 us slower the other
 // way round at 2048 x 4096 x 4096.
-template <int BM, int BN, int RP, bool DROP, bool GRP, bool FULL>
+//
+// ROWS (128 x 256): the wave rows split the tokens instead, 64 each, and multiply
+// whole stages.  Nothing is exchanged after the loop (256 KB through LDS, about
+// a microsecond a tile), for a third more LDS reads a stage.  Measured (whole
+// backward calls, 1350 drawn; k-split time over this one's): 1.06 to 1.09 up to 8
+// stages, 1.05 to 1.08 at 12, 1.03 to 1.07 at 16, 1.02 to 1.05 at 24, 1.00 at 33
+// to 64, 0.97 to 1.00 above.
+template <int BM, int BN, int RP, bool DROP, bool GRP, bool FULL, bool ROWS>
 __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, int m0, int l0, char* smem) {
   constexpr int NT = 512, WN = BM == 128 ? 4 : 2;   // waves along the columns
-  constexpr int NK = 8 / WN, KP = NK / 2;           // n shares, 64-wide n pieces per stage
-  constexpr int NA = BN / WN / 16, NB = BM / 16;    // 16-column and 16-token fragments per wave
+  constexpr int NK = ROWS ? 1 : 8 / WN;             // n shares
+  constexpr int KP = ROWS ? 1 : NK / 2;             // 64-wide n pieces per stage
+  constexpr int NKK = ROWS ? 2 : 1;                 // 32-wide n halves a wave multiplies per stage
+  constexpr int NA = BN / WN / 16, NB = (ROWS ? 64 : BM) / 16;   // 16-column and 16-token fragments per wave
   constexpr int NOB = NB / NK;                      // token fragments a wave finishes
   constexpr int PIECE = BM * 128 + 64 * BN * 2, STAGE = KP * PIECE;
   constexpr int NBUF = dx_ks_bufs(BM, BN);
@@ -987,10 +996,12 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
   constexpr int CPR = BN / 8;                      // 16-byte chunks per W tile row
   constexpr int NCOPY = KP * (BM / 64 + BN / 64);  // copies per wave and stage
   static_assert(BM == 128 ? BN == 128 || BN == 192 || BN == 256 : BM == 64 && (BN == 64 || BN == 128), "tile shapes");
+  static_assert(!ROWS || BM == 128, "wave rows of 64 tokens");
   const int m = p.m, n = p.n, k = p.k, r = p.r;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = uniform(tid >> 6);
-  const int wk = wave / WN, wn = wave % WN;
+  const int wk = ROWS ? 0 : wave / WN, wn = wave % WN;
+  const int i0 = ROWS ? 64 * (wave / WN) : 0;       // the wave's first token in the tile
   const bool second = wave >= 4;                    // the waves that run one slot behind
   const int g = lane >> 4, c16 = lane & 15;
   const uint32_t wrow = (uint32_t)k * 2, urow = (uint32_t)KS2 * 2;
@@ -1076,8 +1087,8 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
   for (int a = 0; a < NA; ++a)
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-  short8 fy[NB];
-  short4v wl[NA], wh[NA];
+  short8 fy[NKK][NB];
+  short4v wl[NKK * NA], wh[NKK * NA];
   auto slot_end = [&]() LORA_INLINE {
     asm volatile("s_barrier" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
@@ -1103,17 +1114,28 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
     if constexpr (MODE == 0) advance();
     const char* Ys = smem + rb + (wk >> 1) * PIECE;
 #pragma unroll
-    for (int b = 0; b < NB; ++b) fy[b] = kc_read(Ys, 16 * b + c16, 4 * (wk & 1) + g);
+    for (int kk = 0; kk < NKK; ++kk)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) fy[kk][b] = kc_read(Ys, i0 + 16 * b + c16, 4 * ((wk & 1) + kk) + g);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int a = 0; a < NA; ++a) {
       ds_read_tr_b64_asm<0>(wl[a], wa[a] + (uint32_t)rb);
       ds_read_tr_b64_asm<4 * BN * 2>(wh[a], wa[a] + (uint32_t)rb);
+      if constexpr (ROWS) {
+        ds_read_tr_b64_asm<32 * BN * 2>(wl[NA + a], wa[a] + (uint32_t)rb);
+        ds_read_tr_b64_asm<36 * BN * 2>(wh[NA + a], wa[a] + (uint32_t)rb);
+      }
     }
     if constexpr (MODE == 0) copy_main(wb);
     if constexpr (MODE == 1) copy_slab(kb + NBUF - 1, wb);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (NA == 4)
+    if constexpr (NA == 4 && ROWS)
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : "+v"(wl[0]), "+v"(wh[0]), "+v"(wl[1]), "+v"(wh[1]), "+v"(wl[2]), "+v"(wh[2]), "+v"(wl[3]),
+                     "+v"(wh[3]), "+v"(wl[4]), "+v"(wh[4]), "+v"(wl[5]), "+v"(wh[5]), "+v"(wl[6]), "+v"(wh[6]),
+                     "+v"(wl[7]), "+v"(wh[7]));
+    else if constexpr (NA == 4)
       asm volatile("s_waitcnt lgkmcnt(0)"
                    : "+v"(wl[0]), "+v"(wh[0]), "+v"(wl[1]), "+v"(wh[1]), "+v"(wl[2]), "+v"(wh[2]), "+v"(wl[3]),
                      "+v"(wh[3]));
@@ -1122,15 +1144,17 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
                    : "+v"(wl[0]), "+v"(wh[0]), "+v"(wl[1]), "+v"(wh[1]), "+v"(wl[2]), "+v"(wh[2]));
     else
       asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(wl[0]), "+v"(wh[0]), "+v"(wl[1]), "+v"(wh[1]));
-    static_assert(NA >= 2 && NA <= 4, "fragments of the wait");
+    static_assert(NA >= 2 && NA <= 4 && (!ROWS || NA == 4), "fragments of the wait");
     if (second) wait_vmcnt<MODE == 2 ? 0 : (NBUF - 2) * NCOPY>();
     slot_end();
 #pragma unroll
-    for (int a = 0; a < NA; ++a) {
-      const short8 w8 = join4(wl[a], wh[a]);
+    for (int kk = 0; kk < NKK; ++kk)
 #pragma unroll
-      for (int b = 0; b < NB; ++b) acc[a][b] = mfma16x16x32(w8, fy[b], acc[a][b]);
-    }
+      for (int a = 0; a < NA; ++a) {
+        const short8 w8 = join4(wl[kk * NA + a], wh[kk * NA + a]);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[a][b] = mfma16x16x32(w8, fy[kk][b], acc[a][b]);
+      }
     __builtin_amdgcn_sched_barrier(0);
     if (!second) wait_vmcnt<MODE == 2 ? 0 : (NBUF - 2) * NCOPY>();
     slot_end();
@@ -1147,8 +1171,9 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
   // Exchange: wave wk finishes its token fragments NOB wk .., moved to own[..][0
   // .. NOB - 1]; partial sums are added in n-share order.
   auto& own = acc;
-  floatx4* xin = reinterpret_cast<floatx4*>(smem) + (size_t)(NK == 2 ? wave : wn * 4 + wk) * NA * 4 * 64;   // to this wave
-  if constexpr (NK == 2) {   // (branches on wk: selects of every element cost a microsecond)
+  floatx4* xin = reinterpret_cast<floatx4*>(smem) + (size_t)(NK == 4 ? wn * 4 + wk : wave) * NA * 4 * 64;   // to this wave
+  if constexpr (ROWS) {   // the tile's sums are whole
+  } else if constexpr (NK == 2) {   // (branches on wk: selects of every element cost a microsecond)
     floatx4* dst = reinterpret_cast<floatx4*>(smem) + (size_t)(wave ^ 4) * NA * 4 * 64;
     if (wk == 0) {
 #pragma unroll
@@ -1183,7 +1208,7 @@ __device__ __forceinline__ void dx_ks_tile(const DxArgs& p, const DxGroup& grp, 
       for (int q = 1; q < 4; ++q) own[a][0] += xin[(q * NA + a) * 64 + lane];
     }
   }
-  const int i1 = 16 * NOB * wk;                     // the wave's first token in the tile
+  const int i1 = i0 + 16 * NOB * wk;                // the first token that the wave finishes
 
   if constexpr (GRP || DROP) {
     constexpr int UP = KS2 + 8;                    // Us row pitch in elements (16-byte multiple)
@@ -1528,7 +1553,26 @@ __global__ __launch_bounds__(512) void lora_bwd_dx_kernel(
   tile_coords(tiles_m, tiles_n, 8, (int)blockIdx.x, tm, tn);
   const DxArgs p{dY, W, dU2, A, keep, dX, m, n, k, r, mp, inv_keep};
   if constexpr (BM == 256) dx_big_tile<RP, GRP>(p, grp, tm * BM, l_begin + tn * BN, smem);
-  else dx_ks_tile<BM, BN, RP, DROP, GRP, FULL>(p, grp, tm * BM, l_begin + tn * BN, smem);
+  else dx_ks_tile<BM, BN, RP, DROP, GRP, FULL, false>(p, grp, tm * BM, l_begin + tn * BN, smem);
+  const int first = (int)blockIdx.x * 512 + (int)threadIdx.x, stride = (int)gridDim.x * 512;
+  if (GRP) {
+    for (int pq = 0; pq < grp.count; ++pq) finalize_partials(pick(grp.fin, pq), first, stride);
+  } else {
+    finalize_partials(fin, first, stride);
+  }
+}
+
+template <int BM, int BN, int WM, int WN, int RP, bool DROP, bool GRP, bool FULL>
+__global__ __launch_bounds__(512) void lora_bwd_rows_dx_kernel(
+    const u16* __restrict__ dY, const u16* __restrict__ W, const u16* __restrict__ dU2,
+    const u16* __restrict__ A, const uint8_t* __restrict__ keep, u16* __restrict__ dX, int m, int n, int k,
+    int r, int mp, float inv_keep, int tiles_m, int tiles_n, int l_begin, FinalizeArgs fin, DxGroup grp) {
+  static_assert(BM == 64 * WM && BN == 64 * WN && WM * WN == 8, "wave tiles of 64 x 64");
+  __shared__ __attribute__((aligned(1024))) char smem[dx_ks_smem(BM, BN)];
+  int tm, tn;
+  tile_coords(tiles_m, tiles_n, 8, (int)blockIdx.x, tm, tn);
+  const DxArgs p{dY, W, dU2, A, keep, dX, m, n, k, r, mp, inv_keep};
+  dx_ks_tile<BM, BN, RP, DROP, GRP, FULL, true>(p, grp, tm * BM, l_begin + tn * BN, smem);
   const int first = (int)blockIdx.x * 512 + (int)threadIdx.x, stride = (int)gridDim.x * 512;
   if (GRP) {
     for (int pq = 0; pq < grp.count; ++pq) finalize_partials(pick(grp.fin, pq), first, stride);
@@ -1853,6 +1897,27 @@ constexpr bool dx_instantiated() {
 static hipError_t run_dx(const Launch& L, const BwdArgs& a, const u16* dU2, int mp, const FinalizeArgs& fin,
                          const DxGroup& grp, hipStream_t st) {
   const dim3 grid((unsigned)L.grid), block((unsigned)L.block);
+  if (L.id == K_DX_ROWS) {
+    return with_int<16, 32, 48, 64>(L.rp, [&](auto rc) {
+      return with_bool(L.drop, [&](auto dr) {
+        return with_bool(L.grp, [&](auto gr) {
+          return with_bool(L.full, [&](auto fu) {
+            constexpr int RP = decltype(rc)::value;
+            constexpr bool DROP = decltype(dr)::value, GRP = decltype(gr)::value, FULL = decltype(fu)::value;
+            if constexpr (DROP && GRP) {
+              return hipErrorInvalidValue;
+            } else {
+              hipLaunchKernelGGL((lora_bwd_rows_dx_kernel<128, 256, 2, 4, RP, DROP, GRP, FULL>), grid, block, 0, st,
+                                 a.dY, a.W, dU2, a.A, a.keep, a.dX, (int)a.m, (int)a.n, (int)a.k, (int)a.r, mp,
+                                 a.inv_keep, L.tiles_m, L.tiles_n, (int)L.col_begin, L.finalize ? fin : FinalizeArgs{},
+                                 grp);
+              return hipGetLastError();
+            }
+          });
+        });
+      });
+    });
+  }
   return with_int<64, 65, 128, 192, 256, 257>(tile_code(L), [&](auto tc) {
     constexpr int T = decltype(tc)::value;
     constexpr int BM = T == 257 ? 256 : (T <= 65 ? 64 : 128), BN = T == 257 ? 256 : (T == 65 ? 128 : T);
@@ -1957,7 +2022,8 @@ hipError_t launch_bwd(const BwdArgs& a, hipStream_t st) {
         break;
       }
       case K_TOKRED: e = run_tokred(L, a, BL, st); break;
-      case K_DX: e = run_dx(L, a, dU2, (int)BL.mp, fin, none, st); break;
+      case K_DX:
+      case K_DX_ROWS: e = run_dx(L, a, dU2, (int)BL.mp, fin, none, st); break;
       default: break;
     }
     if (e != hipSuccess) return e;
@@ -2115,7 +2181,7 @@ hipError_t launch_bwd_group(const GroupBwdArgs& a, hipStream_t st) {
     } else if (L.id == K_TOKRED) {
       const BwdArgs b = member_args(L.member, GL);
       e = run_tokred(L, b, GL.L[L.member], st);
-    } else if (L.id == K_DX) {
+    } else if (L.id == K_DX || L.id == K_DX_ROWS) {
       e = run_dx(L, d, nullptr, (int)GL.L[0].mp, FinalizeArgs{}, L.finalize ? grp : rest, st);
     }
     if (e != hipSuccess) return e;

@@ -18,10 +18,11 @@ inline int64_t pad_tokens(int64_t m) { return (m + 63) / 64 * 64; }
 // waves (two per SIMD) as 2 x 4 waves of 128 x 64, the others 8 waves that
 // split k.  Forward only: 128x128 shared by a pair of workgroups of 64 tokens
 // each, and 128x128 staged in registers by four waves, two workgroups to a
-// compute unit (TILE_REG).  dX only: 64x128 and 64x64.
+// compute unit (TILE_REG).  dX only: 64x128 and 64x64, and 128x256 whose wave
+// rows split the tokens (TILE_ROWS).
 enum GemmTile {
   TILE_256x256 = 0, TILE_128x256 = 1, TILE_128x128 = 2, TILE_128x192 = 3, TILE_PAIR = 4, TILE_64x128 = 5, TILE_64x64 = 6,
-  TILE_REG = 7
+  TILE_REG = 7, TILE_ROWS = 8
 };
 
 // A candidate tile: the output area a workgroup computes, and the workgroup's
@@ -37,21 +38,33 @@ struct TileCost { GemmTile t; int bm, bn, wgs; double eff; };
 constexpr TileCost kFwdTiles[5] = {{TILE_256x256, 256, 256, 1, 1.0}, {TILE_128x256, 128, 256, 1, 0.8},
                                    {TILE_128x128, 128, 128, 1, 0.61}, {TILE_128x192, 128, 192, 1, 0.71},
                                    {TILE_PAIR, 128, 128, 2, 0.4}};
-// dX tiles (per 64-wide n stage: 1.39 us, 0.77, 0.48, 0.61, about 0.27, 0.16).
+// dX tiles (per 64-wide n stage with the chip full: 1.39 us, 0.77, 0.48, 0.61;
+// with W read from memory and the chip part full 1.17, 0.80, 0.50, 0.67, and
+// 0.39 and 0.28 of the 64-token tiles).
 constexpr TileCost kDxTiles[6] = {{TILE_256x256, 256, 256, 1, 1.0}, {TILE_128x256, 128, 256, 1, 0.9},
                                   {TILE_128x128, 128, 128, 1, 0.72}, {TILE_128x192, 128, 192, 1, 0.82},
-                                  {TILE_64x128, 64, 128, 1, 0.6},    {TILE_64x64, 64, 64, 1, 0.5}};
+                                  {TILE_64x128, 64, 128, 1, 0.44},   {TILE_64x64, 64, 64, 1, 0.33}};
+// Below kMidTileDepth contraction steps: 128x256 with nothing to exchange; it and
+// 256x256, which has nothing to exchange either, gain 8% on the others.
+constexpr TileCost kDxShallowTiles[5] = {{TILE_256x256, 256, 256, 1, 1.08}, {TILE_ROWS, 128, 256, 1, 0.97}, kDxTiles[2],
+                                         kDxTiles[4], kDxTiles[5]};
 // The tiles that have the dropout epilogue.
 constexpr TileCost kDxDropTiles[5] = {kDxTiles[1], kDxTiles[2], kDxTiles[3], kDxTiles[4], kDxTiles[5]};
+constexpr TileCost kDxDropShallowTiles[4] = {kDxShallowTiles[1], kDxTiles[2], kDxTiles[4], kDxTiles[5]};
 // Tiles a call may take beside 256x256, 128x256, 128x128 and pairs.  128x192
-// serves single projections of at least kMidTileDepth contraction steps (with
-// fewer stages a launch is mostly its fixed cost).  The 64-token tiles serve
-// calls of few tokens, where the larger ones leave compute units idle: up to
+// serves single projections of at least kMidTileDepth contraction steps, and
+// from there dX's 128x256 splits k instead of tokens (equal at 33 to 64 stages).
+// Measured with 128x192 open to all (500 drawn steps, the better plan of each
+// call): groups 1.7% forward and 1.0% backward, single projections below
+// kMidTileDepth 1.1% and 0.2%; groups have no kernel of it.  The 64-token tiles
+// serve calls of few tokens, where the larger ones leave compute units idle: up to
 // kFewTokens at any depth, up to kShortTokens from kShortDepth steps on.  (Whole
 // backward call with the best of them against 128x128: 130 x 4096 x 4096 38 ->
 // 29 us, 333 x 4096 x 4096 41 -> 36, 1024 x 4096 x 2048 54 -> 47, 256 x 512 x 512
 // 16 -> 13; 257 x 1024 x 4096, outside, 19.6 and 18.1; above 1024 tokens an
-// output of so few tiles has few columns.)
+// output of so few tiles has few columns.  Rounds of them past the first are no
+// longer cheap: 296 x 5120 x 11008, r = 8 77.6 us on one round of 128x256, 85.7
+// on two of 64x128.)
 constexpr int64_t kMidTileDepth = 3072, kFewTokens = 256, kShortTokens = 1024, kShortDepth = 2048;
 enum TileSet { TILES_BASE = 0, TILES_MID = 1, TILES_SHORT = 2 };
 inline bool tile_allowed(GemmTile t, int set) {

@@ -27,6 +27,7 @@ enum KernelId : int {
   K_MASK = 9,      // lora_keep_mask_kernel: the dropout keep mask from the counter-based generator
   K_FWD_PAIR = 11,     // lora_fwd_pair_ks_kernel<RP, GRP, KFULL, UPRE>: 128 x 128 tiles, two workgroups each
   K_FWD_SKINNY = 10,   // lora_fwd_skinny_ks_kernel<XR, F, AR, UPRE>: forward of few tokens
+  K_DX_ROWS = 13,      // lora_bwd_rows_dx_kernel<128, 256, 2, 4, RP, DROP, GRP, FULL>: dX of few stages
   K_FWD_REG = 12,      // lora_fwd_reg_kernel<128, 128, 2, 2, RP, GRP, UPRE, KFULL>: two workgroups to a compute unit
 };
 
@@ -69,6 +70,7 @@ inline int fwd_rank(int64_t r) { return r <= 16 ? 16 : (r <= 32 ? 32 : 64); }
 inline void tile_dims(GemmTile t, int& bm, int& bn, int& wm, int& wn) {
   switch (t) {
     case TILE_256x256: bm = 256; bn = 256; wm = 2; wn = 4; break;
+    case TILE_ROWS:
     case TILE_128x256: bm = 128; bn = 256; wm = 2; wn = 4; break;
     case TILE_128x192: bm = 128; bn = 192; wm = 2; wn = 2; break;
     case TILE_64x128: bm = 64; bn = 128; wm = 1; wn = 2; break;
@@ -286,18 +288,19 @@ inline Plan plan_group_fwd(int count, const int64_t* n, int64_t m, int64_t k, in
 
 // dX GEMM launch over columns [cb, ce).  FULL (no bound checks on the copies)
 // needs every n a multiple of 64 and whole column tiles.  The 256 x 256 tile
-// runs only FULL; otherwise the range takes the 128 x 256 tile.
-inline void plan_dx_part(Plan& p, GemmTile t, int64_t m, int rp, int64_t cb, int64_t ce, bool n_whole, bool drop,
-                         bool grp, bool finalize) {
+// runs only FULL; otherwise the range takes a 128 x 256 tile, of `depth`
+// contraction steps in all.
+inline void plan_dx_part(Plan& p, GemmTile t, int64_t m, int rp, int64_t depth, int64_t cb, int64_t ce, bool n_whole,
+                         bool drop, bool grp, bool finalize) {
   int bm, bn, wm, wn;
   tile_dims(t, bm, bn, wm, wn);
   bool full = n_whole && (ce - cb) % bn == 0;
   if (t == TILE_256x256 && !full) {
-    t = TILE_128x256;
+    t = depth < kMidTileDepth ? TILE_ROWS : TILE_128x256;
     tile_dims(t, bm, bn, wm, wn);
     full = n_whole && (ce - cb) % bn == 0;
   }
-  Launch x = gemm_launch(K_DX, t, m, cb, ce, -1);
+  Launch x = gemm_launch(t == TILE_ROWS ? K_DX_ROWS : K_DX, t, m, cb, ce, -1);
   x.rp = rp;
   x.drop = drop;
   x.grp = grp;
@@ -310,6 +313,11 @@ inline void plan_dx_part(Plan& p, GemmTile t, int64_t m, int rp, int64_t cb, int
 // Tiles open to the dX GEMM of m tokens over `depth` output features.
 inline int dx_tile_set(int64_t m, int64_t depth, bool grp) {
   return (!grp && depth >= kMidTileDepth ? TILES_MID : 0) | (m <= kFewTokens || (m <= kShortTokens && depth >= kShortDepth) ? TILES_SHORT : 0);
+}
+
+inline GemmSplit dx_split(int64_t m, int64_t k, int64_t depth, bool grp) {
+  const int set = dx_tile_set(m, depth, grp);
+  return depth < kMidTileDepth ? plan_gemm_split(kDxShallowTiles, m, k, set) : plan_gemm_split(kDxTiles, m, k, set);
 }
 
 // dU of `count` projections of one rank and token count in one launch.
@@ -353,13 +361,15 @@ inline Plan plan_bwd(int64_t m, int64_t n, int64_t k, int64_t r, bool drop) {
   p.add(tokred_launch(L, drop, 0));
   const bool n_whole = n % 64 == 0;
   if (drop) {
-    const GemmTile t = cheapest_tile(kDxDropTiles, m, k, dx_tile_set(m, n, false)).t;
-    plan_dx_part(p, t, m, L.rp, 0, k, n_whole, true, false, true);
+    const int set = dx_tile_set(m, n, false);
+    const GemmTile t = (n < kMidTileDepth ? cheapest_tile(kDxDropShallowTiles, m, k, set)
+                                          : cheapest_tile(kDxDropTiles, m, k, set)).t;
+    plan_dx_part(p, t, m, L.rp, n, 0, k, n_whole, true, false, true);
     return p;
   }
-  const GemmSplit s = plan_gemm_split(kDxTiles, m, k, dx_tile_set(m, n, false));
-  plan_dx_part(p, s.t1, m, L.rp, 0, s.n1, n_whole, false, false, true);
-  if (s.n1 < k) plan_dx_part(p, s.t2, m, L.rp, s.n1, k, n_whole, false, false, false);
+  const GemmSplit s = dx_split(m, k, n, false);
+  plan_dx_part(p, s.t1, m, L.rp, n, 0, s.n1, n_whole, false, false, true);
+  if (s.n1 < k) plan_dx_part(p, s.t2, m, L.rp, n, s.n1, k, n_whole, false, false, false);
   return p;
 }
 
@@ -392,9 +402,9 @@ inline Plan plan_group_bwd(int count, const int64_t* n, int64_t m, int64_t k, in
     p.add(x);
   }
   const int rp = G.L[0].rp;
-  const GemmSplit s = plan_gemm_split(kDxTiles, m, k, dx_tile_set(m, depth, true));
-  plan_dx_part(p, s.t1, m, rp, 0, s.n1, n_whole, false, true, true);
-  if (s.n1 < k) plan_dx_part(p, s.t2, m, rp, s.n1, k, n_whole, false, true, false);
+  const GemmSplit s = dx_split(m, k, depth, true);
+  plan_dx_part(p, s.t1, m, rp, depth, 0, s.n1, n_whole, false, true, true);
+  if (s.n1 < k) plan_dx_part(p, s.t2, m, rp, depth, s.n1, k, n_whole, false, true, false);
   return p;
 }
 
@@ -470,6 +480,10 @@ inline void launch_name(const Launch& x, char* buf, size_t len) {
       break;
     case K_DX:
       snprintf(buf, len, "lora::lora_bwd_dx_kernel<%d, %d, %d, %d, %d, %s, %s, %s>", x.bm, x.bn, x.wm, x.wn, x.rp,
+               b(x.drop), b(x.grp), b(x.full));
+      break;
+    case K_DX_ROWS:
+      snprintf(buf, len, "lora::lora_bwd_rows_dx_kernel<%d, %d, %d, %d, %d, %s, %s, %s>", x.bm, x.bn, x.wm, x.wn, x.rp,
                b(x.drop), b(x.grp), b(x.full));
       break;
     case K_DXF: snprintf(buf, len, "lora::lora_bwd_dxf_kernel<%s, %s>", b(x.full), b(x.fastb)); break;

@@ -82,7 +82,9 @@ SHAPES = [Shape("drop_tiny", 256, 512, 512, 8, 16.0, 21), Shape("drop_ragged", 2
     Shape("drop_dx128m_r33f", 300, 64, 1024, 33, 66.0, 212), Shape("drop_dx128m_r64f", 300, 64, 1024, 64, 128.0, 213),
     # the register-staged forward tiles reading U back: 128 x 128, and the k-split one over several rounds
     Shape("drop_reg", 1100, 13824, 64, 8, 16.0, 214), Shape("drop_reg_r24", 300, 11008, 192, 24, 48.0, 215),
-    Shape("drop_ks_staged", 1538, 18944, 384, 8, 16.0, 216)]
+    Shape("drop_ks_staged", 1538, 18944, 384, 8, 16.0, 216)] + [
+    # the masked k-split 128 x 256 dX of deep calls, with and without whole stages
+    Shape(f"drop_deep_n{n}_r{r}", 1100, n, 6144, r, 2.0 * r, 220 + r) for n in (3136, 3080) for r in (1, 24, 33, 64)]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)

@@ -119,6 +119,12 @@ CASES = [  # (ns, m, k, r, alpha)
         ([13824] * 2, 130, 520, 33), ([13824] * 2, 130, 1024, 33), ([4096] * 3, 1100, 136, 1), ([4096] * 3, 1100, 256, 1),
         ([4096] * 3, 1100, 72, 24), ([4096] * 3, 1100, 256, 24), ([4096] * 3, 1100, 64, 33), ([64, 64], 300, 520, 24),
         ([64, 64], 300, 200, 33), ([2048] * 2, 4096, 136, 1))
+] + [
+    # the k-split 128 x 256 dX over members of 3072 steps in all and more
+    (ns, m, k, r, 2.0 * r) for ns, m, k, r in (
+        ([1536] * 2, 1100, 4096, 24), ([1536] * 2, 1100, 4096, 33), ([1536] * 2, 1100, 4096, 64),
+        ([1544] * 2, 1100, 4104, 1), ([1544] * 2, 1100, 4104, 24), ([1544] * 2, 1100, 4104, 33),
+        ([1544] * 2, 1100, 4104, 64))
 ]
 
 

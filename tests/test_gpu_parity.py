@@ -105,6 +105,12 @@ RAGGED = [
     for i, (m, n, k, r) in enumerate([(300, 11008, 520, 24), (300, 11008, 1024, 33), (1100, 11008, 72, 24),
                                       (1100, 11008, 64, 24), (8200, 1024, 72, 33), (8200, 1024, 512, 1),
                                       (1538, 18944, 384, 8), (1538, 18944, 448, 13)])
+] + [
+    # the k-split 128 x 256 dX, which calls of fewer than 3072 steps leave to the one whose wave rows split the
+    # tokens, with and without whole stages and columns
+    Shape("deep", m, n, k, r, 2.0 * r, 240 + i)
+    for i, (m, n, k, r) in enumerate([(1100, 3136, 6144, 24), (1100, 3136, 6144, 33), (1100, 3136, 6144, 64),
+                                      (1100, 3080, 6152, 24), (1100, 3080, 6152, 33), (8200, 64, 448, 64)])
 ]
 
 

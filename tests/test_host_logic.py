@@ -206,6 +206,24 @@ def test_forward_kernel_of_measured_calls(lora, op, m, ns, k, r, kernel):
     assert lora.lora_linear_plan(op, m, ns, k, r)[-1]["kernel"] == "lora::" + kernel
 
 
+@pytest.mark.parametrize("op, m, ns, k, r, kernel", [
+    # few contraction steps: 128 x 256 with nothing to exchange, or 256 x 256
+    ("bwd", 1183, 512, 4096, 4, "lora_bwd_rows_dx_kernel<128, 256, 2, 4, 16, false, false, true>"),
+    ("bwd", 1952, 592, 13824, 8, "lora_bwd_rows_dx_kernel<128, 256, 2, 4, 16, false, false, false>"),
+    ("bwd_dropout", 7828, 512, 5888, 4, "lora_bwd_rows_dx_kernel<128, 256, 2, 4, 16, true, false, true>"),
+    # one round of a larger tile over two of 64 x 128, and not 128 x 128 with 64 x 64 for the rest
+    ("bwd", 296, 5120, 11008, 8, "lora_bwd_dx_kernel<128, 192, 2, 2, 16, false, false, false>"),
+    ("bwd", 320, 2856, 11008, 16, "lora_bwd_rows_dx_kernel<128, 256, 2, 4, 16, false, false, false>"),
+    ("group_bwd", 576, [11008, 11008], 8280, 8, "lora_bwd_dx_kernel<128, 256, 2, 4, 16, false, true, false>"),
+    # and the ones that stay
+    ("bwd", 333, 4096, 4096, 8, "lora_bwd_dx_kernel<64, 128, 1, 2, 16, false, false, true>"),
+    ("bwd", 2048, 4096, 4096, 8, "lora_bwd_dx_kernel<128, 256, 2, 4, 16, false, false, true>"),
+    ("bwd", 1531, 4104, 3208, 12, "lora_bwd_dx_kernel<128, 192, 2, 2, 16, false, false, false>")])
+def test_dx_kernel_of_measured_calls(lora, op, m, ns, k, r, kernel):
+    """The dX kernel each of these calls was measured to be fastest on."""
+    assert lora.lora_linear_plan(op, m, ns, k, r)[-1]["kernel"] == "lora::" + kernel
+
+
 @pytest.mark.parametrize("m, tpw", [(1000, 8), (1366, 16), (2731, 32)])
 def test_grouped_u_pass_counts_the_tokens_of_all_members(lora, m, tpw):
     """Tokens per workgroup of a group's one U pass: the most that still gives
