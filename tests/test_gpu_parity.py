@@ -151,6 +151,27 @@ EXACT = [
     Shape("exact", 8200, 520, 1032, 40, 80.0, 209),      # the same at padded rank 48, ragged tokens
 ]
 
+
+# Edges of single tiles, each with the forward and dX kernels that it is there for (checked against the plans):
+# forward tiles shared by pairs of workgroups (an empty second half, and ones of 13 tokens and of one; a number of
+# tiles that is no multiple of 8), the 128 x 192 tiles with whole and partial last stages, and the register-staged
+# forward and the dX whose wave rows split the tokens, with a last tile of one token and of eight columns.
+TILE_EDGE = [  # (m, n, k, r), seed, forward kernel, dX kernel
+    ((300, 1096, 1096, 8), 505, "lora_fwd_pair_ks_kernel<16, false, false, false>", None),
+    ((333, 520, 1088, 13), 506, "lora_fwd_pair_ks_kernel<16, false, true, false>", None),
+    ((333, 2048, 2056, 13), 511, "lora_fwd_pair_ks_kernel<16, false, false, false>", None),
+    ((321, 1096, 1096, 24), 513, "lora_fwd_pair_ks_kernel<32, false, false, true>", None),
+    ((321, 1032, 2056, 40), 514, "lora_fwd_pair_ks_kernel<64, false, false, true>", None),
+    ((300, 11008, 3080, 8), 508, "lora_fwd_kernel<128, 192, 2, 2, 16, false, false, false, false>", None),
+    ((300, 11008, 3080, 24), 515, "lora_fwd_kernel<128, 192, 2, 2, 32, false, true, false, false>", None),
+    ((300, 11008, 3072, 24), 516, "lora_fwd_kernel<128, 192, 2, 2, 32, false, true, true, false>", None),
+    ((1025, 3080, 520, 8), 517, "lora_fwd_reg_kernel<128, 128, 2, 2, 16, false, false, false>", None),
+    ((1409, 2056, 512, 13), 518, "lora_fwd_reg_kernel<128, 128, 2, 2, 16, false, false, true>", None),
+    ((1281, 520, 4104, 13), 519, None, "lora_bwd_rows_dx_kernel<128, 256, 2, 4, 16, false, false, false>"),
+    ((1281, 512, 4096, 40), 520, None, "lora_bwd_rows_dx_kernel<128, 256, 2, 4, 48, false, false, true>"),
+    ((1281, 1032, 4104, 64), 521, None, "lora_bwd_rows_dx_kernel<128, 256, 2, 4, 64, false, false, false>"),
+]
+
 # dX plans at the edges of the tile choice: n not a multiple of 64 where the
 # dX would otherwise take the 256 x 256 tile (the 128 x 256 tile with bound
 # checks serves it), and the 256 x 256 direct-to-LDS dX at padded ranks 32
@@ -160,13 +181,10 @@ SPLIT_EDGE = [
     Shape("edge", 4096, 4000, 4096, 64, 128.0, 502),
     Shape("edge", 4096, 1024, 4096, 24, 48.0, 503),
     Shape("edge", 4096, 1024, 4096, 40, 80.0, 504),
-    # forward tiles shared by pairs of workgroups (an empty and a nearly empty second half, a number of tiles that
-    # is no multiple of 8), and the 128 x 192 tiles, whole and partial last stages
-    Shape("edge", 300, 1096, 1096, 8, 16.0, 505), Shape("edge", 333, 520, 1088, 13, 26.0, 506),
-    Shape("edge", 193, 1032, 320, 40, 80.0, 507), Shape("edge", 300, 11008, 3080, 8, 16.0, 508),
+    # few-token forwards of more than 64 tokens, and 128 x 128 tiles, over ragged depths and widths
+    Shape("edge", 193, 1032, 320, 40, 80.0, 507), Shape("edge", 100, 2120, 520, 8, 16.0, 512),
     Shape("edge", 300, 10816, 3072, 24, 48.0, 509), Shape("edge", 1030, 3080, 4360, 13, 26.0, 510),
-    Shape("edge", 333, 2048, 2056, 13, 26.0, 511), Shape("edge", 100, 2120, 520, 8, 16.0, 512),
-]
+] + [Shape("edge", *shape, 2.0 * shape[3], seed) for shape, seed, _, _ in TILE_EDGE]
 
 
 @pytest.mark.parametrize("shape", SPLIT_EDGE, ids=_shape_id)

@@ -4,7 +4,7 @@ parity suites, and properties of the suites themselves."""
 import pytest
 
 from lora_synth import CONFIGS
-from test_gpu_parity import DEPTH, EXACT, FULL, RAGGED, SPLIT_EDGE
+from test_gpu_parity import DEPTH, EXACT, FULL, RAGGED, SPLIT_EDGE, TILE_EDGE
 from test_gpu_dropout import SHAPES as DROP_SHAPES
 from test_gpu_group import CASES as GROUP_CASES, EXACT_CASES as GROUP_EXACT, FULL_GROUPS
 
@@ -240,6 +240,58 @@ def test_ragged_n_avoids_the_register_staged_256_tile(lora):
         plan = lora.lora_linear_plan("bwd", 4096, 4000, 4096, r)
         dx = [x["kernel"] for x in plan if "dx_kernel" in x["kernel"]]
         assert dx and all(k.startswith("lora::lora_bwd_dx_kernel<128, 256,") and k.endswith("false>") for k in dx), dx
+
+
+@pytest.mark.parametrize("shape, seed, fwd, dx", TILE_EDGE, ids=lambda x: str(x) if isinstance(x, tuple) else "")
+def test_tile_edge_shapes_run_the_kernels_they_name(lora, shape, seed, fwd, dx):
+    for op, kernel in (("fwd", fwd), ("bwd", dx)):
+        if kernel:
+            assert "lora::" + kernel in [x["kernel"] for x in lora.lora_linear_plan(op, *shape)]
+
+
+# Sizes in and at the borders of every regime of the plans: the few-token forward (to 64 and to 256 tokens), the
+# 64-token dX tiles (to 256 and to 1024), one and several rounds of the larger tiles, few and many stages.
+MORE_M = (1, 16, 24, 40, 64, 70, 100, 200, 256, 321, 600, 1024, 1100, 1500, 2431, 8200)
+MORE_N = (64, 136, 512, 1088, 2056, 4096, 5120, 6656, 13824)
+MORE_K = (64, 136, 200, 256, 448, 512, 520, 1032, 1536, 2056, 3072, 3080, 4104, 11008)
+
+
+def test_parity_suites_reach_every_kernel_of_every_regime(lora):
+    """As test_parity_suites_reach_every_plannable_kernel, over sizes in and at
+    the borders of every regime of the plans."""
+    suites = {x["kernel"] for s in SINGLE for op in ("fwd", "bwd") for x in lora.lora_linear_plan(op, s.m, s.n, s.k, s.r)}
+    suites |= {x["kernel"] for s in DROP_SHAPES for op in ("fwd_dropout", "bwd_dropout")
+               for x in lora.lora_linear_plan(op, s.m, s.n, s.k, s.r)}
+    missing = {}
+    for m in MORE_M:
+        for n in MORE_N:
+            for k in MORE_K:
+                for r in (5, 16, 24, 33, 64):
+                    for op in ("fwd", "bwd") + (("fwd_dropout", "bwd_dropout") if k % 64 == 0 else ()):
+                        for x in lora.lora_linear_plan(op, m, n, k, r):
+                            if x["kernel"] not in suites:
+                                missing.setdefault(x["kernel"], (op, m, n, k, r))
+    assert not missing, missing
+
+
+def test_group_suites_reach_every_kernel_of_every_regime(lora):
+    """The same for groups, over members of equal and of different widths."""
+    groups = [(ns, m, k, r) for ns, m, k, r, _ in GROUP_CASES] + [(ns, m, k, r) for m, k, ns, r in GROUP_EXACT]
+    groups += list(FULL_GROUPS)
+    suites = {x["kernel"] for ns, m, k, r in groups for op in ("group_fwd", "group_bwd")
+              for x in lora.lora_linear_plan(op, m, ns, k, r)}
+    suites |= {x["kernel"] for s in SINGLE for op in ("fwd", "bwd") for x in lora.lora_linear_plan(op, s.m, s.n, s.k, s.r)}
+    missing = {}
+    for m in MORE_M:
+        for k in MORE_K:
+            for r in (5, 16, 24, 33, 64):
+                for ns in ([64, 64], [136, 264, 72], [512, 128, 128], [1024, 1088, 64], [2048] * 2, [4096] * 3,
+                           [13824] * 2, [64, 72, 80, 88, 96, 104, 112, 120]):
+                    for op in ("group_fwd", "group_bwd"):
+                        for x in lora.lora_linear_plan(op, m, ns, k, r):
+                            if x["kernel"] not in suites:
+                                missing.setdefault(x["kernel"], (op, m, ns, k, r))
+    assert not missing, missing
 
 
 def _group_dx(lora, ns, m, k, r):
