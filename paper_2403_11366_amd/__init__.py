@@ -323,7 +323,8 @@ def lora_linear_group_bwd_workspace_size(ns, m: int, k: int, r: int) -> int:
 
 def lora_linear_group_fwd(X, Ws, As, Bs, Ys, Us, alpha: float, stream=None) -> None:
     """Projections g that read one X: U_g = X A_g^T, Y_g = X W_g^T + (alpha/r) U_g B_g^T,
-    in one launch.  X [m,k], W_g [n_g,k], A_g [r,k], B_g [n_g,r], Y_g [m,n_g]:
+    in one GEMM launch (after a launch forming every U_g where U has a pass of its
+    own).  X [m,k], W_g [n_g,k], A_g [r,k], B_g [n_g,r], Y_g [m,n_g]:
     torch.bfloat16; U_g [m,r]: torch.float32."""
     if _BF16 is None:
         _bind_torch()

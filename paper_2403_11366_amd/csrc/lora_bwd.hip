@@ -1542,6 +1542,7 @@ __device__ __forceinline__ void dx_big_tile(const DxArgs& p, const DxGroup& grp,
 
 // After its tile, every workgroup sums a slice of the dA, dB partials
 // (complete: the token reductions ran before this launch in stream order).
+// (WM and WN stand in the kernel's name alone.)
 template <int BM, int BN, int WM, int WN, int RP, bool DROP, bool GRP, bool FULL>
 __global__ __launch_bounds__(512) void lora_bwd_dx_kernel(
     const u16* __restrict__ dY, const u16* __restrict__ W, const u16* __restrict__ dU2,
@@ -1584,9 +1585,10 @@ __global__ __launch_bounds__(512) void lora_bwd_rows_dx_kernel(
 // ---------------------------------------------------------------------------
 // Fused backward for ranks up to 16 (no dropout): the dX GEMM also forms dU
 // and the dB partials from the dY tiles it stages, so no other launch reads
-// dY.  Tile of 128 tokens x 256 input features, waves and k loop as in
-// lora_bwd_dx_kernel (stages of 64 along n, loads two stages ahead in
-// registers, the products of the last substep after the barrier).
+// dY.  Tile of 128 tokens x 256 input features, 2 x 4 waves of 64 x 64 all in
+// step, stages of 64 along n in two LDS buffers, loaded two stages ahead into
+// registers; each stage's last substep multiplies after its barrier, while the
+// next stage's first fragments are read.
 //   dU^T = B^T dY^T: each stage also stages its 64 B rows ([64][16] bf16,
 //     zero beyond r and n); at substep wn of every stage, wave (wm, wn)
 //     multiplies the transposed B rows (rows t >= 16 of the operand zero)
@@ -1721,7 +1723,7 @@ __global__ __launch_bounds__(512) void lora_bwd_dxf_kernel(
 #pragma unroll
   for (int b = 0; b < FI; ++b) dacc[b] = floatx16{};
 
-  // Fragments of substep ks (16 n): W and dY as in lora_bwd_dx_kernel, and at
+  // Fragments of substep ks (16 n): W read transposed, dY as rows, and at
   // this wave's substep (ks == wn) the B^T operand: lane (g, c32) row t = c32
   // (zero for c32 >= 16), k = n 16 ks + 8g .. +7, read transposed from Bs
   // (rows of 32 bytes, no swizzle: a 16-lane read covers 128 contiguous bytes).
@@ -1805,8 +1807,8 @@ __global__ __launch_bounds__(512) void lora_bwd_dxf_kernel(
 #pragma unroll
   for (int pc = 0; pc < 3; ++pc) swrite(0, pc);
   __syncthreads();
-  // (stages with run-time buffer parity: the paired loop of lora_bwd_dx_kernel
-  // spills here)
+  // (stages with run-time buffer parity: a loop over pairs of stages, each
+  // buffer a compile-time constant, spills here)
   using BR = std::integral_constant<int, -1>;
   int st = 0;
   if (nkb >= 2) {

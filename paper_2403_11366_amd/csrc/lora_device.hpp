@@ -1,15 +1,17 @@
 // Device-side building blocks shared by the LoRA-linear kernels (gfx950 only).
 //
 // Matrix-core primitives (bf16 in, fp32 accumulate):
-//   v_mfma_f32_32x32x16_bf16 -- the GEMM workhorse.  With lane l, c = l % 32,
-//     g = l / 32:  A operand (32 x 16, M x K): lane holds row c, k = 8g .. 8g+7;
-//     B operand (16 x 32, K x N): lane holds column c, k = 8g .. 8g+7;
-//     result (32 x 32): lane holds column c, rows 8(q/4) + 4g + q%4, q = 0..15.
-//     On gfx950 it issues at the full bf16 rate (1024 flop/clk per SIMD).
-//   v_mfma_f32_16x16x32_bf16 -- used by the small rank-r kernels.  With
-//     c = l % 16, g = l / 16: A holds row c, k = 8g .. 8g+7; B holds column c,
-//     the same k; the result holds column c, rows 4g .. 4g+3.  It issues at
-//     about half the flop rate of the 32x32 form.
+//   v_mfma_f32_16x16x32_bf16 -- the turn-taking GEMM tiles, the few-token
+//     forward and the rank-r kernels.  With c = l % 16, g = l / 16: A holds row
+//     c, k = 8g .. 8g+7; B holds column c, the same k; the result holds column
+//     c, rows 4g .. 4g+3.  It does half the flops of the other form on the same
+//     operand registers, and the tiles on it are faster all the same (8192 x 4096
+//     x 11008 forward at rank 64 533 us against 582).
+//   v_mfma_f32_32x32x16_bf16 -- the register-staged forward tiles and the fused
+//     backward.  With c = l % 32, g = l / 32: A operand (32 x 16, M x K): lane
+//     holds row c, k = 8g .. 8g+7; B operand (16 x 32, K x N): lane holds column
+//     c, k = 8g .. 8g+7; result (32 x 32): lane holds column c, rows 8(q/4) + 4g
+//     + q%4, q = 0..15.
 // Both operands carry k in the same positions, so any matrix stored with k
 // contiguous is read with one 16-byte load per lane.
 //

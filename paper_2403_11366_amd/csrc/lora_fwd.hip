@@ -1,9 +1,9 @@
 // Forward of the LoRA-adapted linear layer (Eq. 1 of JORA, Section 3):
 //   U = X A^T,   Y = X W^T + s U B^T,   s = alpha / r.
 //
-// Kernels (one launch per call; a U pass before it for rank > 16, on the
-// 256 x 256 tile and under dropout, and a second GEMM launch when the columns
-// are split between two tiles):
+// Kernels (one launch per call; a U pass before it for rank > 16 -- but a group's
+// on the register-staged tile --, on the 256 x 256 tile and under dropout, and a
+// second GEMM launch when the columns are split between two tiles):
 //   lora_fwd_kernel     the 256 x 256 tile (below), and the 128-token tiles of
 //                       lora_fwd_ks.hpp: 128 x 128, 128 x 192 and, beyond rank
 //                       16, 128 x 256.
@@ -288,7 +288,8 @@ __device__ __forceinline__ void fwd_big_tile(const u16* __restrict__ X, const u1
 }
 
 // One kernel template for the 256 x 256 tile (BIG) and the 128-token tiles that
-// lora_fwd_ks_kernel does not serve.
+// lora_fwd_ks_kernel does not serve.  WM and WN, the waves along the tokens and
+// the features of a k share, stand in the kernels' names alone.
 template <int BM, int BN, int WM, int WN, int RP, bool GRP, bool UPRE, bool KFULL, bool BIG>
 __global__ __launch_bounds__(512) void lora_fwd_kernel(
     const u16* __restrict__ X, const u16* __restrict__ W, const u16* __restrict__ A, const u16* __restrict__ B,
@@ -485,7 +486,8 @@ __global__ __launch_bounds__(256) void lora_u_kernel(const u16* __restrict__ X, 
 
 // ---------------------------------------------------------------------------
 // The 128 x 256 tile for rank <= 16, the k substeps of each stage split between
-// wave pairs.  DMA (single-round launches with whole stages): fwd_ks_tile.
+// wave pairs.  DMA (whole stages, and one round of workgroups or k from 512
+// on): fwd_ks_tile.
 // Otherwise the same split with both halves of a pair in step and the stages
 // staged in registers two ahead, stored to the free one of two LDS buffers
 // during the stage before their use.  Wave (wk, wm, wn) multiplies the 64
@@ -544,8 +546,9 @@ __global__ __launch_bounds__(512) void lora_fwd_ks_kernel(
   const __amdgpu_buffer_rsrc_t rsW = make_rsrc(W + (size_t)n0 * k, (uint64_t)min(BN, n - n0) * rowbytes);
   const __amdgpu_buffer_rsrc_t rsA = make_rsrc(A, (uint64_t)r * rowbytes);
 
-  // Register staging of one k-block as in lora_fwd_kernel, stored in two
-  // pieces (0 = X and A rows, 1 = W rows), one per substep of the stage.
+  // Register staging of one k-block (thread chunk q = tid + i NT of a region is
+  // row q/8, k-chunk q%8), stored in two pieces (0 = X and A rows, 1 = W rows),
+  // one per substep of the stage.
   int4v gx[LX], gw[LW], ga[LA];
   auto gload = [&](int kb, int piece) LORA_INLINE {
     const int k0 = kb * 64;
@@ -637,7 +640,7 @@ __global__ __launch_bounds__(512) void lora_fwd_ks_kernel(
       for (int gg = 0; gg < GPW; ++gg) uacc16[gg] = mfma16x16x32(fa16, fxu16[gg], uacc16[gg]);
     }
   };
-  // Pipeline of lora_fwd_kernel with two substeps per wave and stage: at the
+  // Two substeps per wave and stage: at the
   // top of stage kb the registers hold block kb+1; each piece is stored to the
   // free buffer and reloaded with block kb+2; fragments of substep 1 are read
   // while substep 0 multiplies.

@@ -212,7 +212,6 @@ struct FwdArgs {
   float s;
   const uint8_t* keep = nullptr;   // dropout keep bits [m][k/8], or none
   float inv_keep = 1.0f;           // 1 / (1 - p)
-  bool u_ready = false;            // U already in place (second launch of a column split)
 };
 
 struct BwdArgs {

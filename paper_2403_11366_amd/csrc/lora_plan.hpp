@@ -67,6 +67,9 @@ inline Launch blank_launch(KernelId id) {
 // all use 64); backward ones for 16, 32, 48 and 64.
 inline int fwd_rank(int64_t r) { return r <= 16 ? 16 : (r <= 32 ? 32 : 64); }
 
+// Output area of a tile, and the two wave counts of its kernel's name: waves
+// along the tokens and the columns (of the k-split tiles, which run four waves a
+// k share, they name a square arrangement whatever the tile runs).
 inline void tile_dims(GemmTile t, int& bm, int& bn, int& wm, int& wn) {
   switch (t) {
     case TILE_256x256: bm = 256; bn = 256; wm = 2; wn = 4; break;
@@ -108,10 +111,12 @@ inline Launch upass_launch(int count, int64_t m, int64_t r, bool drop) {
   return u;
 }
 
-// Forward of few tokens: up to kSkinnyTokens, and up to kFewTokens for outputs
-// of at most kSkinnyTiles tiles of 128 x 128.  There the GEMM tiles leave most
-// compute units idle or multiply mostly padding, and a kernel that streams W
-// past blocks of up to 64 tokens is faster (n = k = 4096: 4 tokens 39 -> 10 us,
+// Forward of few tokens: up to kSkinnyTokens, unless the output is so wide and
+// the call of so few stages that the register-staged tile is estimated faster
+// (faster_fwd), and up to kFewTokens for outputs of at most kSkinnyTiles tiles of
+// 128 x 128.  There the GEMM tiles leave most compute units idle or multiply
+// mostly padding, and a kernel that streams W past blocks of up to 64 tokens is
+// faster (n = k = 4096: 4 tokens 39 -> 10 us,
 // 64 tokens 40 -> 18; against paired 128 x 128 tiles: 128 tokens 24.2 -> 18.2,
 // 256 x 2048 x 2048 14.7 -> 11.5, 256 x 512 x 512 7.4 -> 5.5; at 64 tiles, 192 x
 // 4096 x 4096, 24.4 and 24.2; at 86, 128 x 11008 x 4096, 25.6 and 37.5).

@@ -75,8 +75,8 @@ def test_built_library_assembly_passes():
     assert asm_check.count_checked(files) >= 1
 
 
-# One asm block that forms its addresses and then issues the reads (the form of
-# the 256x256 forward tile's reads): the reads inside the block are tracked.
+# One asm block that forms its addresses and then issues the reads: the reads
+# inside the block are tracked.
 XOR_BLOCK = """
 	;;#ASMSTART
 	v_xor_b32 v2, 32, v1
