@@ -52,11 +52,12 @@ constexpr TileCost kDxShallowTiles[5] = {{TILE_256x256, 256, 256, 1, 1.08}, {TIL
 constexpr TileCost kDxDropTiles[5] = {kDxTiles[1], kDxTiles[2], kDxTiles[3], kDxTiles[4], kDxTiles[5]};
 constexpr TileCost kDxDropShallowTiles[4] = {kDxShallowTiles[1], kDxTiles[2], kDxTiles[4], kDxTiles[5]};
 // Tiles a call may take beside 256x256, 128x256, 128x128 and pairs.  128x192
-// serves single projections of at least kMidTileDepth contraction steps, and
-// from there dX's 128x256 splits k instead of tokens (equal at 33 to 64 stages).
-// Measured with 128x192 open to all (500 drawn steps, the better plan of each
-// call): groups 1.7% forward and 1.0% backward, single projections below
-// kMidTileDepth 1.1% and 0.2%; groups have no kernel of it.  The 64-token tiles
+// serves single projections of at least kMidTileDepth contraction steps (the
+// forward's of fewer by estimated time, plan_fwd), and from there dX's 128x256
+// splits k instead of tokens (equal at 33 to 64 stages).  Measured with 128x192
+// open to all (500 drawn steps, the better plan of each call): groups 1.7%
+// forward and 1.0% backward, single dX below kMidTileDepth 0.2%; groups have no
+// kernel of it.  The 64-token tiles
 // serve calls of few tokens, where the larger ones leave compute units idle: up to
 // kFewTokens at any depth, up to kShortTokens from kShortDepth steps on.  (Whole
 // backward call with the best of them against 128x128: 130 x 4096 x 4096 38 ->

@@ -255,20 +255,38 @@ inline Plan faster_fwd(const Plan& p, const Plan& reg, int64_t k, int64_t r) {
 }
 
 // lora_linear_fwd / lora_linear_fwd_dropout (the same tiles and column split;
-// under dropout the U pass applies the mask).
-inline Plan plan_fwd_tiles(int64_t m, int64_t n, int64_t k, int64_t r, bool drop, bool reg) {
-  if (!reg && fwd_skinny(1, &n, m)) return plan_fwd_skinny(1, &n, m, k, r, drop);
+// under dropout the U pass applies the mask).  Below kMidTileDepth, where the
+// rounds alone do not say which tile is faster, outputs of more than
+// kNarrowCols columns take 128 x 192 where it is estimated at least 3% faster
+// than the plan without it (786 x 5120 x 1064, r = 45 29.8 us on 128 x 256, 26.1;
+// 330 x 13824 x 1040, r = 23 33.3 and 29.5; 1241 x 4096 x 512, r = 16 15.1 and 13.4;
+// of 90 drawn calls that it changes 87 gain, 4 to 20%, and one loses, 1.5%).
+// Narrower ones would gain 5 to 10% and keep their tiles.
+constexpr int64_t kNarrowCols = 768;
+enum FwdTiles { FWD_BY_ROUNDS, FWD_REG_TILE, FWD_MID_TILE };   // how plan_fwd_tiles chooses: by rounds, or this tile
+inline Plan plan_fwd_tiles(int64_t m, int64_t n, int64_t k, int64_t r, bool drop, FwdTiles tiles) {
+  if (tiles == FWD_BY_ROUNDS && fwd_skinny(1, &n, m)) return plan_fwd_skinny(1, &n, m, k, r, drop);
   Plan p;
-  const GemmSplit s = reg ? GemmSplit{TILE_REG, TILE_REG, n}
+  const GemmSplit s = tiles == FWD_REG_TILE ? GemmSplit{TILE_REG, TILE_REG, n}
+                      : tiles == FWD_MID_TILE
+                          ? GemmSplit{TILE_128x192, TILE_128x192, n}
                           : plan_gemm_split(kFwdTiles, m, n, k >= kMidTileDepth ? TILES_MID : TILES_BASE);
   plan_fwd_part(p, s.t1, m, k, r, 0, s.n1, true, drop, false, 1, -1);
   if (s.n1 < n) plan_fwd_part(p, s.t2, m, k, r, s.n1, n, false, drop, false, 1, -1);
   return p;
 }
 inline Plan plan_fwd(int64_t m, int64_t n, int64_t k, int64_t r, bool drop) {
-  const Plan p = plan_fwd_tiles(m, n, k, r, false, false), reg = plan_fwd_tiles(m, n, k, r, false, true);
-  const Plan best = faster_fwd(p, reg, k, r);
-  return drop ? plan_fwd_tiles(m, n, k, r, true, best.l[best.count - 1].id == K_FWD_REG) : best;
+  const Plan p = plan_fwd_tiles(m, n, k, r, false, FWD_BY_ROUNDS), reg = plan_fwd_tiles(m, n, k, r, false, FWD_REG_TILE);
+  Plan best = faster_fwd(p, reg, k, r);
+  FwdTiles tiles = best.l[best.count - 1].id == K_FWD_REG ? FWD_REG_TILE : FWD_BY_ROUNDS;
+  if (k < kMidTileDepth && n > kNarrowCols && best.l[best.count - 1].id != K_FWD_SKINNY) {
+    const Plan mid = plan_fwd_tiles(m, n, k, r, false, FWD_MID_TILE);
+    if (fwd_time(mid, k, r) < 0.97 * fwd_time(best, k, r)) {
+      best = mid;
+      tiles = FWD_MID_TILE;
+    }
+  }
+  return drop ? plan_fwd_tiles(m, n, k, r, true, tiles) : best;
 }
 
 // lora_linear_group_fwd: one GEMM launch over the output tiles of all members,

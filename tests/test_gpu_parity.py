@@ -104,7 +104,8 @@ RAGGED = [
     Shape("stages", m, n, k, r, 2.0 * r, 230 + i)
     for i, (m, n, k, r) in enumerate([(300, 11008, 520, 24), (300, 11008, 1024, 33), (1100, 11008, 72, 24),
                                       (1100, 11008, 64, 24), (8200, 1024, 72, 33), (8200, 1024, 512, 1),
-                                      (1538, 18944, 384, 8), (1538, 18944, 448, 13)])
+                                      (1538, 18944, 384, 8), (1538, 18944, 448, 13), (600, 13824, 520, 24),
+                                      (600, 13824, 520, 33), (600, 13824, 1536, 33)])
 ] + [
     # the k-split 128 x 256 dX, which calls of fewer than 3072 steps leave to the one whose wave rows split the
     # tokens, with and without whole stages and columns
@@ -165,6 +166,8 @@ TILE_EDGE = [  # (m, n, k, r), seed, forward kernel, dX kernel
     ((300, 11008, 3080, 8), 508, "lora_fwd_kernel<128, 192, 2, 2, 16, false, false, false, false>", None),
     ((300, 11008, 3080, 24), 515, "lora_fwd_kernel<128, 192, 2, 2, 32, false, true, false, false>", None),
     ((300, 11008, 3072, 24), 516, "lora_fwd_kernel<128, 192, 2, 2, 32, false, true, true, false>", None),
+    ((385, 10976, 520, 8), 522, "lora_fwd_kernel<128, 192, 2, 2, 16, false, false, false, false>", None),
+    ((257, 13832, 576, 33), 523, "lora_fwd_kernel<128, 192, 2, 2, 64, false, true, true, false>", None),
     ((1025, 3080, 520, 8), 517, "lora_fwd_reg_kernel<128, 128, 2, 2, 16, false, false, false>", None),
     ((1409, 2056, 512, 13), 518, "lora_fwd_reg_kernel<128, 128, 2, 2, 16, false, false, true>", None),
     ((1281, 520, 4104, 13), 519, None, "lora_bwd_rows_dx_kernel<128, 256, 2, 4, 16, false, false, false>"),

@@ -196,6 +196,11 @@ def test_group_suites_reach_every_plannable_kernel(lora):
     ("group_fwd", 64, [13824, 13824], 1024, 64, "lora_fwd_reg_kernel<128, 128, 2, 2, 64, true, false, true>"),
     ("group_fwd", 39, [13824] * 3, 512, 32, "lora_fwd_reg_kernel<128, 128, 2, 2, 32, true, false, true>"),
     ("fwd", 64, 32000, 1024, 16, "lora_fwd_reg_kernel<128, 128, 2, 2, 16, false, false, true>"),
+    # 128 x 192 of few stages; narrow outputs keep their tiles
+    ("fwd", 786, 5120, 1064, 45, "lora_fwd_kernel<128, 192, 2, 2, 64, false, true, false, false>"),
+    ("fwd", 330, 13824, 1040, 23, "lora_fwd_kernel<128, 192, 2, 2, 32, false, true, false, false>"),
+    ("fwd_dropout", 1241, 4096, 512, 16, "lora_fwd_kernel<128, 192, 2, 2, 16, false, true, true, false>"),
+    ("fwd", 8200, 520, 1032, 40, "lora_fwd_kernel<128, 256, 2, 2, 64, false, true, false, false>"),
     # and the calls that stay: the few-token kernel's one pass over W, the turn-taking tiles' many stages
     ("fwd", 4, 4096, 4096, 8, "lora_fwd_skinny_ks_kernel<16, 16, 16, false>"),
     ("group_fwd", 5, [13824, 13824], 13824, 8, "lora_fwd_skinny_ks_kernel<16, 64, 16, false>"),
