@@ -216,6 +216,12 @@ inline FwdTime fwd_tile_time(const Launch& x) {
   if (x.bn == 192) return {7, {1.6, 2.4}, {0.58, 0.73}};
   return {6, {0.1, 1}, {0.495, 0.58}};
 }
+// A group's U pass takes longer than a single projection's of as many
+// workgroups, by about kGroupTokens us for every 1000 tokens of its members
+// (6381 x (3 x 512) x 512, r = 8: forward 27.7 us, 22.1 without the pass); on
+// deeper calls that is lost in the error of the rest.
+constexpr int64_t kRegDepth = 1536;
+constexpr double kGroupTokens = 0.6;
 inline double fwd_time(const Plan& p, int64_t k, int64_t r) {
   const double stages = (double)((k + 63) / 64);
   const int rag = k % 64 != 0, wide = fwd_rank(r) / 32;   // 0, 1, 2
@@ -225,6 +231,7 @@ inline double fwd_time(const Plan& p, int64_t k, int64_t r) {
     const double rounds = (double)((x.grid + 255) / 256);
     if (x.id == K_UPASS) {
       t += 2.3 + rounds * stages * (x.tpw + x.rp) * 0.0013;
+      if (x.grid > x.tiles_m && k <= kRegDepth) t += kGroupTokens * (double)(x.grid * x.tpw) / 1000;
     } else if (x.id == K_FWD_SKINNY) {
       const double ranks = (wide == 0 ? 0.45 : 0.85) * (double)r / 16;
       t += rag ? rounds * (3.25 + ranks + stages * (0.0052 * x.bn + 0.00175 * x.bm))
@@ -248,7 +255,6 @@ inline double fwd_time(const Plan& p, int64_t k, int64_t r) {
 // 512, r = 32 18.7 and 13.9.  The few-token kernel keeps calls deeper than
 // kRegDepth, where its one pass over W wins even over wide outputs (5 x (2 x 13824)
 // x 13824 133 and 180; 39 x (3 x 13824) x 512, r = 32 26.5 and 18.2).
-constexpr int64_t kRegDepth = 1536;
 inline Plan faster_fwd(const Plan& p, const Plan& reg, int64_t k, int64_t r) {
   if (p.l[p.count - 1].id == K_FWD_SKINNY && k > kRegDepth) return p;
   return fwd_time(reg, k, r) < 0.97 * fwd_time(p, k, r) ? reg : p;

@@ -95,6 +95,9 @@ CASES = [  # (ns, m, k, r, alpha)
     ([64, 64], 300, 1024, 33, 66.0), ([64, 64], 300, 1024, 64, 128.0), ([64, 64], 300, 72, 24, 48.0),
     ([64, 64], 300, 72, 33, 66.0),
     ([4096, 4096, 4096], 7, 64, 33, 66.0), ([4096, 4096, 4096], 7, 64, 5, 10.0), ([5120, 5120, 5120], 7, 64, 5, 10.0),
+    # 256 x 256 tiles of few stages, the paired tiles at padded rank 64, the widest few-token tile with U from the pass
+    ([13824, 3456, 3456], 600, 136, 1, 2.0), ([11008, 11008], 300, 448, 1, 2.0), ([13824, 3456, 3456], 600, 72, 24, 48.0),
+    ([64, 64], 300, 520, 33, 66.0), ([13824, 3456, 3456], 1, 448, 33, 66.0),
 ] + [
     # the remaining grouped tiles a plan can name, at padded ranks 16 .. 64 with and without whole k stages:
     # the 128 x 128 forward and dX (few tokens), the 128 x 256 forward and k-split forward (130 tokens over

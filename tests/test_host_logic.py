@@ -196,6 +196,9 @@ def test_group_suites_reach_every_plannable_kernel(lora):
     ("group_fwd", 64, [13824, 13824], 1024, 64, "lora_fwd_reg_kernel<128, 128, 2, 2, 64, true, false, true>"),
     ("group_fwd", 39, [13824] * 3, 512, 32, "lora_fwd_reg_kernel<128, 128, 2, 2, 32, true, false, true>"),
     ("fwd", 64, 32000, 1024, 16, "lora_fwd_reg_kernel<128, 128, 2, 2, 16, false, false, true>"),
+    # a group's U pass costs by its tokens: many tokens leave 256 x 256 tiles for the register-staged one, few do not
+    ("group_fwd", 6337, [528] * 3, 512, 8, "lora_fwd_reg_kernel<128, 128, 2, 2, 16, true, false, true>"),
+    ("group_fwd", 466, [11008] * 2, 512, 4, "lora_fwd_kernel<256, 256, 2, 4, 16, true, true, true, true>"),
     # 128 x 192 of few stages; narrow outputs keep their tiles
     ("fwd", 786, 5120, 1064, 45, "lora_fwd_kernel<128, 192, 2, 2, 64, false, true, false, false>"),
     ("fwd", 330, 13824, 1040, 23, "lora_fwd_kernel<128, 192, 2, 2, 32, false, true, false, false>"),
